@@ -296,6 +296,21 @@ int launch_schedule(ckv_ctx* c, hipStream_t s) {
   return CKV_OK;
 }
 
+// Eviction of `count` units from `begin` on: select, then move.  A unit's keys sit in the registers of one workgroup:
+// 1024 threads, or 256 where every unit fits (32 entries per thread) and there are enough units to fill the chip
+// with small workgroups anyway.
+int launch_evict(ckv_ctx* c, hipStream_t s, int begin, int count, int n_sink) {
+  if (c->lay.cap <= 32 * kThreads && count >= 4 * c->n_cu)
+    hipLaunchKernelGGL(evict_kernel<kThreads>, dim3((unsigned)count), dim3(kThreads), 0, s, c->dev, begin, n_sink);
+  else
+    hipLaunchKernelGGL(evict_kernel<kWideThreads>, dim3((unsigned)count), dim3(kWideThreads), 0, s, c->dev, begin, n_sink);
+  CKV_HIP(c, hipGetLastError());
+  const int y = std::max(1, std::min({16 * c->n_cu / count, (c->lay.cap / 2 + 15) / 16, 64}));
+  hipLaunchKernelGGL(evict_move_kernel, dim3((unsigned)count, (unsigned)y), dim3(kThreads), 0, s, c->dev, begin);
+  CKV_HIP(c, hipGetLastError());
+  return CKV_OK;
+}
+
 int upload_budgets(ckv_ctx* c, const int32_t* budgets, hipStream_t s) {
   const ckv_layout& l = c->lay;
   std::vector<long long> tot(l.batch, 0);
@@ -405,8 +420,8 @@ int ckv_init(ckv_ctx** out, const ckv_layout* layout, const int32_t* budgets, co
     delete c;
     return CKV_EINVAL;
   }
-  const void* lds_kernels[4] = {reinterpret_cast<const void*>(finish_kernel), reinterpret_cast<const void*>(evict_kernel),
-                                reinterpret_cast<const void*>(probe_kernel), reinterpret_cast<const void*>(seed_hits_kernel)};
+  const void* lds_kernels[3] = {reinterpret_cast<const void*>(finish_kernel), reinterpret_cast<const void*>(probe_kernel),
+                                reinterpret_cast<const void*>(seed_hits_kernel)};
   if (hipFuncSetAttribute(reinterpret_cast<const void*>(seed_scan_kernel<false>), hipFuncAttributeMaxDynamicSharedMemorySize, kSeedTiles * 4096) != hipSuccess ||
       hipFuncSetAttribute(reinterpret_cast<const void*>(seed_scan_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize, kSeedTiles * 4096) != hipSuccess) {
     delete c;
@@ -780,8 +795,7 @@ int ckv_evict(ckv_ctx* c, int32_t layer, void* stream) {
   if (int rc = layer_range(c, layer, &begin, &count)) return rc;
   for (int l = (layer == -1 ? 0 : layer); l < (layer == -1 ? c->lay.n_layers : layer + 1); ++l) c->prompt_len[l] = -1;
   if (int rc = join_side(c, (hipStream_t)stream)) return rc;
-  hipLaunchKernelGGL(evict_kernel, dim3((unsigned)count), dim3(kThreads), c->finish_lds, (hipStream_t)stream, c->dev, begin, -1);
-  CKV_HIP(c, hipGetLastError());
+  if (int rc = launch_evict(c, (hipStream_t)stream, begin, count, -1)) return rc;
   if (layer == -1 || layer == c->lay.n_layers - 1) return rebalance_after_eviction(c);
   return CKV_OK;
 }
@@ -793,9 +807,7 @@ int ckv_evict_window(ckv_ctx* c, int32_t layer, int32_t n_sink, void* stream) {
   if (int rc = layer_range(c, layer, &begin, &count)) return rc;
   for (int l = (layer == -1 ? 0 : layer); l < (layer == -1 ? c->lay.n_layers : layer + 1); ++l) c->prompt_len[l] = -1;
   if (int rc = join_side(c, (hipStream_t)stream)) return rc;
-  hipLaunchKernelGGL(evict_kernel, dim3((unsigned)count), dim3(kThreads), c->finish_lds, (hipStream_t)stream, c->dev, begin,
-                     (int)n_sink);
-  CKV_HIP(c, hipGetLastError());
+  if (int rc = launch_evict(c, (hipStream_t)stream, begin, count, (int)n_sink)) return rc;
   if (layer == -1 || layer == c->lay.n_layers - 1) return rebalance_after_eviction(c);
   return CKV_OK;
 }

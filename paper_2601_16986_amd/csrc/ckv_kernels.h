@@ -19,7 +19,7 @@
 //
 //   load_cache_kernel, seed_state_kernel   fill a layer's caches
 //   seed_scan_kernel, seed_stats_kernel, seed_hits_kernel, seed_crf_kernel   scores of a loaded prompt from its last queries
-//   evict_kernel     eviction + compaction on its own (Alg. 1 Step 4, or the sink + recent window policy)
+//   evict_kernel, evict_move_kernel   eviction + compaction on its own (Alg. 1 Step 4, or the sink + recent window policy)
 //   probe_kernel     answer-probe classes
 //   rebudget_kernel  Alg. 2 with integer apportionment, one workgroup/sequence
 //   rebalance_kernel pool segments between units after budgets have changed
@@ -40,12 +40,14 @@ namespace ckv {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned long long u64;
 
 // SC_CLAIM is a 64-bit counter (8-byte aligned): low word = work items published, high word = their blocks
 enum { SC_T = 0, SC_WINDOW_STEPS = 1, SC_SEQ = 2, SC_DONE = 3, SC_STATUS = 4, SC_DONE_RB = 5, SC_QUEUE = 6, SC_SPARE = 7, SC_CLAIM = 8, SC_COUNT = 64 };
 enum { FLAG_HIT = 1, FLAG_SLIP = 2 };
 constexpr int kThreads = 256;
+constexpr int kWideThreads = 1024;        // kernels with one workgroup per unit and few units
 constexpr int kMaxChunks = 128;           // cap <= 32768
 constexpr float kFixedOne = 1048576.0f;   // 2^20: resolution of the aggregated-CRF accumulator
 constexpr int kTabLds = 256;              // decay-table entries kept in LDS by the LRFU kernels
@@ -200,8 +202,8 @@ __device__ __forceinline__ u64 wave_min_u64(u64 v) {
 // several in its workgroup and must not touch the workgroup barrier: its LDS and memory operations
 // already execute in program order, only the compiler has to keep them so.
 struct alignas(16) RedBuf {
-  u64 v[2][8];          // one slot per wavefront: up to 512 threads
-  float t[2][8][4];
+  u64 v[2][16];         // one slot per wavefront: up to 1024 threads
+  float t[2][16][4];
 };
 
 template <int NT>
@@ -1605,6 +1607,234 @@ __device__ __forceinline__ void evict_phase(const Dev& d, int u, Slots base, int
   }
 }
 
+// ------------------------------------------------------------------ eviction of many entries, keys in registers
+// Thread tid of NT owns R entries in groups of four consecutive ones, 4 (tid + c NT) + e (group c), as in
+// lrfu_regs below: b[4 c + e] = the entry's score pattern (0xFFFFFFFF beyond the unit), np[4 c + e] = ~position.
+// n <= R NT <= 32 NT, so the eviction mask has at most one 32-bit word per thread.
+struct alignas(16) CutBuf {
+  uint32_t hist[3][256];  // digit counts of a round; three in turn, so that one barrier per round is enough
+  uint32_t lo[16], hi[16];
+  int a[16], b[16];
+};
+
+template <int kCtrl>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
+  return (uint32_t)dpp_i32<kCtrl>((int)v);
+}
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
+  v = min(v, dpp_u32<kDppQuadSwap1>(v));
+  v = min(v, dpp_u32<kDppQuadSwap2>(v));
+  v = min(v, dpp_u32<kDppRowHalfMirror>(v));
+  v = min(v, dpp_u32<kDppRowMirror>(v));
+  const uint32_t x = (uint32_t)__builtin_amdgcn_readlane((int)v, 0), y = (uint32_t)__builtin_amdgcn_readlane((int)v, 16);
+  const uint32_t z = (uint32_t)__builtin_amdgcn_readlane((int)v, 32), w = (uint32_t)__builtin_amdgcn_readlane((int)v, 48);
+  return min(min(x, y), min(z, w));
+}
+
+// The k-th smallest key is (S, P): an entry is among the k smallest (score, then higher position first) if its
+// pattern is below S, or equal to S with ~position <= P.
+struct KeyCut {
+  uint32_t S, P;
+  __device__ __forceinline__ bool operator()(uint32_t b, uint32_t np) const { return (b < S) | ((b == S) & (np <= P)); }
+};
+
+// Eight bits per round from the highest bit in which the values differ (positions share most of theirs: 14 bits are
+// left of 32 for a unit that spans 16384 tokens): a histogram of the digit in LDS over the entries that still
+// match the prefix, then every wavefront finds the digit at which the count passes `want` by itself.  Scores that have decayed to
+// zero (most of a prompt's) are counted first: their common digit would serialise the LDS atomics of every round.
+// 64 units of 9350 entries, 7300 of them evicted, the whole kernel: 26 us; with two-bit rounds that count with ballots
+// 70 us (16 entries per thread and three compares each make such a round 2.5 us of issue); with two-bit rounds over
+// scores in LDS and positions in memory by 256 threads, moves included, 632 us.
+template <int R, int NT>
+__device__ __forceinline__ KeyCut select_low_keys(const uint32_t (&b)[R], const uint32_t (&np)[R], int k, CutBuf& cb, int tid) {
+  const int lane = tid & 63, wave = tid >> 6;
+  constexpr int W = NT / 64;
+  int turn = 0;
+  int zeros = 0;
+#pragma unroll
+  for (int i = 0; i < R; ++i) zeros += __popcll(__ballot(b[i] == 0u));
+  if (lane == 0) cb.a[wave] = zeros;
+  for (int i = tid; i < 256; i += NT) cb.hist[0][i] = 0u;
+  __syncthreads();
+  zeros = 0;
+#pragma unroll
+  for (int w = 0; w < W; ++w) zeros += cb.a[w];
+  // The `want`-th smallest of the values for which `value(i, v)` is true; all of them equal to the result are
+  // wanted if all_equal comes back true (the result may then lie above the value itself, below the next larger one).
+  auto radix = [&](auto value, int want, bool& all_equal) -> uint32_t {
+    uint32_t lo = 0xFFFFFFFFu, nhi = 0xFFFFFFFFu;              // minimum, and ~maximum
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      uint32_t v;
+      if (value(i, v)) {
+        lo = min(lo, v);
+        nhi = min(nhi, ~v);
+      }
+    }
+    lo = wave_min_u32(lo);
+    nhi = wave_min_u32(nhi);
+    if (lane == 0) {
+      cb.lo[wave] = lo;
+      cb.hi[wave] = nhi;
+    }
+    __syncthreads();
+    lo = cb.lo[0];
+    nhi = cb.hi[0];
+#pragma unroll
+    for (int w = 1; w < W; ++w) {
+      lo = min(lo, cb.lo[w]);
+      nhi = min(nhi, cb.hi[w]);
+    }
+    const uint32_t diff = lo ^ ~nhi;
+    int top = diff ? 32 - __builtin_clz(diff) : 0;             // the values agree in all bits from `top` on
+    uint32_t X = top < 32 ? lo >> top << top : 0u;
+    all_equal = false;
+    while (top > 0) {
+      const int s = max(top - 8, 0);
+      const uint32_t digits = 1u << (top - s);
+      uint32_t* h = cb.hist[turn];
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        uint32_t v;
+        if (value(i, v) && ((v ^ X) >> s) < digits) atomicAdd(&h[(v >> s) & (digits - 1)], 1u);
+      }
+      turn = turn == 2 ? 0 : turn + 1;
+      for (int i = tid; i < 256; i += NT) cb.hist[turn][i] = 0u;       // read last two rounds ago
+      __syncthreads();
+      const u32x4 q = *reinterpret_cast<const u32x4*>(h + 4 * lane);
+      const int mine = (int)(q[0] + q[1] + q[2] + q[3]);
+      int incl = mine;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(incl, o);
+        if (lane >= o) incl += y;
+      }
+      const int at = __ffsll((long long)__ballot(incl >= want)) - 1;   // the lane whose four digits hold the wanted one
+      int below = __builtin_amdgcn_readlane(incl - mine, at);
+      uint32_t digit = 4u * (uint32_t)at;
+      int count = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        count = __builtin_amdgcn_readlane((int)q[e], at);
+        if (below + count >= want) {
+          digit += e;
+          break;
+        }
+        below += count;
+      }
+      want -= below;
+      X |= digit << s;
+      top = s;
+      if (count == want) {                                     // the whole digit is wanted: no need to look inside
+        X |= (1u << s) - 1u;
+        all_equal = true;
+        break;
+      }
+    }
+    return X;
+  };
+  KeyCut cut;
+  cut.P = 0xFFFFFFFFu;
+  bool all_equal = false;
+  int want = k;
+  if (zeros >= k) {
+    cut.S = 0u;
+    if (zeros == k) return cut;
+  } else {
+    want = k - zeros;
+    cut.S = radix([&](int i, uint32_t& v) { v = b[i]; return b[i] - 1u < 0xFFFFFFFEu; }, want, all_equal);      // neither zero nor beyond the unit
+    if (all_equal) return cut;
+    int below = 0;
+#pragma unroll
+    for (int i = 0; i < R; ++i) below += __popcll(__ballot(b[i] < cut.S));
+    if (lane == 0) cb.b[wave] = below;
+    __syncthreads();
+    want = k;
+#pragma unroll
+    for (int w = 0; w < W; ++w) want -= cb.b[w];
+  }
+  // of the entries equal to S the `want` highest positions go (radix() returns at once if that is all of them)
+  cut.P = radix([&](int i, uint32_t& v) { v = np[i]; return b[i] == cut.S; }, want, all_equal);
+  return cut;
+}
+
+// What an eviction leaves for the kernel that moves the survivors: destination slots (evicted slots below the
+// budget) from the front of the unit's list, source slots (survivors at or above it) from its end, and their number.
+// The lists lie in the decode paths' logits, dead between calls, the numbers in the partials' maxima.
+__device__ __forceinline__ int* move_list(const Dev& d, int u) { return reinterpret_cast<int*>(d.logits + (size_t)u * d.cap * d.G); }
+__device__ __forceinline__ int* move_count(const Dev& d, int u) { return reinterpret_cast<int*>(d.ml + (size_t)u * d.slots * d.G * 2); }
+
+// Alg. 1 Step 4 for a unit of n > B entries up to the moves: the survivors' lists go to `lst` (the unit's list in
+// memory), evicted entries at or above B get their flag, the records are written.  evm: 32 NT bits of LDS.
+template <int R, int NT>
+__device__ __forceinline__ int evict_lists(const Dev& d, int u, Slots base, int n, int B, const uint32_t (&b)[R], const uint32_t (&np)[R],
+                                           int* lst, uint32_t* evm, CutBuf& cb, int tid) {
+  const int lane = tid & 63, wave = tid >> 6, k = n - B;
+  const KeyCut cut = select_low_keys<R, NT>(b, np, k, cb, tid);
+  evm[tid] = 0u;
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < R / 4; ++c) {
+    const int e0 = 4 * (tid + c * NT);
+    uint32_t m = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool ev = b[4 * c + e] != 0xFFFFFFFFu && cut(b[4 * c + e], np[4 * c + e]);
+      m |= (ev ? 1u : 0u) << e;
+      if (ev && e0 + e >= B) d.flags[base + (e0 + e)] = FLAG_SLIP;       // movers' sources get theirs when they have moved
+    }
+    if (m) atomicOr(&evm[e0 >> 5], m << (e0 & 31));
+  }
+  __syncthreads();
+  // holes = evicted slots below B, movers = surviving slots at or above B (equal counts), in ascending order
+  const uint32_t ev = evm[tid];
+  const int s0 = tid << 5;
+  const uint32_t below = (B >= s0 + 32) ? 0xFFFFFFFFu : (B <= s0 ? 0u : ((1u << (B - s0)) - 1u));
+  const uint32_t valid = (n >= s0 + 32) ? 0xFFFFFFFFu : (n <= s0 ? 0u : ((1u << (n - s0)) - 1u));
+  uint32_t hm = ev & below, mm = ~ev & ~below & valid;
+  const uint32_t packed = __popc(hm) | (__popc(mm) << 16);
+  uint32_t incl = packed;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t y = __shfl_up(incl, o);
+    if (lane >= o) incl += y;
+  }
+  if (lane == 63) cb.a[wave] = (int)incl;
+  __syncthreads();
+  uint32_t before = incl - packed, total = 0;
+#pragma unroll
+  for (int w = 0; w < NT / 64; ++w) {
+    if (w < wave) before += (uint32_t)cb.a[w];
+    total += (uint32_t)cb.a[w];
+  }
+  int hrank = (int)(before & 0xFFFFu), mrank = (int)(before >> 16);
+  while (hm) {
+    lst[hrank++] = s0 + __builtin_ctz(hm);
+    hm &= hm - 1;
+  }
+  while (mm) {
+    lst[d.cap - 1 - (mrank++)] = s0 + __builtin_ctz(mm);
+    mm &= mm - 1;
+  }
+  if (tid == 0) {
+    d.n[u] = B;
+    d.nev[u] = k;
+  }
+  return (int)(total & 0xFFFFu);
+}
+
+// Second kernel of an eviction: the survivors' rows, four per wavefront at a time (every load of a batch before
+// its first store), the unit's batches dealt over the workgroups along y (a unit's own y-th, as many as fill the
+// chip: one workgroup per unit leaves a layer of 64 units to 64 compute units and needs 100 round trips each).
+// Units along x, so that a unit's workgroups share an XCD's cache when their number is a multiple of eight.
+__global__ __launch_bounds__(kThreads) void evict_move_kernel(Dev d, int unit_begin) {
+  const int u = unit_begin + blockIdx.x;
+  const int h = *move_count(d, u);
+  const int first = 4 * (blockIdx.y * (kThreads / 64) + (threadIdx.x >> 6)), stride = 4 * gridDim.y * (kThreads / 64);
+  const Slots base = slots_of(d, u);
+  for (int r0 = first; r0 < h; r0 += stride) move_entries4(d, base, move_list(d, u), d.cap, r0, min(4, h - r0), threadIdx.x & 63);
+}
+
 // ------------------------------------------------------------------ finish
 // Ends a kernel that must leave the step scalars consistent: the last block
 // to arrive resets the work list and, if asked, advances time.  No fence: the
@@ -1894,7 +2124,7 @@ __device__ __forceinline__ u64 lrfu_update(const Dev& d, int u, Slots base, int 
   return block_sum_u64<NT>(sfix, rb, phase, tid);   // its barrier also completes val() for what follows
 }
 
-typedef int i32x4 __attribute__((ext_vector_type(4)));
+
 
 // Register-resident bookkeeping: thread tid of NT owns R = 4 C entries, in C
 // groups of four consecutive entries 4 (tid + c NT) .. + 3 (group c), so that
@@ -2742,42 +2972,104 @@ __global__ __launch_bounds__(kThreads) void seed_crf_kernel(Dev d, int unit_begi
   }
 }
 
-// Alg. 1 Step 4 on its own: scores decayed to the unit's last step, no update.
+// Alg. 1 Step 4 on its own: scores decayed to the unit's last step, no update.  One workgroup per unit; what is to
+// move follows in evict_move_kernel, except a single entry (one eviction per step), which moves here.
 // n_sink < 0: Alg. 1 Step 4 (retain the highest CRF_temp).  n_sink >= 0: the comparison policy of Sec. 2.3
 // that keeps the initial and the most recent tokens; the retention key is then the position itself, carried
 // as a bit pattern (the eviction only ever compares the bits), and the largest pattern for positions below n_sink.
-__global__ __launch_bounds__(kThreads) void evict_kernel(Dev d, int unit_begin, int n_sink) {
-  extern __shared__ unsigned char smem[];
-  float* val = reinterpret_cast<float*>(smem);
-  uint32_t* evm = reinterpret_cast<uint32_t*>(smem + (size_t)d.cap * 4);
+template <int R, int NT>
+__device__ __forceinline__ void evict_unit(const Dev& d, int u, Slots base, int n, int B, int n_sink, const float* s_tab, int s_tab_n,
+                                           uint32_t* evm, CutBuf& cb, RedBuf& rb, int* sh, int tid) {
+  const int t = d.t_unit[u];
+  uint32_t b[R], np[R];
+#pragma unroll
+  for (int c = 0; c < R / 4; ++c) {
+    const int e0 = 4 * (tid + c * NT);
+    f32x4 crf;
+    i32x4 tau, ps;
+    if (n_sink < 0)
+      load_meta<NT>(d, base, n, t, c, tid, crf, tau, ps);
+    else
+      ps = *reinterpret_cast<const i32x4*>(d.pos + (base + min(e0, (n - 1) & ~3)));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      uint32_t key;
+      if (n_sink >= 0) {
+        key = ps[e] < n_sink ? 0x7FFFFFFFu : (uint32_t)ps[e];
+      } else {
+        const int delta = min(max(t - tau[e], 0), d.tab_last);
+        const float tmp = __fmul_rn(decay_of(d, delta, s_tab, s_tab_n), crf[e]);
+        key = tmp < FLT_MIN ? 0u : __float_as_uint(tmp);
+      }
+      b[4 * c + e] = e0 + e < n ? key : 0xFFFFFFFFu;
+      np[4 * c + e] = ~(uint32_t)ps[e];
+    }
+    if (R > 16 && (c & 1)) __builtin_amdgcn_sched_barrier(0);          // two groups' state in flight: the keys need the registers
+  }
+  if (n - B == 1) {
+    u64 best = ~0ull;
+    int best_i = -1;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const u64 key = ((u64)b[i] << 32) | np[i];
+      if (b[i] != 0xFFFFFFFFu && key < best) {
+        best = key;
+        best_i = 4 * (tid + (i >> 2) * NT) + (i & 3);
+      }
+    }
+    int phase = 0;
+    const u64 gbest = block_min_u64<NT>(best, rb, phase, tid);
+    if (best == gbest && best_i >= 0) sh[0] = best_i;     // keys are unique: one writer
+    __syncthreads();
+    const int e = sh[0];
+    if (tid < 64) {
+      if (e != n - 1)
+        move_entry(d, base, n - 1, e, tid);
+      else if (tid == 0)
+        d.flags[base + e] = FLAG_SLIP;
+    }
+    if (tid == 0) {
+      d.n[u] = B;
+      d.nev[u] = 1;
+      *move_count(d, u) = 0;
+    }
+    return;
+  }
+  const int h = evict_lists<R, NT>(d, u, base, n, B, b, np, move_list(d, u), evm, cb, tid);
+  if (tid == 0) *move_count(d, u) = h;
+}
+
+template <int NT>
+__global__ __launch_bounds__(NT) void evict_kernel(Dev d, int unit_begin, int n_sink) {
+  __shared__ uint32_t evm[NT];
+  __shared__ int32_t s_row[kMaxChunks];
+  __shared__ float s_tab[kTabLds];
+  __shared__ CutBuf cb;
   __shared__ RedBuf rb;
-  __shared__ int sh[8];
+  __shared__ int sh[1];
   const int tid = threadIdx.x;
   const int u = unit_begin + blockIdx.x;
   const int n = d.n[u], B = d.budget[u];
-  const Slots base = slots_of(d, u);
-  int phase = 0;
   if (n <= B) {
-    if (tid == 0) d.nev[u] = 0;
+    if (tid == 0) {
+      d.nev[u] = 0;
+      *move_count(d, u) = 0;
+    }
     return;
   }
-  const int t = d.t_unit[u];
-  if (n_sink >= 0) {
-    for (int i = tid; i < n; i += kThreads) {
-      const int p = d.pos[base + i];
-      val[i] = __uint_as_float(p < n_sink ? 0x7FFFFFFFu : (uint32_t)p);
-    }
-  } else {
-    for (int i = tid; i < n; i += kThreads) {
-      int delta = t - d.tau[base + i];
-      delta = delta < 0 ? 0 : (delta > d.tab_last ? d.tab_last : delta);
-      float tmp = __fmul_rn(d.tab[delta], d.crf[base + i]);
-      if (tmp < FLT_MIN) tmp = 0.0f;
-      val[i] = tmp;
-    }
-  }
+  const int s_tab_n = min(kTabLds, d.tab_last + 1);
+  for (int i = tid; i < s_tab_n; i += NT) s_tab[i] = d.tab[i];
+  if (tid < d.max_seg) s_row[tid] = d.tbl[(size_t)u * d.max_seg + tid];
   __syncthreads();
-  evict_phase(d, u, base, n, B, ValLinear{val}, evm, reinterpret_cast<int*>(val), d.cap, rb, phase, sh, tid);
+  const Slots base{s_row};
+  if (n <= 4 * NT)
+    evict_unit<4, NT>(d, u, base, n, B, n_sink, s_tab, s_tab_n, evm, cb, rb, sh, tid);
+  else if (n <= 8 * NT)
+    evict_unit<8, NT>(d, u, base, n, B, n_sink, s_tab, s_tab_n, evm, cb, rb, sh, tid);
+  else if (n <= 16 * NT)
+    evict_unit<16, NT>(d, u, base, n, B, n_sink, s_tab, s_tab_n, evm, cb, rb, sh, tid);
+  else
+    evict_unit<32, NT>(d, u, base, n, B, n_sink, s_tab, s_tab_n, evm, cb, rb, sh, tid);
 }
 
 // ------------------------------------------------------------------ probe

@@ -1,0 +1,87 @@
+"""Evictions of any number of entries at the sizes where the selection changes its width (entries per thread, threads
+per unit) and the moves their distribution, against a plain sort by (score descending, position ascending)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+LAM = 0.5
+
+
+def _decay(delta):
+    x = np.power(LAM, np.minimum(delta, 200).astype(np.float64)).astype(np.float32)
+    x[x < np.finfo(np.float32).tiny] = 0.0
+    return x
+
+
+def _keep(crf, tau, pos, B, t, n_sink):
+    """Indices that stay: highest score (or the window policy's key) first, then lower position."""
+    if n_sink is None:
+        tmp = _decay(t - tau) * crf
+        tmp[tmp < np.finfo(np.float32).tiny] = 0.0
+        order = np.lexsort((pos, -tmp.astype(np.float64)))
+    else:
+        sink = pos < n_sink
+        order = np.lexsort((np.where(sink, pos, -pos), ~sink))
+    return np.sort(order[:B])
+
+
+def _check(units, cap, lengths, budgets, n_sink, sample, ties):
+    import torch
+    from paper_2601_16986_amd import ckv
+    rng = np.random.default_rng(5)
+    n_max = int(max(lengths))
+    t = 40000
+    budgets = np.asarray(budgets, np.int32).reshape(1, units, 1)
+    g = ckv.CrystalKV(1, units, 1, 1, 128, cap, budgets, lam=LAM, t0=t + 1, budget_min=1, budget_max=cap - 1)
+    gen = torch.Generator(device=g.device)
+    gen.manual_seed(1)
+    k = torch.randn((units, 1, n_max, 128), generator=gen, device=g.device).to(torch.bfloat16)
+    v = torch.randn((units, 1, n_max, 128), generator=gen, device=g.device).to(torch.bfloat16)
+    pos = np.stack([rng.permutation(t - 1)[:n_max] for _ in range(units)]).astype(np.int32)
+    tau = np.maximum(pos, (t - rng.geometric(0.05 if ties else 0.3, pos.shape)).astype(np.int32))
+    if ties:                                     # few distinct scores, most of them long decayed to zero
+        crf = rng.integers(1, 3, pos.shape).astype(np.float32)
+        tau = np.where(rng.random(pos.shape) < 0.7, pos, tau).astype(np.int32)
+    else:
+        crf = (1 + rng.random(pos.shape)).astype(np.float32)
+    dev = lambda x: torch.from_numpy(x.reshape(units, 1, n_max)).to(g.device).contiguous()
+    g.load_cache(0, k, v, torch.tensor(np.asarray(lengths, np.int32).reshape(units, 1), device=g.device), dev(crf), dev(tau), dev(pos))
+    if n_sink is None:
+        g.evict(0)
+    else:
+        g.evict_window(n_sink, 0)
+    assert g.status() == 0
+    for u in sample:
+        n, B = int(lengths[u]), int(budgets[0, u, 0])
+        keep = _keep(crf[u, :n], tau[u, :n], pos[u, :n], B, t, n_sink) if n > B else np.arange(n)
+        e = g.export_unit(0, u, 0)
+        assert e["n"] == len(keep) and e["n_evicted"] == n - len(keep)
+        order, want = np.argsort(e["pos"]), keep[np.argsort(pos[u, keep])]
+        assert np.array_equal(e["pos"][order], pos[u, want]), (u, n, B)
+        assert np.array_equal(e["crf"][order], crf[u, want]) and np.array_equal(e["tau"][order], tau[u, want])
+        assert np.array_equal(e["K"][order], k[u, 0].float().cpu().numpy()[want])
+        assert np.array_equal(e["V"][order], v[u, 0].float().cpu().numpy()[want])
+        gone = np.setdiff1d(np.arange(n), keep)
+        assert np.array_equal(e["evicted_pos"], np.sort(pos[u, gone])) and np.all(e["evicted_flags"] == 2)
+    g.close()
+
+
+@pytest.mark.parametrize("ties,n_sink", [(False, None), (True, None), (False, 3000)])
+@pytest.mark.parametrize("cap,lengths,budgets", [
+    (64, [33, 34, 40, 5], [32, 32, 1, 7]),
+    (4128, [4095, 4096, 4097, 1025], [2048, 4094, 4096, 1024]),
+    (8224, [8191, 8192, 8193, 300], [100, 8191, 4097, 299]),
+    (32768, [16384, 16385, 32767, 9350], [257, 16000, 16384, 2049]),
+])
+def test_wide_selection(cap, lengths, budgets, ties, n_sink):
+    _check(4, cap, lengths, budgets, n_sink, range(4), ties)
+
+
+@pytest.mark.parametrize("ties", [False, True])
+def test_many_small_units(ties):
+    """Enough units for workgroups of 256 threads, with lengths at the edges of 4, 8, 16 and 32 entries per thread."""
+    units, edge = 1056, [1, 33, 1023, 1024, 1025, 2048, 2049, 4096, 4097, 4600]
+    lengths = [edge[i % len(edge)] for i in range(units)]
+    budgets = [max(1, (n * (1 + i % 7)) // 8) for i, n in enumerate(lengths)]
+    _check(units, 4608, lengths, budgets, None, range(0, units, 37), ties)
