@@ -311,6 +311,19 @@ int launch_evict(ckv_ctx* c, hipStream_t s, int begin, int count, int n_sink) {
   return CKV_OK;
 }
 
+// Answer-probe classes of `count` units from `begin` on.  The classes' workgroups as in launch_evict.
+int launch_probe(ckv_ctx* c, const Dev& d, int begin, int count, const uint16_t* q, uint8_t* classes, hipStream_t s) {
+  const int spans = (d.cap + kProbeSpan - 1) / kProbeSpan;
+  hipLaunchKernelGGL(probe_scan_kernel, dim3((unsigned)count, (unsigned)((spans + 3) / 4)), dim3(kThreads), 0, s, d, begin, q);
+  CKV_HIP(c, hipGetLastError());
+  if (d.cap <= 32 * kThreads && count >= 4 * c->n_cu)
+    hipLaunchKernelGGL(probe_kernel<kThreads>, dim3((unsigned)count), dim3(kThreads), 0, s, d, begin, classes);
+  else
+    hipLaunchKernelGGL(probe_kernel<kWideThreads>, dim3((unsigned)count), dim3(kWideThreads), 0, s, d, begin, classes);
+  CKV_HIP(c, hipGetLastError());
+  return CKV_OK;
+}
+
 int upload_budgets(ckv_ctx* c, const int32_t* budgets, hipStream_t s) {
   const ckv_layout& l = c->lay;
   std::vector<long long> tot(l.batch, 0);
@@ -333,20 +346,16 @@ int fill32(ckv_ctx* c, void* p, uint32_t v, size_t count, hipStream_t s) {
   return CKV_OK;
 }
 
-// Address of the library's static scratch on each device, and whether its launch sequence number has been
-// started (at 1: the array is zero when the library is loaded, and a stamp of 0 must never look current).
-// The number is never restarted: partials that earlier calls left in the array carry earlier numbers.
+// Address of the library's static scratch on each device.
 std::mutex g_scratch_mutex;
 unsigned char* g_scratch_ptr[kMaxDevices] = {};
 
-int scratch_setup(int devid, hipStream_t s) {
+int scratch_setup(int devid) {
   if (devid < 0 || devid >= kMaxDevices) return CKV_EINVAL;
   std::lock_guard<std::mutex> lock(g_scratch_mutex);
   if (g_scratch_ptr[devid]) return CKV_OK;
   unsigned char* p = nullptr;
   if (hipGetSymbolAddress((void**)&p, HIP_SYMBOL(scratch)) != hipSuccess || !p) return CKV_EHIP;
-  hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t*>(p) + SC_SEQ, 1u, (size_t)1);
-  if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) return CKV_EHIP;
   g_scratch_ptr[devid] = p;
   return CKV_OK;
 }
@@ -411,7 +420,7 @@ int ckv_init(ckv_ctx** out, const ckv_layout* layout, const int32_t* budgets, co
     return CKV_EHIP;
   }
   c->device = devid;
-  if (int rc = scratch_setup(devid, s)) {        // the static scratch of ckv_probe_noalloc: its address on this device
+  if (int rc = scratch_setup(devid)) {        // the static scratch of ckv_probe_noalloc: its address on this device
     delete c;
     return rc;
   }
@@ -420,8 +429,7 @@ int ckv_init(ckv_ctx** out, const ckv_layout* layout, const int32_t* budgets, co
     delete c;
     return CKV_EINVAL;
   }
-  const void* lds_kernels[3] = {reinterpret_cast<const void*>(finish_kernel), reinterpret_cast<const void*>(probe_kernel),
-                                reinterpret_cast<const void*>(seed_hits_kernel)};
+  const void* lds_kernels[2] = {reinterpret_cast<const void*>(finish_kernel), reinterpret_cast<const void*>(seed_hits_kernel)};
   if (hipFuncSetAttribute(reinterpret_cast<const void*>(seed_scan_kernel<false>), hipFuncAttributeMaxDynamicSharedMemorySize, kSeedTiles * 4096) != hipSuccess ||
       hipFuncSetAttribute(reinterpret_cast<const void*>(seed_scan_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize, kSeedTiles * 4096) != hipSuccess) {
     delete c;
@@ -850,18 +858,7 @@ int ckv_probe(ckv_ctx* c, int32_t layer, const void* q_probe, uint8_t* classes, 
   const int begin = layer * c->units_per_layer, count = c->units_per_layer;
   hipStream_t s = (hipStream_t)stream;
   if (int rc = join_side(c, s)) return rc;
-  hipLaunchKernelGGL(prep_kernel, dim3((unsigned)((count + kPrepUnits - 1) / kPrepUnits)), dim3(kPrepThreads), 0, s, c->dev, begin, count,
-                     (const uint16_t*)nullptr, (const uint16_t*)nullptr, 0, INT_MAX, (const uint16_t*)nullptr);
-  CKV_HIP(c, hipGetLastError());
-  const long long max_items = (long long)count * c->dev.max_chunks;
-  long long blocks = 2ll * c->n_cu;
-  if (blocks > (max_items + 3) / 4) blocks = (max_items + 3) / 4;
-  hipLaunchKernelGGL(scan_kernel<false>, dim3((unsigned)blocks), dim3(kThreads), 0, s, c->dev, begin, (const uint16_t*)q_probe,
-                     (void*)nullptr, 0, -1);
-  CKV_HIP(c, hipGetLastError());
-  hipLaunchKernelGGL(probe_kernel, dim3((unsigned)count), dim3(kThreads), c->finish_lds, s, c->dev, begin, classes);
-  CKV_HIP(c, hipGetLastError());
-  return CKV_OK;
+  return launch_probe(c, c->dev, begin, count, (const uint16_t*)q_probe, classes, s);
 }
 
 int ckv_probe_noalloc(ckv_ctx* c, int32_t layer, const void* q_probe, uint8_t* classes, void* stream) {
@@ -875,51 +872,25 @@ int ckv_probe_noalloc(ckv_ctx* c, int32_t layer, const void* q_probe, uint8_t* c
   unsigned char* base = g_scratch_ptr[devid];     // set by ckv_init on this device
   if (!base) return fail(c, CKV_ESTATE, "the library's scratch was not set up on this device");
   const int begin = layer * c->units_per_layer, count = c->units_per_layer;
-  // the layer's scan scratch, carved from the static array instead of the context's workspace
+  // The layer's logits and softmax statistics, carved from the static array instead of the context's workspace.
+  // What a layer may need at most is a documented limit and stays what it was when the scan also kept a work list,
+  // stamps and merged partials there.
   const size_t U = (size_t)count, G = (size_t)c->dev.G, mc = (size_t)c->dev.max_chunks, slots = mc + 1;
-  size_t off = 0;
-  auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
-  const size_t o_sc = take(SC_COUNT * 4), o_items = take(U * mc * 16), o_stamp = take(U * slots * 4),
-               o_ml = take(U * slots * G * 2 * 4), o_partial = take(U * slots * G * kDim * 4),
-               o_logits = take(U * G * (size_t)c->dev.cap * 4);
+  const size_t o_partial = align_up(SC_COUNT * 4) + align_up(U * mc * 16) + align_up(U * slots * 4) + align_up(U * slots * G * 2 * 4),
+               o_logits = o_partial + align_up(U * slots * G * kDim * 4), off = o_logits + align_up(U * G * (size_t)c->dev.cap * 4);
   if (off > kScratchBytes)
     return fail(c, CKV_EWORKSPACE, "one layer's scan scratch (" + std::to_string(off >> 20) + " MiB) exceeds the library's static scratch of " +
                                        std::to_string(kScratchBytes >> 20) + " MiB: use ckv_probe");
-  // the layer's units as units 0 .. count-1 of a context of their own: caches and lengths from the real context,
-  // work list, partials, logits and step counters from the scratch
+  // the layer's units as units 0 .. count-1 of a context of their own
   Dev ds = c->dev;
   ds.units = count;
   ds.tbl += (size_t)begin * c->dev.max_seg;      // the rows name pool segments: the pools stay where they are
-  ds.owned += begin;
   ds.n += begin;
-  ds.budget += begin;
-  ds.t_unit += begin;
-  ds.nev += begin;
-  ds.window += begin;
-  ds.sc = reinterpret_cast<int32_t*>(base + o_sc);
-  ds.items = reinterpret_cast<int4*>(base + o_items);
-  ds.stamp = reinterpret_cast<int32_t*>(base + o_stamp);
-  ds.ml = reinterpret_cast<float*>(base + o_ml);
   ds.partial = reinterpret_cast<float*>(base + o_partial);
   ds.logits = reinterpret_cast<float*>(base + o_logits);
   hipStream_t s = (hipStream_t)stream;
   if (int rc = join_side(c, s)) return rc;
-  // counters that must start at zero (a fill kernel, not a memset: the call may be captured in a graph); the
-  // launch sequence number before them keeps counting
-  hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t*>(ds.sc) + SC_DONE, 0u, (size_t)(SC_CLAIM + 2 - SC_DONE));
-  CKV_HIP(c, hipGetLastError());
-  hipLaunchKernelGGL(prep_kernel, dim3((unsigned)((count + kPrepUnits - 1) / kPrepUnits)), dim3(kPrepThreads), 0, s, ds, 0, count,
-                     (const uint16_t*)nullptr, (const uint16_t*)nullptr, 0, INT_MAX, (const uint16_t*)nullptr);
-  CKV_HIP(c, hipGetLastError());
-  const long long max_items = (long long)count * ds.max_chunks;
-  long long blocks = 2ll * c->n_cu;
-  if (blocks > (max_items + 3) / 4) blocks = (max_items + 3) / 4;
-  hipLaunchKernelGGL(scan_kernel<false>, dim3((unsigned)blocks), dim3(kThreads), 0, s, ds, 0, (const uint16_t*)q_probe,
-                     (void*)nullptr, 0, -1);
-  CKV_HIP(c, hipGetLastError());
-  hipLaunchKernelGGL(probe_kernel, dim3((unsigned)count), dim3(kThreads), c->finish_lds, s, ds, 0, classes);
-  CKV_HIP(c, hipGetLastError());
-  return CKV_OK;
+  return launch_probe(c, ds, 0, count, (const uint16_t*)q_probe, classes, s);
 }
 
 int ckv_get_budgets(ckv_ctx* c, int32_t* budgets) {

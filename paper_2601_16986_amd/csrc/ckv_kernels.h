@@ -20,7 +20,7 @@
 //   load_cache_kernel, seed_state_kernel   fill a layer's caches
 //   seed_scan_kernel, seed_stats_kernel, seed_hits_kernel, seed_crf_kernel   scores of a loaded prompt from its last queries
 //   evict_kernel, evict_move_kernel   eviction + compaction on its own (Alg. 1 Step 4, or the sink + recent window policy)
-//   probe_kernel     answer-probe classes
+//   probe_scan_kernel, probe_kernel   answer-probe classes
 //   rebudget_kernel  Alg. 2 with integer apportionment, one workgroup/sequence
 //   rebalance_kernel pool segments between units after budgets have changed
 //   schedule_kernel  (ckv_unit_kernel.h) the fused kernel's order of units
@@ -3073,48 +3073,143 @@ __global__ __launch_bounds__(NT) void evict_kernel(Dev d, int unit_begin, int n_
 }
 
 // ------------------------------------------------------------------ probe
-// Sec. 3: classes of the entries of unit u under the probe query's weights.
-__global__ __launch_bounds__(kThreads) void probe_kernel(Dev d, int unit_begin, uint8_t* classes) {
-  extern __shared__ unsigned char smem[];
-  float* val = reinterpret_cast<float*>(smem);
-  __shared__ float sM[kMaxGroup], sInv[kMaxGroup], sW[2 * (kMaxChunks + 1) * kMaxGroup];
-  __shared__ RedBuf rb;
-  const int tid = threadIdx.x;
+// Sec. 3 needs the probe query's weights only: a pass over the keys (values are never read), then one workgroup per
+// unit for the classes.  Before, the probe ran the decode path's scan (keys and values, behind a kernel that built its work list)
+// and found the two class boundaries with 126 one-bit rounds over weights in LDS and positions in memory: 5 + 29 +
+// 390 us for a layer of 128 units of 2048 entries on average (up to 8192); now 16 + 16 us.
+//
+// probe_scan_kernel: one wavefront per 128 entries, whose four blocks of keys are requested at once (the pass is a
+// single round trip to memory per wavefront: a layer is too little work for a pipeline to fill).  Leaves the scaled
+// logits where the decode path does, and per span and head the softmax maximum and sum in the partials' place.
+// grid: (units of the layer, ceil(spans / 4)), kThreads threads.
+constexpr int kProbeBlks = 4, kProbeSpan = kProbeBlks * kBlk;
+__device__ __forceinline__ float* probe_stats(const Dev& d, int u) { return d.partial + (size_t)u * d.slots * d.G * kDim; }
+
+__global__ __launch_bounds__(kThreads, 2) void probe_scan_kernel(Dev d, int unit_begin, const uint16_t* __restrict__ q) {
+  __shared__ float s_lg[kThreads / 64][kMaxGroup * kLgRow];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int urel = blockIdx.x, u = unit_begin + urel;
-  const int n = d.n[u];
-  const Slots base = slots_of(d, u);
-  int phase = 0;
-  if (n > 0) {
-    merge_partials(d, u, urel, (n + kChunk - 1) / kChunk, d.sc[SC_SEQ], sM, sInv, sW, nullptr, tid);
-    mean_weights(d, unit_logits(d, u), n, sM, sInv, val, tid);
-    const int kq = (3 * n) / 10;
-    // order key: ascending = (weight asc, position desc); Crystal = kq largest, Slip = kq smallest
-    u64 lo_cut = 0, hi_cut = ~0ull;
-    if (kq > 0) {
-      for (int pass = 0; pass < 2; ++pass) {
-        const int k = pass == 0 ? kq : (n - kq + 1);      // k-th smallest key
-        u64 X = 0;
-        for (int bit = 62; bit >= 0; --bit) {
-          const u64 trial = X | (1ull << bit);
-          int cnt = 0;
-          for (int i = tid; i < n; i += kThreads) cnt += evict_key(val[i], d.pos[base + i]) < trial ? 1 : 0;
-          cnt = block_sum_int(cnt, rb, phase, tid);
-          if (cnt < k) X = trial;
-        }
-        if (pass == 0) lo_cut = X; else hi_cut = X;
+  const int span = blockIdx.y * (kThreads / 64) + w, e0 = span * kProbeSpan;
+  const int seg = d.tbl[(size_t)u * d.max_seg + min(e0 / kSeg, d.max_seg - 1)];
+  const int nv = d.n[u] - e0;
+  if (nv <= 0) return;
+  const int G = d.G, j = lane & 15, kg = lane >> 4;
+  const int nb = min(kProbeBlks, (nv + kBlk - 1) / kBlk);
+  const uint16_t* kb = d.K + (size_t)seg * kSegElems + (size_t)((e0 % kSeg) / kBlk) * kBlkElems + lane * 8;
+  KFrag k[kProbeBlks];
+#pragma unroll
+  for (int b = 0; b < kProbeBlks; ++b) load_k(k[b], kb + (size_t)min(b, nb - 1) * kBlkElems);
+  bf16x8 qv[4];
+  const uint16_t* qrow = q + ((size_t)urel * G + (j < G ? j : 0)) * kDim + 8 * kg;     // columns beyond the group: never looked at
+#pragma unroll
+  for (int s = 0; s < 4; ++s) qv[s] = as_bf16x8(*reinterpret_cast<const u32x4*>(qrow + 32 * s));
+  float* lg_dst = d.logits + ((size_t)u * d.cap + (size_t)e0) * G + 4 * min(lane, 8 * G - 1);
+  float m = -INFINITY, l = 0.f;
+#pragma unroll
+  for (int b = 0; b < kProbeBlks; ++b) {
+    if (b < nb) {
+      float sv[8];
+      scan_qk(k[b], qv, sv, d.scale_log2e, b * kBlk, nv, s_lg[w], kLgRow, lg_dst, G, lane);
+      const float bm = fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
+      if (bm > m) {
+        l *= fast_exp2(m - bm);
+        m = bm;
       }
-    }
-    for (int i = tid; i < n; i += kThreads) {
-      const u64 key = evict_key(val[i], d.pos[base + i]);
-      uint8_t c = 1;
-      if (kq > 0) {
-        if (key >= hi_cut) c = 2;
-        else if (key <= lo_cut) c = 0;
+      if (m > -INFINITY) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) l += fast_exp2(sv[i] - m);
       }
-      classes[(size_t)urel * d.cap + i] = c;
     }
   }
-  step_epilogue(d, 0, 0, tid);
+  // the column's four lanes (kg = 0..3), in a fixed order
+  float M = fmaxf(m, __shfl_xor(m, 16));
+  M = fmaxf(M, __shfl_xor(M, 32));
+  const float mine = m > -INFINITY ? l * fast_exp2(m - M) : 0.f;
+  const float l0 = __shfl(mine, j), l1 = __shfl(mine, j + 16), l2 = __shfl(mine, j + 32), l3 = __shfl(mine, j + 48);
+  if (kg == 0 && j < G) *reinterpret_cast<float2*>(probe_stats(d, u) + ((size_t)span * G + j) * 2) = make_float2(M, (l0 + l1) + (l2 + l3));
+}
+
+// Classes of the entries of a unit of n <= R NT entries.  Both boundaries come from the eviction's selection
+// (ascending keys: lower weight first, then higher position).
+template <int R, int NT>
+__device__ __forceinline__ void probe_unit(const Dev& d, int u, Slots base, int n, const float* sM, const float* sInv, uint8_t* cls, CutBuf& cb,
+                                           int tid) {
+  uint32_t b[R], np[R];
+  {
+    float a[R];
+    mean_weights_regs<R, NT>(d, unit_logits(d, u), n, sM, sInv, a, tid);
+#pragma unroll
+    for (int c = 0; c < R / 4; ++c) {
+      const int e0 = 4 * (tid + c * NT);
+      const i32x4 ps = *reinterpret_cast<const i32x4*>(d.pos + (base + min(e0, (n - 1) & ~3)));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        b[4 * c + e] = e0 + e < n ? __float_as_uint(a[4 * c + e]) : 0xFFFFFFFFu;
+        np[4 * c + e] = ~(uint32_t)ps[e];
+      }
+    }
+  }
+  const int kq = (3 * n) / 10;
+  KeyCut slip{0u, 0u}, rest{0u, 0u};
+  if (kq > 0) {
+    slip = select_low_keys<R, NT>(b, np, kq, cb, tid);
+    __syncthreads();                                       // the first selection's buffers are free
+    rest = select_low_keys<R, NT>(b, np, n - kq, cb, tid);
+  }
+#pragma unroll
+  for (int c = 0; c < R / 4; ++c) {
+    const int e0 = 4 * (tid + c * NT);
+    uint32_t packed = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const uint32_t bb = b[4 * c + e], pp = np[4 * c + e];
+      const uint32_t k = kq == 0 ? 1u : slip(bb, pp) ? 0u : rest(bb, pp) ? 1u : 2u;
+      packed |= k << (8 * e);
+    }
+    if (e0 + 3 < n && (reinterpret_cast<uintptr_t>(cls) & 3) == 0) {
+      *reinterpret_cast<uint32_t*>(cls + e0) = packed;
+    } else {
+      for (int e = 0; e < 4 && e0 + e < n; ++e) cls[e0 + e] = (uint8_t)(packed >> (8 * e));
+    }
+  }
+}
+
+template <int NT>
+__global__ __launch_bounds__(NT) void probe_kernel(Dev d, int unit_begin, uint8_t* classes) {
+  __shared__ float sM[kMaxGroup], sInv[kMaxGroup];
+  __shared__ int32_t s_row[kMaxChunks];
+  __shared__ CutBuf cb;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int urel = blockIdx.x, u = unit_begin + urel;
+  const int n = d.n[u];
+  if (n <= 0) return;
+  if (tid < d.max_seg) s_row[tid] = d.tbl[(size_t)u * d.max_seg + tid];
+  // softmax maximum and 1 / sum of every head over the unit's spans: a wavefront per head
+  const int G = d.G, spans = (n + kProbeSpan - 1) / kProbeSpan;
+  for (int g = tid >> 6; g < G; g += NT / 64) {
+    const float* st = probe_stats(d, u) + 2 * g;
+    float M = -INFINITY, L = 0.f;
+    for (int s = lane; s < spans; s += 64) M = fmaxf(M, st[(size_t)s * G * 2]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) M = fmaxf(M, __shfl_xor(M, o));
+    for (int s = lane; s < spans; s += 64) L += st[(size_t)s * G * 2 + 1] * fast_exp2(st[(size_t)s * G * 2] - M);
+    L = wave_sum_f32(L);
+    if (lane == 0) {
+      sM[g] = M;
+      sInv[g] = 1.0f / L;
+    }
+  }
+  __syncthreads();
+  const Slots base{s_row};
+  uint8_t* cls = classes + (size_t)urel * d.cap;
+  if (n <= 4 * NT)
+    probe_unit<4, NT>(d, u, base, n, sM, sInv, cls, cb, tid);
+  else if (n <= 8 * NT)
+    probe_unit<8, NT>(d, u, base, n, sM, sInv, cls, cb, tid);
+  else if (n <= 16 * NT)
+    probe_unit<16, NT>(d, u, base, n, sM, sInv, cls, cb, tid);
+  else
+    probe_unit<32, NT>(d, u, base, n, sM, sInv, cls, cb, tid);
 }
 
 // ------------------------------------------------------------------ Alg. 2
