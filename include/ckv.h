@@ -265,8 +265,8 @@ int ckv_probe(ckv_ctx* ctx, int32_t layer, const void* q_probe, uint8_t* classes
 
 /* ckv_probe for callers that cannot allocate or bring a workspace of their own for it: code under HIP graph
  * capture, tight serving loops that probe beside decode steps, harnesses that forbid hipMalloc.  Same
- * arguments, same result (the classes are identical, byte for byte), but the scan's scratch - work list,
- * partial results, logits, launch counters - lives in a static device array of 128 MiB that the library
+ * arguments, same result (the classes are identical, byte for byte), but the scan's scratch - logits and
+ * softmax statistics - lives in a static device array of 128 MiB that the library
  * owns on every GPU it is loaded on (held until the process ends), not in the context's workspace; so the
  * call leaves the context's workspace alone.  It calls no hipMalloc, hipFree or
  * other allocating routine.  A layer whose scratch (about batch * n_kv_heads * cap * 6 * G bytes, G = n_q_heads / n_kv_heads) does

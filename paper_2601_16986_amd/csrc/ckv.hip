@@ -57,7 +57,7 @@ struct ckv_ctx {
   } fused[2];                   // [0]: 4 wavefronts, 2 workgroups per CU; [1]: 2 wavefronts, 4 workgroups per CU
   std::vector<uint8_t> prompt_loaded;
   std::vector<int32_t> prompt_len;   // per layer: length of a prompt loaded whole and untouched since, else -1
-  // Deferred bookkeeping of single-layer steps (CKV_DEFER_BOOKKEEPING): finish_kernel (late = 1) runs on
+  // Deferred bookkeeping of single-layer steps (CKV_DEFER_BOOKKEEPING): finish_kernel runs on
   // one of the `side` streams (layer l on side[l % kSide], so that the bookkeeping of consecutive layers, which
   // share nothing, can overlap), ordered by events against the caller's stream.  pending[l]: layer l's
   // bookkeeping has been queued there and nothing on the caller's side has waited for it yet.
@@ -153,7 +153,7 @@ std::vector<float> make_decay_table(float lambda) {
 }
 
 struct Carve {
-  size_t n, budget, t_unit, nev, window, sc, stamp, tab, items, partial, ml, logits, btotal, order, layer_ts, arrive, msum, tbl, owned, spare, seedml, seedmi, seedrw, total;
+  size_t n, budget, t_unit, nev, window, sc, tab, partial, ml, logits, btotal, order, layer_ts, arrive, msum, tbl, owned, spare, seedml, seedmi, seedrw, total;
 };
 
 Carve carve(const ckv_layout* l, size_t tab_len) {
@@ -170,15 +170,13 @@ Carve carve(const ckv_layout* l, size_t tab_len) {
   c.arrive = take(U * 4);
   c.window = take(U * 8);
   c.sc = take(SC_COUNT * 4);
-  c.stamp = take(U * (mc + 1) * 4);
   c.tab = take(tab_len * 4);
-  c.items = take(U * mc * 16);
   c.partial = take(U * (mc + 1) * G * kDim * 4);
   c.ml = take(U * (mc + 1) * G * 2 * 4);
   c.logits = take(U * G * (size_t)l->cap * 4);
   c.btotal = take((size_t)l->batch * 8);
   c.order = take(U * 4);
-  c.layer_ts = take((size_t)l->n_layers * 8);
+  c.layer_ts = take((size_t)l->n_layers * 4);
   c.msum = take(U * kMaxGroup * 2 * 4);
   c.tbl = take(U * mc * 4);
   c.owned = take(U * 4);
@@ -226,6 +224,28 @@ int profile_events(ckv_ctx* c, hipEvent_t* e0, hipEvent_t* e1) {
   return CKV_OK;
 }
 
+// The bookkeeping of `count` units from `begin` on, behind their scan.  Workgroups of 256 threads where no unit can
+// hold more than eight entries per thread, else 1024.
+int launch_finish(ckv_ctx* c, hipStream_t s, int begin, int count, uint32_t flags, int advance, int layer_time) {
+  if (c->lay.cap <= 8 * kThreads)
+    hipLaunchKernelGGL(finish_kernel<kThreads>, dim3((unsigned)count), dim3(kThreads), c->finish_lds, s, c->dev, begin, flags, advance, layer_time);
+  else
+    hipLaunchKernelGGL(finish_kernel<kWideThreads>, dim3((unsigned)count), dim3(kWideThreads), c->finish_lds, s, c->dev, begin, flags, advance, layer_time);
+  CKV_HIP(c, hipGetLastError());
+  return CKV_OK;
+}
+
+// Attention of `count` units from `begin` on, the new entries included.  At most two workgroups fit on a compute unit
+// (the unused dynamic LDS sees to that): the kernel's registers would allow three, and the dispatcher then crowds some
+// compute units while others idle (2.43 against 2.11 ms per step of 48 layers of 128 units; one per compute unit: 2.22).
+int launch_layer_scan(ckv_ctx* c, hipStream_t s, int begin, int count, const uint16_t* q, const uint16_t* k_new, const uint16_t* v_new, void* out,
+                      int logits, int defer_layer, int advance) {
+  hipLaunchKernelGGL((layer_scan_kernel<4, 1>), dim3((unsigned)count, (unsigned)((c->dev.max_chunks + 3) / 4)), dim3(256), kLayerScanPad, s, c->dev,
+                     begin, q, k_new, v_new, out, logits, defer_layer, advance);
+  CKV_HIP(c, hipGetLastError());
+  return CKV_OK;
+}
+
 // Queue the bookkeeping of the layers scanned since the last group went out.
 int flush_group(ckv_ctx* c) {
   if (c->group_count == 0) return CKV_OK;
@@ -235,9 +255,7 @@ int flush_group(ckv_ctx* c) {
   CKV_HIP(c, hipEventRecord(c->ev_out, c->group_stream));
   hipStream_t side = c->side[c->group_launches++ % kSide];
   CKV_HIP(c, hipStreamWaitEvent(side, c->ev_out, 0));
-  hipLaunchKernelGGL(finish_kernel, dim3((unsigned)(count * upl)), dim3(kThreads), c->finish_lds, side, c->dev, first * upl,
-                     (void*)nullptr, c->group_flags, 0, INT_MAX, -1, 2, -2);
-  CKV_HIP(c, hipGetLastError());
+  if (int rc = launch_finish(c, side, first * upl, count * upl, c->group_flags, 0, 1)) return rc;
   CKV_HIP(c, hipEventRecord(c->ev_book[first], side));
   for (int l = first; l < first + count; ++l) c->pending[l] = 1 + first;     // whose event to wait for
   c->any_pending = true;
@@ -429,7 +447,8 @@ int ckv_init(ckv_ctx** out, const ckv_layout* layout, const int32_t* budgets, co
     delete c;
     return CKV_EINVAL;
   }
-  const void* lds_kernels[2] = {reinterpret_cast<const void*>(finish_kernel), reinterpret_cast<const void*>(seed_hits_kernel)};
+  const void* lds_kernels[3] = {reinterpret_cast<const void*>(finish_kernel<kThreads>), reinterpret_cast<const void*>(finish_kernel<kWideThreads>),
+                                reinterpret_cast<const void*>(seed_hits_kernel)};
   if (hipFuncSetAttribute(reinterpret_cast<const void*>(seed_scan_kernel<false>), hipFuncAttributeMaxDynamicSharedMemorySize, kSeedTiles * 4096) != hipSuccess ||
       hipFuncSetAttribute(reinterpret_cast<const void*>(seed_scan_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize, kSeedTiles * 4096) != hipSuccess) {
     delete c;
@@ -493,10 +512,8 @@ int ckv_init(ckv_ctx** out, const ckv_layout* layout, const int32_t* budgets, co
   d.window = (u64*)(ws + cv.window);
   d.sc = (int32_t*)(ws + cv.sc);
   d.tab = (const float*)(ws + cv.tab);
-  d.items = (int4*)(ws + cv.items);
   d.partial = (float*)(ws + cv.partial);
   d.ml = (float*)(ws + cv.ml);
-  d.stamp = (int32_t*)(ws + cv.stamp);
   d.logits = (float*)(ws + cv.logits);
   d.btotal = (long long*)(ws + cv.btotal);
   d.order = (int32_t*)(ws + cv.order);
@@ -536,7 +553,6 @@ int ckv_init(ckv_ctx** out, const ckv_layout* layout, const int32_t* budgets, co
   if ((rc = fill32(c, ws, 0u, cv.tab / 4, s))) return bail(rc);
   if ((rc = fill32(c, d.t_unit, (uint32_t)(params->t0 - 1), (size_t)c->units, s))) return bail(rc);
   if ((rc = fill32(c, d.sc + SC_T, (uint32_t)params->t0, 1, s))) return bail(rc);
-  if ((rc = fill32(c, d.sc + SC_SEQ, 1u, 1, s))) return bail(rc);
   if ((rc = fill32(c, d.sc + SC_QUEUE, 0u, 1, s))) return bail(rc);
   if (hipMemcpyAsync((void*)d.tab, tab.data(), tab.size() * 4, hipMemcpyHostToDevice, s) != hipSuccess) return bail(CKV_EHIP);
   if ((rc = upload_budgets(c, budgets, s))) return bail(rc);
@@ -657,17 +673,8 @@ int ckv_decode_step(ckv_ctx* c, int32_t layer, const void* q, const void* k_new,
       if (int rc = profile_events(c, &e0, &e1)) return rc;
       CKV_HIP(c, hipEventRecord(e0, s));
     }
-    // At most two of its workgroups fit on a compute unit (the unused dynamic LDS sees to that): the kernel's
-    // registers would allow three, and the dispatcher then crowds some compute units while others idle
-    // (2.43 against 2.11 ms per step of 48 layers of 128 units; one per compute unit: 2.22).
-    hipLaunchKernelGGL((layer_scan_kernel<4, 1>), dim3((unsigned)count, (unsigned)((c->dev.max_chunks + 3) / 4)), dim3(256), kLayerScanPad, s,
-                       c->dev, begin, (const uint16_t*)q, (const uint16_t*)k_new, (const uint16_t*)v_new, out, (int)layer);
-    CKV_HIP(c, hipGetLastError());
+    if (int rc = launch_layer_scan(c, s, begin, count, (const uint16_t*)q, (const uint16_t*)k_new, (const uint16_t*)v_new, out, 1, (int)layer, advance)) return rc;
     if (c->profile) CKV_HIP(c, hipEventRecord(e1, s));
-    if (advance) {
-      hipLaunchKernelGGL(advance_kernel, dim3(1), dim3(64), 0, s, c->dev);
-      CKV_HIP(c, hipGetLastError());
-    }
     const uint32_t kflags = flags & CKV_FUSE_EVICT;
     if (c->group_count && (c->group_flags != kflags || c->group_stream != s || c->group_first + c->group_count != layer))
       if (int rc = flush_group(c)) return rc;
@@ -682,13 +689,6 @@ int ckv_decode_step(ckv_ctx* c, int32_t layer, const void* q, const void* k_new,
     if (c->group_count == kBookGroup || advance) return flush_group(c);
     return CKV_OK;
   }
-  // unit_kernel<W> appends by itself; the separate kernels get the new entries and their work list from prep_kernel
-  if (!fused) {
-    hipLaunchKernelGGL(prep_kernel, dim3((unsigned)((count + kPrepUnits - 1) / kPrepUnits)), dim3(kPrepThreads), 0, s, c->dev, begin, count,
-                       (const uint16_t*)k_new, (const uint16_t*)v_new, 1, INT_MAX, (const uint16_t*)q);
-    CKV_HIP(c, hipGetLastError());
-  }
-
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (c->profile) {
     if (int rc = profile_events(c, &e0, &e1)) return rc;
@@ -714,26 +714,19 @@ int ckv_decode_step(ckv_ctx* c, int32_t layer, const void* q, const void* k_new,
     if (advance && (flags & CKV_FUSE_EVICT)) return rebalance_after_eviction(c);
     return CKV_OK;
   }
-  const long long max_items = (long long)count * c->dev.max_chunks;
-  long long blocks = 2ll * c->n_cu;
-  if (blocks > (max_items + 3) / 4) blocks = (max_items + 3) / 4;
-  const uint32_t kflags = flags & CKV_FUSE_EVICT;
-  // when nothing but the output is due on the caller's stream, the scan merges its own partials and ends the step
-  const bool scan_merges = (flags & CKV_ATTENTION_ONLY) != 0;
-  if (scan_merges)
-    hipLaunchKernelGGL(scan_kernel<true>, dim3((unsigned)blocks), dim3(kThreads), 0, s, c->dev, begin, (const uint16_t*)q, out,
-                       advance, -1);
-  else
-    hipLaunchKernelGGL(scan_kernel<false>, dim3((unsigned)blocks), dim3(kThreads), 0, s, c->dev, begin, (const uint16_t*)q,
-                       (void*)nullptr, 0, -1);
-  CKV_HIP(c, hipGetLastError());
+  // Few units: several workgroups per unit attend and write the output, then the bookkeeping (or, without it, what
+  // the append leaves behind).
+  const bool attention_only = (flags & CKV_ATTENTION_ONLY) != 0;
+  if (int rc = launch_layer_scan(c, s, begin, count, (const uint16_t*)q, (const uint16_t*)k_new, (const uint16_t*)v_new, out, attention_only ? 0 : 1, -1, 0))
+    return rc;
   if (c->profile) CKV_HIP(c, hipEventRecord(e1, s));
-  if (flags & CKV_ATTENTION_ONLY) return CKV_OK;
-
-  hipLaunchKernelGGL(finish_kernel, dim3((unsigned)count), dim3(kThreads), c->finish_lds, s, c->dev, begin, out,
-                     kflags, advance, INT_MAX, -1, 0, 0);
-  CKV_HIP(c, hipGetLastError());
-  if (advance && kflags) return rebalance_after_eviction(c);
+  if (attention_only) {
+    hipLaunchKernelGGL(append_kernel, dim3(1), dim3(kWideThreads), 0, s, c->dev, begin, count, advance);
+    CKV_HIP(c, hipGetLastError());
+    return CKV_OK;
+  }
+  if (int rc = launch_finish(c, s, begin, count, flags & CKV_FUSE_EVICT, advance, 0)) return rc;
+  if (advance && (flags & CKV_FUSE_EVICT)) return rebalance_after_eviction(c);
   return CKV_OK;
 }
 

@@ -2,18 +2,11 @@
 // v_mfma_f32_16x16x32_bf16).  One decode step runs as one of
 //
 //   unit_kernel<W> (ckv_unit_kernel.h)  everything in one persistent kernel, a workgroup per unit at a time
-//   layer_scan_kernel + finish_kernel   one layer: append, attention and output in one kernel on the caller's
-//                  stream, the bookkeeping (finish_kernel, late = 2) afterwards on a stream of the context's
-//   prep_kernel, scan_kernel, finish_kernel   the separate path:
-//     prep_kernel    append (k_new, v_new) into the tiled cache, build the list
-//                    of scan work items (unit, chunk of 256 entries)
-//     scan_kernel    the HBM-bound pass: stream K and V once, QK^T and PV on the
-//                    matrix cores, online softmax per work item; leaves the
-//                    scaled logits and one partial (max, sum, acc) per item;
-//                    on request also merges the partials -> out and ends the step
-//     finish_kernel  one workgroup per unit: merge partials -> out, mean
-//                    attention weight per entry, top-p hit mask, CRF update,
-//                    aggregated CRF, and (optionally) eviction + compaction
+//   layer_scan_kernel, finish_kernel   the units of one layer, or of a small context: append, attention and output in
+//                  one kernel with several workgroups per unit, then the bookkeeping, one workgroup per unit: mean
+//                  attention weight per entry, top-p hit mask, CRF update, aggregated CRF, and (optionally) eviction +
+//                  compaction; on the caller's stream, or later on a stream of the context's (deferred)
+//   layer_scan_kernel, append_kernel   the same without bookkeeping (attention-only steps)
 //
 // and beside the step:
 //
@@ -33,6 +26,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "ckv_layout.h"
 
 namespace ckv {
@@ -43,8 +38,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned long long u64;
 
-// SC_CLAIM is a 64-bit counter (8-byte aligned): low word = work items published, high word = their blocks
-enum { SC_T = 0, SC_WINDOW_STEPS = 1, SC_SEQ = 2, SC_DONE = 3, SC_STATUS = 4, SC_DONE_RB = 5, SC_QUEUE = 6, SC_SPARE = 7, SC_CLAIM = 8, SC_COUNT = 64 };
+enum { SC_T = 0, SC_WINDOW_STEPS = 1, SC_DONE = 2, SC_STATUS = 3, SC_DONE_RB = 4, SC_QUEUE = 5, SC_SPARE = 6, SC_COUNT = 64 };
 enum { FLAG_HIT = 1, FLAG_SLIP = 2 };
 constexpr int kThreads = 256;
 constexpr int kWideThreads = 1024;        // kernels with one workgroup per unit and few units
@@ -76,16 +70,14 @@ struct Dev {
   u64* window;           // [units] fixed-point sum of aggregated CRF since the last re-allocation
   int32_t* sc;           // scalars, SC_*
   const float* tab;      // lambda^delta, delta = 0..tab_last
-  int4* items;           // scan work list: {unit, chunk, entries from the chunk's start, blocks before this item}
-  float* partial;        // [units*slots][G][128]
+  float* partial;        // [units*slots][G][128] attention accumulated by one workgroup of a scan, a slot each
   float* ml;             // [units*slots][G][2] (running max, sum)
-  int32_t* stamp;        // [units*slots] launch sequence number that last wrote the slot
   float* logits;         // [units][cap/32][G][32] scaled logits (base-2 domain)
   long long* btotal;     // [Bz] budget total per sequence
   int32_t* order;        // [units] unit indices by descending budget (schedule of the fused kernel)
-  int32_t* layer_ts;     // [layers][2] time and launch sequence number of a layer's last deferred step (scan_kernel<true> -> finish_kernel with late = 1)
-  int32_t* arrive;       // [units] runs of the unit published so far by a scan that also merges (zero between launches)
-  float* msum;           // [units][8][2] softmax maximum (base-2 domain) and 1 / sum per query head, left by layer_scan_kernel for its bookkeeping
+  int32_t* layer_ts;     // [layers] time of a layer's last step with deferred bookkeeping (layer_scan_kernel -> finish_kernel)
+  int32_t* arrive;       // [units] workgroups of the unit that have published their partial (zero between launches)
+  float* msum;           // [units][8][2] softmax maximum (base-2 domain) and 1 / sum per query head, left by layer_scan_kernel for finish_kernel
 };
 
 
@@ -219,15 +211,36 @@ __device__ __forceinline__ void block_sync(RedBuf& rb) {
 // Block-wide reductions over NT threads with a fixed combination order
 // (deterministic).  `rb` is a [2][NT/64] LDS array used alternately, so one
 // barrier per call suffices.  NT = 64: the wavefront's own reduction, nothing else.
+// With 8 or 16 wavefronts a lane reads one wavefront's value and the row of 16 lanes adds them up (every thread
+// reading all 16 would put 256 LDS reads on the compute unit per call); with fewer every thread reads them all.
+template <int NT>
+constexpr bool kRowReduce = NT >= 512;
+
+template <int NT, class T, class Op, class Dpp1, class Dpp2, class Dpp3, class Dpp4>
+__device__ __forceinline__ T row_combine(T r, Op op, Dpp1 d1, Dpp2 d2, Dpp3 d3, Dpp4 d4) {
+  static_assert(NT == 512 || NT == 1024, "8 or 16 wavefronts");
+  r = op(r, d1(r));
+  r = op(r, d2(r));
+  r = op(r, d3(r));
+  if constexpr (NT == 1024) r = op(r, d4(r));
+  return r;
+}
+
 template <int NT = kThreads>
 __device__ __forceinline__ u64 block_sum_u64(u64 v, RedBuf& rb, int& phase, int tid) {
   v = wave_sum_u64(v);
   if constexpr (NT == 64) return v;
   if ((tid & 63) == 0) rb.v[phase][tid >> 6] = v;
   block_sync<NT>(rb);
-  u64 r = rb.v[phase][0];
+  u64 r;
+  if constexpr (kRowReduce<NT>) {
+    r = row_combine<NT>(rb.v[phase][tid & (NT / 64 - 1)], [](u64 a, u64 b) { return a + b; }, dpp_u64<kDppQuadSwap1>, dpp_u64<kDppQuadSwap2>,
+                        dpp_u64<kDppRowHalfMirror>, dpp_u64<kDppRowMirror>);
+  } else {
+    r = rb.v[phase][0];
 #pragma unroll
-  for (int w = 1; w < NT / 64; ++w) r += rb.v[phase][w];
+    for (int w = 1; w < NT / 64; ++w) r += rb.v[phase][w];
+  }
   phase ^= 1;
   return r;
 }
@@ -238,11 +251,22 @@ __device__ __forceinline__ int block_sum_int(int v, RedBuf& rb, int& phase, int 
   if constexpr (NT == 64) return v;
   if ((tid & 63) == 0) rb.v[phase][tid >> 6] = (u64)(uint32_t)v;
   block_sync<NT>(rb);
-  int r = (int)(uint32_t)rb.v[phase][0];
+  int r;
+  if constexpr (kRowReduce<NT>) {
+    r = row_combine<NT>((int)(uint32_t)rb.v[phase][tid & (NT / 64 - 1)], [](int a, int b) { return a + b; }, dpp_i32<kDppQuadSwap1>,
+                        dpp_i32<kDppQuadSwap2>, dpp_i32<kDppRowHalfMirror>, dpp_i32<kDppRowMirror>);
+  } else {
+    r = (int)(uint32_t)rb.v[phase][0];
 #pragma unroll
-  for (int w = 1; w < NT / 64; ++w) r += (int)(uint32_t)rb.v[phase][w];
+    for (int w = 1; w < NT / 64; ++w) r += (int)(uint32_t)rb.v[phase][w];
+  }
   phase ^= 1;
   return r;
+}
+
+template <int kCtrl>
+__device__ __forceinline__ float dpp_f32(float v) {
+  return __int_as_float(dpp_i32<kCtrl>(__float_as_int(v)));
 }
 
 template <int NT = kThreads>
@@ -251,9 +275,15 @@ __device__ __forceinline__ float block_sum_f32(float v, RedBuf& rb, int& phase, 
   if constexpr (NT == 64) return v;
   if ((tid & 63) == 0) rb.v[phase][tid >> 6] = (u64)__float_as_uint(v);
   block_sync<NT>(rb);
-  float r = __uint_as_float((uint32_t)rb.v[phase][0]);
+  float r;
+  if constexpr (kRowReduce<NT>) {
+    r = row_combine<NT>(__uint_as_float((uint32_t)rb.v[phase][tid & (NT / 64 - 1)]), [](float a, float b) { return a + b; },
+                        dpp_f32<kDppQuadSwap1>, dpp_f32<kDppQuadSwap2>, dpp_f32<kDppRowHalfMirror>, dpp_f32<kDppRowMirror>);
+  } else {
+    r = __uint_as_float((uint32_t)rb.v[phase][0]);
 #pragma unroll
-  for (int w = 1; w < NT / 64; ++w) r += __uint_as_float((uint32_t)rb.v[phase][w]);
+    for (int w = 1; w < NT / 64; ++w) r += __uint_as_float((uint32_t)rb.v[phase][w]);
+  }
   phase ^= 1;
   return r;
 }
@@ -267,13 +297,22 @@ __device__ __forceinline__ void block_sum3_f32(float& x, float& y, float& z, Red
   if constexpr (NT == 64) return;
   if ((tid & 63) == 0) *reinterpret_cast<f32x4*>(rb.t[phase][tid >> 6]) = f32x4{x, y, z, 0.f};
   block_sync<NT>(rb);
-  f32x4 r = *reinterpret_cast<const f32x4*>(rb.t[phase][0]);
+  f32x4 r;
+  if constexpr (kRowReduce<NT>) {
+    r = *reinterpret_cast<const f32x4*>(rb.t[phase][tid & (NT / 64 - 1)]);
 #pragma unroll
-  for (int w = 1; w < NT / 64; ++w) {
-    const f32x4 q = *reinterpret_cast<const f32x4*>(rb.t[phase][w]);
-    r[0] += q[0];
-    r[1] += q[1];
-    r[2] += q[2];
+    for (int i = 0; i < 3; ++i)
+      r[i] = row_combine<NT>(r[i], [](float a, float b) { return a + b; }, dpp_f32<kDppQuadSwap1>, dpp_f32<kDppQuadSwap2>,
+                             dpp_f32<kDppRowHalfMirror>, dpp_f32<kDppRowMirror>);
+  } else {
+    r = *reinterpret_cast<const f32x4*>(rb.t[phase][0]);
+#pragma unroll
+    for (int w = 1; w < NT / 64; ++w) {
+      const f32x4 q = *reinterpret_cast<const f32x4*>(rb.t[phase][w]);
+      r[0] += q[0];
+      r[1] += q[1];
+      r[2] += q[2];
+    }
   }
   x = r[0];
   y = r[1];
@@ -287,9 +326,15 @@ __device__ __forceinline__ u64 block_min_u64(u64 v, RedBuf& rb, int& phase, int 
   if constexpr (NT == 64) return v;
   if ((tid & 63) == 0) rb.v[phase][tid >> 6] = v;
   block_sync<NT>(rb);
-  u64 r = rb.v[phase][0];
+  u64 r;
+  if constexpr (kRowReduce<NT>) {
+    r = row_combine<NT>(rb.v[phase][tid & (NT / 64 - 1)], [](u64 a, u64 b) { return min_u64(a, b); }, dpp_u64<kDppQuadSwap1>,
+                        dpp_u64<kDppQuadSwap2>, dpp_u64<kDppRowHalfMirror>, dpp_u64<kDppRowMirror>);
+  } else {
+    r = rb.v[phase][0];
 #pragma unroll
-  for (int w = 1; w < NT / 64; ++w) r = rb.v[phase][w] < r ? rb.v[phase][w] : r;
+    for (int w = 1; w < NT / 64; ++w) r = rb.v[phase][w] < r ? rb.v[phase][w] : r;
+  }
   phase ^= 1;
   return r;
 }
@@ -493,78 +538,6 @@ __global__ __launch_bounds__(kThreads) void seed_state_kernel(Dev d, int unit_be
   }
 }
 
-// ------------------------------------------------------------------ prep
-// 32 threads per unit, 32 units per workgroup: append the new entry (unless
-// bit 0 of `append` is clear) and publish the unit's scan work items {unit, chunk, entries
-// from the chunk's start to the unit's end, blocks in the list before this
-// item}.  One 64-bit atomic per workgroup claims the list range and the block
-// range together, so the list is sorted by block offset and unit-major (its
-// order only affects scheduling, never results).
-constexpr int kPrepThreads = 1024;
-constexpr int kPrepUnits = 32;
-
-__global__ __launch_bounds__(kPrepThreads) void prep_kernel(Dev d, int unit_begin, int unit_count, const uint16_t* k_new,
-                                                            const uint16_t* v_new, int append, int n_limit,
-                                                            const uint16_t* __restrict__ q) {
-  __shared__ int s_nch[kPrepUnits], s_nblk[kPrepUnits];
-  __shared__ u64 s_base;
-  const int tid = threadIdx.x, sub = tid & 31, slot = tid >> 5;
-  const int w = blockIdx.x * kPrepUnits + slot;
-  const bool active = w < unit_count;
-  const int u = unit_begin + w;
-  int n = 0, n_before = 0;
-  if (active) {
-    n = min(d.n[u], n_limit);            // n_limit < n: only the unit's first n_limit entries take part (prompt replay)
-    n_before = n;
-    if (append & 1) {
-      const int t = d.sc[SC_T];
-      if (n >= unit_cap(d, u)) {
-        if (sub == 0) atomicOr(&d.sc[SC_STATUS], 1);
-      } else {
-        const Slots sl = slots_of(d, u);
-        if (sub < 16)
-          *reinterpret_cast<u32x4*>(d.K + sl.k(n, sub * 8)) =
-              *reinterpret_cast<const u32x4*>(k_new + (size_t)w * kDim + sub * 8);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) d.V[sl.v(n, sub * 4 + e)] = v_new[(size_t)w * kDim + sub * 4 + e];
-        if (sub == 0) {
-          const size_t s = sl + n;
-          d.crf[s] = 0.0f;
-          d.tau[s] = t;
-          d.pos[s] = t;
-          d.flags[s] = 0;
-          d.n[u] = n + 1;
-        }
-        n += 1;
-      }
-    }
-  }
-  const int nch = active ? (n + kChunk - 1) / kChunk : 0;
-  const int nblk = active ? (n + kBlk - 1) / kBlk : 0;
-  if (sub == 0) {
-    s_nch[slot] = nch;
-    s_nblk[slot] = nblk;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    int tot = 0, totb = 0;
-    for (int i = 0; i < kPrepUnits; ++i) {
-      const int c = s_nch[i], b = s_nblk[i];
-      s_nch[i] = tot;
-      s_nblk[i] = totb;
-      tot += c;
-      totb += b;
-    }
-    s_base = atomicAdd(reinterpret_cast<u64*>(&d.sc[SC_CLAIM]), (u64)(uint32_t)tot | ((u64)(uint32_t)totb << 32));
-  }
-  __syncthreads();
-  if (active) {
-    const int base = (int)(uint32_t)s_base + s_nch[slot];
-    const int bbase = (int)(uint32_t)(s_base >> 32) + s_nblk[slot];
-    for (int c = sub; c < nch; c += 32) d.items[base + c] = make_int4(u, c, n - c * kChunk, bbase + c * kChunkBlocks);
-  }
-}
-
 // ------------------------------------------------------------------ scan
 struct KFrag {
   u32x4 k[8];
@@ -574,7 +547,7 @@ struct VFrag {
 };
 
 // K and V are read once per step and never reused: non-temporal loads keep
-// them from displacing the partials and logits that the finish kernel re-reads.
+// them from displacing the logits that the finish kernel re-reads.
 __device__ __forceinline__ u32x4 stream_load(const uint16_t* p) {
   return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
 }
@@ -688,349 +661,36 @@ __device__ __forceinline__ void scan_pv(const float (&sv)[8], const VFrag& fv, f
   }
 }
 
-struct Item {
-  int u, c, n_valid, blk_off;
-};
-
-__device__ __forceinline__ Item fetch_item(const Dev& d, int it) {
-  const int4 r = d.items[it];
-  Item m;
-  m.u = __builtin_amdgcn_readfirstlane(r.x);
-  m.c = __builtin_amdgcn_readfirstlane(r.y);
-  m.n_valid = __builtin_amdgcn_readfirstlane(r.z);
-  m.blk_off = __builtin_amdgcn_readfirstlane(r.w);
-  return m;
-}
-
-// Index of the work item that holds global block `b` (largest i with
-// items[i].blk_off <= b): 64-way search, one probe per lane and round.
-__device__ __forceinline__ int find_item(const Dev& d, int n_items, int b, int lane) {
-  int lo = 0, hi = n_items;
-  while (hi - lo > 1) {
-    const int step = (hi - lo + 63) >> 6;
-    const int idx = lo + lane * step;
-    const int off = idx < hi ? d.items[idx].w : 0x7FFFFFFF;
-    const u64 mask = __ballot(off <= b);
-    const int k = __popcll(mask) - 1;            // lane 0 always qualifies
-    lo += k * step;
-    hi = min(hi, lo + step);
-  }
-  return __builtin_amdgcn_readfirstlane(lo);
-}
-
-// What step_epilogue leaves behind, written by the one thread that knows the launch is complete (the end of
-// the kernel makes it visible).
-__device__ __forceinline__ void scan_epilogue(const Dev& d, int seq, int advance, int layer) {
-  const int t = d.sc[SC_T];
-  if (layer >= 0) {
-    d.layer_ts[2 * layer] = t;
-    d.layer_ts[2 * layer + 1] = seq;
-  }
-  d.sc[SC_DONE] = 0;
-  d.sc[SC_CLAIM] = 0;
-  d.sc[SC_CLAIM + 1] = 0;
-  d.sc[SC_SEQ] = seq + 1;
-  if (advance) {
-    d.sc[SC_T] = t + 1;
-    d.sc[SC_WINDOW_STEPS] = d.sc[SC_WINDOW_STEPS] + 1;
-  }
-}
-
 // Stores and loads that are coherent across the chip's L2 caches one by one (no cache-wide write-back or
-// invalidation, which a fence at that scope would cost every wavefront): how a scan that merges hands its
-// partials from the wavefronts that wrote them to the one that combines them.
-template <bool COHERENT, class T>
-__device__ __forceinline__ void put(T* p, T v) {
-  if constexpr (COHERENT)
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  else
-    *p = v;
+// invalidation, which a fence at that scope would cost every workgroup): how a scan hands its partials from the
+// workgroups that wrote them to the one that combines them.
+template <class T>
+__device__ __forceinline__ void put_coherent(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 template <class T>
 __device__ __forceinline__ T get_coherent(const T* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// LDS floats one wavefront needs for merge_unit_wave: maximum/weight and sum of every run and head
-constexpr int kMergeLds = 2 * (kMaxChunks + 1) * kMaxGroup;
-
-// merge_partials for one wavefront of a scan that merges: the same values combined in the same order (slot
-// after slot), so the output has the same bits; only the distribution over lanes differs.  The reads are
-// coherent ones, since the partials come from other wavefronts of the same launch, and no stamp is read:
-// the unit's blocks start at global block u0 and shares are `per` blocks long, so run r > 0 begins at the
-// r-th share boundary inside the unit, which names its slot.  `sw` holds kMergeLds floats.
-__device__ __forceinline__ void merge_unit_wave(const Dev& d, int u, int urel, int u0, int per, int runs, float* sw, void* out,
-                                                int lane) {
-  const int G = d.G;
-  const size_t slot0 = (size_t)u * d.slots;
-  float* sl = sw + (kMaxChunks + 1) * kMaxGroup;
-  const int first = u0 / per;
-  auto slot_of = [&](int r) { return r == 0 ? 0 : 1 + ((first + r) * per - u0) / kChunkBlocks; };
-  const int g_lane = lane & 7;                         // i & 7 for every i this lane visits
-  // four runs' partials (all heads, two dims per lane) are requested at once, the first four before anything else
-  float2 x[4][kMaxGroup];
-  auto request = [&](int r0) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const size_t slot = slot0 + slot_of(min(r0 + k, runs - 1));
-#pragma unroll
-      for (int g = 0; g < kMaxGroup; ++g) {
-        const float* pp = d.partial + (slot * G + min(g, G - 1)) * kDim + 2 * lane;
-        x[k][g] = make_float2(get_coherent(pp), get_coherent(pp + 1));
-      }
-    }
-  };
-  if (out) request(0);
-  for (int i = lane; i < runs * kMaxGroup; i += 64) {
-    const float* mlp = d.ml + ((slot0 + slot_of(i >> 3)) * G + min(g_lane, G - 1)) * 2;
-    const float m = get_coherent(mlp), l = get_coherent(mlp + 1);
-    sw[i] = g_lane < G ? m : -INFINITY;
-    sl[i] = g_lane < G ? l : 0.f;
-  }
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  float M = -INFINITY;
-  if (lane < G)
-    for (int r = 0; r < runs; ++r) M = fmaxf(M, sw[r * kMaxGroup + lane]);
-  const float Mg = __shfl(M, g_lane);
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  for (int i = lane; i < runs * kMaxGroup; i += 64) {
-    const float m = sw[i];
-    sw[i] = (g_lane < G && m > -INFINITY) ? fast_exp2(m - Mg) : 0.f;
-  }
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  float inv = 0.f;
-  if (lane < G) {
-    float Lsum = 0.f;
-    for (int r = 0; r < runs; ++r) {
-      const float w = sw[r * kMaxGroup + lane];
-      if (w != 0.f) Lsum += sl[r * kMaxGroup + lane] * w;
-    }
-    inv = 1.0f / Lsum;
-  }
-  if (!out) return;
-  float2 o[kMaxGroup];
-#pragma unroll
-  for (int g = 0; g < kMaxGroup; ++g) o[g] = make_float2(0.f, 0.f);
-  for (int r0 = 0; r0 < runs; r0 += 4) {
-    if (r0 > 0) request(r0);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      if (r0 + k < runs) {
-#pragma unroll
-        for (int g = 0; g < kMaxGroup; ++g) {
-          const float w = sw[(r0 + k) * kMaxGroup + g];
-          if (w != 0.f) {
-            o[g].x += x[k][g].x * w;
-            o[g].y += x[k][g].y * w;
-          }
-        }
-      }
-    }
-  }
-#pragma unroll
-  for (int g = 0; g < kMaxGroup; ++g) {
-    const float inv_g = __shfl(inv, g);
-    if (g < G) {
-      const size_t oi = ((size_t)urel * G + g) * kDim + 2 * lane;
-      const float ox = o[g].x * inv_g, oy = o[g].y * inv_g;
-      if (d.out_bf16) {
-        __bf16* dst = reinterpret_cast<__bf16*>(out) + oi;
-        dst[0] = (__bf16)ox;
-        dst[1] = (__bf16)oy;
-      } else {
-        *reinterpret_cast<float2*>(reinterpret_cast<float*>(out) + oi) = make_float2(ox, oy);
-      }
-    }
-  }
-}
-
-// Persistent grid.  The blocks (32 entries) of all work items form one
-// sequence, sorted unit-major; every wavefront takes an equal contiguous share
-// of it.  Its share is a few long RUNS: consecutive blocks of one unit,
-// contiguous in memory, over which the online softmax simply continues.  A run
-// is streamed block by block: while block b is computed the K tile of block
-// b+1 (the next run's first block at the end of a run) is in flight, and V
-// follows as soon as the previous V has been consumed.  All loads in the loop
-// are unconditional, so the waits the compiler inserts are exact.  A run
-// leaves one partial (max, sum, acc), stamped with the launch sequence number,
-// in slot 0 of its unit if it starts the unit, else in slot 1 + chunk of its
-// first block (shares are at least one chunk long, so no two runs collide).
-// `q` holds the query rows of the units [unit_begin, ...) of this call:
-// row (u - unit_begin) * G + g.
-//
-// MERGE: the kernel also finishes the attention.  Every run is counted on its
-// unit; the wavefront that publishes a unit's last run merges the unit's
-// partials and writes its output rows, so no second kernel stands between the
-// scan and the caller.  The wavefront that accounts for the launch's last block
-// leaves the step scalars as step_epilogue would and, for a single-layer step
-// whose bookkeeping follows later, notes the step's time and sequence number
-// under `layer`.
-template <bool MERGE>
-__global__ __launch_bounds__(kThreads, 2) void scan_kernel(Dev d, int unit_begin, const uint16_t* __restrict__ q, void* out,
-                                                           int advance, int layer) {
-  __shared__ float s_lg[kThreads / 64][kMaxGroup * kLgRow];
-  __shared__ float s_mw[MERGE ? kThreads / 64 : 1][MERGE ? kMergeLds : 1];
-  const int lane = threadIdx.x & 63;
-  const int nw = gridDim.x * (kThreads / 64);
-  const int gw = __builtin_amdgcn_readfirstlane(blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6));
-  const int n_items = d.sc[SC_CLAIM];
-  const int n_blocks = d.sc[SC_CLAIM + 1];
-  const int seq = d.sc[SC_SEQ];
-  const int per = max(kChunkBlocks, (n_blocks + nw - 1) / nw);
-  int b_cur = gw * per;                                  // global block index
-  const int b_end = min(n_blocks, b_cur + per);
-  // MERGE: the launch is complete when every block is accounted for; a workgroup reports its blocks once, through
-  // its last wavefront to finish (one atomic per workgroup on the shared counter instead of one per wavefront)
-  __shared__ int s_waves_done;
-  if (MERGE) {
-    if (threadIdx.x == 0) s_waves_done = 0;
-    __syncthreads();
-  }
-  auto wave_done = [&]() {
-    if (lane != 0 || atomicAdd(&s_waves_done, 1) != kThreads / 64 - 1) return;
-    const int w0 = blockIdx.x * (kThreads / 64);
-    const int wg_blocks = min(n_blocks, (w0 + kThreads / 64) * per) - min(n_blocks, w0 * per);
-    if (wg_blocks > 0 && atomicAdd(&d.sc[SC_DONE], wg_blocks) + wg_blocks == n_blocks) scan_epilogue(d, seq, advance, layer);
-  };
-  if (b_cur >= b_end) {
-    if (MERGE) {
-      if (n_blocks == 0 && gw == 0 && lane == 0) scan_epilogue(d, seq, advance, layer);   // nothing to scan at all
-      wave_done();
-    }
-    return;
-  }
-  float* lds_lg = s_lg[threadIdx.x >> 6];
-  const int j = lane & 15, kg = lane >> 4;
-  const int G = d.G;
-  const bool head_lane = j < G;
-  const int jq = head_lane ? j : 0;
-
-  int it = find_item(d, n_items, b_cur, lane);
-  Item cur = fetch_item(d, it);
-  KFrag ka;
-  VFrag va;
-  {
-    const size_t off = slots_of(d, cur.u).blk(cur.c * kChunkBlocks + (b_cur - cur.blk_off)) + lane * 8;
-    load_k(ka, d.K + off);
-    load_v(va, d.V + off);
-  }
-  while (true) {
-    // ---- one run: blocks [fb, fb + nblk) of unit cur.u, fb counted from the unit's start
-    const int fb_item = b_cur - cur.blk_off;                                   // first block, inside item `it`
-    const int fb = cur.c * kChunkBlocks + fb_item;
-    const int run_valid = cur.n_valid - fb_item * kBlk;                        // entries from the run's start to the unit's end
-    const int nblk = min((run_valid + kBlk - 1) / kBlk, b_end - b_cur);
-    const int b_next = b_cur + nblk;
-    const bool have_next = b_next < b_end;
-    const int it_next = it + (fb_item + nblk + kChunkBlocks - 1) / kChunkBlocks;   // next unit's first item
-    const Item nxt = have_next ? fetch_item(d, it_next) : cur;
-    bf16x8 qv[4];
-    {
-      const uint16_t* qrow = q + ((size_t)(cur.u - unit_begin) * G + jq) * kDim + 8 * kg;
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        u32x4 x = *reinterpret_cast<const u32x4*>(qrow + 32 * s);
-        if (!head_lane) x = u32x4{0u, 0u, 0u, 0u};
-        qv[s] = as_bf16x8(x);
-      }
-    }
-    // The run's blocks are consecutive in the unit but contiguous in memory only inside a segment (8 blocks):
-    // lane i holds the pool segment of the unit's segment fb / 8 + i (reloaded every 64 segments), and a
-    // block's address comes from there without another trip to memory.
-    const int32_t* seg_row = d.tbl + (size_t)cur.u * d.max_seg;
-    int seg_first = fb >> 3;
-    int seg_reg = seg_row[min(seg_first + lane, d.max_seg - 1)];
-    auto block_off = [&](int b) -> size_t {            // element offset of the unit's block b (b >= fb)
-      if ((b >> 3) - seg_first >= 64) {
-        seg_first = b >> 3;
-        seg_reg = seg_row[min(seg_first + lane, d.max_seg - 1)];
-      }
-      return (size_t)__builtin_amdgcn_readlane(seg_reg, (b >> 3) - seg_first) * kSegElems + (size_t)(b & (kSegBlocks - 1)) * kBlkElems +
-             lane * 8;
-    };
-    // after the run's last block the stream continues with the next run (whose first segment is asked for now
-    // and looked at then), or re-reads this block at the very end
-    const int nxt_seg = d.tbl[(size_t)nxt.u * d.max_seg + nxt.c];
-    // logits of a block are stored as [head][32 entries]: 128 G contiguous bytes, 16 per lane
-    float* lg_dst = d.logits + ((size_t)cur.u * d.cap + (size_t)fb * kBlk) * G + 4 * min(lane, 8 * G - 1);
-    f32x4 acc[8];
-#pragma unroll
-    for (int dt = 0; dt < 8; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float m_run = -INFINITY, l_run = 0.f;
-    int blk = 0;
-
-    // stream: the K tile of block b+1 is requested right after block b's logits are done, the V tile
-    // right after block b's PV; at the end of the run both continue with the next run's first block
-    while (true) {
-      const bool last = blk + 1 == nblk;
-      const size_t n_off = !last ? block_off(fb + blk + 1) : have_next ? (size_t)nxt_seg * kSegElems + lane * 8 : block_off(fb + blk);
-      float sv[8];
-      scan_qk(ka, qv, sv, d.scale_log2e, blk * kBlk, run_valid, lds_lg, kLgRow, lg_dst, G, lane);
-      load_k(ka, d.K + n_off);
-      scan_pv(sv, va, acc, m_run, l_run, lane);
-      load_v(va, d.V + n_off);
-      ++blk;
-      if (last) break;
-    }
-    // ---- publish the run's partial
-    l_run += __shfl_xor(l_run, 16);
-    l_run += __shfl_xor(l_run, 32);
-    const size_t slot = (size_t)cur.u * d.slots + (fb == 0 ? 0 : 1 + fb / kChunkBlocks);
-    if (head_lane && kg == 0) {
-      put<MERGE>(&d.ml[(slot * G + j) * 2], m_run);
-      put<MERGE>(&d.ml[(slot * G + j) * 2 + 1], l_run);
-    }
-    if (lane == 0) put<MERGE>(&d.stamp[slot], seq);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int head = 4 * kg + v;
-      if (head < G) {
-        float* dst = d.partial + (slot * G + head) * kDim + j;
-#pragma unroll
-        for (int dt = 0; dt < 8; ++dt) put<MERGE>(&dst[16 * dt], acc[dt][v]);
-      }
-    }
-    if (MERGE) {
-      // the partial before the count: its stores are coherent across the chip, so it is enough that they have completed
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      // runs of this unit = shares that its blocks [u0, u0 + unb) touch
-      const int u0 = cur.blk_off - cur.c * kChunkBlocks;
-      const int unb = (cur.n_valid + cur.c * kChunk + kBlk - 1) / kBlk;
-      const int runs = (u0 + unb - 1) / per - u0 / per + 1;
-      int last = 0;
-      if (lane == 0) {
-        last = atomicAdd(&d.arrive[cur.u], 1) == runs - 1;
-        if (last) __hip_atomic_store(&d.arrive[cur.u], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // the word other wavefronts update atomically
-      }
-      if (__builtin_amdgcn_readfirstlane(last))          // the other runs' partials are read with coherent loads
-        merge_unit_wave(d, cur.u, cur.u - unit_begin, u0, per, runs, s_mw[threadIdx.x >> 6], out, lane);
-    }
-    if (!have_next) break;
-    b_cur = b_next;
-    it = it_next;
-    cur = nxt;
-  }
-  if (MERGE) wave_done();
-}
-
-// ------------------------------------------------------------------ single-layer scan that appends by itself
+// ------------------------------------------------------------------ scan of few units, which appends by itself
 // The shape a model imposes is one call per layer, a few hundred units at most: too few for the fused kernel
-// (one workgroup per unit) and too little work for the persistent scan above to amortise its work list.  Here
-// the grid itself is the work list: workgroup (x, y) takes chunks 4 y .. 4 y + 3 (256 entries each, one per
+// (one workgroup per unit).  Here several workgroups share a unit and the grid itself is the work list: workgroup (x, y) takes chunks 4 y .. 4 y + 3 (256 entries each, one per
 // wavefront) of the layer's unit x and leaves at once if the unit is shorter.  (Units along x: consecutive
 // workgroups go to different XCDs, so the workgroups that have work - every unit's first, most units' second -
 // spread over all of them; with the chunk groups along x, and eight or a multiple of them, each XCD would get
 // one group index, the first few all the work, and a step takes 1.6 times as long.)  Nothing has to run before it:
 // every workgroup derives the unit's length after the append from the stored one (which stays as it is until
-// the bookkeeping that follows, finish_kernel with late = 2, has recorded the append), and the wavefront whose
+// finish_kernel or append_kernel, which follows, has recorded the append), and the wavefront whose
 // chunk receives the new entry puts its key and value rows into the block it has just loaded (and into the
 // cache), so that the entry takes part like any cached one.  The four wavefronts combine their softmax states
 // in LDS; a unit of one workgroup (up to 1024 entries) is finished there and then, a longer one goes through
-// one partial per workgroup, merged by the workgroup that publishes the last (coherent stores and loads as in
-// scan_kernel<true>).  The unit's softmax maximum and 1 / sum per head stay in `msum` for the bookkeeping.
+// one partial per workgroup, merged by the workgroup that publishes the last (coherent stores and loads).  The unit's softmax maximum and 1 / sum per head stay in `msum` for the bookkeeping.
+// In place of a kernel that appended and built a work list, a persistent scan over it and a merge of its partials by the
+// bookkeeping kernel: 7.6 + 35 us per layer of the 14B geometry then, 36 us now.
+// defer_layer >= 0: the bookkeeping follows on another stream, perhaps after the time has moved on; the step's time
+// is left for it, and moves on here if `advance` says that this was the step's last layer (nothing else in
+// this launch reads it).  logits = 0: attention only, nobody looks at the logits afterwards.
 // kW wavefronts per workgroup, each over 1 / kSplit of a chunk; the text above describes <4, 1>, the shape in
 // use.  Measured beside it on 128 units of 257 .. 8193 entries: fewer wavefronts per workgroup (<2, 1>, <1, 1>)
 // 2 % and 15 % slower per step, more (<8, 1>) 8 %, shorter spans (<4, 2>, <8, 2>, <8, 4>) 8 %, 23 % and 49 %
@@ -1067,7 +727,8 @@ __device__ __forceinline__ void inject_entry(KFrag& ka, VFrag& va, int rr, const
 template <int kW, int kSplit>
 __global__ __launch_bounds__(64 * kW, 3) void layer_scan_kernel(Dev d, int unit_begin, const uint16_t* __restrict__ q,
                                                                 const uint16_t* __restrict__ k_new,
-                                                                const uint16_t* __restrict__ v_new, void* out, int layer) {
+                                                                const uint16_t* __restrict__ v_new, void* out, int logits,
+                                                                int defer_layer, int advance) {
   constexpr int kT = 64 * kW;
   constexpr int kSpanBlk = kChunkBlocks / kSplit, kSpan = kSpanBlk * kBlk;      // blocks and entries one wavefront takes
   __shared__ float s_lg[kW][kMaxGroup * kLgRow];
@@ -1087,7 +748,14 @@ __global__ __launch_bounds__(64 * kW, 3) void layer_scan_kernel(Dev d, int unit_
   const int n = n_old + (full ? 0 : 1);
   const int nch = (n + kSpan - 1) / kSpan;          // spans of the unit
   if (cg == 0 && tid == 0) {
-    if (urel == 0) d.layer_ts[2 * layer] = d.sc[SC_T];      // the bookkeeping runs later, perhaps after the time has moved on
+    if (urel == 0 && defer_layer >= 0) {
+      const int t = d.sc[SC_T];
+      d.layer_ts[defer_layer] = t;
+      if (advance) {
+        d.sc[SC_T] = t + 1;
+        d.sc[SC_WINDOW_STEPS] = d.sc[SC_WINDOW_STEPS] + 1;
+      }
+    }
     if (full) atomicOr(&d.sc[SC_STATUS], 1);
   }
   if (cg * kW >= nch) return;
@@ -1138,9 +806,9 @@ __global__ __launch_bounds__(64 * kW, 3) void layer_scan_kernel(Dev d, int unit_
       vdst[v_offset(row, lane + 64)] = v_new[(size_t)urel * kDim + lane + 64];
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     }
-    float* lds_lg = s_lg[w];
+    float* lds_lg = logits ? s_lg[w] : nullptr;
     float* lg_dst = d.logits + ((size_t)u * d.cap + (size_t)e0) * G + 4 * min(lane, 8 * G - 1);
-    // one block ahead, as in scan_kernel (two ahead is slower here as well); the loads stay unconditional (the
+    // one block ahead (two ahead is slower here as well); the loads stay unconditional (the
     // last block is read twice), so that the waits the compiler inserts are exact
     for (int blk = 0; blk < nb; ++blk) {
       const bool last = blk + 1 == nb;
@@ -1224,10 +892,10 @@ __global__ __launch_bounds__(64 * kW, 3) void layer_scan_kernel(Dev d, int unit_
   for (int k = 0; k < kPer; ++k) {
     const int e = tid + k * kT, g = e >> 7, dim = e & 127;
     if (g < G) {
-      put<true>(&d.partial[((slot0 + cg) * G + g) * kDim + dim], o[k]);
+      put_coherent(&d.partial[((slot0 + cg) * G + g) * kDim + dim], o[k]);
       if (dim == 0) {
-        put<true>(&d.ml[((slot0 + cg) * G + g) * 2], Mg[k]);
-        put<true>(&d.ml[((slot0 + cg) * G + g) * 2 + 1], Lg[k]);
+        put_coherent(&d.ml[((slot0 + cg) * G + g) * 2], Mg[k]);
+        put_coherent(&d.ml[((slot0 + cg) * G + g) * 2 + 1], Lg[k]);
       }
     }
   }
@@ -1307,10 +975,24 @@ __global__ __launch_bounds__(64 * kW, 3) void layer_scan_kernel(Dev d, int unit_
   }
 }
 
-// The step's time moves on after the last layer (the single-layer scan above leaves the step scalars alone).
-__global__ void advance_kernel(Dev d) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    d.sc[SC_T] = d.sc[SC_T] + 1;
+// What an attention-only step records of its append, behind layer_scan_kernel (whose late workgroups may still read a
+// unit's length, so it cannot do this itself): one workgroup over all units of the call.
+__global__ __launch_bounds__(kWideThreads) void append_kernel(Dev d, int unit_begin, int count, int advance) {
+  const int t = d.sc[SC_T];
+  for (int u = unit_begin + (int)threadIdx.x; u < unit_begin + count; u += kWideThreads) {
+    const int n = d.n[u];
+    if (n < unit_cap(d, u)) {
+      const size_t s = slots_of(d, u) + n;
+      d.crf[s] = 0.0f;
+      d.tau[s] = t;
+      d.pos[s] = t;
+      d.flags[s] = 0;
+      d.n[u] = n + 1;
+    }
+  }
+  __syncthreads();                                       // every wavefront has read the time
+  if (advance && threadIdx.x == 0) {
+    d.sc[SC_T] = t + 1;
     d.sc[SC_WINDOW_STEPS] = d.sc[SC_WINDOW_STEPS] + 1;
   }
 }
@@ -1837,7 +1519,7 @@ __global__ __launch_bounds__(kThreads) void evict_move_kernel(Dev d, int unit_be
 
 // ------------------------------------------------------------------ finish
 // Ends a kernel that must leave the step scalars consistent: the last block
-// to arrive resets the work list and, if asked, advances time.  No fence: the
+// to arrive resets the queue and, if asked, advances time.  No fence: the
 // last block reads nothing the others wrote (the scalars it updates are read-only
 // during the launch, and every claim on the queue has returned before its
 // workgroup gets here); the end of the kernel publishes what it writes.  A
@@ -1848,9 +1530,6 @@ __device__ __forceinline__ void step_epilogue(const Dev& d, int t, int advance, 
     const int prev = atomicAdd(&d.sc[SC_DONE], 1);
     if (prev == (int)gridDim.x - 1) {
       d.sc[SC_DONE] = 0;
-      d.sc[SC_CLAIM] = 0;
-      d.sc[SC_CLAIM + 1] = 0;
-      d.sc[SC_SEQ] = d.sc[SC_SEQ] + 1;
       if (queue_reset >= 0) d.sc[SC_QUEUE] = queue_reset;
       if (advance) {
         d.sc[SC_T] = t + 1;
@@ -1859,76 +1538,6 @@ __device__ __forceinline__ void step_epilogue(const Dev& d, int t, int advance, 
     }
   }
 }
-
-// Merge the scan partials of unit u (the slots stamped by this launch).  Leaves
-// sM[g] (global max) and sInv[g] (1 / softmax denominator) in LDS and, if `out`
-// is given, writes the attention output.
-__device__ __forceinline__ void merge_partials(const Dev& d, int u, int urel, int nch, int seq, float* sM, float* sInv,
-                                               float* sW, void* out, int tid) {
-  const int G = d.G;
-  const size_t slot0 = (size_t)u * d.slots;
-  const int ns = nch + 1;
-  float* sL = sW + (kMaxChunks + 1) * kMaxGroup;      // second half of the caller's array: the slots' sums
-  // running maxima and sums of the live slots (m = -inf, l = 0 for the others), one 8-byte read each
-  for (int i = tid; i < ns * kMaxGroup; i += kThreads) {
-    const int sidx = i >> 3, g = i & 7;
-    // both reads are issued at once (the slot's record exists whether or not this launch wrote it)
-    const int stamp = d.stamp[slot0 + sidx];
-    const float2 ml = *reinterpret_cast<const float2*>(d.ml + ((slot0 + sidx) * G + min(g, G - 1)) * 2);
-    const bool live = g < G && stamp == seq;
-    sW[i] = live ? ml.x : -INFINITY;
-    sL[i] = live ? ml.y : 0.f;
-  }
-  __syncthreads();
-  if (tid < G) {
-    const int g = tid;
-    float M = -INFINITY;
-    for (int sidx = 0; sidx < ns; ++sidx) M = fmaxf(M, sW[sidx * kMaxGroup + g]);
-    sM[g] = M;
-  }
-  __syncthreads();
-  // weights: sW[s * 8 + g] = exp2(m_s - M) for live slots, 0 for the others
-  for (int i = tid; i < ns * kMaxGroup; i += kThreads) {
-    const int g = i & 7;
-    const float m = sW[i];
-    sW[i] = (g < G && m > -INFINITY) ? fast_exp2(m - sM[g]) : 0.f;
-  }
-  __syncthreads();
-  if (tid < G) {
-    const int g = tid;
-    float Lsum = 0.f;
-    for (int sidx = 0; sidx < ns; ++sidx) {
-      const float w = sW[sidx * kMaxGroup + g];
-      if (w != 0.f) Lsum += sL[sidx * kMaxGroup + g] * w;
-    }
-    sInv[g] = 1.0f / Lsum;
-  }
-  __syncthreads();
-  if (out) {
-    for (int idx = tid; idx < G * kDim; idx += kThreads) {
-      const int g = idx >> 7, dim = idx & 127;
-      float o = 0.f;
-      // eight slots' partials are requested at once (dead slots hold stale data: read, never used)
-      for (int s0 = 0; s0 < ns; s0 += 8) {
-        float x[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) x[k] = d.partial[((slot0 + min(s0 + k, ns - 1)) * G + g) * kDim + dim];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const float w = s0 + k < ns ? sW[(s0 + k) * kMaxGroup + g] : 0.f;
-          if (w != 0.f) o += x[k] * w;
-        }
-      }
-      o *= sInv[g];
-      const size_t oi = ((size_t)urel * G + g) * kDim + dim;
-      if (d.out_bf16)
-        reinterpret_cast<__bf16*>(out)[oi] = (__bf16)o;
-      else
-        reinterpret_cast<float*>(out)[oi] = o;
-    }
-  }
-}
-
 
 // lambda^delta from the decay table: its first s_tab_n entries sit in LDS, the rest (long tables: lambda
 // close to 1) in global memory.  Written as two loads in two address spaces on purpose: a conditional
@@ -1965,35 +1574,6 @@ struct LgView {
 };
 __device__ __forceinline__ LgView unit_logits(const Dev& d, int u) {
   return LgView{d.logits + (size_t)u * d.G * d.cap, d.G * kBlk};
-}
-
-// Mean attention weight of every entry of a unit into val[0..n).
-template <int NT = kThreads>
-__device__ __forceinline__ void mean_weights(const Dev& d, LgView lv, int n, const float* sM, const float* sInv, float* val,
-                                             int tid) {
-  const int G = d.G;
-  const float invG = 1.0f / (float)G;
-  const float* lg = lv.p;
-  for (int i0 = tid; i0 < n; i0 += 4 * NT) {
-    float x[4][kMaxGroup];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int i = i0 + r * NT;
-      const float* row = lg + (size_t)(i >> 5) * lv.blk_stride + (i & 31);
-#pragma unroll
-      for (int g = 0; g < kMaxGroup; ++g) x[r][g] = (i < n && g < G) ? row[g * kBlk] : -INFINITY;
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int i = i0 + r * NT;
-      float a = 0.f;
-#pragma unroll
-      for (int g = 0; g < kMaxGroup; ++g)
-        if (g < G) a += fast_exp2(x[r][g] - sM[g]) * sInv[g];
-      if (i < n) val[i] = a * invG;
-    }
-  }
-  __syncthreads();
 }
 
 // Alg. 1 Steps 1-3 for one unit: top-p hit set from the mean weights val(i),
@@ -2157,6 +1737,7 @@ __device__ __forceinline__ void mean_weights_regs(const Dev& d, LgView lv, int n
         if (g < G) acc += fast_exp2(x[g][e] - sM[g]) * sInv[g];
       a[4 * c + e] = (e0 + e < n) ? acc * invG : 0.f;
     }
+    if (R > 8 && (c & 1)) __builtin_amdgcn_sched_barrier(0);     // two groups' logits at a time: 1024 threads have 128 registers each
   }
 }
 
@@ -2532,105 +2113,85 @@ __device__ __forceinline__ void lrfu_regs(const Dev& d, int u, Slots base, int n
   }
 }
 
-// Mean weights of the unit's first n entries from its logits (softmax maxima sM and reciprocal denominators
-// sInv per head in LDS), then Alg. 1 Steps 1-3 at time t and, if asked, Step 4.  One workgroup of kThreads.
+// Mean weights of the unit's n entries from its logits (softmax maxima sM and reciprocal denominators
+// sInv per head in LDS), then Alg. 1 Steps 1-3 at time t and, if asked, Step 4.  One workgroup of NT threads with up
+// to 32 entries each (256 threads: up to 8).
 // val: n floats of LDS, evm: the eviction bit mask behind them.
 // sh: 4 + NT / 64 ints.
-template <int NT = kThreads>
-__device__ __forceinline__ void unit_bookkeeping(const Dev& d, int u, int n, int B, int t, LgView lv, const float* sM,
+template <int NT>
+__device__ __forceinline__ void unit_bookkeeping(const Dev& d, int u, Slots base, int n, int B, int t, LgView lv, const float* sM,
                                                  const float* sInv, bool evict, float* val, uint32_t* evm, const float* s_tab,
                                                  int s_tab_n, RedBuf& rb, int& phase, int* sh, int tid) {
-  const Slots base = slots_of(d, u);
-  if (n <= 8 * NT) {
-    float a[8];
-    mean_weights_regs<8, NT>(d, lv, n, sM, sInv, a, tid);
-    f32x4 crf[2];
-    i32x4 tau[2], ps[2];
-    lrfu_regs<8, 2, 0, ValLinear, NT>(d, u, base, n, B, t, a, crf, tau, ps, ValLinear{val}, evict, evm, reinterpret_cast<int*>(val), d.cap,
-                                      s_tab, s_tab_n, rb, phase, sh, tid);
-  } else if (n <= 16 * NT) {
-    float a[16];
-    mean_weights_regs<16, NT>(d, lv, n, sM, sInv, a, tid);
-    f32x4 crf[4];
-    i32x4 tau[4], ps[4];
-    lrfu_regs<16, 4, 0, ValLinear, NT>(d, u, base, n, B, t, a, crf, tau, ps, ValLinear{val}, evict, evm, reinterpret_cast<int*>(val), d.cap,
+  auto regs = [&](auto rc) {
+    constexpr int R = decltype(rc)::value, C = R / 4, CH = C < 2 ? C : 2;
+    float a[R];
+    mean_weights_regs<R, NT>(d, lv, n, sM, sInv, a, tid);
+    f32x4 crf[CH];
+    i32x4 tau[CH], ps[CH];
+    lrfu_regs<R, CH, 0, ValLinear, NT>(d, u, base, n, B, t, a, crf, tau, ps, ValLinear{val}, evict, evm, reinterpret_cast<int*>(val), d.cap,
                                        s_tab, s_tab_n, rb, phase, sh, tid);
-  } else if (n <= 32 * NT) {
-    float a[32];
-    mean_weights_regs<32, NT>(d, lv, n, sM, sInv, a, tid);
-    f32x4 crf[8];
-    i32x4 tau[8], ps[8];
-    lrfu_regs<32, 8, 0, ValLinear, NT>(d, u, base, n, B, t, a, crf, tau, ps, ValLinear{val}, evict, evm, reinterpret_cast<int*>(val), d.cap,
-                                       s_tab, s_tab_n, rb, phase, sh, tid);
-  } else {
-    mean_weights<NT>(d, lv, n, sM, sInv, val, tid);
-    const u64 sfix = lrfu_update<ValLinear, NT>(d, u, base, n, t, ValLinear{val}, s_tab, s_tab_n, rb, phase, tid);
-    if (tid == 0) {
-      d.window[u] += sfix;
-      d.t_unit[u] = t;
-    }
-    if (evict && n > B)
-      evict_phase<ValLinear, NT>(d, u, base, n, B, ValLinear{val}, evm, reinterpret_cast<int*>(val), d.cap, rb, phase, sh, tid);
-    else if (tid == 0)
-      d.nev[u] = 0;
+  };
+  if (n <= 4 * NT) {
+    regs(std::integral_constant<int, 4>{});
+  } else if (NT < kWideThreads || n <= 8 * NT) {
+    regs(std::integral_constant<int, 8>{});
+  } else if constexpr (NT == kWideThreads) {
+    if (n <= 16 * NT)
+      regs(std::integral_constant<int, 16>{});
+    else
+      regs(std::integral_constant<int, 32>{});
   }
 }
 
-// n_limit / t_fixed: the replay of a prompt's last queries runs the step over the unit's first n_limit
-// entries at time t_fixed (otherwise INT_MAX and -1: all entries, the context's time).
-// late: 0 = the whole step.  1 = the bookkeeping alone (mean weights, Alg. 1 Steps 1-4) of a single-layer
-// step whose scan has already merged the partials, written the output and ended the step: it runs later,
-// on another stream, from the partials and logits of that launch, whose time and sequence number the scan
-// left in d.layer_ts[layer], and touches no step scalar.
-__global__ __launch_bounds__(kThreads) void finish_kernel(Dev d, int unit_begin, void* out, uint32_t call_flags,
-                                                          int advance, int n_limit, int t_fixed, int late, int layer) {
+// The bookkeeping of a step behind layer_scan_kernel, one workgroup per unit: the new entry's rows are in the cache
+// and its logits with the others, the unit's records still describe the step before.  Records the append, then
+// Alg. 1 Steps 1-4.  layer_time = 0: at the context's time, which moves on at the end if `advance` says so.
+// layer_time = 1 (deferred): at the time that the scan left for the unit's layer.
+// A unit is a chain of about 15 block reductions and as many memory round trips, so few units take 1024 threads each
+// (at most 8 entries per thread up to 8192): 128 units of 2048 entries on average in 21 us, with 256 threads 46.
+template <int NT>
+__global__ __launch_bounds__(NT) void finish_kernel(Dev d, int unit_begin, uint32_t call_flags, int advance, int layer_time) {
   extern __shared__ unsigned char smem[];
   float* val = reinterpret_cast<float*>(smem);
   uint32_t* evm = reinterpret_cast<uint32_t*>(smem + (size_t)d.cap * 4);
-  __shared__ float sM[kMaxGroup], sInv[kMaxGroup], sW[2 * (kMaxChunks + 1) * kMaxGroup];
+  __shared__ float sM[kMaxGroup], sInv[kMaxGroup];
+  __shared__ int32_t s_row[kMaxChunks];
   __shared__ RedBuf rb;
-  __shared__ int sh[8];
+  __shared__ int sh[4 + (NT / 64 < 4 ? 4 : NT / 64)];
   __shared__ float s_tab[kTabLds];
   const int tid = threadIdx.x;
-  const int urel = blockIdx.x, u = unit_begin + urel;
-  int n = min(d.n[u], n_limit);
-  if (layer == -2) layer = u / (d.Bz * d.Hkv);          // a launch over several layers: each unit looks up its own
-  const int t = late ? d.layer_ts[2 * layer] : t_fixed >= 0 ? t_fixed : d.sc[SC_T];
-  const int seq = late == 1 ? d.layer_ts[2 * layer + 1] : d.sc[SC_SEQ];
+  const int u = unit_begin + blockIdx.x;
+  int n = d.n[u];
+  const int t = layer_time ? d.layer_ts[u / (d.Bz * d.Hkv)] : d.sc[SC_T];
   const int B = d.budget[u];
   const int s_tab_n = min(kTabLds, d.tab_last + 1);
+  const bool room = n < unit_cap(d, u);
   if (tid < s_tab_n) s_tab[tid] = d.tab[tid];
+  if (tid < d.max_seg) s_row[tid] = d.tbl[(size_t)u * d.max_seg + tid];
+  if (tid < d.G) {
+    sM[tid] = d.msum[((size_t)u * kMaxGroup + tid) * 2];
+    sInv[tid] = d.msum[((size_t)u * kMaxGroup + tid) * 2 + 1];
+  }
   int phase = 0;
-  if (late == 2) {
-    // after layer_scan_kernel: the new entry's rows are in the cache and its logits with the others, the
-    // unit's records still describe the step before.  Record the append, then go on as after any scan.
-    // (Every wavefront has read the stored length before the first thread replaces it: a wavefront that
-    // started late would otherwise count the new entry twice and part ways with the others.)
-    __syncthreads();
-    if (n < unit_cap(d, u)) {
-      if (tid == 0) {
-        const size_t s = slots_of(d, u) + n;
-        d.crf[s] = 0.0f;
-        d.tau[s] = t;
-        d.pos[s] = t;
-        d.flags[s] = 0;
-        d.n[u] = n + 1;
-      }
-      n += 1;
+  // Every wavefront has read the stored length before the first thread replaces it: a wavefront that started late
+  // would otherwise count the new entry twice and part ways with the others.
+  __syncthreads();
+  const Slots base{s_row};
+  if (room) {
+    if (tid == 0) {
+      const size_t s = base + n;
+      d.crf[s] = 0.0f;
+      d.tau[s] = t;
+      d.pos[s] = t;
+      d.flags[s] = 0;
+      d.n[u] = n + 1;
     }
-    if (tid < d.G) {
-      sM[tid] = d.msum[((size_t)u * kMaxGroup + tid) * 2];
-      sInv[tid] = d.msum[((size_t)u * kMaxGroup + tid) * 2 + 1];
-    }
-    __threadfence_block();
-    __syncthreads();
+    n += 1;
   }
-  if (n > 0) {
-    const int nch = (n + kChunk - 1) / kChunk;
-    if (late != 2) merge_partials(d, u, urel, nch, seq, sM, sInv, sW, late ? nullptr : out, tid);
-    unit_bookkeeping(d, u, n, B, t, unit_logits(d, u), sM, sInv, (call_flags & 1u) != 0, val, evm, s_tab, s_tab_n, rb, phase, sh, tid);
-  }
-  if (!late) step_epilogue(d, t, advance, tid);
+  __threadfence_block();
+  __syncthreads();
+  if (n > 0) unit_bookkeeping<NT>(d, u, base, n, B, t, unit_logits(d, u), sM, sInv, (call_flags & 1u) != 0, val, evm, s_tab, s_tab_n, rb, phase, sh, tid);
+  if (!layer_time) step_epilogue(d, t, advance, tid);
 }
 
 // ------------------------------------------------------------------ prompt replay (scores of a loaded prompt)

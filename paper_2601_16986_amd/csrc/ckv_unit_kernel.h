@@ -23,8 +23,6 @@
 // follow the tile.  Units whose logits do not fit spill the logits of their
 // last blocks to the global logits buffer (same layout as the scan kernel's).
 #pragma once
-#include <type_traits>
-
 #include "ckv_kernels.h"
 
 namespace ckv {
