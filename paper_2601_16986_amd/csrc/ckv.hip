@@ -21,7 +21,6 @@ using namespace ckv;
 
 constexpr int kSide = 2;   // streams of the context's own for deferred bookkeeping
 constexpr int kBookGroup = 8;   // layers whose deferred bookkeeping goes out as one launch
-constexpr size_t kLayerScanPad = 48 << 10;      // dynamic LDS of layer_scan_kernel: with its 32 KB of static LDS, two workgroups per 160 KB
 
 // Scratch of ckv_probe_noalloc: device memory the library owns from the moment it is loaded, so that the
 // call never needs a caller's workspace or an allocation.  In host code `scratch` is only a handle: the
@@ -38,6 +37,7 @@ struct ckv_ctx {
   Dev dev;
   int units = 0;
   int units_per_layer = 0;
+  long long budget_total = 0;   // of all units, as last set by the host (a re-allocation keeps every sequence's total)
   int next_layer = 0;
   int n_cu = 256;
   float* seedmi = nullptr;      // workspace of the prompt replay
@@ -235,13 +235,21 @@ int launch_finish(ckv_ctx* c, hipStream_t s, int begin, int count, uint32_t flag
   return CKV_OK;
 }
 
-// Attention of `count` units from `begin` on, the new entries included.  At most two workgroups fit on a compute unit
-// (the unused dynamic LDS sees to that): the kernel's registers would allow three, and the dispatcher then crowds some
-// compute units while others idle (2.43 against 2.11 ms per step of 48 layers of 128 units; one per compute unit: 2.22).
+// Attention of `count` units from `begin` on, the new entries included.  Workgroups of eight wavefronts, each over one
+// block of 32 entries or over a chunk of 256.  One block each is a single round trip to memory and decides what the
+// smallest layers wait for; it needs eight times the workgroups, whose starts and partials cost more than they save
+// once they no longer fit the chip side by side.  The line lies at two workgroups per compute unit by the entries that
+// the budgets allow (us per layer, scan alone, one block / one chunk: 8 units of 2048 entries 10 / 23, 32 units 17 / 25,
+// 64 units of 1024 12 / 15, 64 units of 2048 25 / 28, 128 units of 2048 41 / 34, 256 units of 1024 32 / 28).
 int launch_layer_scan(ckv_ctx* c, hipStream_t s, int begin, int count, const uint16_t* q, const uint16_t* k_new, const uint16_t* v_new, void* out,
                       int logits, int defer_layer, int advance) {
-  hipLaunchKernelGGL((layer_scan_kernel<4, 1>), dim3((unsigned)count, (unsigned)((c->dev.max_chunks + 3) / 4)), dim3(256), kLayerScanPad, s, c->dev,
-                     begin, q, k_new, v_new, out, logits, defer_layer, advance);
+  const int mc = c->dev.max_chunks;
+  if (c->budget_total / c->units * count <= 2ll * c->n_cu * kChunk)
+    hipLaunchKernelGGL((layer_scan_kernel<8, 8>), dim3((unsigned)count, (unsigned)mc), dim3(512), 0, s, c->dev, begin, q, k_new, v_new, out, logits,
+                       defer_layer, advance);
+  else
+    hipLaunchKernelGGL((layer_scan_kernel<8, 1>), dim3((unsigned)count, (unsigned)((mc + 7) / 8)), dim3(512), 0, s, c->dev, begin, q, k_new, v_new, out,
+                       logits, defer_layer, advance);
   CKV_HIP(c, hipGetLastError());
   return CKV_OK;
 }
@@ -348,6 +356,8 @@ int upload_budgets(ckv_ctx* c, const int32_t* budgets, hipStream_t s) {
   for (int i = 0; i < l.n_layers; ++i)
     for (int b = 0; b < l.batch; ++b)
       for (int h = 0; h < l.n_kv_heads; ++h) tot[b] += budgets[((size_t)i * l.batch + b) * l.n_kv_heads + h];
+  c->budget_total = 0;
+  for (long long t : tot) c->budget_total += t;
   CKV_HIP(c, hipMemcpyAsync(c->dev.budget, budgets, (size_t)c->units * 4, hipMemcpyHostToDevice, s));
   CKV_HIP(c, hipMemcpyAsync(c->dev.btotal, tot.data(), (size_t)l.batch * 8, hipMemcpyHostToDevice, s));
   if (int rc = launch_schedule(c, s)) return rc;

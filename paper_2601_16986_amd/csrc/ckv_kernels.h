@@ -675,27 +675,28 @@ __device__ __forceinline__ T get_coherent(const T* p) {
 
 // ------------------------------------------------------------------ scan of few units, which appends by itself
 // The shape a model imposes is one call per layer, a few hundred units at most: too few for the fused kernel
-// (one workgroup per unit).  Here several workgroups share a unit and the grid itself is the work list: workgroup (x, y) takes chunks 4 y .. 4 y + 3 (256 entries each, one per
-// wavefront) of the layer's unit x and leaves at once if the unit is shorter.  (Units along x: consecutive
+// (one workgroup per unit).  Here several workgroups share a unit and the grid itself is the work list: workgroup (x, y) takes the y-th few chunks (256 entries each) of the layer's unit x and leaves at once if the unit is shorter.  (Units along x: consecutive
 // workgroups go to different XCDs, so the workgroups that have work - every unit's first, most units' second -
 // spread over all of them; with the chunk groups along x, and eight or a multiple of them, each XCD would get
 // one group index, the first few all the work, and a step takes 1.6 times as long.)  Nothing has to run before it:
 // every workgroup derives the unit's length after the append from the stored one (which stays as it is until
 // finish_kernel or append_kernel, which follows, has recorded the append), and the wavefront whose
 // chunk receives the new entry puts its key and value rows into the block it has just loaded (and into the
-// cache), so that the entry takes part like any cached one.  The four wavefronts combine their softmax states
-// in LDS; a unit of one workgroup (up to 1024 entries) is finished there and then, a longer one goes through
+// cache), so that the entry takes part like any cached one.  The wavefronts combine their softmax states
+// in LDS; a unit of one workgroup is finished there and then, a longer one goes through
 // one partial per workgroup, merged by the workgroup that publishes the last (coherent stores and loads).  The unit's softmax maximum and 1 / sum per head stay in `msum` for the bookkeeping.
 // In place of a kernel that appended and built a work list, a persistent scan over it and a merge of its partials by the
 // bookkeeping kernel: 7.6 + 35 us per layer of the 14B geometry then, 36 us now.
 // defer_layer >= 0: the bookkeeping follows on another stream, perhaps after the time has moved on; the step's time
 // is left for it, and moves on here if `advance` says that this was the step's last layer (nothing else in
 // this launch reads it).  logits = 0: attention only, nobody looks at the logits afterwards.
-// kW wavefronts per workgroup, each over 1 / kSplit of a chunk; the text above describes <4, 1>, the shape in
-// use.  Measured beside it on 128 units of 257 .. 8193 entries: fewer wavefronts per workgroup (<2, 1>, <1, 1>)
-// 2 % and 15 % slower per step, more (<8, 1>) 8 %, shorter spans (<4, 2>, <8, 2>, <8, 4>) 8 %, 23 % and 49 %
-// (also with three wavefronts per SIMD); rotating the units against the chunk groups, or the long units' last
-// chunks first: no difference.  What does matter is how many workgroups a compute unit may hold: see the launch.
+// kW wavefronts per workgroup, each over 1 / kSplit of a chunk; in use are <8, 1> (eight chunks per workgroup, the
+// blocks of a chunk streamed one ahead) and, for few units, <8, 8> (one chunk per workgroup, a block per wavefront; at
+// most kW = 8 wavefronts may share a chunk, a unit has one partial slot per chunk).  Also measured, us per layer, scan
+// alone, on 8 units / 128 units of 2048 entries on average (257 .. 8193) / 256 units of 1024: <8, 8> 10 / 41 / 32;
+// <16, 8> 11 / 45 / 36; <8, 4> 11 / 45 / 36; <4, 4> 11 / 39 / 31; <4, 2> 12 / 40 / 34; <4, 1> 15 / 36 / 32 (15 % more
+// without unused LDS that keeps a third workgroup off a compute unit); <8, 1> 23 / 34 / 28; <16, 2> 36 / 51 / 40;
+// <16, 1> 49 / 68 / 41.
 // grid: (units of the layer, ceil(max_chunks * kSplit / kW)), 64 kW threads.
 // Entry rr of the block in (ka, va) is replaced by the rows in `rows` (LDS: 128 bf16 of the key, then 128 of the
 // value), piece by piece, so that few registers are live at a time.
@@ -725,7 +726,7 @@ __device__ __forceinline__ void inject_entry(KFrag& ka, VFrag& va, int rr, const
 }
 
 template <int kW, int kSplit>
-__global__ __launch_bounds__(64 * kW, 3) void layer_scan_kernel(Dev d, int unit_begin, const uint16_t* __restrict__ q,
+__global__ __launch_bounds__(64 * kW, kSplit >= 4 ? 2 : 3) void layer_scan_kernel(Dev d, int unit_begin, const uint16_t* __restrict__ q,
                                                                 const uint16_t* __restrict__ k_new,
                                                                 const uint16_t* __restrict__ v_new, void* out, int logits,
                                                                 int defer_layer, int advance) {
@@ -775,10 +776,14 @@ __global__ __launch_bounds__(64 * kW, 3) void layer_scan_kernel(Dev d, int unit_
     const size_t off = (size_t)my_seg * kSegElems + (size_t)(c % kSplit) * kSpanBlk * kBlkElems + lane * 8;
     const uint16_t* kcur = d.K + off;
     const uint16_t* vcur = d.V + off;
-    KFrag ka;
-    VFrag va;
-    load_k(ka, kcur);
-    load_v(va, vcur);
+    // a span of one or two blocks is requested whole, a longer one block by block
+    constexpr int kAhead = kSpanBlk <= 2 ? kSpanBlk : 1;
+    KFrag ka[kAhead];
+    VFrag va[kAhead];
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) load_k(ka[i], kcur + (size_t)min(i, nb - 1) * kBlkElems);
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) load_v(va[i], vcur + (size_t)min(i, nb - 1) * kBlkElems);
     bf16x8 qv[4];
     {
       const uint16_t* qrow = q + ((size_t)urel * G + (head_lane ? j : 0)) * kDim + 8 * kg;
@@ -808,25 +813,40 @@ __global__ __launch_bounds__(64 * kW, 3) void layer_scan_kernel(Dev d, int unit_
     }
     float* lds_lg = logits ? s_lg[w] : nullptr;
     float* lg_dst = d.logits + ((size_t)u * d.cap + (size_t)e0) * G + 4 * min(lane, 8 * G - 1);
-    // one block ahead (two ahead is slower here as well); the loads stay unconditional (the
-    // last block is read twice), so that the waits the compiler inserts are exact
-    for (int blk = 0; blk < nb; ++blk) {
-      const bool last = blk + 1 == nb;
-      const size_t nxt = (size_t)(last ? blk : blk + 1) * kBlkElems;
-      if (last && inject) {
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        inject_entry(ka, va, (n_old - e0) & 31, s_new[w], lane);
+    if constexpr (kAhead == kSpanBlk) {
+#pragma unroll
+      for (int blk = 0; blk < kSpanBlk; ++blk) {
+        if (blk < nb) {
+          if (blk + 1 == nb && inject) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            inject_entry(ka[blk], va[blk], (n_old - e0) & 31, s_new[w], lane);
+          }
+          float sv[8];
+          scan_qk(ka[blk], qv, sv, d.scale_log2e, blk * kBlk, nv, lds_lg, kLgRow, lg_dst, G, lane);
+          scan_pv(sv, va[blk], acc, m_run, l_run, lane);
+        }
       }
-      float sv[8];
-      scan_qk(ka, qv, sv, d.scale_log2e, blk * kBlk, nv, lds_lg, kLgRow, lg_dst, G, lane);
-      load_k(ka, kcur + nxt);
-      scan_pv(sv, va, acc, m_run, l_run, lane);
-      load_v(va, vcur + nxt);
+    } else {
+      // one block ahead (two ahead is slower here as well); the loads stay unconditional (the
+      // last block is read twice), so that the waits the compiler inserts are exact
+      for (int blk = 0; blk < nb; ++blk) {
+        const bool last = blk + 1 == nb;
+        const size_t nxt = (size_t)(last ? blk : blk + 1) * kBlkElems;
+        if (last && inject) {
+          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+          inject_entry(ka[0], va[0], (n_old - e0) & 31, s_new[w], lane);
+        }
+        float sv[8];
+        scan_qk(ka[0], qv, sv, d.scale_log2e, blk * kBlk, nv, lds_lg, kLgRow, lg_dst, G, lane);
+        load_k(ka[0], kcur + nxt);
+        scan_pv(sv, va[0], acc, m_run, l_run, lane);
+        load_v(va[0], vcur + nxt);
+      }
     }
     l_run += __shfl_xor(l_run, 16);
     l_run += __shfl_xor(l_run, 32);
   }
-  // ---- the workgroup's four states into one
+  // ---- the workgroup's states into one
   if (head_lane && kg == 0) {
     s_m[w][j] = m_run;
     s_l[w][j] = l_run;
