@@ -158,17 +158,16 @@ def seed_prompt_bench(cfg, device, P, W):
     bytes_layer = entries * 512
     # what the replay needs at the least: every key row once (weights only, so no values), the queries, and the
     # scores read and written once per query
-    # as built: a tile of 16 query columns holds Q = 16 // G queries; a batch of tiles (as many as the decode
-    # workspace holds, at most 16) makes two passes over the keys (softmax partials, then mean weights: 4 B per
-    # entry and query written); the rewards kernel reads the weights and writes the rewards in their place, the
-    # recurrence reads them; the scores are read and written once per batch
-    Q = max(1, 16 // cfg.group)
-    tiles = (W + Q - 1) // Q
-    fit = min(cfg.n_layers * cfg.group // Q, 16)
+    # as built: 16 queries fill G tiles of 16 columns; a batch of such groups (as many as the decode workspace holds,
+    # at most 16 tiles) makes two passes over the keys (softmax partials, then mean weights: 4 B per entry and query
+    # written); the hits kernel reads the weights and writes a bit per entry and query, which the recurrence reads;
+    # the scores are written (from the second batch on also read) once per batch
+    groups = (W + 15) // 16
+    fit = min(cfg.n_layers * cfg.group // 16, 16 // cfg.group)
     per_batch = fit if fit >= 2 else 1
-    passes = (tiles + per_batch - 1) // per_batch
+    passes = (groups + per_batch - 1) // per_batch
     min_bytes = upl * (P * 256 + W * cfg.group * 256 + W * P * 16)
-    pass_bytes = upl * (passes * P * (2 * 256 + 16) + 2 * W * cfg.group * 256 + W * P * 16)
+    pass_bytes = upl * (passes * P * (2 * 256 + 8) + (passes - 1) * P * 8 + 2 * W * cfg.group * 256 + W * P * 8 + W * P // 4)
     sec = ms / cfg.n_layers * 1e-3
     assert g.status() == 0
     g.close()
@@ -176,7 +175,7 @@ def seed_prompt_bench(cfg, device, P, W):
             "n_gpus": 1, "ms_per_layer": ms / cfg.n_layers, "higher_is_better": True, "dtype": "bf16", "data": "synthetic",
             "config": {"workload": f"{cfg.name} geometry: {cfg.n_layers} layers, batch {cfg.batch}, {cfg.n_q_heads}/{cfg.n_kv_heads} heads, "
                                    f"prompt of {P} tokens, window of {W} queries", "units_per_layer": upl,
-                       "entries_scanned_per_layer": entries, "queries_per_tile": Q, "tiles": tiles, "batches": passes, "passes_over_the_keys": 2 * passes},
+                       "entries_scanned_per_layer": entries, "groups_of_16_queries": groups, "batches": passes, "passes_over_the_keys": 2 * passes},
             # K and V of the W visible prefixes, the bytes a query-by-query replay of decode steps moves (the figure of
             # the first version, kept for comparison; the replay as built reads far less, so this can exceed 1)
             "decode_replay_equivalent_gbps": bytes_layer / sec / 1e9,
@@ -428,7 +427,7 @@ def main():
         fused_bytes = step_bytes = scan_bytes + int(cfg.n_units) * cfg.group * 512
     fused_waves, _ = g.path_info()
     # dominant kernel of an all-layers step: the fused per-unit kernel if the context uses it, else the scan kernel
-    kernel_name = f"unit_kernel<{fused_waves}>" if fused_waves else "scan_kernel<false>"
+    kernel_name = f"unit_kernel<{fused_waves}>" if fused_waves else "layer_scan_kernel"
     kernel_bytes = fused_bytes if fused_waves else scan_bytes
     scan_avg_ms = scan_ms / max(launches, 1)
     achieved = kernel_bytes / (scan_avg_ms * 1e-3) / 1e9

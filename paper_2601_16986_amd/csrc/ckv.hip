@@ -182,11 +182,11 @@ Carve carve(const ckv_layout* l, size_t tab_len) {
   c.owned = take(U * 4);
   c.spare = take((size_t)(l->pool_slots / kSeg) * 4);
   // prompt replay (ckv_seed_prompt), one layer at a time: softmax maximum and 1 / sum per query column of a
-  // batch; and, for contexts whose decode workspace is too small to lend the replay room for several tiles of
-  // queries, one tile's softmax partials per chunk and the weights (then rewards) of its up to 16 queries
+  // batch; and, for contexts whose decode workspace is too small to lend the replay room for several groups of
+  // queries, one group's softmax partials (per block at most) and the weights (then hits) of its 16 queries
   const size_t UL = (size_t)l->batch * l->n_kv_heads;
   c.seedmi = take((size_t)kSeedTiles * UL * kSeedCols * 2 * 4);
-  c.seedml = take(UL * mc * kSeedCols * 2 * 4);
+  c.seedml = take(UL * mc * kSegBlocks * G * kSeedCols * 2 * 4);
   c.seedrw = take(UL * (size_t)l->cap * kSeedCols * 4);
   c.total = off;
   return c;
@@ -350,6 +350,27 @@ int launch_probe(ckv_ctx* c, const Dev& d, int begin, int count, const uint16_t*
   return CKV_OK;
 }
 
+// Wavefronts that share a unit's blocks in the replay's passes over the keys: a multiple of four (a workgroup's), at
+// most one per block.  Three workgroups fit on a compute unit; of the splits that the partials have room for, the one
+// that leaves the least of the chip idle (places in the last round, and the unit's blocks not dividing evenly),
+// the coarsest of equals.
+int seed_spans(const ckv_ctx* c, int entries, int count) {
+  const long long blocks = (entries + kBlk - 1) / kBlk, places = 3ll * c->n_cu;
+  const long long most = std::min<long long>((blocks + 3) / 4 * 4, (long long)kSegBlocks * c->dev.max_chunks);
+  int best = 4;
+  double best_eff = 0.0;
+  for (long long S = 4; S <= most; S += 4) {
+    const long long per = (blocks + S - 1) / S, wgs = (long long)count * S / 4, rounds = (wgs + places - 1) / places;
+    const double eff = (double)(blocks * count) / (double)(rounds * places * 4 * per);
+    if (eff > 1.02 * best_eff) {
+      best_eff = eff;
+      best = (int)S;
+    }
+    if (rounds > 4) break;
+  }
+  return best;
+}
+
 int upload_budgets(ckv_ctx* c, const int32_t* budgets, hipStream_t s) {
   const ckv_layout& l = c->lay;
   std::vector<long long> tot(l.batch, 0);
@@ -458,9 +479,9 @@ int ckv_init(ckv_ctx** out, const ckv_layout* layout, const int32_t* budgets, co
     return CKV_EINVAL;
   }
   const void* lds_kernels[3] = {reinterpret_cast<const void*>(finish_kernel<kThreads>), reinterpret_cast<const void*>(finish_kernel<kWideThreads>),
-                                reinterpret_cast<const void*>(seed_hits_kernel)};
-  if (hipFuncSetAttribute(reinterpret_cast<const void*>(seed_scan_kernel<false>), hipFuncAttributeMaxDynamicSharedMemorySize, kSeedTiles * 4096) != hipSuccess ||
-      hipFuncSetAttribute(reinterpret_cast<const void*>(seed_scan_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize, kSeedTiles * 4096) != hipSuccess) {
+                                reinterpret_cast<const void*>(seed_hits_kernel<0>)};
+  if (hipFuncSetAttribute(reinterpret_cast<const void*>(seed_scan_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kSeedTiles * 4096) != hipSuccess ||
+      hipFuncSetAttribute(reinterpret_cast<const void*>(seed_weights_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kSeedTiles * 4096) != hipSuccess) {
     delete c;
     return CKV_EHIP;
   }
@@ -751,52 +772,53 @@ int ckv_seed_prompt(ckv_ctx* c, int32_t layer, const void* q_obs, int32_t W, voi
   hipStream_t s = (hipStream_t)stream;
   if (int rc = join_side(c, s)) return rc;
   const int begin = layer * c->units_per_layer, count = c->units_per_layer;
-  const dim3 sgrid((unsigned)std::min((P + kThreads - 1) / kThreads, 64), (unsigned)count);
-  hipLaunchKernelGGL(seed_state_kernel, sgrid, dim3(kThreads), 0, s, c->dev, begin, P, (int)W, 0, 0);
-  CKV_HIP(c, hipGetLastError());
-  // A tile of 16 query columns holds the G heads of Q queries.  Per batch of tiles: a pass over the keys for the
-  // softmax partials of all its queries, their maxima and sums, a second pass for the mean weights, the
-  // rewards (top-p rule), the score recurrence.  The batch's weights and softmax partials live in the decode
-  // paths' logits and partials (idle here, rewritten by the next scan before anything reads them) when those
-  // hold at least two tiles, else in the replay's own one-tile buffers.
-  const int G = c->dev.G, Q = kSeedCols / G;
-  const size_t UL = (size_t)count, cap = (size_t)c->lay.cap, mc = (size_t)c->dev.max_chunks;
-  const size_t tile_rw = (size_t)Q * UL * cap * 4, tile_ml = UL * mc * kSeedCols * 2 * 4;
-  const size_t big_lg = (size_t)c->units * cap * (size_t)G * 4, big_ml = (size_t)c->units * (size_t)c->dev.slots * (size_t)G * kDim * 4;
-  const int fit = (int)std::min<size_t>({big_lg / tile_rw, big_ml / tile_ml, (size_t)kSeedTiles});
+  // Groups of 16 queries fill G tiles of 16 columns each.  Per batch of groups: a pass over the keys for the softmax
+  // partials of all its queries, their maxima and sums, a second pass for the mean weights, the hits (top-p rule),
+  // the score recurrence.  The batch's weights and softmax partials live in the decode paths' logits (a row of cap
+  // floats per unit and query: G rows of every unit) and partials (idle here, rewritten by the next scan before anything
+  // reads them) when those hold at least two groups, else in the replay's own buffers for one.
+  const int G = c->dev.G;
+  const int fit = std::min(c->lay.n_layers * G / kSeedGroup, kSeedTiles / G);
   float *ml = c->seedml, *rw = c->seedrw, *mi = c->seedmi;
-  int tiles = 1;
+  int groups = 1;
   if (fit >= 2) {
-    tiles = fit;
+    groups = fit;
     rw = c->dev.logits;
     ml = c->dev.partial;
   }
+  const int batch = groups * kSeedGroup;
   const bool topp = c->par.reward_mode == CKV_REWARD_TOPP_HIT;
-  for (int j0 = 0; j0 < W; j0 += tiles * Q) {
-    const int nq = std::min(tiles * Q, (int)W - j0), nt = (nq + Q - 1) / Q;
-    const int n_last = P - W + j0 + nq;                    // entries the batch's last query sees
-    const int chunks = (n_last + kChunk - 1) / kChunk;
-    const dim3 sgrid2((unsigned)((chunks + kThreads / 64 - 1) / (kThreads / 64)), (unsigned)count);
-    hipLaunchKernelGGL(seed_scan_kernel<false>, sgrid2, dim3(kThreads), (size_t)nt * 4096, s, c->dev, begin, (const uint16_t*)q_obs, j0,
-                       nq, Q, P, (int)W, ml, (const float*)mi, rw);
+  for (int j0 = 0; j0 < W; j0 += batch) {
+    const int nq = std::min(batch, (int)W - j0), nt = (nq + kSeedGroup - 1) / kSeedGroup * G;
+    const int S = seed_spans(c, P - W + j0 + nq, count);
+    const dim3 sgrid((unsigned)((S + 3) / 4), (unsigned)count);
+    hipLaunchKernelGGL(seed_scan_kernel, sgrid, dim3(kThreads), (size_t)nt * 4096, s, c->dev, begin, (const uint16_t*)q_obs, j0, nq, P, (int)W, S, ml);
     CKV_HIP(c, hipGetLastError());
-    hipLaunchKernelGGL(seed_stats_kernel, dim3((unsigned)count), dim3(kSeedTiles * kSeedCols), 0, s, c->dev, j0, nq, Q, P, (int)W,
-                       (const float*)ml, mi);
+    hipLaunchKernelGGL(seed_stats_kernel, dim3((unsigned)count), dim3(kSeedTiles * kSeedCols), 0, s, c->dev, nq, S, (const float*)ml, mi);
     CKV_HIP(c, hipGetLastError());
-    hipLaunchKernelGGL(seed_scan_kernel<true>, sgrid2, dim3(kThreads), (size_t)nt * 4096, s, c->dev, begin, (const uint16_t*)q_obs, j0,
-                       nq, Q, P, (int)W, ml, (const float*)mi, rw);
+    hipLaunchKernelGGL(seed_weights_kernel, sgrid, dim3(kThreads), (size_t)nt * 4096, s, c->dev, begin, (const uint16_t*)q_obs, j0, nq, P, (int)W, S,
+                       (const float*)mi, rw);
     CKV_HIP(c, hipGetLastError());
     if (topp) {
-      hipLaunchKernelGGL(seed_hits_kernel, dim3((unsigned)nq, (unsigned)count), dim3(kSeedThreads), c->finish_lds, s, c->dev, begin, j0, P,
-                         (int)W, rw);
+      const int per = (P - W + j0 + nq + kSeedThreads - 1) / kSeedThreads;          // entries per thread of the longest row
+      auto hits = [&](auto kernel, size_t lds) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)nq, (unsigned)count), dim3(kSeedThreads), lds, s, c->dev, begin, j0, P, (int)W, rw);
+      };
+      if (per <= 8) hits(seed_hits_kernel<8>, kSeedList * 4);
+      else if (per <= 16) hits(seed_hits_kernel<16>, kSeedList * 4);
+      else if (per <= 20) hits(seed_hits_kernel<20>, kSeedList * 4);
+      else if (per <= 24) hits(seed_hits_kernel<24>, kSeedList * 4);
+      else if (per <= 32) hits(seed_hits_kernel<32>, kSeedList * 4);
+      else hits(seed_hits_kernel<0>, c->finish_lds);
       CKV_HIP(c, hipGetLastError());
     }
-    hipLaunchKernelGGL(seed_crf_kernel, dim3((unsigned)((P + 4 * kThreads - 1) / (4 * kThreads)), (unsigned)count), dim3(kThreads), 0, s,
-                       c->dev, begin, j0, nq, P, (int)W, (const float*)rw);
+    const dim3 cgrid((unsigned)((P + 4 * kThreads - 1) / (4 * kThreads)), (unsigned)count);
+    if (topp)
+      hipLaunchKernelGGL(seed_crf_kernel<true>, cgrid, dim3(kThreads), 0, s, c->dev, begin, j0, nq, P, (int)W, c->par.t0 - 1, (const float*)rw);
+    else
+      hipLaunchKernelGGL(seed_crf_kernel<false>, cgrid, dim3(kThreads), 0, s, c->dev, begin, j0, nq, P, (int)W, c->par.t0 - 1, (const float*)rw);
     CKV_HIP(c, hipGetLastError());
   }
-  hipLaunchKernelGGL(seed_state_kernel, dim3(1, (unsigned)count), dim3(kThreads), 0, s, c->dev, begin, P, (int)W, 1, c->par.t0 - 1);
-  CKV_HIP(c, hipGetLastError());
   return CKV_OK;
 }
 

@@ -10,8 +10,8 @@
 //
 // and beside the step:
 //
-//   load_cache_kernel, seed_state_kernel   fill a layer's caches
-//   seed_scan_kernel, seed_stats_kernel, seed_hits_kernel, seed_crf_kernel   scores of a loaded prompt from its last queries
+//   load_cache_kernel   fills a layer's caches
+//   seed_scan_kernel, seed_stats_kernel, seed_weights_kernel, seed_hits_kernel, seed_crf_kernel   scores of a loaded prompt from its last queries
 //   evict_kernel, evict_move_kernel   eviction + compaction on its own (Alg. 1 Step 4, or the sink + recent window policy)
 //   probe_scan_kernel, probe_kernel   answer-probe classes
 //   rebudget_kernel  Alg. 2 with integer apportionment, one workgroup/sequence
@@ -264,6 +264,9 @@ __device__ __forceinline__ int block_sum_int(int v, RedBuf& rb, int& phase, int 
   return r;
 }
 
+// a value that is the same in all lanes, into scalar registers
+__device__ __forceinline__ float uniform_f32(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
+
 template <int kCtrl>
 __device__ __forceinline__ float dpp_f32(float v) {
   return __int_as_float(dpp_i32<kCtrl>(__float_as_int(v)));
@@ -515,26 +518,6 @@ __global__ __launch_bounds__(kThreads) void load_cache_kernel(Dev d, int unit_be
       d.tau[base + r] = tau0 ? tau0[(size_t)urel * P + r] : (P - 1);
       d.flags[base + r] = 0;
     }
-  }
-}
-
-// Before the replay of a prompt's last W queries (done = 0): every entry of the layer's units starts as
-// referenced once, on arrival (CRF 1, tau = position), the W entries of the window as not yet arrived
-// (CRF 0; their own query's step is their arrival).  After it (done = 1): the replay leaves no trace in
-// the units' aggregated-CRF window, and their last-step time is the one a fresh context has.
-__global__ __launch_bounds__(kThreads) void seed_state_kernel(Dev d, int unit_begin, int P, int W, int done, int t_unit) {
-  const int u = unit_begin + blockIdx.y;
-  if (done) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-      d.window[u] = 0;
-      d.t_unit[u] = t_unit;
-    }
-    return;
-  }
-  const Slots base = slots_of(d, u);
-  for (int i = blockIdx.x * kThreads + threadIdx.x; i < P; i += gridDim.x * kThreads) {
-    d.crf[base + i] = i < P - W ? 1.0f : 0.0f;
-    d.tau[base + i] = i;
   }
 }
 
@@ -1813,17 +1796,46 @@ __device__ __forceinline__ EntryRow load_row_input(const NewEntry& ne, int tid) 
   return r;
 }
 
+// Entries equal to the threshold: only as many as needed, lower positions first.  above = total weight of the entries
+// above theta, ties = entries equal to it.
+template <int R, int NT>
+__device__ __forceinline__ HitRule tie_rule(const Dev& d, Slots base, int n, const float (&a)[R], uint32_t theta, float above, int ties,
+                                            int new_last_t, RedBuf& rb, int& phase, int tid) {
+  HitRule rule{theta, true, 0x7FFFFFFF};
+  if (ties <= 1) return rule;
+  const float th = __uint_as_float(theta);
+  float c = above;
+  int r = 0;
+  do {
+    c += th;
+    ++r;
+  } while (c <= d.top_p && r < ties);
+  if (r >= ties) return rule;
+  rule.ties_all = false;
+  int X = 0;   // r-th smallest position among the ties (rare: positions are re-read from memory)
+  for (int bit = 30; bit >= 0; --bit) {
+    const int trial = X | (1 << bit);
+    int cnt = 0;
+    for (int k = 0; k < R; ++k) {
+      const int i = 4 * (tid + (k >> 2) * NT) + (k & 3);
+      if (__float_as_uint(a[k]) == theta && i < n && ((new_last_t >= 0 && i == n - 1) ? new_last_t : d.pos[base + i]) < trial) ++cnt;
+    }
+    cnt = block_sum_int<NT>(cnt, rb, phase, tid);
+    if (cnt < r) X = trial;
+  }
+  rule.pos_cut = X;
+  return rule;
+}
+
 // Step 1 over weights in registers (a[4 c + e] = mean weight of entry 4 (tid + c NT) + e, 0 beyond n).  lst: 64 ints of
 // LDS (lst_cap >= 64, or the short list is not used); sh: the callers' exchange words (5 .. 7 are used here).
 // new_last_t >= 0: the unit's last entry is not in the cache and has this position.
-// kList: candidates the short list may hold (64: one per lane of the wavefront that finishes the bisection;
-// 128, 256: two or four per lane, for long units with flat weights, whose bucket holds more).
-template <int R, int NT = kThreads, int kList = 64>
+// (Fewer rounds by bracketing, top_p_flat below, gain nothing here, where other wavefronts stream meanwhile or the
+// other phases' round trips decide: fused step 0.99-1.00 of the speed, bookkeeping of 128 units 21 us either way.)
+template <int R, int NT = kThreads>
 __device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, const float (&a)[R], int* lst, int lst_cap, int new_last_t,
                                               RedBuf& rb, int& phase, int* sh, int tid) {
   uint32_t theta = 0;
-  bool ties_all = true;
-  int pos_cut = 0x7FFFFFFF;
   if (d.reward_mode == 0) {
     // largest pattern theta with sum{a >= theta} > p, two bits per round (one barrier each): the three
     // candidates' sums are nested, so the largest candidate that passes is what bit-by-bit bisection
@@ -1848,7 +1860,7 @@ __device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, c
     float list_above = 0.f;             //   total weight of the entries above theta
     for (; bit > kListBit; bit -= 2) round(bit);
     // With the top 12 bits fixed, the weights that can still decide a candidate, those in
-    // [theta, theta + 2^18), are usually a handful.  If at most kList, they are collected in LDS (in a fixed
+    // [theta, theta + 2^18), are usually a handful.  If at most 64, they are collected in LDS (in a fixed
     // order: by wavefront, register index, lane) and one wavefront finishes the bisection on them alone:
     // nine rounds without barriers over one register instead of R.
     {
@@ -1877,7 +1889,7 @@ __device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, c
         m += cw;
       }
       phase ^= 1;
-      if (m <= kList && lst_cap >= kList) {
+      if (m <= 64 && lst_cap >= 64) {
 #pragma unroll
         for (int k = 0; k < R; ++k) {
           const uint32_t b = __float_as_uint(a[k]);
@@ -1894,62 +1906,24 @@ __device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, c
           // bucket, exceeds p (what the remaining rounds of the bisection would arrive at).  Every entry
           // equal to theta is in the list too, so the number of such ties and the weight above theta are
           // known here as well, without two more reductions over all entries.
-          if constexpr (kList == 64) {
-            const uint32_t bj = lane < m ? (uint32_t)lst[lane] : 0u;
-            const float aj = __uint_as_float(bj);
-            float sj = 0.f;
-            for (int k = 0; k < m; ++k) {                       // m is uniform; candidates in list order
-              const uint32_t bk = (uint32_t)__builtin_amdgcn_readlane((int)bj, k);
-              sj += (bk >= bj) ? __uint_as_float(bk) : 0.f;
-            }
-            const uint32_t mine_ok = (lane < m && above_bucket + sj > d.top_p) ? bj : 0u;
-            uint32_t th = mine_ok;
+          const uint32_t bj = lane < m ? (uint32_t)lst[lane] : 0u;
+          const float aj = __uint_as_float(bj);
+          float sj = 0.f;
+          for (int k = 0; k < m; ++k) {                       // m is uniform; candidates in list order
+            const uint32_t bk = (uint32_t)__builtin_amdgcn_readlane((int)bj, k);
+            sj += (bk >= bj) ? __uint_as_float(bk) : 0.f;
+          }
+          const uint32_t mine_ok = (lane < m && above_bucket + sj > d.top_p) ? bj : 0u;
+          uint32_t th = mine_ok;
 #pragma unroll
-            for (int o = 32; o > 0; o >>= 1) th = max(th, (uint32_t)__shfl_xor((int)th, o));
-            if (th != 0u) theta = th;
-            const int n_ties = __popcll(__ballot(lane < m && bj == theta));
-            const float above_l = above_bucket + wave_sum_f32((lane < m && bj > theta) ? aj : 0.f);
-            if (lane == 0) {
-              sh[7] = (int)theta;
-              sh[5] = n_ties;
-              sh[6] = __float_as_int(above_l);
-            }
-          } else {
-            // the same with kList / 64 candidates per lane (candidate lane + 64 c), the others read from LDS
-            constexpr int kC = kList / 64;
-            uint32_t bj[kC];
-            float sj[kC];
-#pragma unroll
-            for (int c = 0; c < kC; ++c) {
-              bj[c] = lane + 64 * c < m ? (uint32_t)lst[lane + 64 * c] : 0u;
-              sj[c] = 0.f;
-            }
-            for (int k = 0; k < m; ++k) {                     // candidates in list order
-              const uint32_t bk = (uint32_t)lst[k];
-              const float ak = __uint_as_float(bk);
-#pragma unroll
-              for (int c = 0; c < kC; ++c) sj[c] += (bk >= bj[c]) ? ak : 0.f;
-            }
-            uint32_t th = 0u;
-#pragma unroll
-            for (int c = 0; c < kC; ++c) th = max(th, (lane + 64 * c < m && above_bucket + sj[c] > d.top_p) ? bj[c] : 0u);
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) th = max(th, (uint32_t)__shfl_xor((int)th, o));
-            if (th != 0u) theta = th;
-            int n_ties = 0;
-            float mine_above = 0.f;
-#pragma unroll
-            for (int c = 0; c < kC; ++c) {
-              const bool in = lane + 64 * c < m;
-              n_ties += __popcll(__ballot(in && bj[c] == theta));
-              mine_above += (in && bj[c] > theta) ? __uint_as_float(bj[c]) : 0.f;
-            }
-            const float above_l = above_bucket + wave_sum_f32(mine_above);
-            if (lane == 0) {
-              sh[7] = (int)theta;
-              sh[5] = n_ties;
-              sh[6] = __float_as_int(above_l);
-            }
+          for (int o = 32; o > 0; o >>= 1) th = max(th, (uint32_t)__shfl_xor((int)th, o));
+          if (th != 0u) theta = th;
+          const int n_ties = __popcll(__ballot(lane < m && bj == theta));
+          const float above_l = above_bucket + wave_sum_f32((lane < m && bj > theta) ? aj : 0.f);
+          if (lane == 0) {
+            sh[7] = (int)theta;
+            sh[5] = n_ties;
+            sh[6] = __float_as_int(above_l);
           }
         }
         block_sync<NT>(rb);
@@ -1976,33 +1950,175 @@ __device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, c
         above = block_sum_f32<NT>(above, rb, phase, tid);
         ties = block_sum_int<NT>(ties, rb, phase, tid);
       }
-      if (ties > 1) {
-        const float th = __uint_as_float(theta);
-        float c = above;
-        int r = 0;
-        do {
-          c += th;
-          ++r;
-        } while (c <= d.top_p && r < ties);
-        if (r < ties) {
-          ties_all = false;
-          int X = 0;   // r-th smallest position among the ties (rare: positions are re-read from memory)
-          for (int bit = 30; bit >= 0; --bit) {
-            const int trial = X | (1 << bit);
-            int cnt = 0;
-            for (int k = 0; k < R; ++k) {
-              const int i = 4 * (tid + (k >> 2) * NT) + (k & 3);
-              if (__float_as_uint(a[k]) == theta && i < n && ((new_last_t >= 0 && i == n - 1) ? new_last_t : d.pos[base + i]) < trial) ++cnt;
-            }
-            cnt = block_sum_int<NT>(cnt, rb, phase, tid);
-            if (cnt < r) X = trial;
-          }
-          pos_cut = X;
-        }
-      }
+      return tie_rule<R, NT>(d, base, n, a, theta, above, ties, new_last_t, rb, phase, tid);
     }
   }
-  return HitRule{theta, ties_all, pos_cut};
+  return HitRule{theta, true, 0x7FFFFFFF};
+}
+
+// Step 1 over long units of flat weights (the prompt replay): the same threshold in fewer passes over the registers,
+// with a longer list at the end.  lst: kList ints of LDS; sh[5 .. 7] are used.  theta = 0: every entry is hit.
+template <int R, int NT, int kList>
+__device__ __forceinline__ HitRule top_p_flat(const Dev& d, Slots base, int n, const float (&a)[R], int* lst, RedBuf& rb, int& phase, int* sh,
+                                              int tid) {
+  uint32_t theta = 0;
+  // The largest pattern theta with sum{a >= theta} > p lies in [lo, hi): sum{a >= lo} > p (lo = 0: not known to), and
+  // sum{a >= hi} <= p.  A round (one barrier) tries three patterns.  Patterns of positive floats order like their
+  // logarithms, in which the sum falls smoothly, so after a first round around the mean weight the three are
+  // the linear interpolation and a sixteenth of the bracket to either side of it; every third round, in case
+  // that creeps, the quarters.  It ends when the bracket cannot hold more than kList weights
+  // (each is at least lo, together they are the difference of the two sums): 3 or 4 rounds, where two bits of
+  // the pattern per round took six to reach as short a list (128 units of 9350 entries, 32 queries: 25 us less).
+  // Weights are below 2.
+  uint32_t lo = 0u, hi = 0x40000000u;
+  float s_lo = 1.0f, s_hi = 0.0f;
+  bool from_list = false;             // the tail ran on the short list, which also gave:
+  int list_ties = 0;                  //   entries equal to theta
+  float list_above = 0.f;             //   total weight of the entries above theta
+  bool try_list = true;
+  int turn = 0;
+  // entries below (1 - p) / n cannot make up the rest: theta is rarely lower, nor often far above the mean
+  const float p = d.top_p;
+  uint32_t c1 = min(max(__float_as_uint(fmaxf(1.0f - p, 1e-3f) / (float)n), 1u << 23), 0x3F000000u);
+  uint32_t c2 = c1 + (3u << 22), c3 = min(c1 + (1u << 25), hi - 1u);
+#pragma unroll 1
+  while (true) {
+    float p1 = 0.f, p2 = 0.f, p3 = 0.f;
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      const uint32_t b = __float_as_uint(a[k]);
+      p1 += (b >= c1) ? a[k] : 0.f;
+      p2 += (b >= c2) ? a[k] : 0.f;
+      p3 += (b >= c3) ? a[k] : 0.f;
+    }
+    block_sum3_f32<NT>(p1, p2, p3, rb, phase, tid);
+    p1 = uniform_f32(p1);
+    p2 = uniform_f32(p2);
+    p3 = uniform_f32(p3);
+    // c1 <= c2 <= c3, the sums fall
+    const bool g1 = p1 > p, g2 = p2 > p, g3 = p3 > p;
+    hi = g3 ? hi : g2 ? c3 : g1 ? c2 : c1;
+    s_hi = g3 ? s_hi : g2 ? p3 : g1 ? p2 : p1;
+    lo = g3 ? c3 : g2 ? c2 : g1 ? c1 : lo;
+    s_lo = g3 ? p3 : g2 ? p2 : g1 ? p1 : s_lo;
+    theta = lo;
+    const uint32_t w = hi - lo;
+    if (w <= 1u) break;
+    if (try_list && s_lo - s_hi <= (float)kList * __uint_as_float(lo)) {
+      // The weights that can still decide, collected in LDS (in a fixed order: by wavefront, register index,
+      // lane): one wavefront finishes on them alone.
+      const uint32_t from = max(lo, 1u);
+      const int lane = tid & 63, wave = tid >> 6;
+      int mine = 0;
+#pragma unroll
+      for (int k = 0; k < R; ++k) {
+        mine += __popcll(__ballot(__float_as_uint(a[k]) - from < hi - from));
+      }
+      if (lane == 0) rb.v[phase][wave] = (u64)(uint32_t)mine;
+      block_sync<NT>(rb);
+      const float above_bucket = s_hi;
+      int m = 0, off = 0;
+#pragma unroll
+      for (int ww = 0; ww < NT / 64; ++ww) {
+        const int cw = (int)(uint32_t)rb.v[phase][ww];
+        off += ww < wave ? cw : 0;
+        m += cw;
+      }
+      phase ^= 1;
+      if (m <= kList) {
+        from_list = true;
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+          const uint32_t b = __float_as_uint(a[k]);
+          const bool in = b - from < hi - from;
+          const unsigned long long mask = __ballot(in);
+          if (mask == 0ull) continue;                      // most registers of a wavefront hold none
+          const int r = off + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+          if (in) lst[r] = (int)b;
+          off += __popcll(mask);
+        }
+        block_sync<NT>(rb);
+        if (wave == 0) {
+          // The largest pattern theta with sum{a >= theta} > p is a candidate's own pattern: the largest one whose sum
+          // of candidates at least as large, on top of what lies above the bracket, exceeds p.  Every entry
+          // equal to theta is in the list too, so the number of such ties and the weight above theta are
+          // known here as well, without two more reductions over all entries.
+          // kList / 64 candidates per lane (candidate lane + 64 c), the others read from LDS
+          constexpr int kC = kList / 64;
+          uint32_t bj[kC];
+          float sj[kC];
+#pragma unroll
+          for (int c = 0; c < kC; ++c) {
+            bj[c] = lane + 64 * c < m ? (uint32_t)lst[lane + 64 * c] : 0u;
+            sj[c] = 0.f;
+          }
+          for (int k = 0; k < m; ++k) {                     // candidates in list order
+            const uint32_t bk = (uint32_t)lst[k];
+            const float ak = __uint_as_float(bk);
+#pragma unroll
+            for (int c = 0; c < kC; ++c) sj[c] += (bk >= bj[c]) ? ak : 0.f;
+          }
+          uint32_t th = 0u;
+#pragma unroll
+          for (int c = 0; c < kC; ++c) th = max(th, (lane + 64 * c < m && above_bucket + sj[c] > d.top_p) ? bj[c] : 0u);
+#pragma unroll
+          for (int o = 32; o > 0; o >>= 1) th = max(th, (uint32_t)__shfl_xor((int)th, o));
+          if (th != 0u) theta = th;
+          int n_ties = 0;
+          float mine_above = 0.f;
+#pragma unroll
+          for (int c = 0; c < kC; ++c) {
+            const bool in = lane + 64 * c < m;
+            n_ties += __popcll(__ballot(in && bj[c] == theta));
+            mine_above += (in && bj[c] > theta) ? __uint_as_float(bj[c]) : 0.f;
+          }
+          const float above_l = above_bucket + wave_sum_f32(mine_above);
+          if (lane == 0) {
+            sh[7] = (int)theta;
+            sh[5] = n_ties;
+            sh[6] = __float_as_int(above_l);
+          }
+        }
+        block_sync<NT>(rb);
+        theta = (uint32_t)sh[7];
+        list_ties = sh[5];
+        list_above = __int_as_float(sh[6]);
+        break;
+      }
+      try_list = false;
+    }
+    uint32_t g, step;
+    if (turn == 2 || w <= 16u) {
+      step = max(w >> 2, 1u);
+      g = lo + (w >> 1);
+      turn = 0;
+    } else {
+      step = w >> 4;
+      const float f = (s_lo - p) * __builtin_amdgcn_rcpf(s_lo - s_hi);
+      g = lo + (uint32_t)(fminf(fmaxf(f, 0.0f), 1.0f) * (float)w);
+      g = min(max(g, lo + step + 1u), hi - step - 1u);
+      ++turn;
+    }
+    c1 = max(g - step, lo + 1u);
+    c2 = g;
+    c3 = min(g + step, hi - 1u);
+  }
+  if (theta == 0) return HitRule{0u, true, 0x7FFFFFFF};
+  float above = list_above;
+  int ties = list_ties;
+  if (!from_list) {
+    above = 0.f;
+    ties = 0;
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      const uint32_t b = __float_as_uint(a[k]);
+      above += (b > theta) ? a[k] : 0.f;
+      ties += (b == theta) ? 1 : 0;
+    }
+    above = block_sum_f32<NT>(above, rb, phase, tid);
+    ties = block_sum_int<NT>(ties, rb, phase, tid);
+  }
+  return tie_rule<R, NT>(d, base, n, a, theta, above, ties, -1, rb, phase, tid);
 }
 
 // `after_step1` runs once between Step 1 and the score update (the fused kernel
@@ -2219,219 +2335,296 @@ __global__ __launch_bounds__(NT) void finish_kernel(Dev d, int unit_begin, uint3
 // into a part that does not depend on the scores - its mean attention weights over the entries it sees and,
 // from them, the reward of every entry (Alg. 1 Steps 1-2: hit or not; or the weight itself) - and the score
 // recurrence (Step 3), which is sequential over the queries but independent per entry.  So:
-//   seed_scan_kernel<false>  a pass over the keys for all queries of the batch: softmax partials per chunk
-//   seed_stats_kernel        per query head: softmax maximum and 1 / sum over the entries the query sees
-//   seed_scan_kernel<true>   a second pass: the logits again, normalised, the mean over the heads -> weights
-//   seed_hits_kernel         per (unit, query): hit rule, rewards in place of the weights (top-p rule only)
-//   seed_crf_kernel          per entry: the queries' rewards applied in order
+//   seed_scan_kernel     a pass over the keys for all queries of the batch: softmax partials per span of blocks
+//   seed_stats_kernel    per query head: softmax maximum and 1 / sum over the entries the query sees
+//   seed_weights_kernel  a second pass: the logits again, normalised, the mean over the heads -> weights
+//   seed_hits_kernel     per (unit, query): hit rule, a bit per entry in place of the weights (top-p rule only)
+//   seed_crf_kernel      per entry: the queries' rewards applied in order, from the state before the replay
 // (Two passes over the keys, 256 B per entry each, instead of the logits of every query head going through
 // memory, 4 G B per entry and query written and read back.)  Only the weights are wanted (no output), so V is
 // never read.
 //
-// Columns: the matrix-core tile has 16 query columns, of which a decode step fills G; here a tile holds the G
-// heads of Q = 16 / G queries (column c = head c % G of the tile's query c / G), and a batch is up to
-// kSeedTiles tiles.  Buffers of a batch of nt tiles, nq queries, for the UL units of a layer:
-//   sml [tile][unit][chunk][column][2]    running maximum and sum of the softmax per 256-entry chunk
-//   smi [tile][unit][column][2]           maximum and 1 / sum over all the entries the column's query sees
-//   srw [query][unit][cap]                mean weights, then rewards
+// Columns: the matrix-core tile has 16 query columns.  Sixteen queries (a group) fill G tiles, column c of tile k
+//   k < 4 (G / 4):  head 4 (k / 4) + c % 4 of the group's query 4 (k % 4) + c / 4
+//   else:           head k of the group's query 4 (c % 4) + c / 4
+// so that with the queries as the product's rows (the second pass) lane (j, kg) holds, of entry j, four heads of one
+// query, or one head of the four queries whose other heads it also holds: the sum over a query's heads, in head
+// order, never leaves the lane.  (With the heads of 16 / G queries side by side in a tile, the sum took G - 1 lane
+// shifts per logit, of which one lane in G was used, and a G that does not divide 16 left columns empty.)
+// Both passes share a unit's blocks out over S wavefronts, as many as fill the chip evenly: with a wavefront per chunk of
+// 256 entries, 128 units of 9350 entries were 1280 workgroups on 768 places.  Measured on that shape, 32 queries,
+// G = 5: first pass 116 -> 85 us, second pass 172 -> 98 us.
+// Buffers of a batch of nt = G groups tiles, nq queries, for the UL units of a layer:
+//   sml [tile][unit][span][column][2]     maximum (rounded up) and sum of the softmax over a wavefront's blocks
+//   smi [tile][unit][column][2]           maximum (rounded up) and 1 / sum over all the entries the column's query sees
+//   srw [query][unit][cap]                mean weights, then hits (a bit per entry at the start of the row)
 constexpr int kSeedCols = 16;
-constexpr int kSeedTiles = 16;
+constexpr int kSeedGroup = 16;         // queries that share G tiles
+constexpr int kSeedTiles = 16;         // tiles of a batch, at most
+constexpr float kNoMax = -1e30f;       // maximum of no logit: finite, so that exponents relative to it are zeros, not NaNs
 
-// seed_scan_kernel: one wavefront per 256-entry chunk of a unit; the tiles' queries sit in LDS (per tile and
-// 32-dim slice one 16-byte operand piece per lane), each block of keys is loaded once and multiplied with every
-// tile.  Query j of the window sees the entries of positions <= its own, i.e. indices < P - W + j + 1 (the
-// prompt's entries sit in position order).  WEIGHTS = false: per chunk and column the running maximum and sum
-// of the softmax go to `sml`.  WEIGHTS = true: every logit is normalised with its column's maximum and 1 / sum
-// from `smi`, and the mean over a query's G heads (summed in head order, as the decode path's mean weights
-// are) goes to `srw`; entries a query does not see get 0.
-// grid: (ceil(chunks / 4), units of the layer), kThreads threads, nt * 4096 bytes of dynamic LDS.
-template <bool WEIGHTS>
-__global__ __launch_bounds__(kThreads) void seed_scan_kernel(Dev d, int unit_begin, const uint16_t* __restrict__ q_obs, int j0,
-                                                             int nq, int Q, int P, int W, float* __restrict__ sml,
-                                                             const float* __restrict__ smi, float* __restrict__ srw) {
+// Query (of the batch) and head of column c of tile tl.
+__device__ __forceinline__ int seed_column(int G, int tl, int c, int& head) {
+  const int group = tl / G, k = tl - group * G;
+  const bool four = k < (G & ~3);
+  head = four ? (k & ~3) + (c & 3) : k;
+  return kSeedGroup * group + (four ? 4 * (k & 3) + (c >> 2) : 4 * (c & 3) + (c >> 2));
+}
+
+// The batch's queries as operands in LDS ([tile][32-dim slice][lane], 16 bytes each); 0 in columns without a query.
+__device__ __forceinline__ void seed_stage_queries(const Dev& d, const uint16_t* q_obs, int urel, int j0, int nq, int nt, u32x4* s_q) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, b = urel / d.Hkv, h = urel % d.Hkv;
+  for (int tl = 0; tl < nt; ++tl) {
+    int head;
+    const int qi = seed_column(d.G, tl, lane & 15, head);
+    u32x4 x = {0u, 0u, 0u, 0u};
+    if (qi < nq)
+      x = *reinterpret_cast<const u32x4*>(q_obs + ((((size_t)(j0 + qi) * d.Bz + b) * d.Hq) + (size_t)h * d.G + head) * kDim + 32 * wave + 8 * (lane >> 4));
+    s_q[(tl * 4 + wave) * 64 + lane] = x;
+  }
+}
+
+// This wavefront's blocks [b, b1) of the unit, and where block b lies.
+struct SeedSpan {
+  const int32_t* row;
+  int b, b1;
+  __device__ __forceinline__ SeedSpan(const Dev& d, int u, int slot, int S, int n_last) {
+    const int blocks = (n_last + kBlk - 1) / kBlk, per = (blocks + S - 1) / S;
+    row = d.tbl + (size_t)u * d.max_seg;
+    b = min(slot * per, blocks);
+    b1 = min(b + per, blocks);
+  }
+  __device__ __forceinline__ size_t off(int blk) const { return (size_t)row[blk >> 3] * kSegElems + (size_t)(blk & (kSegBlocks - 1)) * kBlkElems; }
+};
+
+// seed_scan_kernel: per span and column the maximum and sum of the softmax over the entries the column's query sees:
+// query j of the window sees the entries of positions <= its own, i.e. indices < P - W + j + 1 (the prompt's entries
+// sit in position order).
+// grid: (ceil(S / 4), units of the layer), kThreads threads, nt * 4096 bytes of dynamic LDS.
+__global__ __launch_bounds__(kThreads) void seed_scan_kernel(Dev d, int unit_begin, const uint16_t* __restrict__ q_obs, int j0, int nq, int P, int W,
+                                                             int S, float* __restrict__ sml) {
   extern __shared__ unsigned char smem[];
-  u32x4* s_q = reinterpret_cast<u32x4*>(smem);            // [tile][slice][lane]
-  __shared__ float2 s_mi[WEIGHTS ? kSeedTiles * kSeedCols : 1];      // WEIGHTS: every column's maximum and 1 / sum
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int urel = blockIdx.y, u = unit_begin + urel;
-  const int UL = gridDim.y;
-  const int chunk = blockIdx.x * (kThreads / 64) + wave;
-  const int G = d.G;
+  u32x4* s_q = reinterpret_cast<u32x4*>(smem);
+  const int lane = threadIdx.x & 63;
+  const int slot = __builtin_amdgcn_readfirstlane(blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6));
+  const int urel = blockIdx.y, u = unit_begin + urel, UL = gridDim.y;
   const int j = lane & 15, kg = lane >> 4;
-  const int nt = (nq + Q - 1) / Q;
-  const int mc = d.max_chunks;
+  const int G = d.G, nt = (nq + kSeedGroup - 1) / kSeedGroup * G;
   const int n_first = P - W + j0 + 1;                     // entries the batch's first query sees
-  const int n_last = n_first + nq - 1;                    // ... and its last
-  if constexpr (WEIGHTS) {
-    if ((int)threadIdx.x < nt * kSeedCols)
-      s_mi[threadIdx.x] = *reinterpret_cast<const float2*>(smi + (((size_t)(threadIdx.x / kSeedCols) * UL + urel) * kSeedCols + threadIdx.x % kSeedCols) * 2);
-  }
-  {
-    // this thread's piece (slice = wave, lane) of every tile's operand
-    const int b = urel / d.Hkv, h = urel % d.Hkv;
-    for (int tl = 0; tl < nt; ++tl) {
-      const int qn = min(Q, nq - tl * Q);                 // queries in this tile
-      const int qi = min(j / G, qn - 1);
-      const uint16_t* qrow = q_obs + ((((size_t)(j0 + tl * Q + qi) * d.Bz + b) * d.Hq) + (size_t)h * G + (j % G)) * kDim + 8 * kg;
-      u32x4 x = *reinterpret_cast<const u32x4*>(qrow + 32 * wave);
-      if (j >= qn * G) x = u32x4{0u, 0u, 0u, 0u};
-      s_q[(tl * 4 + wave) * 64 + lane] = x;
-    }
-  }
+  seed_stage_queries(d, q_obs, urel, j0, nq, nt, s_q);
   __syncthreads();
-  const int e_chunk = chunk * kChunk;
-  if (e_chunk >= n_last) return;
-  const int nblk = min(kChunkBlocks, (n_last - e_chunk + kBlk - 1) / kBlk);
-  const uint16_t* kb = d.K + (size_t)d.tbl[(size_t)u * d.max_seg + chunk] * kSegElems + lane * 8;     // a chunk is one pool segment
-  // WEIGHTS = false: this lane's running maximum and sum per tile (its entries only; the four lanes of a column
-  // meet at the end)
-  constexpr int kStat = WEIGHTS ? 1 : kSeedTiles;
-  float m_run[kStat], l_run[kStat];
+  if (slot >= S) return;
+  SeedSpan sp(d, u, slot, S, n_first + nq - 1);
+  int q_lo[kSeedTiles];                                   // the tile's first query; its last is 3 (four heads each) or 15 later
 #pragma unroll
-  for (int tl = 0; tl < kStat; ++tl) {
-    m_run[tl] = -INFINITY;
+  for (int tl = 0; tl < kSeedTiles; ++tl) {
+    int head;
+    q_lo[tl] = seed_column(G, tl, 0, head);
+  }
+  const int rem = G & 3;                                  // a group's last G % 4 tiles hold one head of 16 queries
+  const int q4 = j >> 2, q1 = 4 * (j & 3) + (j >> 2);
+  float m_run[kSeedTiles], l_run[kSeedTiles];             // of this lane's entries; the four lanes of a column meet at the end
+#pragma unroll
+  for (int tl = 0; tl < kSeedTiles; ++tl) {
+    m_run[tl] = kNoMax;
     l_run[tl] = 0.f;
   }
-  const float invG = 1.0f / (float)G;
+  const float c = d.scale_log2e;
+  const uint16_t* kp = d.K + lane * 8;
   KFrag ka, kn;
-  load_k(ka, kb);
-  for (int blk = 0; blk < nblk; ++blk) {
-    if (blk + 1 < nblk) load_k(kn, kb + (size_t)(blk + 1) * kBlkElems);
-    const int e0 = e_chunk + blk * kBlk + 4 * kg;
-    auto tile = [&](int tl, float& m_t, float& l_t) {
-      const int qn = min(Q, nq - tl * Q);
-      const bool col_ok = j < qn * G;
-      // entries this column's query sees (columns beyond the tile's queries: none)
-      const int lim = col_ok ? n_first + tl * Q + j / G : 0;
-      if (e_chunk + blk * kBlk >= n_first + tl * Q + qn - 1) return;     // the tile's last query does not see the block (uniform)
-      bf16x8 qv[4];
-#pragma unroll
-      for (int s4 = 0; s4 < 4; ++s4) qv[s4] = as_bf16x8(s_q[(tl * 4 + s4) * 64 + lane]);
-      f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int s4 = 0; s4 < 4; ++s4) s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ka.k[s4]), qv[s4], s0, 0, 0, 0);
-#pragma unroll
-      for (int s4 = 0; s4 < 4; ++s4) s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ka.k[4 + s4]), qv[s4], s1, 0, 0, 0);
-      float sv[8];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        sv[v] = (e0 + v < lim) ? s0[v] * d.scale_log2e : -INFINITY;
-        sv[4 + v] = (e0 + 16 + v < lim) ? s1[v] * d.scale_log2e : -INFINITY;
-      }
-      if constexpr (!WEIGHTS) {
-        const float bm = fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
-        if (bm > m_t) {
-          l_t *= fast_exp2(m_t - bm);                       // exp2(-inf) = 0 the first time
-          m_t = bm;
-        }
-        if (m_t > -INFINITY) {
-#pragma unroll
-          for (int i = 0; i < 8; ++i) l_t += fast_exp2(sv[i] - m_t);
-        }
-      } else {
-        // this head's share of the weight of its 4 + 4 entries, then the query's heads in order
-        const float2 mi = s_mi[tl * kSeedCols + j];
-        float term[8], mean[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          term[i] = sv[i] > -INFINITY ? fast_exp2(sv[i] - mi.x) * mi.y : 0.f;
-        }
-        // lane c + g of the row holds head g of the query whose first head sits in lane c: the sum of a
-        // query's heads, in head order, forms in its first head's lane (row_shl:g brings lane + g's value)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) mean[i] = term[i];
-#pragma unroll
-        for (int g = 1; g < kMaxGroup; ++g) {
-          if (g < G) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) mean[i] += row_shl_f32(term[i], g);
-          }
-        }
-        if (col_ok && j % G == 0) {
-          float* dst = srw + ((size_t)(tl * Q + j / G) * UL + urel) * d.cap + e0;
-          *reinterpret_cast<f32x4*>(dst) = f32x4{mean[0] * invG, mean[1] * invG, mean[2] * invG, mean[3] * invG};
-          *reinterpret_cast<f32x4*>(dst + 16) = f32x4{mean[4] * invG, mean[5] * invG, mean[6] * invG, mean[7] * invG};
-        }
-      }
-    };
-    if constexpr (WEIGHTS) {
-#pragma unroll 1
-      for (int tl = 0; tl < nt; ++tl) tile(tl, m_run[0], l_run[0]);
-    } else {
-#pragma unroll
-      for (int tl = 0; tl < kSeedTiles; ++tl)
-        if (tl < nt) tile(tl, m_run[tl], l_run[tl]);
-    }
-    if (blk + 1 < nblk) ka = kn;
-  }
-  if constexpr (!WEIGHTS) {
-    // per tile, the column's four lanes (kg = 0..3): maximum, then the sums rescaled to it, in a fixed order
+  if (sp.b < sp.b1) load_k(ka, kp + sp.off(sp.b));
+  for (int blk = sp.b; blk < sp.b1; ++blk) {
+    load_k(kn, kp + sp.off(min(blk + 1, sp.b1 - 1)));
+    const int e0 = blk * kBlk + 4 * kg;
+    int k = 0;                                            // tile within its group
 #pragma unroll
     for (int tl = 0; tl < kSeedTiles; ++tl) {
-      if (tl < nt) {
-        float M = fmaxf(m_run[tl], __shfl_xor(m_run[tl], 16));
-        M = fmaxf(M, __shfl_xor(M, 32));
-        const float mine = m_run[tl] > -INFINITY ? l_run[tl] * fast_exp2(m_run[tl] - M) : 0.f;
-        const float l0 = __shfl(mine, j), l1 = __shfl(mine, j + 16), l2 = __shfl(mine, j + 32), l3 = __shfl(mine, j + 48);
-        if (kg == 0) {
-          float* dst = sml + ((((size_t)tl * UL + urel) * mc + chunk) * kSeedCols + j) * 2;
-          dst[0] = M;
-          dst[1] = (l0 + l1) + (l2 + l3);
+      const bool four = k < G - rem;
+      k = k + 1 == G ? 0 : k + 1;
+      if (tl < nt && blk * kBlk < n_first + min(q_lo[tl] + (four ? 3 : 15), nq - 1)) {     // uniform: else no query of the tile sees the block
+        bf16x8 qv[4];
+#pragma unroll
+        for (int s4 = 0; s4 < 4; ++s4) qv[s4] = as_bf16x8(s_q[(tl * 4 + s4) * 64 + lane]);
+        f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s4 = 0; s4 < 4; ++s4) s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ka.k[s4]), qv[s4], s0, 0, 0, 0);
+#pragma unroll
+        for (int s4 = 0; s4 < 4; ++s4) s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ka.k[4 + s4]), qv[s4], s1, 0, 0, 0);
+        float sv[8];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          sv[v] = s0[v];
+          sv[4 + v] = s1[v];
         }
+        if ((blk + 1) * kBlk > n_first + q_lo[tl]) {      // a block that the tile's first query sees whole needs no mask
+          const int lim = n_first + q_lo[tl] + (four ? q4 : q1);       // entries this column's query sees
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            sv[v] = (e0 + v < lim) ? sv[v] : -INFINITY;
+            sv[4 + v] = (e0 + 16 + v < lim) ? sv[4 + v] : -INFINITY;
+          }
+        }
+        // exponents as one fused multiply-add per logit (scale, minus the scaled maximum).  The maximum is kept rounded up
+        // to a whole number: sums are then rescaled by exact powers of two, here and where partials meet.
+        const float bm = c * fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
+        if (bm > m_run[tl]) {
+          const float m_new = ceilf(bm);
+          l_run[tl] *= fast_exp2(m_run[tl] - m_new);      // 0 the first time
+          m_run[tl] = m_new;
+        }
+        float p[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) p[i] = fast_exp2(__builtin_fmaf(sv[i], c, -m_run[tl]));
+        l_run[tl] += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
       }
+    }
+    ka = kn;
+  }
+  // per tile, the column's four lanes (kg = 0..3): maximum, then the sums rescaled to it, in a fixed order
+#pragma unroll
+  for (int tl = 0; tl < kSeedTiles; ++tl) {
+    if (tl < nt) {
+      float M = fmaxf(m_run[tl], __shfl_xor(m_run[tl], 16));
+      M = fmaxf(M, __shfl_xor(M, 32));
+      const float mine = l_run[tl] * fast_exp2(m_run[tl] - M);
+      const float l0 = __shfl(mine, j), l1 = __shfl(mine, j + 16), l2 = __shfl(mine, j + 32), l3 = __shfl(mine, j + 48);
+      if (kg == 0)
+        *reinterpret_cast<float2*>(sml + ((((size_t)tl * UL + urel) * S + slot) * kSeedCols + j) * 2) = make_float2(M, (l0 + l1) + (l2 + l3));
     }
   }
 }
 
-// seed_stats_kernel: thread (tile, column) of a unit: maximum and 1 / sum of the column's softmax over the chunks
-// its query sees, in chunk order.  grid: units of the layer, kSeedTiles * kSeedCols threads.
-__global__ __launch_bounds__(kSeedTiles * kSeedCols) void seed_stats_kernel(Dev d, int j0, int nq, int Q, int P, int W,
-                                                                         const float* __restrict__ sml, float* __restrict__ smi) {
+// seed_stats_kernel: thread (tile, column) of a unit: maximum and 1 / sum of the column's softmax over the spans, in
+// their order.  grid: units of the layer, kSeedTiles * kSeedCols threads.
+__global__ __launch_bounds__(kSeedTiles * kSeedCols) void seed_stats_kernel(Dev d, int nq, int S, const float* __restrict__ sml,
+                                                                            float* __restrict__ smi) {
   const int urel = blockIdx.x, UL = gridDim.x;
   const int tl = threadIdx.x / kSeedCols, col = threadIdx.x % kSeedCols;
-  const int G = d.G, mc = d.max_chunks;
-  const int nt = (nq + Q - 1) / Q;
-  if (tl >= nt) return;
-  const int qn = min(Q, nq - tl * Q);
-  float M = -INFINITY, inv = 0.f;
-  if (col < qn * G) {
-    const int n = P - W + j0 + tl * Q + col / G + 1;      // entries the column's query sees
-    const int nch = (n + kChunk - 1) / kChunk;
-    const float* ml = sml + ((((size_t)tl * UL + urel) * mc) * kSeedCols + col) * 2;
-    // eight chunks' partials are asked for at a time; maxima, then sums, in chunk order
-    for (int c0 = 0; c0 < nch; c0 += 8) {
-      float2 p[8];
+  if (tl >= (nq + kSeedGroup - 1) / kSeedGroup * d.G) return;
+  const float* ml = sml + ((((size_t)tl * UL + urel) * S) * kSeedCols + col) * 2;
+  // eight spans' partials are asked for at a time; maxima, then sums
+  float M = kNoMax;
+  for (int c0 = 0; c0 < S; c0 += 8) {
+    float2 p[8];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) p[k] = *reinterpret_cast<const float2*>(ml + (size_t)min(c0 + k, nch - 1) * kSeedCols * 2);
+    for (int k = 0; k < 8; ++k) p[k] = *reinterpret_cast<const float2*>(ml + (size_t)min(c0 + k, S - 1) * kSeedCols * 2);
 #pragma unroll
-      for (int k = 0; k < 8; ++k)
-        if (c0 + k < nch) M = fmaxf(M, p[k].x);
-    }
-    float L = 0.f;
-    for (int c0 = 0; c0 < nch; c0 += 8) {
-      float2 p[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) p[k] = *reinterpret_cast<const float2*>(ml + (size_t)min(c0 + k, nch - 1) * kSeedCols * 2);
-#pragma unroll
-      for (int k = 0; k < 8; ++k)
-        if (c0 + k < nch && p[k].x > -INFINITY) L += p[k].y * fast_exp2(p[k].x - M);
-    }
-    inv = 1.0f / L;
+    for (int k = 0; k < 8; ++k) M = fmaxf(M, p[k].x);
   }
-  float* dst = smi + (((size_t)tl * UL + urel) * kSeedCols + col) * 2;
-  dst[0] = M;
-  dst[1] = inv;
+  // the spans' sums in eight interleaved accumulators, added up in pairs at the end (one chain of all of them would
+  // round as often as there are spans, in the same direction for every weight of the column)
+  float l[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) l[k] = 0.f;
+  for (int c0 = 0; c0 < S; c0 += 8) {
+    float2 p[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) p[k] = *reinterpret_cast<const float2*>(ml + (size_t)min(c0 + k, S - 1) * kSeedCols * 2);
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if (c0 + k < S) l[k] += p[k].y * fast_exp2(p[k].x - M);
+  }
+  const float L = ((l[0] + l[1]) + (l[2] + l[3])) + ((l[4] + l[5]) + (l[6] + l[7]));
+  *reinterpret_cast<float2*>(smi + (((size_t)tl * UL + urel) * kSeedCols + col) * 2) = make_float2(M, 1.0f / L);
+}
+
+// seed_weights_kernel: every logit normalised with its column's maximum and 1 / sum, the mean over a query's heads
+// (summed in head order, as the decode path's mean weights are) to `srw`; entries that a query does not see, but others of the
+// batch in the same block do, get 0.  Grid and LDS as seed_scan_kernel.
+__global__ __launch_bounds__(kThreads) void seed_weights_kernel(Dev d, int unit_begin, const uint16_t* __restrict__ q_obs, int j0, int nq, int P,
+                                                                int W, int S, const float* __restrict__ smi, float* __restrict__ srw) {
+  extern __shared__ unsigned char smem[];
+  u32x4* s_q = reinterpret_cast<u32x4*>(smem);
+  __shared__ __align__(16) float s_M[kSeedTiles * kSeedCols], s_I[kSeedTiles * kSeedCols];      // every column's maximum and 1 / (G sum)
+  const int lane = threadIdx.x & 63;
+  const int slot = __builtin_amdgcn_readfirstlane(blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6));
+  const int urel = blockIdx.y, u = unit_begin + urel, UL = gridDim.y;
+  const int j = lane & 15, kg = lane >> 4;
+  const int G = d.G, groups = (nq + kSeedGroup - 1) / kSeedGroup, nt = groups * G;
+  const int n_first = P - W + j0 + 1;
+  const float invG = 1.0f / (float)G;
+  if ((int)threadIdx.x < nt * kSeedCols) {
+    const float2 mi = *reinterpret_cast<const float2*>(smi + (((size_t)(threadIdx.x / kSeedCols) * UL + urel) * kSeedCols + threadIdx.x % kSeedCols) * 2);
+    s_M[threadIdx.x] = mi.x;
+    s_I[threadIdx.x] = mi.y * invG;
+  }
+  seed_stage_queries(d, q_obs, urel, j0, nq, nt, s_q);
+  __syncthreads();
+  if (slot >= S) return;
+  SeedSpan sp(d, u, slot, S, n_first + nq - 1);
+  const float c = d.scale_log2e;
+  const uint16_t* kp = d.K + lane * 8;
+  KFrag ka, kn;
+  if (sp.b < sp.b1) load_k(ka, kp + sp.off(sp.b));
+  for (int blk = sp.b; blk < sp.b1; ++blk) {
+    load_k(kn, kp + sp.off(min(blk + 1, sp.b1 - 1)));
+#pragma unroll 1
+    for (int gr = 0; gr < groups; ++gr) {
+      const int q0 = kSeedGroup * gr;
+      if (blk * kBlk >= n_first + min(q0 + kSeedGroup - 1, nq - 1)) continue;      // uniform: no query of the group sees the block
+      float mean[4][2];                                   // queries q0 + 4 t + kg, entries j and 16 + j of the block
+#pragma unroll
+      for (int t = 0; t < 4; ++t) mean[t][0] = mean[t][1] = 0.f;
+      f32x4 s0, s1, M, I;
+      auto tile = [&](int tl) {
+        s0 = s1 = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s4 = 0; s4 < 4; ++s4) {
+          const bf16x8 qv = as_bf16x8(s_q[(tl * 4 + s4) * 64 + lane]);
+          s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qv, as_bf16x8(ka.k[s4]), s0, 0, 0, 0);
+          s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qv, as_bf16x8(ka.k[4 + s4]), s1, 0, 0, 0);
+        }
+        M = *reinterpret_cast<const f32x4*>(s_M + tl * kSeedCols + 4 * kg);
+        I = *reinterpret_cast<const f32x4*>(s_I + tl * kSeedCols + 4 * kg);
+      };
+#pragma unroll 1
+      for (int h = 0; h + 4 <= G; h += 4) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          tile(gr * G + h + t);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            mean[t][0] += fast_exp2(__builtin_fmaf(s0[v], c, -M[v])) * I[v];
+            mean[t][1] += fast_exp2(__builtin_fmaf(s1[v], c, -M[v])) * I[v];
+          }
+        }
+      }
+#pragma unroll 1
+      for (int h = G & ~3; h < G; ++h) {
+        tile(gr * G + h);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          mean[v][0] += fast_exp2(__builtin_fmaf(s0[v], c, -M[v])) * I[v];
+          mean[v][1] += fast_exp2(__builtin_fmaf(s1[v], c, -M[v])) * I[v];
+        }
+      }
+      const int e0 = blk * kBlk + j;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int qi = q0 + 4 * t + kg;
+        if (qi < nq) {
+          const int lim = n_first + qi;                   // entries the query sees
+          float* dst = srw + ((size_t)qi * UL + urel) * d.cap + e0;
+          dst[0] = e0 < lim ? mean[t][0] : 0.f;
+          dst[16] = e0 + 16 < lim ? mean[t][1] : 0.f;
+        }
+      }
+    }
+    ka = kn;
+  }
 }
 
 // seed_hits_kernel (top-p rule only): one workgroup per (query of the batch, unit).  The query's mean weights
-// from `srw`, the hit rule, and in their place the rewards: 1 or 0 (the query's own entry, the last it sees, is
-// always hit).
-// grid: (queries of the batch, units of the layer), kSeedThreads threads, dynamic LDS as finish_kernel.
-constexpr int kSeedThreads = 512;      // twice a decode step's workgroup: prompts are long
+// from // `srw`, the hit rule, and in their place the hits, a bit per entry at the start of the row (the query's own entry,
+// the last it sees, is always hit): every thread has its weights in registers (or LDS) before the first bit is written.
+// (As rewards of 4 bytes they were 153 MB per layer of 128 units of 9350 entries and 32 queries, written and read.)
+// grid: (queries of the batch, units of the layer), kSeedThreads threads, kSeedList ints of dynamic LDS (R = 0: cap floats).
+constexpr int kSeedThreads = 512;      // prompts are long
+constexpr int kSeedList = 256;         // candidates among which a threshold is found by one wavefront
 
 template <int R>
-__device__ __forceinline__ void seed_rewards_regs(const Dev& d, Slots base, int n, bool last_new, float* rw, int* lst, int lst_cap,
-                                                  RedBuf& rb, int& phase, int* sh, int tid) {
+__device__ __forceinline__ void seed_rewards_regs(const Dev& d, Slots base, int n, bool last_new, float* rw, int* lst, RedBuf& rb, int& phase,
+                                                  int* sh, int tid) {
   float a[R];
 #pragma unroll
   for (int c = 0; c < R / 4; ++c) {
@@ -2440,27 +2633,39 @@ __device__ __forceinline__ void seed_rewards_regs(const Dev& d, Slots base, int 
 #pragma unroll
     for (int e = 0; e < 4; ++e) a[4 * c + e] = (e0 + e < n) ? x[e] : 0.f;
   }
-  const HitRule rule = top_p_regs<R, kSeedThreads, 256>(d, base, n, a, lst, lst_cap, -1, rb, phase, sh, tid);
+  const HitRule rule = top_p_flat<R, kSeedThreads, kSeedList>(d, base, n, a, lst, rb, phase, sh, tid);
+  uint32_t* bits = reinterpret_cast<uint32_t*>(rw);
 #pragma unroll
   for (int c = 0; c < R / 4; ++c) {
     const int e0 = 4 * (tid + c * kSeedThreads);
-    if (e0 < n) {
-      i32x4 ps = {0, 0, 0, 0};
-      if (!rule.ties_all) ps = *reinterpret_cast<const i32x4*>(d.pos + (base + e0));      // rare
-      f32x4 r;
+    uint32_t word = 0;
+    if (rule.ties_all) {                                   // uniform, nearly always
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const bool hit = rule(__float_as_uint(a[4 * c + e]), ps[e]) | ((e0 + e == n - 1) & last_new);
-        r[e] = hit ? 1.0f : 0.0f;
-      }
-      *reinterpret_cast<f32x4*>(rw + e0) = r;              // entries >= n of the group: written, never read
+      for (int e = 0; e < 4; ++e) word |= (__float_as_uint(a[4 * c + e]) >= rule.theta ? 1u : 0u) << e;
+    } else if (e0 < n) {
+      const i32x4 ps = *reinterpret_cast<const i32x4*>(d.pos + (base + e0));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) word |= (rule(__float_as_uint(a[4 * c + e]), ps[e]) ? 1u : 0u) << e;
     }
+    // the query's own entry, the row's last; nothing beyond it
+    const int left = n - e0;
+    if (left < 4) word &= left <= 0 ? 0u : (1u << left) - 1u;
+    if (left >= 1 && left <= 4 && last_new) word |= 1u << (left - 1);
+    // the word's eight nibbles sit in eight consecutive lanes
+    word <<= 4 * (tid & 7);
+    word |= dpp_u32<kDppQuadSwap1>(word);
+    word |= dpp_u32<kDppQuadSwap2>(word);
+    word |= dpp_u32<kDppRowHalfMirror>(word);
+    if ((tid & 7) == 0 && e0 < n) bits[e0 >> 5] = word;
   }
 }
 
-__global__ __launch_bounds__(kSeedThreads, 4) void seed_hits_kernel(Dev d, int unit_begin, int j0, int P, int W, float* __restrict__ srw) {
+// R: entries per thread, in registers, chosen by the longest row of the launch, so that short rows do not pay for the
+// registers of long ones (20 of them: three workgroups per compute unit instead of two); 0: weights in LDS, any length.
+template <int R>
+__global__ __launch_bounds__(kSeedThreads, R == 0 || R > 24 ? 4 : R > 16 ? 6 : 8) void seed_hits_kernel(Dev d, int unit_begin, int j0, int P, int W,
+                                                                                                      float* __restrict__ srw) {
   extern __shared__ unsigned char smem[];
-  float* val = reinterpret_cast<float*>(smem);
   __shared__ RedBuf rb;
   __shared__ int sh[4 + kSeedThreads / 64];
   const int tid = threadIdx.x;
@@ -2472,29 +2677,32 @@ __global__ __launch_bounds__(kSeedThreads, 4) void seed_hits_kernel(Dev d, int u
   const bool last_new = d.pos[base + (n - 1)] == t;       // the query's own entry (asked for early: nothing waits for it until the end)
   int phase = 0;
   float* rw = srw + ((size_t)ql * UL + urel) * d.cap;
-  int* lst = reinterpret_cast<int*>(val);
-  if (n <= 8 * kSeedThreads) {
-    seed_rewards_regs<8>(d, base, n, last_new, rw, lst, d.cap, rb, phase, sh, tid);
-  } else if (n <= 16 * kSeedThreads) {
-    seed_rewards_regs<16>(d, base, n, last_new, rw, lst, d.cap, rb, phase, sh, tid);
-  } else if (n <= 32 * kSeedThreads) {
-    seed_rewards_regs<32>(d, base, n, last_new, rw, lst, d.cap, rb, phase, sh, tid);
+  if constexpr (R > 0) {
+    seed_rewards_regs<R>(d, base, n, last_new, rw, reinterpret_cast<int*>(smem), rb, phase, sh, tid);
   } else {
+    float* val = reinterpret_cast<float*>(smem);
     for (int i = tid; i < n; i += kSeedThreads) val[i] = rw[i];
     __syncthreads();
     const HitRule rule = top_p_lds<ValLinear, kSeedThreads>(d, base, n, ValLinear{val}, rb, phase, tid);
-    for (int i = tid; i < n; i += kSeedThreads) {
-      const int pe = !rule.ties_all ? d.pos[base + i] : 0;
-      const bool hit = rule(__float_as_uint(val[i]), pe) | ((i == n - 1) & last_new);
-      rw[i] = hit ? 1.0f : 0.0f;
+    uint32_t* bits = reinterpret_cast<uint32_t*>(rw);
+    for (int i0 = tid & ~63; i0 < n; i0 += kSeedThreads) {          // a wavefront's 64 entries are two words
+      const int i = i0 + (tid & 63), ic = min(i, n - 1);
+      const int pe = !rule.ties_all ? d.pos[base + ic] : 0;
+      const u64 mask = __ballot(i < n && (rule(__float_as_uint(val[ic]), pe) | ((i == n - 1) & last_new)));
+      if ((tid & 31) == 0 && i < n) bits[i >> 5] = (uint32_t)(mask >> (tid & 32));
     }
   }
 }
 
 // seed_crf_kernel: Alg. 1 Step 3 for the batch's queries in order, four consecutive entries per thread: an entry
 // takes part from the query of its own position on; under the top-p rule only a hit replaces (CRF, tau).
+// BITS: the queries' hits, a bit per entry at the start of each query's row (the top-p rule); else the weights themselves.
+// The replay's first batch starts from the state before it (every entry referenced once, on arrival: CRF 1, tau =
+// position; the W entries of the window not yet arrived: CRF 0), the last one leaves the units' records as a fresh
+// context has them: no trace in the aggregated-CRF window, last-step time t_unit.
 // grid: (ceil(P / (4 kThreads)), units of the layer), kThreads threads.
-__global__ __launch_bounds__(kThreads) void seed_crf_kernel(Dev d, int unit_begin, int j0, int nq, int P, int W,
+template <bool BITS>
+__global__ __launch_bounds__(kThreads) void seed_crf_kernel(Dev d, int unit_begin, int j0, int nq, int P, int W, int t_unit,
                                                             const float* __restrict__ srw) {
   __shared__ float s_tab[kTabLds];
   const int tid = threadIdx.x;
@@ -2502,42 +2710,68 @@ __global__ __launch_bounds__(kThreads) void seed_crf_kernel(Dev d, int unit_begi
   const int UL = gridDim.y;
   const int s_tab_n = min(kTabLds, d.tab_last + 1);
   if (tid < s_tab_n) s_tab[tid] = d.tab[tid];
+  if (j0 + nq == W && blockIdx.x == 0 && tid == 0) {
+    d.window[u] = 0;
+    d.t_unit[u] = t_unit;
+  }
   __syncthreads();
   const int e0 = 4 * (blockIdx.x * kThreads + tid);
   if (e0 >= P) return;
   const Slots base = slots_of(d, u);
   const size_t s0 = base + e0;                            // four consecutive entries share a segment
-  f32x4 crf = *reinterpret_cast<const f32x4*>(d.crf + s0);
-  i32x4 tau = *reinterpret_cast<const i32x4*>(d.tau + s0);
-  const bool topp = d.reward_mode == 0;
-  const float* rw = srw + (size_t)urel * d.cap + e0;
+  f32x4 crf;
+  i32x4 tau;
+  if (j0 == 0) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      crf[e] = e0 + e < P - W ? 1.0f : 0.0f;
+      tau[e] = e0 + e;
+    }
+  } else {
+    crf = *reinterpret_cast<const f32x4*>(d.crf + s0);
+    tau = *reinterpret_cast<const i32x4*>(d.tau + s0);
+  }
+  const float* rw = srw + (size_t)urel * d.cap + (BITS ? e0 >> 5 : e0);
   const size_t q_stride = (size_t)UL * d.cap;
   const int t_first = P - W + j0;
-  bool changed = false;
+  bool changed = j0 == 0;
+  // the four entries' updates at time t, side by side; entry e takes part if bit e of m is set
+  auto update = [&](uint32_t m, int t, f32x4 reward) {
+    int delta[4];
+    float dec[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) delta[e] = min(max(t - tau[e], 0), d.tab_last);
+    decay4_of(d, delta, s_tab, s_tab_n, dec);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool in = (m >> e) & 1u;
+      float tmp = __fadd_rn(__fmul_rn(dec[e], crf[e]), reward[e]);
+      tmp = tmp < FLT_MIN ? 0.0f : tmp;
+      crf[e] = in ? tmp : crf[e];
+      tau[e] = in ? t : tau[e];
+    }
+    changed |= m != 0u;
+  };
+  // bits of the entries that the query at time t sees: positions 0 .. t
+  auto seen = [&](int t) -> uint32_t { return t >= e0 + 3 ? 0xFu : t < e0 ? 0u : (2u << (t - e0)) - 1u; };
   for (int q0 = 0; q0 < nq; q0 += 8) {
-    f32x4 r[8];
+    if constexpr (BITS) {
+      uint32_t r[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) r[k] = *reinterpret_cast<const f32x4*>(rw + (size_t)min(q0 + k, nq - 1) * q_stride);
+      for (int k = 0; k < 8; ++k) r[k] = __float_as_uint(rw[(size_t)min(q0 + k, nq - 1) * q_stride]);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const int t = t_first + q0 + k;
-      if (q0 + k < nq) {
+      for (int k = 0; k < 8; ++k) {
+        const int t = t_first + q0 + k;
+        update(q0 + k < nq ? (r[k] >> (e0 & 31)) & seen(t) : 0u, t, f32x4{1.0f, 1.0f, 1.0f, 1.0f});
+      }
+    } else {
+      f32x4 r[8];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          if (e0 + e <= t) {                              // the query sees positions 0 .. t
-            int delta = t - tau[e];
-            delta = delta < 0 ? 0 : (delta > d.tab_last ? d.tab_last : delta);
-            const float dec = decay_of(d, delta, s_tab, s_tab_n);
-            const float reward = r[k][e];
-            float tmp = __fadd_rn(__fmul_rn(dec, crf[e]), reward);
-            if (tmp < FLT_MIN) tmp = 0.0f;
-            if (!topp || reward != 0.0f) {
-              crf[e] = tmp;
-              tau[e] = t;
-              changed = true;
-            }
-          }
-        }
+      for (int k = 0; k < 8; ++k) r[k] = *reinterpret_cast<const f32x4*>(rw + (size_t)min(q0 + k, nq - 1) * q_stride);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int t = t_first + q0 + k;
+        update(q0 + k < nq ? seen(t) : 0u, t, r[k]);
       }
     }
   }

@@ -1,0 +1,63 @@
+"""Prompt replay at every group size (four heads of a query, or one head of sixteen, per tile) and at the row lengths
+where the threshold search changes its width, against weights in 64 bits."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _context(L, batch, hkv, G, P, W, weighted):
+    import torch
+    from paper_2601_16986_amd import ckv
+    g = ckv.CrystalKV(L, batch, hkv * G, hkv, 128, (P + 33) // 32 * 32, np.full((L, batch, hkv), P, np.int32), t0=P, lam=0.5,
+                      reward_mode=ckv.REWARD_ATTN_WEIGHTED if weighted else ckv.REWARD_TOPP_HIT, budget_min=1, budget_max=P + 1)
+    gen = torch.Generator(device=g.device)
+    gen.manual_seed(P + G)
+    rnd = lambda *s: torch.randn(s, generator=gen, device=g.device)
+    k = rnd(batch, hkv, P, 128).to(torch.bfloat16)
+    q = (1.5 * rnd(W, batch, hkv * G, 128)).to(torch.bfloat16)
+    g.load_prompt(0, k, k)
+    g.seed_prompt(0, q)
+    assert g.status() == 0
+    seg = g.pool_slots // (L * batch * hkv)
+    live = lambda x: x[:batch * hkv * seg].view(batch, hkv, seg)[:, :, :P]
+    crf, tau = live(g.crf).double(), live(g.tau).long()
+    kt = k.double().transpose(2, 3).contiguous()
+    weights = []                                              # [W] of [batch][hkv][entries seen]
+    for j in range(W):
+        s = torch.matmul(q[j].view(batch, hkv, G, 128).double(), kt[..., :P - W + j + 1].contiguous()) / np.sqrt(128.0)
+        weights.append(torch.softmax(s, dim=-1).mean(2))
+    g.close()
+    return torch, crf, tau, weights
+
+
+@pytest.mark.parametrize("L", [1, 24])                        # one group of queries at a time, and several
+@pytest.mark.parametrize("G", [1, 2, 3, 4, 5, 6, 7, 8])
+def test_weights_of_every_group_size(G, L):
+    P, W = 395, 37
+    torch, crf, tau, weights = _context(L, 2, 3, G, P, W, True)
+    pos = torch.arange(P, device=crf.device)
+    want, last = (pos < P - W).double().expand_as(crf).clone(), pos.clone()
+    for j, a in enumerate(weights):
+        t = P - W + j
+        want[..., :t + 1] = want[..., :t + 1] * 0.5 ** (t - last[:t + 1]).double() + a
+        last[:t + 1] = t
+    # a weight carries a few rounding errors of 2^-24, a score the last few weights'
+    assert float(((crf - want).abs() / want.clamp(min=1e-30)).max()) < 4e-6
+    assert torch.equal(tau, last.expand_as(tau))
+
+
+@pytest.mark.parametrize("P", [33, 4096, 4097, 8192, 8193, 10240, 10241, 12288, 12289, 16384, 16385])
+def test_hits_of_every_row_length(P):
+    torch, crf, tau, weights = _context(1, 2, 2, 5, P, 1, False)
+    a = weights[0]
+    hit = tau == P - 1
+    assert bool(hit[..., P - 1].all())                        # the query's own entry
+    srt, order = torch.sort(a, dim=-1, descending=True)
+    inside = torch.cumsum(srt, -1) - srt <= 0.9               # the smallest set that exceeds p
+    want = torch.zeros_like(hit).scatter(-1, order, inside)
+    want[..., P - 1] = True
+    edge = torch.where(inside, srt, torch.inf).amin(-1, keepdim=True)
+    # fp32 sums of P weights may put the cut a few entries to either side of the edge, never elsewhere
+    wrong = (hit != want)
+    assert float(torch.where(wrong, (a / edge - 1).abs(), 0.0).max()) < 1e-3 and int(wrong.sum(-1).max()) <= 2
