@@ -199,8 +199,8 @@ int ckv_load_cache(ckv_ctx* ctx, int32_t layer, const void* k, const void* v, in
  * only what the next operation of a model needs: one kernel that attends over the
  * cache and the new entry and writes the output (and the new entry's rows into
  * the cache).  The append's records, the hit set, the scores and the eviction of
- * that layer follow on one of two streams the context owns, up to eight
- * consecutive layers per launch, beside whatever `stream` does next (the next
+ * that layer follow on one of two streams the context owns, eight consecutive
+ * layers per launch (up to 32 if the layers are small), beside whatever `stream` does next (the next
  * layers' steps, the model's other work).  Results are the same up to
  * floating-point summation order.  (A layer with at least two units per compute
  * unit is finished sooner by the fused kernel, bookkeeping included: there the

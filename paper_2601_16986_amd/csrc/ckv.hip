@@ -20,7 +20,7 @@
 using namespace ckv;
 
 constexpr int kSide = 2;   // streams of the context's own for deferred bookkeeping
-constexpr int kBookGroup = 8;   // layers whose deferred bookkeeping goes out as one launch
+constexpr int kBookGroup = 8, kBookGroupMost = 32;   // layers whose deferred bookkeeping goes out as one launch (see book_group)
 
 // Scratch of ckv_probe_noalloc: device memory the library owns from the moment it is loaded, so that the
 // call never needs a caller's workspace or an allocation.  In host code `scratch` is only a handle: the
@@ -61,7 +61,7 @@ struct ckv_ctx {
   // one of the `side` streams (layer l on side[l % kSide], so that the bookkeeping of consecutive layers, which
   // share nothing, can overlap), ordered by events against the caller's stream.  pending[l]: layer l's
   // bookkeeping has been queued there and nothing on the caller's side has waited for it yet.
-  // The bookkeeping of up to kBookGroup consecutive layers goes out as one launch (a fork from the caller's
+  // The bookkeeping of several consecutive layers (book_group) goes out as one launch (a fork from the caller's
   // stream costs about as much as a small kernel, and more units per launch fill the chip better): after a
   // deferred step, layers [group_first, group_first + group_count) have been scanned on group_stream and wait
   // for theirs; the group goes out when it is full, with the last layer, and before anything else looks.
@@ -73,6 +73,9 @@ struct ckv_ctx {
   // Shared pools: budgets (or a prompt) have changed what units should own (dirty); once an eviction over all
   // layers has been issued since, the segments are dealt out again when the next step begins (due).
   bool dirty = false, due = false;
+  // Layers whose budgets have changed since their last eviction: their units may have to give up many entries at once, which
+  // a step then leaves to evict_kernel behind it.
+  std::vector<uint8_t> many;
   int group_first = 0, group_count = 0, group_launches = 0;
   uint32_t group_flags = 0;
   hipStream_t group_stream = nullptr;
@@ -224,6 +227,21 @@ int profile_events(ckv_ctx* c, hipEvent_t* e0, hipEvent_t* e1) {
   return CKV_OK;
 }
 
+// Eviction of `count` units from `begin` on: select, then move.  A unit's keys sit in the registers of one workgroup:
+// 1024 threads, or 256 where every unit fits (32 entries per thread) and there are enough units to fill the chip
+// with small workgroups anyway.
+int launch_evict(ckv_ctx* c, hipStream_t s, int begin, int count, int n_sink, int after_step = 0) {
+  if (c->lay.cap <= 32 * kThreads && count >= 4 * c->n_cu)
+    hipLaunchKernelGGL(evict_kernel<kThreads>, dim3((unsigned)count), dim3(kThreads), 0, s, c->dev, begin, n_sink, after_step);
+  else
+    hipLaunchKernelGGL(evict_kernel<kWideThreads>, dim3((unsigned)count), dim3(kWideThreads), 0, s, c->dev, begin, n_sink, after_step);
+  CKV_HIP(c, hipGetLastError());
+  const int y = std::max(1, std::min({16 * c->n_cu / count, (c->lay.cap / 2 + 15) / 16, 64}));
+  hipLaunchKernelGGL(evict_move_kernel, dim3((unsigned)count, (unsigned)y), dim3(kThreads), 0, s, c->dev, begin);
+  CKV_HIP(c, hipGetLastError());
+  return CKV_OK;
+}
+
 // The bookkeeping of `count` units from `begin` on, behind their scan.  Workgroups of 256 threads where no unit can
 // hold more than eight entries per thread, else 1024.
 int launch_finish(ckv_ctx* c, hipStream_t s, int begin, int count, uint32_t flags, int advance, int layer_time) {
@@ -254,6 +272,11 @@ int launch_layer_scan(ckv_ctx* c, hipStream_t s, int begin, int count, const uin
   return CKV_OK;
 }
 
+// Layers per launch of deferred bookkeeping: eight, or as many as give every compute unit a workgroup if the layers are
+// small (each launch forks from the caller's stream, which costs its next layer about 10 us: 48 layers of eight units,
+// captured, in groups of 32 instead of 8: 706 -> 663 us).
+int book_group(const ckv_ctx* c) { return std::max(kBookGroup, std::min(kBookGroupMost, c->n_cu / c->units_per_layer)); }
+
 // Queue the bookkeeping of the layers scanned since the last group went out.
 int flush_group(ckv_ctx* c) {
   if (c->group_count == 0) return CKV_OK;
@@ -264,6 +287,8 @@ int flush_group(ckv_ctx* c) {
   hipStream_t side = c->side[c->group_launches++ % kSide];
   CKV_HIP(c, hipStreamWaitEvent(side, c->ev_out, 0));
   if (int rc = launch_finish(c, side, first * upl, count * upl, c->group_flags, 0, 1)) return rc;
+  if (c->group_flags & kLeaveMany)
+    if (int rc = launch_evict(c, side, first * upl, count * upl, -1, 1)) return rc;
   CKV_HIP(c, hipEventRecord(c->ev_book[first], side));
   for (int l = first; l < first + count; ++l) c->pending[l] = 1 + first;     // whose event to wait for
   c->any_pending = true;
@@ -318,21 +343,6 @@ int rebalance_if_due(ckv_ctx* c, hipStream_t s) {
 // (Re)build the fused kernel's schedule (units by descending budget) from the budgets in device memory.
 int launch_schedule(ckv_ctx* c, hipStream_t s) {
   hipLaunchKernelGGL(schedule_kernel, dim3(1), dim3(1024), 0, s, c->dev);
-  CKV_HIP(c, hipGetLastError());
-  return CKV_OK;
-}
-
-// Eviction of `count` units from `begin` on: select, then move.  A unit's keys sit in the registers of one workgroup:
-// 1024 threads, or 256 where every unit fits (32 entries per thread) and there are enough units to fill the chip
-// with small workgroups anyway.
-int launch_evict(ckv_ctx* c, hipStream_t s, int begin, int count, int n_sink) {
-  if (c->lay.cap <= 32 * kThreads && count >= 4 * c->n_cu)
-    hipLaunchKernelGGL(evict_kernel<kThreads>, dim3((unsigned)count), dim3(kThreads), 0, s, c->dev, begin, n_sink);
-  else
-    hipLaunchKernelGGL(evict_kernel<kWideThreads>, dim3((unsigned)count), dim3(kWideThreads), 0, s, c->dev, begin, n_sink);
-  CKV_HIP(c, hipGetLastError());
-  const int y = std::max(1, std::min({16 * c->n_cu / count, (c->lay.cap / 2 + 15) / 16, 64}));
-  hipLaunchKernelGGL(evict_move_kernel, dim3((unsigned)count, (unsigned)y), dim3(kThreads), 0, s, c->dev, begin);
   CKV_HIP(c, hipGetLastError());
   return CKV_OK;
 }
@@ -564,6 +574,7 @@ int ckv_init(ckv_ctx** out, const ckv_layout* layout, const int32_t* budgets, co
     return rc;
   };
   c->pending.assign(layout->n_layers, 0);
+  c->many.assign(layout->n_layers, 0);
   for (int i = 0; i < kSide; ++i)
     if (hipStreamCreateWithFlags(&c->side[i], hipStreamNonBlocking) != hipSuccess) return bail(CKV_EHIP);
   if (hipEventCreateWithFlags(&c->ev_out, hipEventDisableTiming) != hipSuccess) return bail(CKV_EHIP);
@@ -685,6 +696,18 @@ int ckv_decode_step(ckv_ctx* c, int32_t layer, const void* q, const void* k_new,
     c->prompt_len[l] = -1;
   }
   hipStream_t s = (hipStream_t)stream;
+  if (flags & CKV_FUSE_EVICT) {
+    // After a change of budgets, once.  Not into a graph: replays would evict what is not there; the kernels' own
+    // evictions, which do without the launches behind them, give the same.
+    bool many = false;
+    for (int l = (layer == -1 ? 0 : layer); l < (layer == -1 ? c->lay.n_layers : layer + 1); ++l) {
+      many |= c->many[l] != 0;
+      c->many[l] = 0;
+    }
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    if (many) CKV_HIP(c, hipStreamIsCapturing(s, &capturing));
+    if (many && capturing == hipStreamCaptureStatusNone) flags |= kLeaveMany;
+  }
 
   // The fused kernel takes whole units: all layers at once, or one layer that has at least a unit per
   // workgroup.  Such a layer it also finishes sooner than a scan with deferred bookkeeping would (Llama-8B
@@ -706,7 +729,7 @@ int ckv_decode_step(ckv_ctx* c, int32_t layer, const void* q, const void* k_new,
     }
     if (int rc = launch_layer_scan(c, s, begin, count, (const uint16_t*)q, (const uint16_t*)k_new, (const uint16_t*)v_new, out, 1, (int)layer, advance)) return rc;
     if (c->profile) CKV_HIP(c, hipEventRecord(e1, s));
-    const uint32_t kflags = flags & CKV_FUSE_EVICT;
+    const uint32_t kflags = flags & (CKV_FUSE_EVICT | kLeaveMany);
     if (c->group_count && (c->group_flags != kflags || c->group_stream != s || c->group_first + c->group_count != layer))
       if (int rc = flush_group(c)) return rc;
     if (c->group_count == 0) {
@@ -717,7 +740,7 @@ int ckv_decode_step(ckv_ctx* c, int32_t layer, const void* q, const void* k_new,
     c->group_count += 1;
     if (advance && (flags & CKV_FUSE_EVICT))
       if (int rc = rebalance_after_eviction(c)) return rc;
-    if (c->group_count == kBookGroup || advance) return flush_group(c);
+    if (c->group_count == book_group(c) || advance) return flush_group(c);
     return CKV_OK;
   }
   hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -742,6 +765,8 @@ int ckv_decode_step(ckv_ctx* c, int32_t layer, const void* q, const void* k_new,
       hipLaunchKernelGGL(unit_kernel<2>, dim3((unsigned)fv->grid), dim3(128), fv->lds, s, dv, qb, ob, flags, advance, fv->lds_main, vb, kb);
     CKV_HIP(c, hipGetLastError());
     if (c->profile) CKV_HIP(c, hipEventRecord(e1, s));
+    if (flags & kLeaveMany)
+      if (int rc = launch_evict(c, s, begin, count, -1, 1)) return rc;
     if (advance && (flags & CKV_FUSE_EVICT)) return rebalance_after_eviction(c);
     return CKV_OK;
   }
@@ -756,7 +781,9 @@ int ckv_decode_step(ckv_ctx* c, int32_t layer, const void* q, const void* k_new,
     CKV_HIP(c, hipGetLastError());
     return CKV_OK;
   }
-  if (int rc = launch_finish(c, s, begin, count, flags & CKV_FUSE_EVICT, advance, 0)) return rc;
+  if (int rc = launch_finish(c, s, begin, count, flags & (CKV_FUSE_EVICT | kLeaveMany), advance, 0)) return rc;
+  if (flags & kLeaveMany)
+    if (int rc = launch_evict(c, s, begin, count, -1, 1)) return rc;
   if (advance && (flags & CKV_FUSE_EVICT)) return rebalance_after_eviction(c);
   return CKV_OK;
 }
@@ -852,6 +879,7 @@ int ckv_rebudget(ckv_ctx* c, void* stream) {
   hipLaunchKernelGGL(rebudget_kernel, dim3((unsigned)c->lay.batch), dim3(kThreads), 0, (hipStream_t)stream, c->dev);
   CKV_HIP(c, hipGetLastError());
   c->dirty = true;             // shared pools: the segments follow once the shrunken units have evicted
+  c->many.assign(c->lay.n_layers, 1);
   return launch_schedule(c, (hipStream_t)stream);
 }
 
@@ -952,6 +980,7 @@ int ckv_set_budgets(ckv_ctx* c, const int32_t* budgets) {
   if (int rc = flush_group(c)) return rc;
   CKV_HIP(c, hipDeviceSynchronize());
   c->dirty = true;
+  c->many.assign(c->lay.n_layers, 1);
   return upload_budgets(c, budgets, nullptr);
 }
 

@@ -40,6 +40,7 @@ typedef unsigned long long u64;
 
 enum { SC_T = 0, SC_WINDOW_STEPS = 1, SC_DONE = 2, SC_STATUS = 3, SC_DONE_RB = 4, SC_QUEUE = 5, SC_SPARE = 6, SC_COUNT = 64 };
 enum { FLAG_HIT = 1, FLAG_SLIP = 2 };
+constexpr uint32_t kLeaveMany = 8u;       // a step's call flag: evictions of several entries from a unit are left to the evict_kernel that follows
 constexpr int kThreads = 256;
 constexpr int kWideThreads = 1024;        // kernels with one workgroup per unit and few units
 constexpr int kMaxChunks = 128;           // cap <= 32768
@@ -381,6 +382,8 @@ __global__ __launch_bounds__(kThreads) void probe_copy_kernel(const u32x4* __res
 // does not depend on timing.  If the spare list is short nobody is given anything and bit 2 of the status
 // word is set; a unit that still holds more entries than its budget (its eviction has not run yet) keeps
 // its segments until a later call.  Unowned columns of a table row hold 0.
+// A unit's segments move eight at a time (every load before the first store): one by one, the 28 segments that a
+// prompt of 9350 entries needs above a budget of 2048 were as many round trips, twice (64 such units: 42 us, now 22).
 constexpr int kBalanceThreads = 1024;
 __global__ __launch_bounds__(kBalanceThreads) void rebalance_kernel(Dev d, int headroom, int x_begin, int x_count, int x_entries,
                                                                     const int32_t* x_len) {
@@ -422,10 +425,18 @@ __global__ __launch_bounds__(kBalanceThreads) void rebalance_kernel(Dev d, int h
   int at = spare_n + scan(local);
   for (int u = u0; u < u1; ++u) {
     const int need = need_of(u), own = ld(d.owned + u);
-    for (int j = need; j < own; ++j) {
-      int32_t* cell = d.tbl + (size_t)u * d.max_seg + j;
-      st(d.spare + at++, ld(cell));
-      st(cell, 0);
+    int32_t* row = d.tbl + (size_t)u * d.max_seg;
+    for (int j = need; j < own; j += 8) {
+      int32_t seg[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) seg[k] = ld(row + min(j + k, own - 1));
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        if (j + k < own) {
+          st(d.spare + at++, seg[k]);
+          st(row + j + k, 0);
+        }
+      }
     }
     if (own > need) st(d.owned + u, need);
   }
@@ -445,7 +456,15 @@ __global__ __launch_bounds__(kBalanceThreads) void rebalance_kernel(Dev d, int h
   }
   for (int u = u0; u < u1; ++u) {
     const int need = need_of(u), own = ld(d.owned + u);
-    for (int j = own; j < need; ++j) st(d.tbl + (size_t)u * d.max_seg + j, ld(d.spare + (spare_n - 1 - from++)));
+    for (int j = own; j < need; j += 8) {
+      int32_t seg[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) seg[k] = ld(d.spare + (spare_n - 1 - (from + min(k, need - 1 - j))));
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        if (j + k < need) st(d.tbl + (size_t)u * d.max_seg + j + k, seg[k]);
+      from += min(8, need - j);
+    }
     if (need > own) st(d.owned + u, need);
   }
   if (tid == 0) d.sc[SC_SPARE] = spare_n - wanted;
@@ -1511,6 +1530,9 @@ __device__ __forceinline__ int evict_lists(const Dev& d, int u, Slots base, int 
 // Second kernel of an eviction: the survivors' rows, four per wavefront at a time (every load of a batch before
 // its first store), the unit's batches dealt over the workgroups along y (a unit's own y-th, as many as fill the
 // chip: one workgroup per unit leaves a layer of 64 units to 64 compute units and needs 100 round trips each).
+// What bounds it is what it has to read: survivors lie seven to a block of 32 on average and bring most of their blocks'
+// lines with them, about 370 MB for 64 units of 9350 entries cut to 2048 in 79 us.  (Destination blocks put together in LDS
+// and stored whole, instead of a row's 48 partial lines: 85 us.)
 // Units along x, so that a unit's workgroups share an XCD's cache when their number is a multiple of eight.
 __global__ __launch_bounds__(kThreads) void evict_move_kernel(Dev d, int unit_begin) {
   const int u = unit_begin + blockIdx.x;
@@ -2121,11 +2143,12 @@ __device__ __forceinline__ HitRule top_p_flat(const Dev& d, Slots base, int n, c
   return tie_rule<R, NT>(d, base, n, a, theta, above, ties, -1, rb, phase, tid);
 }
 
+// leave_many: a unit that has to give up several entries keeps them; evict_kernel follows and is faster at it.
 // `after_step1` runs once between Step 1 and the score update (the fused kernel
 // picks up its queue claim there).
 template <int R, int CH, int CP, class Val, int NT = kThreads, class Hook = NoHook>
 __device__ __forceinline__ void lrfu_regs(const Dev& d, int u, Slots base, int n, int B, int t, float (&a)[R], f32x4 (&crf)[CH],
-                                          i32x4 (&tau)[CH], i32x4 (&ps)[CH], Val val, bool evict, uint32_t* evm, int* lst,
+                                          i32x4 (&tau)[CH], i32x4 (&ps)[CH], Val val, bool evict, bool leave_many, uint32_t* evm, int* lst,
                                           int lst_cap, const float* s_tab, int s_tab_n, RedBuf& rb, int& phase, int* sh,
                                           int tid, Hook after_step1 = Hook{}, NewEntry ne = NewEntry{nullptr, nullptr}) {
   constexpr int C = R / 4;
@@ -2222,7 +2245,7 @@ __device__ __forceinline__ void lrfu_regs(const Dev& d, int u, Slots base, int n
     d.t_unit[u] = t;
   }
   // ---- Step 4
-  if (!(evict && n > B)) {
+  if (!(evict && n > B) || (leave_many && n - B > 1)) {
     if (tid == 0) d.nev[u] = 0;
     return;
   }
@@ -2256,7 +2279,7 @@ __device__ __forceinline__ void lrfu_regs(const Dev& d, int u, Slots base, int n
 // sh: 4 + NT / 64 ints.
 template <int NT>
 __device__ __forceinline__ void unit_bookkeeping(const Dev& d, int u, Slots base, int n, int B, int t, LgView lv, const float* sM,
-                                                 const float* sInv, bool evict, float* val, uint32_t* evm, const float* s_tab,
+                                                 const float* sInv, uint32_t call_flags, float* val, uint32_t* evm, const float* s_tab,
                                                  int s_tab_n, RedBuf& rb, int& phase, int* sh, int tid) {
   auto regs = [&](auto rc) {
     constexpr int R = decltype(rc)::value, C = R / 4, CH = C < 2 ? C : 2;
@@ -2264,8 +2287,8 @@ __device__ __forceinline__ void unit_bookkeeping(const Dev& d, int u, Slots base
     mean_weights_regs<R, NT>(d, lv, n, sM, sInv, a, tid);
     f32x4 crf[CH];
     i32x4 tau[CH], ps[CH];
-    lrfu_regs<R, CH, 0, ValLinear, NT>(d, u, base, n, B, t, a, crf, tau, ps, ValLinear{val}, evict, evm, reinterpret_cast<int*>(val), d.cap,
-                                       s_tab, s_tab_n, rb, phase, sh, tid);
+    lrfu_regs<R, CH, 0, ValLinear, NT>(d, u, base, n, B, t, a, crf, tau, ps, ValLinear{val}, (call_flags & 1u) != 0, (call_flags & kLeaveMany) != 0, evm,
+                                       reinterpret_cast<int*>(val), d.cap, s_tab, s_tab_n, rb, phase, sh, tid);
   };
   if (n <= 4 * NT) {
     regs(std::integral_constant<int, 4>{});
@@ -2326,7 +2349,7 @@ __global__ __launch_bounds__(NT) void finish_kernel(Dev d, int unit_begin, uint3
   }
   __threadfence_block();
   __syncthreads();
-  if (n > 0) unit_bookkeeping<NT>(d, u, base, n, B, t, unit_logits(d, u), sM, sInv, (call_flags & 1u) != 0, val, evm, s_tab, s_tab_n, rb, phase, sh, tid);
+  if (n > 0) unit_bookkeeping<NT>(d, u, base, n, B, t, unit_logits(d, u), sM, sInv, call_flags, val, evm, s_tab, s_tab_n, rb, phase, sh, tid);
   if (!layer_time) step_epilogue(d, t, advance, tid);
 }
 
@@ -2854,8 +2877,10 @@ __device__ __forceinline__ void evict_unit(const Dev& d, int u, Slots base, int 
   if (tid == 0) *move_count(d, u) = h;
 }
 
+// after_step: behind a decode step that has evicted single entries itself and left the rest (units that it dealt with keep
+// their record).
 template <int NT>
-__global__ __launch_bounds__(NT) void evict_kernel(Dev d, int unit_begin, int n_sink) {
+__global__ __launch_bounds__(NT) void evict_kernel(Dev d, int unit_begin, int n_sink, int after_step) {
   __shared__ uint32_t evm[NT];
   __shared__ int32_t s_row[kMaxChunks];
   __shared__ float s_tab[kTabLds];
@@ -2867,7 +2892,7 @@ __global__ __launch_bounds__(NT) void evict_kernel(Dev d, int unit_begin, int n_
   const int n = d.n[u], B = d.budget[u];
   if (n <= B) {
     if (tid == 0) {
-      d.nev[u] = 0;
+      if (!after_step) d.nev[u] = 0;
       *move_count(d, u) = 0;
     }
     return;

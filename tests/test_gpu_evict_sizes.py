@@ -85,3 +85,61 @@ def test_many_small_units(ties):
     lengths = [edge[i % len(edge)] for i in range(units)]
     budgets = [max(1, (n * (1 + i % 7)) // 8) for i, n in enumerate(lengths)]
     _check(units, 4608, lengths, budgets, None, range(0, units, 37), ties)
+
+
+@pytest.mark.parametrize("path,defer", [(1, False), (1, True), (3, False)])
+def test_step_after_a_budget_cut_eager_and_captured(path, defer):
+    """A step after budgets were cut evicts many entries per unit: eagerly in kernels behind it, inside a captured graph
+    by itself.  Same outputs, same survivors with their scores; the step after it evicts one entry per unit again."""
+    import torch
+    from paper_2601_16986_amd import ckv
+    lengths = [40, 300, 1025, 2049, 4100, 8193, 9001, 64]
+    cuts = [40, 100, 1024, 300, 4099, 2000, 8999, 63]           # none, some, one or two entries too many after the append
+    units, cap, t, n_max = len(lengths), 9024, 20000, max(lengths)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(2)
+    rnd = lambda *s: torch.randn(s, generator=gen, device="cuda:0").to(torch.bfloat16)
+    k, v = rnd(units, 1, n_max, 128), rnd(units, 1, n_max, 128)
+    q, kn, vn = rnd(2, 1, units, 4, 128), rnd(2, 1, units, 1, 128), rnd(2, 1, units, 1, 128)
+    pos = torch.stack([torch.randperm(t, generator=gen, device="cuda:0")[:n_max] for _ in range(units)]).reshape(units, 1, n_max).int()
+    tau = torch.maximum(pos, t - 1 - (torch.rand(pos.shape, generator=gen, device="cuda:0") * 300).int())
+    states = []
+    for captured in (False, True):
+        g = ckv.CrystalKV(1, units, 4, 1, 128, cap, np.asarray(lengths, np.int32).reshape(1, units, 1), t0=t, budget_min=1, budget_max=cap - 1,
+                          headroom=1)
+        g.set_path(path)
+        g.load_cache(0, k, v, torch.tensor(lengths, dtype=torch.int32, device=g.device).reshape(units, 1), torch.ones_like(pos, dtype=torch.float32),
+                     tau, pos)
+        g.set_budgets(np.asarray(cuts, np.int32).reshape(1, units, 1))
+        outs = torch.empty((2, 1, units, 4, 128), device=g.device)
+
+        def step(s):
+            if path == 3:
+                g.decode_step(q[s], kn[s], vn[s], out=outs[s])
+            else:
+                g.decode_step(q[s, 0], kn[s, 0], vn[s, 0], layer=0, out=outs[s, 0], defer=defer)
+            g.join()
+
+        if captured:
+            graph = torch.cuda.CUDAGraph()
+            torch.cuda.synchronize()
+            with torch.cuda.graph(graph):
+                step(0)
+            graph.replay()
+        else:
+            step(0)
+        first = [g.export_unit(0, u, 0) for u in range(units)]
+        step(1)
+        states.append((outs.clone(), first, [g.export_unit(0, u, 0) for u in range(units)]))
+        assert g.status() == 0 and g.time() == t + 2
+        g.close()
+    (o1, a1, b1), (o2, a2, b2) = states
+    # the second step's cache is the same set of rows in another order of slots: fp32 sums of the same terms
+    assert torch.equal(o1[0], o2[0]) and torch.allclose(o1[1], o2[1], rtol=1e-5, atol=1e-6)
+    for x, y in ((a1, a2), (b1, b2)):
+        for u, (e, f) in enumerate(zip(x, y)):
+            assert e["n"] == f["n"] == min(cuts[u], lengths[u] + 1) and e["n_evicted"] == f["n_evicted"]
+            assert np.array_equal(e["evicted_pos"], f["evicted_pos"]) and np.all(e["evicted_flags"] == 2)
+            i, j = np.argsort(e["pos"]), np.argsort(f["pos"])
+            for key in ("pos", "crf", "tau", "K", "V"):
+                assert np.array_equal(e[key][i], f[key][j]), (u, key)
