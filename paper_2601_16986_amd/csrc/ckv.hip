@@ -227,6 +227,40 @@ int profile_events(ckv_ctx* c, hipEvent_t* e0, hipEvent_t* e1) {
   return CKV_OK;
 }
 
+// Side streams outlive the context that created them: making and destroying two cost 100 us per context (183 + 59 us for
+// creating and closing a small one, 135 + 5 without), which a server that makes one per batch of sequences pays each time.  Idle ones wait here, at most kIdleStreams per device; more are
+// destroyed.  A stream is handed back after everything on it has completed.
+constexpr size_t kIdleStreams = 16;
+std::mutex g_streams_mutex;
+std::vector<hipStream_t> g_streams[kMaxDevices];
+
+hipError_t take_stream(int devid, hipStream_t* out) {
+  if (devid >= 0 && devid < kMaxDevices) {
+    std::lock_guard<std::mutex> lock(g_streams_mutex);
+    if (!g_streams[devid].empty()) {
+      *out = g_streams[devid].back();
+      g_streams[devid].pop_back();
+      return hipSuccess;
+    }
+  }
+  return hipStreamCreateWithFlags(out, hipStreamNonBlocking);
+}
+
+void give_stream(int devid, hipStream_t s) {
+  const bool idle = hipStreamSynchronize(s) == hipSuccess;
+  if (idle && devid >= 0 && devid < kMaxDevices) {
+    std::lock_guard<std::mutex> lock(g_streams_mutex);
+    if (g_streams[devid].size() < kIdleStreams) {
+      try {
+        g_streams[devid].push_back(s);
+        return;
+      } catch (const std::bad_alloc&) {
+      }
+    }
+  }
+  (void)hipStreamDestroy(s);
+}
+
 // Eviction of `count` units from `begin` on: select, then move.  A unit's keys sit in the registers of one workgroup:
 // 1024 threads, or 256 where every unit fits (32 entries per thread) and there are enough units to fill the chip
 // with small workgroups anyway.
@@ -576,7 +610,7 @@ int ckv_init(ckv_ctx** out, const ckv_layout* layout, const int32_t* budgets, co
   c->pending.assign(layout->n_layers, 0);
   c->many.assign(layout->n_layers, 0);
   for (int i = 0; i < kSide; ++i)
-    if (hipStreamCreateWithFlags(&c->side[i], hipStreamNonBlocking) != hipSuccess) return bail(CKV_EHIP);
+    if (take_stream(devid, &c->side[i]) != hipSuccess) return bail(CKV_EHIP);
   if (hipEventCreateWithFlags(&c->ev_out, hipEventDisableTiming) != hipSuccess) return bail(CKV_EHIP);
   for (int l = 0; l < layout->n_layers; ++l) {
     hipEvent_t e;
@@ -630,10 +664,7 @@ int ckv_init(ckv_ctx** out, const ckv_layout* layout, const int32_t* budgets, co
 void ckv_destroy(ckv_ctx* c) {
   if (!c) return;
   for (int i = 0; i < kSide; ++i)
-    if (c->side[i]) {
-      (void)hipStreamSynchronize(c->side[i]);
-      (void)hipStreamDestroy(c->side[i]);
-    }
+    if (c->side[i]) give_stream(c->device, c->side[i]);
   if (c->ev_out) (void)hipEventDestroy(c->ev_out);
   for (hipEvent_t e : c->ev_book) (void)hipEventDestroy(e);
   for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
