@@ -907,7 +907,9 @@ int ckv_rebudget(ckv_ctx* c, void* stream) {
   if (!c) return CKV_EINVAL;
   if (c->next_layer != 0) return fail(c, CKV_ESTATE, "a per-layer step is in progress");
   if (int rc = join_side(c, (hipStream_t)stream)) return rc;
-  hipLaunchKernelGGL(rebudget_kernel, dim3((unsigned)c->lay.batch), dim3(kThreads), 0, (hipStream_t)stream, c->dev);
+  const size_t level2 = (size_t)c->lay.n_layers * c->lay.n_kv_heads * 25;
+  const bool in_lds = level2 <= 48 * 1024;
+  hipLaunchKernelGGL(rebudget_kernel, dim3((unsigned)c->lay.batch), dim3(kThreads), in_lds ? level2 : 0, (hipStream_t)stream, c->dev, in_lds ? 1 : 0);
   CKV_HIP(c, hipGetLastError());
   c->dirty = true;             // shared pools: the segments follow once the shrunken units have evicted
   c->many.assign(c->lay.n_layers, 1);

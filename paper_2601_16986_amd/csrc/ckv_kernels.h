@@ -3153,8 +3153,11 @@ __device__ __forceinline__ void apportion(const double* x, int m, long long tota
 constexpr int kMaxLayers = 256;
 constexpr int kMaxKvHeads = 32;
 
-// One workgroup per sequence.
-__global__ __launch_bounds__(kThreads) void rebudget_kernel(Dev d) {
+// One workgroup per sequence.  in_lds: there are 25 bytes of dynamic LDS per (layer, head) for the second level; else
+// its arrays are the threads' own, in scratch memory, where every indexed access is a trip to memory: 28 us for 4
+// layers of 4 heads, 16 in LDS; 60 us for 16 layers of 8, 35 in LDS).
+__global__ __launch_bounds__(kThreads) void rebudget_kernel(Dev d, int in_lds) {
+  extern __shared__ unsigned char smem[];
   __shared__ double eta_l[kMaxLayers], y_l[kMaxLayers];
   __shared__ long long tot_l[kMaxLayers];
   __shared__ unsigned char fx_l[kMaxLayers];
@@ -3185,16 +3188,26 @@ __global__ __launch_bounds__(kThreads) void rebudget_kernel(Dev d) {
       }
     }
     __syncthreads();
-    if (ok && tid < L) {
-      double eta_h[kMaxKvHeads], y_h[kMaxKvHeads];
-      long long val_h[kMaxKvHeads];
-      unsigned char fx_h[kMaxKvHeads];
+    auto second_level = [&](double* eta_h, double* y_h, long long* val_h, unsigned char* fx_h) {
       for (int j = 0; j < H; ++j) {
         const int u = (tid * d.Bz + b) * H + j;
         eta_h[j] = ((double)d.window[u] / denom) / (double)d.budget[u];
       }
       apportion(eta_h, H, tot_l[tid], d.bmin, d.bmax, val_h, y_h, fx_h);
       for (int j = 0; j < H; ++j) d.budget[(tid * d.Bz + b) * H + j] = (int32_t)val_h[j];
+    };
+    if (ok && tid < L) {
+      if (in_lds) {
+        double* eta = reinterpret_cast<double*>(smem);
+        double* y = eta + L * H;
+        long long* val = reinterpret_cast<long long*>(y + L * H);
+        second_level(eta + tid * H, y + tid * H, val + tid * H, reinterpret_cast<unsigned char*>(val + L * H) + tid * H);
+      } else {
+        double eta_h[kMaxKvHeads], y_h[kMaxKvHeads];
+        long long val_h[kMaxKvHeads];
+        unsigned char fx_h[kMaxKvHeads];
+        second_level(eta_h, y_h, val_h, fx_h);
+      }
     }
     __syncthreads();
     for (int i = tid; i < L * H; i += kThreads) d.window[((i / H) * d.Bz + b) * H + (i % H)] = 0ull;

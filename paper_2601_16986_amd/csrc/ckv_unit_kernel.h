@@ -52,20 +52,25 @@ __device__ __forceinline__ int resident_entries(int n, int G, int lds_main_bytes
 // it only affects scheduling) in `order`.  Workgroups take the slots in order,
 // largest units first.
 __global__ __launch_bounds__(1024) void schedule_kernel(Dev d) {
-  __shared__ int hist[1025];
+  __shared__ int hist[1024], s_wave[16];
   const int tid = threadIdx.x;
-  for (int i = tid; i < 1025; i += 1024) hist[i] = 0;
+  hist[tid] = 0;
   __syncthreads();
   for (int u = tid; u < d.units; u += 1024) atomicAdd(&hist[1023 - min(1023, d.budget[u] >> 5)], 1);
   __syncthreads();
-  if (tid == 0) {
-    int run = 0;
-    for (int c = 0; c < 1024; ++c) {
-      const int h = hist[c];
-      hist[c] = run;
-      run += h;
-    }
+  // exclusive prefix sums of the classes' counts, one class per thread
+  const int mine = hist[tid], lane = tid & 63, wave = tid >> 6;
+  int incl = mine;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(incl, o);
+    if (lane >= o) incl += y;
   }
+  if (lane == 63) s_wave[wave] = incl;
+  __syncthreads();
+  int before = incl - mine;
+  for (int w = 0; w < wave; ++w) before += s_wave[w];
+  hist[tid] = before;
   __syncthreads();
   for (int u = tid; u < d.units; u += 1024) {
     const int slot = atomicAdd(&hist[1023 - min(1023, d.budget[u] >> 5)], 1);
