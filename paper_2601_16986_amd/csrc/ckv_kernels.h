@@ -2350,7 +2350,7 @@ __global__ __launch_bounds__(NT) void finish_kernel(Dev d, int unit_begin, uint3
   __threadfence_block();
   __syncthreads();
   if (n > 0) unit_bookkeeping<NT>(d, u, base, n, B, t, unit_logits(d, u), sM, sInv, call_flags, val, evm, s_tab, s_tab_n, rb, phase, sh, tid);
-  if (!layer_time) step_epilogue(d, t, advance, tid);
+  if (advance) step_epilogue(d, t, advance, tid);          // the time moves on behind the last layer (deferred steps: in its scan)
 }
 
 // ------------------------------------------------------------------ prompt replay (scores of a loaded prompt)
@@ -2607,8 +2607,8 @@ __global__ __launch_bounds__(kThreads) void seed_weights_kernel(Dev d, int unit_
           tile(gr * G + h + t);
 #pragma unroll
           for (int v = 0; v < 4; ++v) {
-            mean[t][0] += fast_exp2(__builtin_fmaf(s0[v], c, -M[v])) * I[v];
-            mean[t][1] += fast_exp2(__builtin_fmaf(s1[v], c, -M[v])) * I[v];
+            mean[t][0] = __builtin_fmaf(fast_exp2(__builtin_fmaf(s0[v], c, -M[v])), I[v], mean[t][0]);
+            mean[t][1] = __builtin_fmaf(fast_exp2(__builtin_fmaf(s1[v], c, -M[v])), I[v], mean[t][1]);
           }
         }
       }
@@ -2617,8 +2617,8 @@ __global__ __launch_bounds__(kThreads) void seed_weights_kernel(Dev d, int unit_
         tile(gr * G + h);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          mean[v][0] += fast_exp2(__builtin_fmaf(s0[v], c, -M[v])) * I[v];
-          mean[v][1] += fast_exp2(__builtin_fmaf(s1[v], c, -M[v])) * I[v];
+          mean[v][0] = __builtin_fmaf(fast_exp2(__builtin_fmaf(s0[v], c, -M[v])), I[v], mean[v][0]);
+          mean[v][1] = __builtin_fmaf(fast_exp2(__builtin_fmaf(s1[v], c, -M[v])), I[v], mean[v][1]);
         }
       }
       const int e0 = blk * kBlk + j;
