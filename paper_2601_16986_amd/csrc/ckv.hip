@@ -19,6 +19,7 @@
 
 using namespace ckv;
 
+constexpr int kManyEntries = 1 << 20;   // `excess` of a layer about which the host knows nothing
 constexpr int kSide = 2;   // streams of the context's own for deferred bookkeeping
 constexpr int kBookGroup = 8, kBookGroupMost = 32;   // layers whose deferred bookkeeping goes out as one launch (see book_group)
 
@@ -76,6 +77,8 @@ struct ckv_ctx {
   // Layers whose budgets have changed since their last eviction: their units may have to give up many entries at once, which
   // a step then leaves to evict_kernel behind it.
   std::vector<uint8_t> many;
+  // Per layer: entries above its budget that a unit may hold, as far as the host has seen (a replayed graph may have added more).
+  std::vector<int> excess;
   int group_first = 0, group_count = 0, group_launches = 0;
   uint32_t group_flags = 0;
   hipStream_t group_stream = nullptr;
@@ -262,16 +265,29 @@ void give_stream(int devid, hipStream_t s) {
 }
 
 // Eviction of `count` units from `begin` on: select, then move.  A unit's keys sit in the registers of one workgroup:
-// 1024 threads, or 256 where every unit fits (32 entries per thread) and there are enough units to fill the chip
-// with small workgroups anyway.
+// 1024 threads, or 256 where four entries per thread are enough for every unit, or 32 are and there are enough units to
+// fill the chip with small workgroups anyway.
+// The moves' kernel is left out (4 us, 8 with thousands of workgroups) where no unit should hold more than one entry above
+// its budget: `excess` counts what the host has seen.  (Inside a graph it stays: the replays' state is not the host's.)
 int launch_evict(ckv_ctx* c, hipStream_t s, int begin, int count, int n_sink, int after_step = 0) {
-  if (c->lay.cap <= 32 * kThreads && count >= 4 * c->n_cu)
-    hipLaunchKernelGGL(evict_kernel<kThreads>, dim3((unsigned)count), dim3(kThreads), 0, s, c->dev, begin, n_sink, after_step);
+  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+  CKV_HIP(c, hipStreamIsCapturing(s, &capturing));
+  bool moves = after_step || capturing != hipStreamCaptureStatusNone;
+  for (int l = begin / c->units_per_layer; l < (begin + count) / c->units_per_layer; ++l) {
+    moves = moves || c->excess[l] > 1;
+    c->excess[l] = 0;
+  }
+  if (c->lay.cap <= 4 * kThreads)
+    hipLaunchKernelGGL((evict_kernel<kThreads, true>), dim3((unsigned)count), dim3(kThreads), 0, s, c->dev, begin, n_sink, after_step, moves ? 1 : 0);
+  else if (c->lay.cap <= 32 * kThreads && count >= 4 * c->n_cu)
+    hipLaunchKernelGGL(evict_kernel<kThreads>, dim3((unsigned)count), dim3(kThreads), 0, s, c->dev, begin, n_sink, after_step, moves ? 1 : 0);
   else
-    hipLaunchKernelGGL(evict_kernel<kWideThreads>, dim3((unsigned)count), dim3(kWideThreads), 0, s, c->dev, begin, n_sink, after_step);
+    hipLaunchKernelGGL(evict_kernel<kWideThreads>, dim3((unsigned)count), dim3(kWideThreads), 0, s, c->dev, begin, n_sink, after_step, moves ? 1 : 0);
   CKV_HIP(c, hipGetLastError());
+  if (!moves) return CKV_OK;
+  const int x = std::min(count, 4 * c->n_cu);
   const int y = std::max(1, std::min({16 * c->n_cu / count, (c->lay.cap / 2 + 15) / 16, 64}));
-  hipLaunchKernelGGL(evict_move_kernel, dim3((unsigned)count, (unsigned)y), dim3(kThreads), 0, s, c->dev, begin);
+  hipLaunchKernelGGL(evict_move_kernel, dim3((unsigned)x, (unsigned)y), dim3(kThreads), 0, s, c->dev, begin, count);
   CKV_HIP(c, hipGetLastError());
   return CKV_OK;
 }
@@ -609,6 +625,7 @@ int ckv_init(ckv_ctx** out, const ckv_layout* layout, const int32_t* budgets, co
   };
   c->pending.assign(layout->n_layers, 0);
   c->many.assign(layout->n_layers, 0);
+  c->excess.assign(layout->n_layers, 0);
   for (int i = 0; i < kSide; ++i)
     if (take_stream(devid, &c->side[i]) != hipSuccess) return bail(CKV_EHIP);
   if (hipEventCreateWithFlags(&c->ev_out, hipEventDisableTiming) != hipSuccess) return bail(CKV_EHIP);
@@ -681,6 +698,7 @@ int ckv_load_cache(ckv_ctx* c, int32_t layer, const void* k, const void* v, int3
   if (c->prompt_loaded[layer]) return fail(c, CKV_ESTATE, "layer already holds entries");
   c->prompt_loaded[layer] = 1;
   c->prompt_len[layer] = (!lengths && !pos0) ? P : -1;
+  c->excess[layer] = kManyEntries;
   if (int rc = join_side(c, (hipStream_t)stream)) return rc;
   if (c->lay.headroom > 0) {
     // shared pools: the layer's units get room for what is loaded (and an append behind it) from the spare list,
@@ -725,6 +743,7 @@ int ckv_decode_step(ckv_ctx* c, int32_t layer, const void* q, const void* k_new,
   for (int l = (layer == -1 ? 0 : layer); l < (layer == -1 ? c->lay.n_layers : layer + 1); ++l) {
     c->prompt_loaded[l] = 1;
     c->prompt_len[l] = -1;
+    c->excess[l] = (flags & CKV_FUSE_EVICT) ? 0 : std::min(c->excess[l] + 1, kManyEntries);
   }
   hipStream_t s = (hipStream_t)stream;
   if (flags & CKV_FUSE_EVICT) {
@@ -913,6 +932,7 @@ int ckv_rebudget(ckv_ctx* c, void* stream) {
   CKV_HIP(c, hipGetLastError());
   c->dirty = true;             // shared pools: the segments follow once the shrunken units have evicted
   c->many.assign(c->lay.n_layers, 1);
+  c->excess.assign(c->lay.n_layers, kManyEntries);
   return launch_schedule(c, (hipStream_t)stream);
 }
 
@@ -1014,6 +1034,7 @@ int ckv_set_budgets(ckv_ctx* c, const int32_t* budgets) {
   CKV_HIP(c, hipDeviceSynchronize());
   c->dirty = true;
   c->many.assign(c->lay.n_layers, 1);
+  c->excess.assign(c->lay.n_layers, kManyEntries);
   return upload_budgets(c, budgets, nullptr);
 }
 
@@ -1164,6 +1185,7 @@ int ckv_import_unit(ckv_ctx* c, int32_t layer, int32_t seq, int32_t head, int32_
   CKV_HIP(c, hipMemcpy(c->dev.t_unit + u, &t_unit, 4, hipMemcpyHostToDevice));
   c->prompt_loaded[layer] = 1;
   c->prompt_len[layer] = -1;
+  c->excess[layer] = kManyEntries;
   return CKV_OK;
 }
 

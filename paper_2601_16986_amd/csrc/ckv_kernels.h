@@ -1534,12 +1534,14 @@ __device__ __forceinline__ int evict_lists(const Dev& d, int u, Slots base, int 
 // lines with them, about 370 MB for 64 units of 9350 entries cut to 2048 in 79 us.  (Destination blocks put together in LDS
 // and stored whole, instead of a row's 48 partial lines: 85 us.)
 // Units along x, so that a unit's workgroups share an XCD's cache when their number is a multiple of eight.
-__global__ __launch_bounds__(kThreads) void evict_move_kernel(Dev d, int unit_begin) {
-  const int u = unit_begin + blockIdx.x;
-  const int h = *move_count(d, u);
+__global__ __launch_bounds__(kThreads) void evict_move_kernel(Dev d, int unit_begin, int count) {
   const int first = 4 * (blockIdx.y * (kThreads / 64) + (threadIdx.x >> 6)), stride = 4 * gridDim.y * (kThreads / 64);
-  const Slots base = slots_of(d, u);
-  for (int r0 = first; r0 < h; r0 += stride) move_entries4(d, base, move_list(d, u), d.cap, r0, min(4, h - r0), threadIdx.x & 63);
+  for (int w = blockIdx.x; w < count; w += gridDim.x) {
+    const int u = unit_begin + w;
+    const int h = *move_count(d, u);
+    const Slots base = slots_of(d, u);
+    for (int r0 = first; r0 < h; r0 += stride) move_entries4(d, base, move_list(d, u), d.cap, r0, min(4, h - r0), threadIdx.x & 63);
+  }
 }
 
 // ------------------------------------------------------------------ finish
@@ -2816,7 +2818,7 @@ __global__ __launch_bounds__(kThreads) void seed_crf_kernel(Dev d, int unit_begi
 // that keeps the initial and the most recent tokens; the retention key is then the position itself, carried
 // as a bit pattern (the eviction only ever compares the bits), and the largest pattern for positions below n_sink.
 template <int R, int NT>
-__device__ __forceinline__ void evict_unit(const Dev& d, int u, Slots base, int n, int B, int n_sink, const float* s_tab, int s_tab_n,
+__device__ __forceinline__ void evict_unit(const Dev& d, int u, Slots base, int n, int B, int n_sink, int moves_follow, const float* s_tab, int s_tab_n,
                                            uint32_t* evm, CutBuf& cb, RedBuf& rb, int* sh, int tid) {
   const int t = d.t_unit[u];
   uint32_t b[R], np[R];
@@ -2874,13 +2876,21 @@ __device__ __forceinline__ void evict_unit(const Dev& d, int u, Slots base, int 
     return;
   }
   const int h = evict_lists<R, NT>(d, u, base, n, B, b, np, move_list(d, u), evm, cb, tid);
-  if (tid == 0) *move_count(d, u) = h;
+  if (moves_follow) {
+    if (tid == 0) *move_count(d, u) = h;
+    return;
+  }
+  __syncthreads();                                         // the lists are there (and visible inside the workgroup)
+  for (int r0 = 4 * (tid >> 6); r0 < h; r0 += 4 * (NT / 64)) move_entries4(d, base, move_list(d, u), d.cap, r0, min(4, h - r0), tid & 63);
 }
 
 // after_step: behind a decode step that has evicted single entries itself and left the rest (units that it dealt with keep
-// their record).
-template <int NT>
-__global__ __launch_bounds__(NT) void evict_kernel(Dev d, int unit_begin, int n_sink, int after_step) {
+// their record).  moves_follow = 0: nobody is expected to have more than one entry to give up, evict_move_kernel does
+// not run, and a unit that has after all moves its survivors here.
+// kShort: no unit holds more than four entries per thread; the kernel then needs a third of the registers and LDS, and
+// thousands of short units fit side by side (4096 units of 300 entries, one evicted each: 7 us less).
+template <int NT, bool kShort = false>
+__global__ __launch_bounds__(NT) void evict_kernel(Dev d, int unit_begin, int n_sink, int after_step, int moves_follow) {
   __shared__ uint32_t evm[NT];
   __shared__ int32_t s_row[kMaxChunks];
   __shared__ float s_tab[kTabLds];
@@ -2902,14 +2912,16 @@ __global__ __launch_bounds__(NT) void evict_kernel(Dev d, int unit_begin, int n_
   if (tid < d.max_seg) s_row[tid] = d.tbl[(size_t)u * d.max_seg + tid];
   __syncthreads();
   const Slots base{s_row};
-  if (n <= 4 * NT)
-    evict_unit<4, NT>(d, u, base, n, B, n_sink, s_tab, s_tab_n, evm, cb, rb, sh, tid);
-  else if (n <= 8 * NT)
-    evict_unit<8, NT>(d, u, base, n, B, n_sink, s_tab, s_tab_n, evm, cb, rb, sh, tid);
-  else if (n <= 16 * NT)
-    evict_unit<16, NT>(d, u, base, n, B, n_sink, s_tab, s_tab_n, evm, cb, rb, sh, tid);
-  else
-    evict_unit<32, NT>(d, u, base, n, B, n_sink, s_tab, s_tab_n, evm, cb, rb, sh, tid);
+  if (kShort || n <= 4 * NT)
+    evict_unit<4, NT>(d, u, base, n, B, n_sink, moves_follow, s_tab, s_tab_n, evm, cb, rb, sh, tid);
+  else if constexpr (!kShort) {
+    if (n <= 8 * NT)
+      evict_unit<8, NT>(d, u, base, n, B, n_sink, moves_follow, s_tab, s_tab_n, evm, cb, rb, sh, tid);
+    else if (n <= 16 * NT)
+      evict_unit<16, NT>(d, u, base, n, B, n_sink, moves_follow, s_tab, s_tab_n, evm, cb, rb, sh, tid);
+    else
+      evict_unit<32, NT>(d, u, base, n, B, n_sink, moves_follow, s_tab, s_tab_n, evm, cb, rb, sh, tid);
+  }
 }
 
 // ------------------------------------------------------------------ probe

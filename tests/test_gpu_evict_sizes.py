@@ -143,3 +143,36 @@ def test_step_after_a_budget_cut_eager_and_captured(path, defer):
             i, j = np.argsort(e["pos"]), np.argsort(f["pos"])
             for key in ("pos", "crf", "tau", "K", "V"):
                 assert np.array_equal(e[key][i], f[key][j]), (u, key)
+
+
+def test_replayed_steps_leave_more_than_the_host_has_seen():
+    """A graph of steps without eviction is replayed: the units then hold more entries above their budgets than the host
+    has counted, and a window eviction still brings them down to the newest ones."""
+    import torch
+    from paper_2601_16986_amd import ckv
+    P, cap, extra = 60, 128, 9
+    g = ckv.CrystalKV(1, 2, 8, 2, 128, cap, np.full((1, 2, 2), P, np.int32), t0=P, budget_min=1, budget_max=cap - 1)
+    gen = torch.Generator(device=g.device)
+    gen.manual_seed(7)
+    rnd = lambda *s: torch.randn(s, generator=gen, device=g.device).to(torch.bfloat16)
+    k, v = rnd(2, 2, P, 128), rnd(2, 2, P, 128)
+    g.load_prompt(0, k, v)
+    g.evict_window(0)
+    q, kn, vn = rnd(1, 2, 8, 128), rnd(1, 2, 2, 128), rnd(1, 2, 2, 128)
+    out = torch.empty((1, 2, 8, 128), device=g.device)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        g.decode_step(q, kn, vn, out=out, attention_only=True)
+    for _ in range(extra):
+        graph.replay()
+    g.evict_window(0)
+    assert g.status() == 0
+    for b in range(2):
+        for h in range(2):
+            e = g.export_unit(0, b, h)
+            assert sorted(e["pos"].tolist()) == list(range(extra, P + extra)) and e["n_evicted"] == extra
+            rows = {int(p): r for p, r in zip(e["pos"], e["K"])}
+            assert all(np.array_equal(rows[p], k[b, h, p].float().cpu().numpy()) for p in range(extra, P))
+            assert all(np.array_equal(rows[p], kn[0, b, h].float().cpu().numpy()) for p in range(P, P + extra))
+    g.close()
