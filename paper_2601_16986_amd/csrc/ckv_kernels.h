@@ -1593,8 +1593,7 @@ __device__ __forceinline__ void decay4_of(const Dev& d, const int (&delta)[4], c
 }
 
 // Where a unit's scaled logits lie in memory: per block of 32 entries a group of rows [row][32], of which
-// the G rows from `p` on are the unit's heads (the scan kernel leaves exactly G rows per block; the prompt
-// replay leaves 16, G of them per query).
+// the G rows from `p` on are the unit's heads.
 struct LgView {
   const float* p;      // head 0, entry 0
   int blk_stride;      // floats from one block to the next
