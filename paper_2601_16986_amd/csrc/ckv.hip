@@ -14,6 +14,7 @@
 #include <string>
 #include <vector>
 
+#include "ckv_books.h"
 #include "ckv_kernels.h"
 #include "ckv_unit_kernel.h"
 
@@ -21,7 +22,6 @@ using namespace ckv;
 
 constexpr int kManyEntries = 1 << 20;   // `excess` of a layer about which the host knows nothing
 constexpr int kSide = 2;   // streams of the context's own for deferred bookkeeping
-constexpr int kBookGroup = 8, kBookGroupMost = 32;   // layers whose deferred bookkeeping goes out as one launch (see book_group)
 
 // Scratch of ckv_probe_noalloc: device memory the library owns from the moment it is loaded, so that the
 // call never needs a caller's workspace or an allocation.  In host code `scratch` is only a handle: the
@@ -60,8 +60,8 @@ struct ckv_ctx {
   std::vector<int32_t> prompt_len;   // per layer: length of a prompt loaded whole and untouched since, else -1
   // Deferred bookkeeping of single-layer steps (CKV_DEFER_BOOKKEEPING): finish_kernel runs on
   // one of the `side` streams (layer l on side[l % kSide], so that the bookkeeping of consecutive layers, which
-  // share nothing, can overlap), ordered by events against the caller's stream.  pending[l]: layer l's
-  // bookkeeping has been queued there and nothing on the caller's side has waited for it yet.
+  // share nothing, can overlap), ordered by events against the caller's stream.  books: the layers whose
+  // bookkeeping has been queued there and nothing on the caller's side has waited for yet.
   // The bookkeeping of several consecutive layers (book_group) goes out as one launch (a fork from the caller's
   // stream costs about as much as a small kernel, and more units per launch fill the chip better): after a
   // deferred step, layers [group_first, group_first + group_count) have been scanned on group_stream and wait
@@ -69,8 +69,7 @@ struct ckv_ctx {
   hipStream_t side[kSide] = {};
   hipEvent_t ev_out = nullptr;
   std::vector<hipEvent_t> ev_book;
-  std::vector<uint8_t> pending;
-  bool any_pending = false;
+  PendingBooks books;
   // Shared pools: budgets (or a prompt) have changed what units should own (dirty); once an eviction over all
   // layers has been issued since, the segments are dealt out again when the next step begins (due).
   bool dirty = false, due = false;
@@ -322,11 +321,6 @@ int launch_layer_scan(ckv_ctx* c, hipStream_t s, int begin, int count, const uin
   return CKV_OK;
 }
 
-// Layers per launch of deferred bookkeeping: eight, or as many as give every compute unit a workgroup if the layers are
-// small (each launch forks from the caller's stream, which costs its next layer about 10 us: 48 layers of eight units,
-// captured, in groups of 32 instead of 8: 706 -> 663 us).
-int book_group(const ckv_ctx* c) { return std::max(kBookGroup, std::min(kBookGroupMost, c->n_cu / c->units_per_layer)); }
-
 // Queue the bookkeeping of the layers scanned since the last group went out.
 int flush_group(ckv_ctx* c) {
   if (c->group_count == 0) return CKV_OK;
@@ -340,8 +334,7 @@ int flush_group(ckv_ctx* c) {
   if (c->group_flags & kLeaveMany)
     if (int rc = launch_evict(c, side, first * upl, count * upl, -1, 1)) return rc;
   CKV_HIP(c, hipEventRecord(c->ev_book[first], side));
-  for (int l = first; l < first + count; ++l) c->pending[l] = 1 + first;     // whose event to wait for
-  c->any_pending = true;
+  c->books.record(first, count);
   return CKV_OK;
 }
 
@@ -349,19 +342,10 @@ int flush_group(ckv_ctx* c) {
 int join_side(ckv_ctx* c, hipStream_t s, int layer = -1) {
   if (c->group_count && (layer < 0 || (layer >= c->group_first && layer < c->group_first + c->group_count)))
     if (int rc = flush_group(c)) return rc;
-  if (!c->any_pending) return CKV_OK;
-  bool left = false;
-  for (int l = 0; l < c->lay.n_layers; ++l) {
-    if (!c->pending[l]) continue;
-    if (layer >= 0 && l != layer) {
-      left = true;
-      continue;
-    }
-    CKV_HIP(c, hipStreamWaitEvent(s, c->ev_book[c->pending[l] - 1], 0));
-    c->pending[l] = 0;
-  }
-  c->any_pending = left;
-  return CKV_OK;
+  return c->books.join(layer, [&](int first) -> int {
+    CKV_HIP(c, hipStreamWaitEvent(s, c->ev_book[first], 0));
+    return CKV_OK;
+  });
 }
 
 // Deal the pool segments out again (shared pools only); units [x_begin, x_begin + x_count) get room for
@@ -623,7 +607,7 @@ int ckv_init(ckv_ctx** out, const ckv_layout* layout, const int32_t* budgets, co
     ckv_destroy(c);
     return rc;
   };
-  c->pending.assign(layout->n_layers, 0);
+  c->books.reset(layout->n_layers);
   c->many.assign(layout->n_layers, 0);
   c->excess.assign(layout->n_layers, 0);
   for (int i = 0; i < kSide; ++i)
@@ -790,7 +774,7 @@ int ckv_decode_step(ckv_ctx* c, int32_t layer, const void* q, const void* k_new,
     c->group_count += 1;
     if (advance && (flags & CKV_FUSE_EVICT))
       if (int rc = rebalance_after_eviction(c)) return rc;
-    if (c->group_count == book_group(c) || advance) return flush_group(c);
+    if (c->group_count == book_group(c->n_cu, c->units_per_layer) || advance) return flush_group(c);
     return CKV_OK;
   }
   hipEvent_t e0 = nullptr, e1 = nullptr;
