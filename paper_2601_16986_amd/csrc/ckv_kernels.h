@@ -1524,7 +1524,7 @@ __device__ __forceinline__ int evict_lists(const Dev& d, int u, Slots base, int 
     d.n[u] = B;
     d.nev[u] = k;
   }
-  return (int)(total & 0xFFFFu);
+  return (int)min(total & 0xFFFFu, total >> 16);          // equal, unless positions repeat within the unit
 }
 
 // Second kernel of an eviction: the survivors' rows, four per wavefront at a time (every load of a batch before
@@ -2840,7 +2840,8 @@ __device__ __forceinline__ void evict_unit(const Dev& d, int u, Slots base, int 
         const float tmp = __fmul_rn(decay_of(d, delta, s_tab, s_tab_n), crf[e]);
         key = tmp < FLT_MIN ? 0u : __float_as_uint(tmp);
       }
-      b[4 * c + e] = e0 + e < n ? key : 0xFFFFFFFFu;
+      // (a score may be any pattern, a NaN of all ones among them: an entry never looks like none)
+      b[4 * c + e] = e0 + e < n ? min(key, 0xFFFFFFFEu) : 0xFFFFFFFFu;
       np[4 * c + e] = ~(uint32_t)ps[e];
     }
     if (R > 16 && (c & 1)) __builtin_amdgcn_sched_barrier(0);          // two groups' state in flight: the keys need the registers

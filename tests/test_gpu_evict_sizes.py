@@ -176,3 +176,30 @@ def test_replayed_steps_leave_more_than_the_host_has_seen():
             assert all(np.array_equal(rows[p], k[b, h, p].float().cpu().numpy()) for p in range(extra, P))
             assert all(np.array_equal(rows[p], kn[0, b, h].float().cpu().numpy()) for p in range(P, P + extra))
     g.close()
+
+
+@pytest.mark.parametrize("cap,n,B", [(96, 70, 69), (96, 70, 3), (2080, 2000, 1999), (2080, 2000, 200), (9408, 9350, 9349), (9408, 9350, 2048)])
+def test_scores_of_any_pattern(cap, n, B):
+    """Loaded scores are not checked: infinities and NaNs, one of all bits set among them, are patterns like others (the
+    larger, the longer they stay).  More entries to evict than there are finite scores; one entry; all scores the same NaN."""
+    import torch
+    from paper_2601_16986_amd import ckv
+    units, t = 3, 20000
+    rng = np.random.default_rng(9)
+    g = ckv.CrystalKV(1, units, 1, 1, 128, cap, np.full((1, units, 1), B, np.int32), lam=LAM, t0=t + 1, budget_min=1, budget_max=cap - 1)
+    pos = np.stack([rng.permutation(t - 1)[:n] for _ in range(units)]).astype(np.int32)
+    bits = np.full((units, n), 0xFFFFFFFF, np.uint32)
+    bits[1:, rng.random(n) < 0.1] = np.float32(1.5).view(np.uint32)
+    bits[2, rng.random(n) < 0.2] = 0x7FC00000
+    bits[2, rng.random(n) < 0.2] = 0x7F800000
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x).reshape(units, 1, n)).to(g.device)
+    k = torch.randn((units, 1, n, 128), device=g.device).to(torch.bfloat16)
+    g.load_cache(0, k, k, torch.full((units, 1), n, dtype=torch.int32, device=g.device), dev(bits.view(np.int32)).view(torch.float32), dev(np.full_like(pos, t)), dev(pos))
+    g.evict(0)
+    for u in range(units):
+        order = np.lexsort((-pos[u], bits[u]))                       # the first go
+        e = g.export_unit(0, u, 0)
+        assert e["n"] == B and e["n_evicted"] == n - B
+        assert np.array_equal(np.sort(e["pos"]), np.sort(pos[u, order[n - B:]])), u
+        assert np.array_equal(np.sort(e["evicted_pos"]), np.sort(pos[u, order[:n - B]])), u
+    g.close()
