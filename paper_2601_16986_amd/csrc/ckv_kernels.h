@@ -2386,6 +2386,17 @@ constexpr int kSeedCols = 16;
 constexpr int kSeedGroup = 16;         // queries that share G tiles
 constexpr int kSeedTiles = 16;         // tiles of a batch, at most
 constexpr float kNoMax = -1e30f;       // maximum of no logit: finite, so that exponents relative to it are zeros, not NaNs
+// Exponents are one fused multiply-add per logit (scale, minus the scaled maximum), while the maximum itself is a rounded
+// product.  Up to 2^24 the two are within a half of each other; from 2^31 on within more than the exponential's
+// range, and the sum of a column would be 0 or infinite.  Columns whose maximum lies beyond this bound take the product
+// rounded, as the decode path does (which is exact at the maximum).
+constexpr float kFarMax = 16777216.0f;
+__device__ __forceinline__ bool is_far(float max) { return fabsf(max) > kFarMax && max != kNoMax; }
+template <bool ROUNDED>
+__device__ __forceinline__ float seed_exp(float logit, float scale, float max) {
+  if constexpr (ROUNDED) return fast_exp2(logit * scale - max);
+  return fast_exp2(__builtin_fmaf(logit, scale, -max));
+}
 
 // Query (of the batch) and head of column c of tile tl.
 __device__ __forceinline__ int seed_column(int G, int tl, int c, int& head) {
@@ -2455,54 +2466,65 @@ __global__ __launch_bounds__(kThreads) void seed_scan_kernel(Dev d, int unit_beg
   }
   const float c = d.scale_log2e;
   const uint16_t* kp = d.K + lane * 8;
-  KFrag ka, kn;
-  if (sp.b < sp.b1) load_k(ka, kp + sp.off(sp.b));
-  for (int blk = sp.b; blk < sp.b1; ++blk) {
-    load_k(kn, kp + sp.off(min(blk + 1, sp.b1 - 1)));
-    const int e0 = blk * kBlk + 4 * kg;
-    int k = 0;                                            // tile within its group
+  auto sweep = [&](auto rounded) {
+    KFrag ka, kn;
+    if (sp.b < sp.b1) load_k(ka, kp + sp.off(sp.b));
+    for (int blk = sp.b; blk < sp.b1; ++blk) {
+      load_k(kn, kp + sp.off(min(blk + 1, sp.b1 - 1)));
+      const int e0 = blk * kBlk + 4 * kg;
+      int k = 0;                                            // tile within its group
 #pragma unroll
-    for (int tl = 0; tl < kSeedTiles; ++tl) {
-      const bool four = k < G - rem;
-      k = k + 1 == G ? 0 : k + 1;
-      if (tl < nt && blk * kBlk < n_first + min(q_lo[tl] + (four ? 3 : 15), nq - 1)) {     // uniform: else no query of the tile sees the block
-        bf16x8 qv[4];
+      for (int tl = 0; tl < kSeedTiles; ++tl) {
+        const bool four = k < G - rem;
+        k = k + 1 == G ? 0 : k + 1;
+        if (tl < nt && blk * kBlk < n_first + min(q_lo[tl] + (four ? 3 : 15), nq - 1)) {     // uniform: else no query of the tile sees the block
+          bf16x8 qv[4];
 #pragma unroll
-        for (int s4 = 0; s4 < 4; ++s4) qv[s4] = as_bf16x8(s_q[(tl * 4 + s4) * 64 + lane]);
-        f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+          for (int s4 = 0; s4 < 4; ++s4) qv[s4] = as_bf16x8(s_q[(tl * 4 + s4) * 64 + lane]);
+          f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int s4 = 0; s4 < 4; ++s4) s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ka.k[s4]), qv[s4], s0, 0, 0, 0);
+          for (int s4 = 0; s4 < 4; ++s4) s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ka.k[s4]), qv[s4], s0, 0, 0, 0);
 #pragma unroll
-        for (int s4 = 0; s4 < 4; ++s4) s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ka.k[4 + s4]), qv[s4], s1, 0, 0, 0);
-        float sv[8];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          sv[v] = s0[v];
-          sv[4 + v] = s1[v];
-        }
-        if ((blk + 1) * kBlk > n_first + q_lo[tl]) {      // a block that the tile's first query sees whole needs no mask
-          const int lim = n_first + q_lo[tl] + (four ? q4 : q1);       // entries this column's query sees
+          for (int s4 = 0; s4 < 4; ++s4) s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ka.k[4 + s4]), qv[s4], s1, 0, 0, 0);
+          float sv[8];
 #pragma unroll
           for (int v = 0; v < 4; ++v) {
-            sv[v] = (e0 + v < lim) ? sv[v] : -INFINITY;
-            sv[4 + v] = (e0 + 16 + v < lim) ? sv[4 + v] : -INFINITY;
+            sv[v] = s0[v];
+            sv[4 + v] = s1[v];
           }
-        }
-        // exponents as one fused multiply-add per logit (scale, minus the scaled maximum).  The maximum is kept rounded up
-        // to a whole number: sums are then rescaled by exact powers of two, here and where partials meet.
-        const float bm = c * fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
-        if (bm > m_run[tl]) {
-          const float m_new = ceilf(bm);
-          l_run[tl] *= fast_exp2(m_run[tl] - m_new);      // 0 the first time
-          m_run[tl] = m_new;
-        }
-        float p[8];
+          if ((blk + 1) * kBlk > n_first + q_lo[tl]) {      // a block that the tile's first query sees whole needs no mask
+            const int lim = n_first + q_lo[tl] + (four ? q4 : q1);       // entries this column's query sees
 #pragma unroll
-        for (int i = 0; i < 8; ++i) p[i] = fast_exp2(__builtin_fmaf(sv[i], c, -m_run[tl]));
-        l_run[tl] += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+            for (int v = 0; v < 4; ++v) {
+              sv[v] = (e0 + v < lim) ? sv[v] : -INFINITY;
+              sv[4 + v] = (e0 + 16 + v < lim) ? sv[4 + v] : -INFINITY;
+            }
+          }
+          // The maximum is kept rounded up to a whole number: sums are then rescaled by exact powers of two, here and
+          // where partials meet.
+          const float bm = c * fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
+          if (bm > m_run[tl]) {
+            const float m_new = ceilf(bm);
+            l_run[tl] *= fast_exp2(m_run[tl] - m_new);      // 0 the first time
+            m_run[tl] = m_new;
+          }
+          float p[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) p[i] = seed_exp<decltype(rounded)::value>(sv[i], c, m_run[tl]);
+          l_run[tl] += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+        }
       }
+      ka = kn;
     }
-    ka = kn;
+  };
+  sweep(std::false_type{});
+  bool far = false;
+#pragma unroll
+  for (int tl = 0; tl < kSeedTiles; ++tl) far |= is_far(m_run[tl]);
+  if (__any(far)) {                                       // the maxima stand; the sums once more
+#pragma unroll
+    for (int tl = 0; tl < kSeedTiles; ++tl) l_run[tl] = 0.f;
+    sweep(std::true_type{});
   }
   // per tile, the column's four lanes (kg = 0..3): maximum, then the sums rescaled to it, in a fixed order
 #pragma unroll
@@ -2576,66 +2598,74 @@ __global__ __launch_bounds__(kThreads) void seed_weights_kernel(Dev d, int unit_
   __syncthreads();
   if (slot >= S) return;
   SeedSpan sp(d, u, slot, S, n_first + nq - 1);
+  bool far = false;
+  for (int i = lane; i < nt * kSeedCols; i += 64) far |= is_far(s_M[i]);
   const float c = d.scale_log2e;
   const uint16_t* kp = d.K + lane * 8;
-  KFrag ka, kn;
-  if (sp.b < sp.b1) load_k(ka, kp + sp.off(sp.b));
-  for (int blk = sp.b; blk < sp.b1; ++blk) {
-    load_k(kn, kp + sp.off(min(blk + 1, sp.b1 - 1)));
+  auto sweep = [&](auto rounded) {
+    KFrag ka, kn;
+    if (sp.b < sp.b1) load_k(ka, kp + sp.off(sp.b));
+    for (int blk = sp.b; blk < sp.b1; ++blk) {
+      load_k(kn, kp + sp.off(min(blk + 1, sp.b1 - 1)));
 #pragma unroll 1
-    for (int gr = 0; gr < groups; ++gr) {
-      const int q0 = kSeedGroup * gr;
-      if (blk * kBlk >= n_first + min(q0 + kSeedGroup - 1, nq - 1)) continue;      // uniform: no query of the group sees the block
-      float mean[4][2];                                   // queries q0 + 4 t + kg, entries j and 16 + j of the block
+      for (int gr = 0; gr < groups; ++gr) {
+        const int q0 = kSeedGroup * gr;
+        if (blk * kBlk >= n_first + min(q0 + kSeedGroup - 1, nq - 1)) continue;      // uniform: no query of the group sees the block
+        float mean[4][2];                                   // queries q0 + 4 t + kg, entries j and 16 + j of the block
 #pragma unroll
-      for (int t = 0; t < 4; ++t) mean[t][0] = mean[t][1] = 0.f;
-      f32x4 s0, s1, M, I;
-      auto tile = [&](int tl) {
-        s0 = s1 = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < 4; ++t) mean[t][0] = mean[t][1] = 0.f;
+        f32x4 s0, s1, M, I;
+        auto tile = [&](int tl) {
+          s0 = s1 = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int s4 = 0; s4 < 4; ++s4) {
-          const bf16x8 qv = as_bf16x8(s_q[(tl * 4 + s4) * 64 + lane]);
-          s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qv, as_bf16x8(ka.k[s4]), s0, 0, 0, 0);
-          s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qv, as_bf16x8(ka.k[4 + s4]), s1, 0, 0, 0);
+          for (int s4 = 0; s4 < 4; ++s4) {
+            const bf16x8 qv = as_bf16x8(s_q[(tl * 4 + s4) * 64 + lane]);
+            s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qv, as_bf16x8(ka.k[s4]), s0, 0, 0, 0);
+            s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qv, as_bf16x8(ka.k[4 + s4]), s1, 0, 0, 0);
+          }
+          M = *reinterpret_cast<const f32x4*>(s_M + tl * kSeedCols + 4 * kg);
+          I = *reinterpret_cast<const f32x4*>(s_I + tl * kSeedCols + 4 * kg);
+        };
+#pragma unroll 1
+        for (int h = 0; h + 4 <= G; h += 4) {
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            tile(gr * G + h + t);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              mean[t][0] = __builtin_fmaf(seed_exp<decltype(rounded)::value>(s0[v], c, M[v]), I[v], mean[t][0]);
+              mean[t][1] = __builtin_fmaf(seed_exp<decltype(rounded)::value>(s1[v], c, M[v]), I[v], mean[t][1]);
+            }
+          }
         }
-        M = *reinterpret_cast<const f32x4*>(s_M + tl * kSeedCols + 4 * kg);
-        I = *reinterpret_cast<const f32x4*>(s_I + tl * kSeedCols + 4 * kg);
-      };
 #pragma unroll 1
-      for (int h = 0; h + 4 <= G; h += 4) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          tile(gr * G + h + t);
+        for (int h = G & ~3; h < G; ++h) {
+          tile(gr * G + h);
 #pragma unroll
           for (int v = 0; v < 4; ++v) {
-            mean[t][0] = __builtin_fmaf(fast_exp2(__builtin_fmaf(s0[v], c, -M[v])), I[v], mean[t][0]);
-            mean[t][1] = __builtin_fmaf(fast_exp2(__builtin_fmaf(s1[v], c, -M[v])), I[v], mean[t][1]);
+            mean[v][0] = __builtin_fmaf(seed_exp<decltype(rounded)::value>(s0[v], c, M[v]), I[v], mean[v][0]);
+            mean[v][1] = __builtin_fmaf(seed_exp<decltype(rounded)::value>(s1[v], c, M[v]), I[v], mean[v][1]);
+          }
+        }
+        const int e0 = blk * kBlk + j;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const int qi = q0 + 4 * t + kg;
+          if (qi < nq) {
+            const int lim = n_first + qi;                   // entries the query sees
+            float* dst = srw + ((size_t)qi * UL + urel) * d.cap + e0;
+            dst[0] = e0 < lim ? mean[t][0] : 0.f;
+            dst[16] = e0 + 16 < lim ? mean[t][1] : 0.f;
           }
         }
       }
-#pragma unroll 1
-      for (int h = G & ~3; h < G; ++h) {
-        tile(gr * G + h);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          mean[v][0] = __builtin_fmaf(fast_exp2(__builtin_fmaf(s0[v], c, -M[v])), I[v], mean[v][0]);
-          mean[v][1] = __builtin_fmaf(fast_exp2(__builtin_fmaf(s1[v], c, -M[v])), I[v], mean[v][1]);
-        }
-      }
-      const int e0 = blk * kBlk + j;
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int qi = q0 + 4 * t + kg;
-        if (qi < nq) {
-          const int lim = n_first + qi;                   // entries the query sees
-          float* dst = srw + ((size_t)qi * UL + urel) * d.cap + e0;
-          dst[0] = e0 < lim ? mean[t][0] : 0.f;
-          dst[16] = e0 + 16 < lim ? mean[t][1] : 0.f;
-        }
-      }
+      ka = kn;
     }
-    ka = kn;
-  }
+  };
+  if (__any(far))
+    sweep(std::true_type{});
+  else
+    sweep(std::false_type{});
 }
 
 // seed_hits_kernel (top-p rule only): one workgroup per (query of the batch, unit).  The query's mean weights

@@ -6,7 +6,7 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-def _context(L, batch, hkv, G, P, W, weighted):
+def _context(L, batch, hkv, G, P, W, weighted, shape_qk=None):
     import torch
     from paper_2601_16986_amd import ckv
     g = ckv.CrystalKV(L, batch, hkv * G, hkv, 128, (P + 33) // 32 * 32, np.full((L, batch, hkv), P, np.int32), t0=P, lam=0.5,
@@ -16,6 +16,8 @@ def _context(L, batch, hkv, G, P, W, weighted):
     rnd = lambda *s: torch.randn(s, generator=gen, device=g.device)
     k = rnd(batch, hkv, P, 128).to(torch.bfloat16)
     q = (1.5 * rnd(W, batch, hkv * G, 128)).to(torch.bfloat16)
+    if shape_qk:
+        q, k = shape_qk(torch, q, k)
     g.load_prompt(0, k, k)
     g.seed_prompt(0, q)
     assert g.status() == 0
@@ -61,3 +63,34 @@ def test_hits_of_every_row_length(P):
     # fp32 sums of P weights may put the cut a few entries to either side of the edge, never elsewhere
     wrong = (hit != want)
     assert float(torch.where(wrong, (a / edge - 1).abs(), 0.0).max()) < 1e-3 and int(wrong.sum(-1).max()) <= 2
+
+
+@pytest.mark.parametrize("weighted", [True, False])
+@pytest.mark.parametrize("G", [3, 8])
+@pytest.mark.parametrize("q_exp,k_exp", [(9, 9), (14, 14), (18, 18), (40, 36)])
+def test_logits_far_beyond_the_exponential(q_exp, k_exp, G, weighted):
+    """Logits of about 2^21, 2^31, 2^39 and 2^79 in base 2: every head's weight is all on its largest logit, or shared by what lies
+    within a unit of it; nothing overflows, however far the logits are from 1."""
+    P, W = 395, 37
+    scale = lambda torch, q, k: ((q.float() * 2.0 ** q_exp).to(torch.bfloat16), (k.float() * 2.0 ** k_exp).to(torch.bfloat16))
+    torch, crf, tau, weights = _context(1, 2, 3, G, P, W, weighted, scale)
+    _check_far(torch, crf, tau, weights, P, W, weighted)
+
+
+def _check_far(torch, crf, tau, weights, P, W, weighted):
+    pos = torch.arange(P, device=crf.device)
+    want, last = (pos < P - W).double().expand_as(crf).clone(), pos.expand(crf.shape).clone()
+    for j, a in enumerate(weights):
+        t = P - W + j
+        # G heads of weight 1 / G each: all of them are needed to exceed 0.9 of the whole; and the query's own entry
+        reward = a if weighted else ((a > 1e-3) | (pos[:t + 1] == t)).double()
+        new = want[..., :t + 1] * 0.5 ** (t - last[..., :t + 1]).double() + reward
+        take = torch.ones_like(new, dtype=torch.bool) if weighted else reward > 0
+        want[..., :t + 1] = torch.where(take, new, want[..., :t + 1])
+        last[..., :t + 1] = torch.where(take, t, last[..., :t + 1])
+    assert bool(torch.isfinite(crf).all())
+    # a logit of 128 products carries an error of a few 2^-24 of their sum's size: two logits that close share a head's weight
+    # in another ratio.  Two of 395 logits are that close in about one head of 10^4.
+    off = (crf - want).abs() > 4e-6
+    assert int(off.sum()) <= 4, int(off.sum())
+    assert int((tau != last).sum()) <= 4
