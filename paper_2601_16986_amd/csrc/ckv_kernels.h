@@ -2385,7 +2385,7 @@ __global__ __launch_bounds__(NT) void finish_kernel(Dev d, int unit_begin, uint3
 constexpr int kSeedCols = 16;
 constexpr int kSeedGroup = 16;         // queries that share G tiles
 constexpr int kSeedTiles = 16;         // tiles of a batch, at most
-constexpr float kNoMax = -1e30f;       // maximum of no logit: finite, so that exponents relative to it are zeros, not NaNs
+constexpr float kNoMax = -FLT_MAX;     // maximum of no logit: finite, so that exponents relative to it are zeros, not NaNs
 // Exponents are one fused multiply-add per logit (scale, minus the scaled maximum), while the maximum itself is a rounded
 // product.  Up to 2^24 the two are within a half of each other; from 2^31 on within more than the exponential's
 // range, and the sum of a column would be 0 or infinite.  Columns whose maximum lies beyond this bound take the product
@@ -2571,7 +2571,8 @@ __global__ __launch_bounds__(kSeedTiles * kSeedCols) void seed_stats_kernel(Dev 
       if (c0 + k < S) l[k] += p[k].y * fast_exp2(p[k].x - M);
   }
   const float L = ((l[0] + l[1]) + (l[2] + l[3])) + ((l[4] + l[5]) + (l[6] + l[7]));
-  *reinterpret_cast<float2*>(smi + (((size_t)tl * UL + urel) * kSeedCols + col) * 2) = make_float2(M, 1.0f / L);
+  // a head none of whose logits is above -inf weighs nothing
+  *reinterpret_cast<float2*>(smi + (((size_t)tl * UL + urel) * kSeedCols + col) * 2) = make_float2(M, L == 0.0f ? 0.0f : 1.0f / L);
 }
 
 // seed_weights_kernel: every logit normalised with its column's maximum and 1 / sum, the mean over a query's heads

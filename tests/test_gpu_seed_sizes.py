@@ -94,3 +94,42 @@ def _check_far(torch, crf, tau, weights, P, W, weighted):
     off = (crf - want).abs() > 4e-6
     assert int(off.sum()) <= 4, int(off.sum())
     assert int((tau != last).sum()) <= 4
+
+
+@pytest.mark.parametrize("weighted", [True, False])
+@pytest.mark.parametrize("G", [3, 8])
+def test_logits_all_far_below_zero(G, weighted):
+    """Every logit about -1e32: finite, and the largest of them takes its head's weight like any other."""
+    P, W = 395, 37
+    scale = lambda torch, q, k: ((q.float().abs() * 2.0 ** 52).to(torch.bfloat16), (-k.float().abs() * 2.0 ** 52).to(torch.bfloat16))
+    torch, crf, tau, weights = _context(1, 2, 3, G, P, W, weighted, scale)
+    _check_far(torch, crf, tau, weights, P, W, weighted)
+
+
+def test_a_head_whose_logits_are_all_minus_infinity():
+    """Products that overflow to -inf: that head weighs nothing, the others' weights stand."""
+    P, W, G = 395, 5, 4
+    kept = []
+
+    def scale(torch, q, k):
+        q, k = q.float(), k.float()
+        k[..., 0] = -2.0 ** 10
+        q[..., 0] = 0.0
+        q[:, :, 1::G] = 0.0
+        q[:, :, 1::G, 0] = 2.0 ** 126
+        kept.append((q.to(torch.bfloat16), k.to(torch.bfloat16)))
+        return kept[0]
+
+    torch, crf, tau, weights = _context(1, 2, 3, G, P, W, True, scale)
+    q, k = kept[0]
+    kt = k.double().transpose(2, 3).contiguous()
+    pos = torch.arange(P, device=crf.device)
+    want, last = (pos < P - W).double().expand_as(crf).clone(), pos.clone()
+    for j in range(W):
+        t = P - W + j
+        s = torch.matmul(q[j].view(2, 3, G, 128).double(), kt[..., :t + 1].contiguous()) / np.sqrt(128.0)
+        a = torch.softmax(s, dim=-1)
+        a[:, :, 1] = 0.0
+        want[..., :t + 1] = want[..., :t + 1] * 0.5 ** (t - last[:t + 1]).double() + a.mean(2)
+        last[:t + 1] = t
+    assert float(((crf - want).abs() / want.clamp(min=1e-30)).max()) < 4e-6
