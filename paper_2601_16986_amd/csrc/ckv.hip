@@ -291,6 +291,18 @@ int launch_evict(ckv_ctx* c, hipStream_t s, int begin, int count, int n_sink, in
   return CKV_OK;
 }
 
+// Whether a step after a change of budgets leaves evictions of several entries per unit to the kernels behind it.  Those
+// use more threads per unit, but with many units evict_move_kernel has few workgroups for each and waits for the
+// units with the most moves, while the step's own kernel deals units out as workgroups come free.  Measured, re-allocation and
+// the two steps behind it beyond two ordinary steps, us, in the step's kernel / left: all layers 128 units 126 / 57,
+// 512 units 219 / 174, 1024 units 476 / 377, 2048 units 790 / 938, 6144 units 1705 / 2474, 8192 units 1326 / 1615 (medians of three
+// processes: where the pools lie moves the large ones by a fifth); one call per layer of 1280 units 971 / 897, of 2048 units
+// 782 / 913.  Deferred bookkeeping, several layers per launch: 512 units 273 / 253, 1024 units 551 / 613, 2048 units 476 / 641.
+bool leave_many_pays(const ckv_ctx* c, int count, bool deferred) {
+  if (deferred) return count * std::min(book_group(c->n_cu, c->units_per_layer), c->lay.n_layers) <= 3 * c->n_cu;
+  return count <= 5 * c->n_cu;
+}
+
 // The bookkeeping of `count` units from `begin` on, behind their scan.  Workgroups of 256 threads where no unit can
 // hold more than eight entries per thread, else 1024.
 int launch_finish(ckv_ctx* c, hipStream_t s, int begin, int count, uint32_t flags, int advance, int layer_time) {
@@ -730,6 +742,13 @@ int ckv_decode_step(ckv_ctx* c, int32_t layer, const void* q, const void* k_new,
     c->excess[l] = (flags & CKV_FUSE_EVICT) ? 0 : std::min(c->excess[l] + 1, kManyEntries);
   }
   hipStream_t s = (hipStream_t)stream;
+  // The fused kernel takes whole units: all layers at once, or one layer that has at least a unit per
+  // workgroup.  Such a layer it also finishes sooner than a scan with deferred bookkeeping would (Llama-8B
+  // shape, 512 units per layer: 74 against 78 us), so there the flag is not followed.
+  const ckv_ctx::Fused* fv = fused_variant(c);
+  if (fv && (c->path_mode == 0 || layer >= 0) && count < fv->grid) fv = nullptr;   // fewer units than workgroups: split the units instead
+  const bool fused = fv != nullptr;
+  if (fused) flags &= ~CKV_DEFER_BOOKKEEPING;
   if (flags & CKV_FUSE_EVICT) {
     // After a change of budgets, once.  Not into a graph: replays would evict what is not there; the kernels' own
     // evictions, which do without the launches behind them, give the same.
@@ -740,16 +759,8 @@ int ckv_decode_step(ckv_ctx* c, int32_t layer, const void* q, const void* k_new,
     }
     hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
     if (many) CKV_HIP(c, hipStreamIsCapturing(s, &capturing));
-    if (many && capturing == hipStreamCaptureStatusNone) flags |= kLeaveMany;
+    if (many && capturing == hipStreamCaptureStatusNone && leave_many_pays(c, count, (flags & CKV_DEFER_BOOKKEEPING) != 0)) flags |= kLeaveMany;
   }
-
-  // The fused kernel takes whole units: all layers at once, or one layer that has at least a unit per
-  // workgroup.  Such a layer it also finishes sooner than a scan with deferred bookkeeping would (Llama-8B
-  // shape, 512 units per layer: 74 against 78 us), so there the flag is not followed.
-  const ckv_ctx::Fused* fv = fused_variant(c);
-  if (fv && (c->path_mode == 0 || layer >= 0) && count < fv->grid) fv = nullptr;   // fewer units than workgroups: split the units instead
-  const bool fused = fv != nullptr;
-  if (fused) flags &= ~CKV_DEFER_BOOKKEEPING;
   if (layer <= 0)
     if (int rc = rebalance_if_due(c, s)) return rc;
   if (int rc = join_side(c, s, layer)) return rc;

@@ -87,6 +87,14 @@ def test_many_small_units(ties):
     _check(units, 4608, lengths, budgets, None, range(0, units, 37), ties)
 
 
+def test_more_units_than_the_moves_have_workgroups_for():
+    """Thousands of units with moves: one workgroup per unit, and workgroups that take several units."""
+    units, edge = 4500, [1, 40, 300, 511, 700]
+    lengths = [edge[i % len(edge)] for i in range(units)]
+    budgets = [max(1, (n * (1 + i % 7)) // 8) for i, n in enumerate(lengths)]
+    _check(units, 704, lengths, budgets, None, range(0, units, 101), False)
+
+
 @pytest.mark.parametrize("path,defer", [(1, False), (1, True), (3, False)])
 def test_step_after_a_budget_cut_eager_and_captured(path, defer):
     """A step after budgets were cut evicts many entries per unit: eagerly in kernels behind it, inside a captured graph
