@@ -194,13 +194,14 @@ __device__ __forceinline__ u64 wave_min_u64(u64 v) {
 // Barrier among the NT threads that work on one unit.  NT = 64: a single wavefront, which may be one of
 // several in its workgroup and must not touch the workgroup barrier: its LDS and memory operations
 // already execute in program order, only the compiler has to keep them so.
+template <int NT>
 struct alignas(16) RedBuf {
-  u64 v[2][16];         // one slot per wavefront: up to 1024 threads
-  float t[2][16][4];
+  u64 v[2][NT / 64];    // one slot per wavefront
+  float t[2][NT / 64][4];
 };
 
 template <int NT>
-__device__ __forceinline__ void block_sync(RedBuf& rb) {
+__device__ __forceinline__ void block_sync(RedBuf<NT>& rb) {
   if constexpr (NT == 64) {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -228,7 +229,7 @@ __device__ __forceinline__ T row_combine(T r, Op op, Dpp1 d1, Dpp2 d2, Dpp3 d3, 
 }
 
 template <int NT = kThreads>
-__device__ __forceinline__ u64 block_sum_u64(u64 v, RedBuf& rb, int& phase, int tid) {
+__device__ __forceinline__ u64 block_sum_u64(u64 v, RedBuf<NT>& rb, int& phase, int tid) {
   v = wave_sum_u64(v);
   if constexpr (NT == 64) return v;
   if ((tid & 63) == 0) rb.v[phase][tid >> 6] = v;
@@ -247,7 +248,7 @@ __device__ __forceinline__ u64 block_sum_u64(u64 v, RedBuf& rb, int& phase, int 
 }
 
 template <int NT = kThreads>
-__device__ __forceinline__ int block_sum_int(int v, RedBuf& rb, int& phase, int tid) {
+__device__ __forceinline__ int block_sum_int(int v, RedBuf<NT>& rb, int& phase, int tid) {
   v = wave_sum_i32(v);
   if constexpr (NT == 64) return v;
   if ((tid & 63) == 0) rb.v[phase][tid >> 6] = (u64)(uint32_t)v;
@@ -274,7 +275,7 @@ __device__ __forceinline__ float dpp_f32(float v) {
 }
 
 template <int NT = kThreads>
-__device__ __forceinline__ float block_sum_f32(float v, RedBuf& rb, int& phase, int tid) {
+__device__ __forceinline__ float block_sum_f32(float v, RedBuf<NT>& rb, int& phase, int tid) {
   v = wave_sum_f32(v);
   if constexpr (NT == 64) return v;
   if ((tid & 63) == 0) rb.v[phase][tid >> 6] = (u64)__float_as_uint(v);
@@ -294,7 +295,7 @@ __device__ __forceinline__ float block_sum_f32(float v, RedBuf& rb, int& phase, 
 
 // Three sums at once (one barrier).
 template <int NT = kThreads>
-__device__ __forceinline__ void block_sum3_f32(float& x, float& y, float& z, RedBuf& rb, int& phase, int tid) {
+__device__ __forceinline__ void block_sum3_f32(float& x, float& y, float& z, RedBuf<NT>& rb, int& phase, int tid) {
   x = wave_sum_f32(x);
   y = wave_sum_f32(y);
   z = wave_sum_f32(z);
@@ -325,7 +326,7 @@ __device__ __forceinline__ void block_sum3_f32(float& x, float& y, float& z, Red
 }
 
 template <int NT = kThreads>
-__device__ __forceinline__ u64 block_min_u64(u64 v, RedBuf& rb, int& phase, int tid) {
+__device__ __forceinline__ u64 block_min_u64(u64 v, RedBuf<NT>& rb, int& phase, int tid) {
   v = wave_min_u64(v);
   if constexpr (NT == 64) return v;
   if ((tid & 63) == 0) rb.v[phase][tid >> 6] = v;
@@ -1162,7 +1163,7 @@ struct ValLinear {
 // evm = LDS bit mask of n bits, lst = LDS scratch of lst_cap >= n ints that may
 // overlap the storage behind `val` (the scores are dead by the time it is used).
 template <class Val, int NT = kThreads>
-__device__ __forceinline__ void evict_phase(const Dev& d, int u, Slots base, int n, int B, Val val, uint32_t* evm, int* lst, int lst_cap, RedBuf& rb,
+__device__ __forceinline__ void evict_phase(const Dev& d, int u, Slots base, int n, int B, Val val, uint32_t* evm, int* lst, int lst_cap, RedBuf<NT>& rb,
                             int& phase, int* sh, int tid) {
   const int lane = tid & 63, wave = tid >> 6;
   const int k = n - B;
@@ -1617,7 +1618,7 @@ struct HitRule {
 
 // Step 1 over weights in val(0 .. n - 1) (LDS), any n
 template <class Val, int NT = kThreads>
-__device__ __forceinline__ HitRule top_p_lds(const Dev& d, Slots base, int n, Val val, RedBuf& rb, int& phase, int tid) {
+__device__ __forceinline__ HitRule top_p_lds(const Dev& d, Slots base, int n, Val val, RedBuf<NT>& rb, int& phase, int tid) {
   uint32_t theta = 0;
   bool ties_all = true;
   int pos_cut = 0x7FFFFFFF;
@@ -1672,7 +1673,7 @@ __device__ __forceinline__ HitRule top_p_lds(const Dev& d, Slots base, int n, Va
 }
 
 template <class Val, int NT = kThreads>
-__device__ __forceinline__ u64 lrfu_update(const Dev& d, int u, Slots base, int n, int t, Val val, const float* s_tab, int s_tab_n, RedBuf& rb,
+__device__ __forceinline__ u64 lrfu_update(const Dev& d, int u, Slots base, int n, int t, Val val, const float* s_tab, int s_tab_n, RedBuf<NT>& rb,
                            int& phase, int tid) {
   // ---- Alg. 1 Step 1: top-p hit set as a threshold on the weight's bit pattern
   const HitRule rule = top_p_lds<Val, NT>(d, base, n, val, rb, phase, tid);
@@ -1823,7 +1824,7 @@ __device__ __forceinline__ EntryRow load_row_input(const NewEntry& ne, int tid) 
 // above theta, ties = entries equal to it.
 template <int R, int NT>
 __device__ __forceinline__ HitRule tie_rule(const Dev& d, Slots base, int n, const float (&a)[R], uint32_t theta, float above, int ties,
-                                            int new_last_t, RedBuf& rb, int& phase, int tid) {
+                                            int new_last_t, RedBuf<NT>& rb, int& phase, int tid) {
   HitRule rule{theta, true, 0x7FFFFFFF};
   if (ties <= 1) return rule;
   const float th = __uint_as_float(theta);
@@ -1857,7 +1858,7 @@ __device__ __forceinline__ HitRule tie_rule(const Dev& d, Slots base, int n, con
 // other phases' round trips decide: fused step 0.99-1.00 of the speed, bookkeeping of 128 units 21 us either way.)
 template <int R, int NT = kThreads>
 __device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, const float (&a)[R], int* lst, int lst_cap, int new_last_t,
-                                              RedBuf& rb, int& phase, int* sh, int tid) {
+                                              RedBuf<NT>& rb, int& phase, int* sh, int tid) {
   uint32_t theta = 0;
   if (d.reward_mode == 0) {
     // largest pattern theta with sum{a >= theta} > p, two bits per round (one barrier each): the three
@@ -1982,7 +1983,7 @@ __device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, c
 // Step 1 over long units of flat weights (the prompt replay): the same threshold in fewer passes over the registers,
 // with a longer list at the end.  lst: kList ints of LDS; sh[5 .. 7] are used.  theta = 0: every entry is hit.
 template <int R, int NT, int kList>
-__device__ __forceinline__ HitRule top_p_flat(const Dev& d, Slots base, int n, const float (&a)[R], int* lst, RedBuf& rb, int& phase, int* sh,
+__device__ __forceinline__ HitRule top_p_flat(const Dev& d, Slots base, int n, const float (&a)[R], int* lst, RedBuf<NT>& rb, int& phase, int* sh,
                                               int tid) {
   uint32_t theta = 0;
   // The largest pattern theta with sum{a >= theta} > p lies in [lo, hi): sum{a >= lo} > p (lo = 0: not known to), and
@@ -2150,7 +2151,7 @@ __device__ __forceinline__ HitRule top_p_flat(const Dev& d, Slots base, int n, c
 template <int R, int CH, int CP, class Val, int NT = kThreads, class Hook = NoHook>
 __device__ __forceinline__ void lrfu_regs(const Dev& d, int u, Slots base, int n, int B, int t, float (&a)[R], f32x4 (&crf)[CH],
                                           i32x4 (&tau)[CH], i32x4 (&ps)[CH], Val val, bool evict, bool leave_many, uint32_t* evm, int* lst,
-                                          int lst_cap, const float* s_tab, int s_tab_n, RedBuf& rb, int& phase, int* sh,
+                                          int lst_cap, const float* s_tab, int s_tab_n, RedBuf<NT>& rb, int& phase, int* sh,
                                           int tid, Hook after_step1 = Hook{}, NewEntry ne = NewEntry{nullptr, nullptr}) {
   constexpr int C = R / 4;
   static_assert(C % CH == 0 && CP <= CH, "groups come in chunks of CH");
@@ -2281,7 +2282,7 @@ __device__ __forceinline__ void lrfu_regs(const Dev& d, int u, Slots base, int n
 template <int NT>
 __device__ __forceinline__ void unit_bookkeeping(const Dev& d, int u, Slots base, int n, int B, int t, LgView lv, const float* sM,
                                                  const float* sInv, uint32_t call_flags, float* val, uint32_t* evm, const float* s_tab,
-                                                 int s_tab_n, RedBuf& rb, int& phase, int* sh, int tid) {
+                                                 int s_tab_n, RedBuf<NT>& rb, int& phase, int* sh, int tid) {
   auto regs = [&](auto rc) {
     constexpr int R = decltype(rc)::value, C = R / 4, CH = C < 2 ? C : 2;
     float a[R];
@@ -2316,7 +2317,7 @@ __global__ __launch_bounds__(NT) void finish_kernel(Dev d, int unit_begin, uint3
   uint32_t* evm = reinterpret_cast<uint32_t*>(smem + (size_t)d.cap * 4);
   __shared__ float sM[kMaxGroup], sInv[kMaxGroup];
   __shared__ int32_t s_row[kMaxChunks];
-  __shared__ RedBuf rb;
+  __shared__ RedBuf<NT> rb;
   __shared__ int sh[4 + (NT / 64 < 4 ? 4 : NT / 64)];
   __shared__ float s_tab[kTabLds];
   const int tid = threadIdx.x;
@@ -2678,7 +2679,7 @@ constexpr int kSeedThreads = 512;      // prompts are long
 constexpr int kSeedList = 256;         // candidates among which a threshold is found by one wavefront
 
 template <int R>
-__device__ __forceinline__ void seed_rewards_regs(const Dev& d, Slots base, int n, bool last_new, float* rw, int* lst, RedBuf& rb, int& phase,
+__device__ __forceinline__ void seed_rewards_regs(const Dev& d, Slots base, int n, bool last_new, float* rw, int* lst, RedBuf<kSeedThreads>& rb, int& phase,
                                                   int* sh, int tid) {
   float a[R];
 #pragma unroll
@@ -2721,7 +2722,7 @@ template <int R>
 __global__ __launch_bounds__(kSeedThreads, R == 0 || R > 24 ? 4 : R > 16 ? 6 : 8) void seed_hits_kernel(Dev d, int unit_begin, int j0, int P, int W,
                                                                                                       float* __restrict__ srw) {
   extern __shared__ unsigned char smem[];
-  __shared__ RedBuf rb;
+  __shared__ RedBuf<kSeedThreads> rb;
   __shared__ int sh[4 + kSeedThreads / 64];
   const int tid = threadIdx.x;
   const int ql = blockIdx.x, urel = blockIdx.y, u = unit_begin + urel;
@@ -2849,7 +2850,7 @@ __global__ __launch_bounds__(kThreads) void seed_crf_kernel(Dev d, int unit_begi
 // as a bit pattern (the eviction only ever compares the bits), and the largest pattern for positions below n_sink.
 template <int R, int NT>
 __device__ __forceinline__ void evict_unit(const Dev& d, int u, Slots base, int n, int B, int n_sink, int moves_follow, const float* s_tab, int s_tab_n,
-                                           uint32_t* evm, CutBuf& cb, RedBuf& rb, int* sh, int tid) {
+                                           uint32_t* evm, CutBuf& cb, RedBuf<NT>& rb, int* sh, int tid) {
   const int t = d.t_unit[u];
   uint32_t b[R], np[R];
 #pragma unroll
@@ -2926,7 +2927,7 @@ __global__ __launch_bounds__(NT) void evict_kernel(Dev d, int unit_begin, int n_
   __shared__ int32_t s_row[kMaxChunks];
   __shared__ float s_tab[kTabLds];
   __shared__ CutBuf cb;
-  __shared__ RedBuf rb;
+  __shared__ RedBuf<NT> rb;
   __shared__ int sh[1];
   const int tid = threadIdx.x;
   const int u = unit_begin + blockIdx.x;

@@ -108,7 +108,7 @@ __global__ __launch_bounds__(64 * W, 2) void unit_kernel(Dev d, const uint16_t* 
   __shared__ __align__(16) float sM[kMaxGroup];
   __shared__ __align__(16) float sInv[kMaxGroup];
   __shared__ float s_tab[kTabLds];
-  __shared__ RedBuf rb;
+  __shared__ RedBuf<NT> rb;
   __shared__ int sh[8];
 
   const int tid = threadIdx.x, lane = tid & 63;
