@@ -2870,10 +2870,10 @@ __device__ __forceinline__ void evict_unit(const Dev& d, int u, Slots base, int 
       } else {
         const int delta = min(max(t - tau[e], 0), d.tab_last);
         const float tmp = __fmul_rn(decay_of(d, delta, s_tab, s_tab_n), crf[e]);
-        key = tmp < FLT_MIN ? 0u : __float_as_uint(tmp);
+        // a score may be any pattern, a NaN of all ones among them: an entry must not look like none
+        key = tmp < FLT_MIN ? 0u : min(__float_as_uint(tmp), 0xFFFFFFFEu);
       }
-      // (a score may be any pattern, a NaN of all ones among them: an entry never looks like none)
-      b[4 * c + e] = e0 + e < n ? min(key, 0xFFFFFFFEu) : 0xFFFFFFFFu;
+      b[4 * c + e] = e0 + e < n ? key : 0xFFFFFFFFu;
       np[4 * c + e] = ~(uint32_t)ps[e];
     }
     if (R > 16 && (c & 1)) __builtin_amdgcn_sched_barrier(0);          // two groups' state in flight: the keys need the registers
