@@ -864,7 +864,7 @@ int ckv_seed_prompt(ckv_ctx* c, int32_t layer, const void* q_obs, int32_t W, voi
     const int nq = std::min(batch, (int)W - j0), nt = (nq + kSeedGroup - 1) / kSeedGroup * G;
     const int S = seed_spans(c, P - W + j0 + nq, count);
     const dim3 sgrid((unsigned)((S + 3) / 4), (unsigned)count);
-    hipLaunchKernelGGL(seed_scan_kernel, sgrid, dim3(kThreads), (size_t)nt * 4096, s, c->dev, begin, (const uint16_t*)q_obs, j0, nq, P, (int)W, S, ml);
+    hipLaunchKernelGGL(seed_scan_kernel, sgrid, dim3(kThreads), (size_t)seed_scan_tiles(G, nq) * 4096, s, c->dev, begin, (const uint16_t*)q_obs, j0, nq, P, (int)W, S, ml);
     CKV_HIP(c, hipGetLastError());
     hipLaunchKernelGGL(seed_stats_kernel, dim3((unsigned)count), dim3(kSeedTiles * kSeedCols), 0, s, c->dev, nq, S, (const float*)ml, mi);
     CKV_HIP(c, hipGetLastError());
@@ -876,11 +876,11 @@ int ckv_seed_prompt(ckv_ctx* c, int32_t layer, const void* q_obs, int32_t W, voi
       auto hits = [&](auto kernel, size_t lds) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)nq, (unsigned)count), dim3(kSeedThreads), lds, s, c->dev, begin, j0, P, (int)W, rw);
       };
-      if (per <= 8) hits(seed_hits_kernel<8>, kSeedList * 4);
-      else if (per <= 16) hits(seed_hits_kernel<16>, kSeedList * 4);
-      else if (per <= 20) hits(seed_hits_kernel<20>, kSeedList * 4);
-      else if (per <= 24) hits(seed_hits_kernel<24>, kSeedList * 4);
-      else if (per <= 32) hits(seed_hits_kernel<32>, kSeedList * 4);
+      if (per <= 8) hits(seed_hits_kernel<8>, (kSeedList + 8) * 4);
+      else if (per <= 16) hits(seed_hits_kernel<16>, (kSeedList + 8) * 4);
+      else if (per <= 20) hits(seed_hits_kernel<20>, (kSeedList + 8) * 4);
+      else if (per <= 24) hits(seed_hits_kernel<24>, (kSeedList + 8) * 4);
+      else if (per <= 32) hits(seed_hits_kernel<32>, (kSeedList + 8) * 4);
       else hits(seed_hits_kernel<0>, c->finish_lds);
       CKV_HIP(c, hipGetLastError());
     }

@@ -1981,7 +1981,7 @@ __device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, c
 }
 
 // Step 1 over long units of flat weights (the prompt replay): the same threshold in fewer passes over the registers,
-// with a longer list at the end.  lst: kList ints of LDS; sh[5 .. 7] are used.  theta = 0: every entry is hit.
+// with a longer list at the end.  lst: kList + 8 ints of LDS, 16-byte aligned; sh[5] and sh[6] are used.  theta = 0: every entry is hit.
 template <int R, int NT, int kList>
 __device__ __forceinline__ HitRule top_p_flat(const Dev& d, Slots base, int n, const float (&a)[R], int* lst, RedBuf<NT>& rb, int& phase, int* sh,
                                               int tid) {
@@ -2061,33 +2061,41 @@ __device__ __forceinline__ HitRule top_p_flat(const Dev& d, Slots base, int n, c
           if (in) lst[r] = (int)b;
           off += __popcll(mask);
         }
+        // The list is padded with zeros, which add nothing, to be read four at a time.
+        if (tid < 8) lst[m + tid] = 0;
         block_sync<NT>(rb);
+        // The largest pattern theta with sum{a >= theta} > p is a candidate's own pattern: the largest one whose sum of
+        // candidates at least as large, on top of what lies above the bracket, exceeds p.  A candidate per
+        // thread (by one wavefront, four per lane, the walk over a full list took 4 us of a row that is on its own),
+        // the others read from LDS, the next four asked for ahead.
+        static_assert(kList <= NT, "a candidate per thread");
+        uint32_t th = 0u;
+        if (64 * wave < m) {
+          const uint32_t bj = tid < m ? (uint32_t)lst[tid] : 0u;
+          float sj = 0.f;
+          u32x4 four = *reinterpret_cast<const u32x4*>(lst);
+          for (int k = 0; k < m; k += 4) {                  // candidates in list order
+            const u32x4 ahead = *reinterpret_cast<const u32x4*>(lst + k + 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sj += (four[e] >= bj) ? __uint_as_float(four[e]) : 0.f;
+            four = ahead;
+          }
+          th = (tid < m && above_bucket + sj > d.top_p) ? bj : 0u;
+        }
+        th = ~wave_min_u32(~th);
+        if (lane == 0) rb.v[phase][wave] = (u64)th;
+        block_sync<NT>(rb);
+#pragma unroll
+        for (int ww = 0; ww < NT / 64; ++ww) th = max(th, (uint32_t)rb.v[phase][ww]);
+        phase ^= 1;
+        if (th != 0u) theta = th;
         if (wave == 0) {
-          // The largest pattern theta with sum{a >= theta} > p is a candidate's own pattern: the largest one whose sum
-          // of candidates at least as large, on top of what lies above the bracket, exceeds p.  Every entry
-          // equal to theta is in the list too, so the number of such ties and the weight above theta are
+          // Every entry equal to theta is in the list too, so the number of such ties and the weight above theta are
           // known here as well, without two more reductions over all entries.
-          // kList / 64 candidates per lane (candidate lane + 64 c), the others read from LDS
-          constexpr int kC = kList / 64;
+          constexpr int kC = kList / 64;                    // kList / 64 candidates per lane (candidate lane + 64 c)
           uint32_t bj[kC];
-          float sj[kC];
 #pragma unroll
-          for (int c = 0; c < kC; ++c) {
-            bj[c] = lane + 64 * c < m ? (uint32_t)lst[lane + 64 * c] : 0u;
-            sj[c] = 0.f;
-          }
-          for (int k = 0; k < m; ++k) {                     // candidates in list order
-            const uint32_t bk = (uint32_t)lst[k];
-            const float ak = __uint_as_float(bk);
-#pragma unroll
-            for (int c = 0; c < kC; ++c) sj[c] += (bk >= bj[c]) ? ak : 0.f;
-          }
-          uint32_t th = 0u;
-#pragma unroll
-          for (int c = 0; c < kC; ++c) th = max(th, (lane + 64 * c < m && above_bucket + sj[c] > d.top_p) ? bj[c] : 0u);
-#pragma unroll
-          for (int o = 32; o > 0; o >>= 1) th = max(th, (uint32_t)__shfl_xor((int)th, o));
-          if (th != 0u) theta = th;
+          for (int c = 0; c < kC; ++c) bj[c] = lane + 64 * c < m ? (uint32_t)lst[lane + 64 * c] : 0u;
           int n_ties = 0;
           float mine_above = 0.f;
 #pragma unroll
@@ -2098,13 +2106,11 @@ __device__ __forceinline__ HitRule top_p_flat(const Dev& d, Slots base, int n, c
           }
           const float above_l = above_bucket + wave_sum_f32(mine_above);
           if (lane == 0) {
-            sh[7] = (int)theta;
             sh[5] = n_ties;
             sh[6] = __float_as_int(above_l);
           }
         }
         block_sync<NT>(rb);
-        theta = (uint32_t)sh[7];
         list_ties = sh[5];
         list_above = __int_as_float(sh[6]);
         break;
@@ -2369,17 +2375,21 @@ __global__ __launch_bounds__(NT) void finish_kernel(Dev d, int unit_begin, uint3
 // memory, 4 G B per entry and query written and read back.)  Only the weights are wanted (no output), so V is
 // never read.
 //
-// Columns: the matrix-core tile has 16 query columns.  Sixteen queries (a group) fill G tiles, column c of tile k
+// Columns: the matrix-core tile has 16 query columns.  In the first pass, to which heads are all alike, column c of tile k is
+// head i % G of query i / G, i = 16 k + c: ceil(G queries / 16) tiles.  In the second pass sixteen queries (a group) fill G
+// tiles, column c of tile k
 //   k < 4 (G / 4):  head 4 (k / 4) + c % 4 of the group's query 4 (k % 4) + c / 4
 //   else:           head k of the group's query 4 (c % 4) + c / 4
 // so that with the queries as the product's rows (the second pass) lane (j, kg) holds, of entry j, four heads of one
 // query, or one head of the four queries whose other heads it also holds: the sum over a query's heads, in head
-// order, never leaves the lane.  (With the heads of 16 / G queries side by side in a tile, the sum took G - 1 lane
+// order, never leaves the lane; the tiles of four heads that hold no query of a short group are left out.  (The second
+// pass's columns in the first one too: a single query on G = 8 heads is 8 tiles instead of 1, of which the leftover heads' stay
+// even if tiles without queries are skipped.  With the heads of 16 / G queries side by side in a tile, the sum took G - 1 lane
 // shifts per logit, of which one lane in G was used, and a G that does not divide 16 left columns empty.)
 // Both passes share a unit's blocks out over S wavefronts, as many as fill the chip evenly: with a wavefront per chunk of
 // 256 entries, 128 units of 9350 entries were 1280 workgroups on 768 places.  Measured on that shape, 32 queries,
 // G = 5: first pass 116 -> 85 us, second pass 172 -> 98 us.
-// Buffers of a batch of nt = G groups tiles, nq queries, for the UL units of a layer:
+// Buffers of a batch of nq queries for the UL units of a layer (tiles and columns as in the first pass):
 //   sml [tile][unit][span][column][2]     maximum (rounded up) and sum of the softmax over a wavefront's blocks
 //   smi [tile][unit][column][2]           maximum (rounded up) and 1 / sum over all the entries the column's query sees
 //   srw [query][unit][cap]                mean weights, then hits (a bit per entry at the start of the row)
@@ -2399,7 +2409,16 @@ __device__ __forceinline__ float seed_exp(float logit, float scale, float max) {
   return fast_exp2(__builtin_fmaf(logit, scale, -max));
 }
 
-// Query (of the batch) and head of column c of tile tl.
+// Tiles of the first pass.
+__host__ __device__ __forceinline__ int seed_scan_tiles(int G, int nq) { return (nq * G + kSeedCols - 1) / kSeedCols; }
+
+// Query (of the batch) and head of column c of tile tl: first pass (of any tile's columns those beyond the batch have queries
+// from nq on), second pass.
+__device__ __forceinline__ int seed_scan_column(int G, int tl, int c, int& head) {
+  const int i = kSeedCols * tl + c, q = i / G;
+  head = i - q * G;
+  return q;
+}
 __device__ __forceinline__ int seed_column(int G, int tl, int c, int& head) {
   const int group = tl / G, k = tl - group * G;
   const bool four = k < (G & ~3);
@@ -2408,11 +2427,12 @@ __device__ __forceinline__ int seed_column(int G, int tl, int c, int& head) {
 }
 
 // The batch's queries as operands in LDS ([tile][32-dim slice][lane], 16 bytes each); 0 in columns without a query.
-__device__ __forceinline__ void seed_stage_queries(const Dev& d, const uint16_t* q_obs, int urel, int j0, int nq, int nt, u32x4* s_q) {
+template <class Column>
+__device__ __forceinline__ void seed_stage_queries(const Dev& d, const uint16_t* q_obs, int urel, int j0, int nq, int nt, Column column, u32x4* s_q) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, b = urel / d.Hkv, h = urel % d.Hkv;
   for (int tl = 0; tl < nt; ++tl) {
     int head;
-    const int qi = seed_column(d.G, tl, lane & 15, head);
+    const int qi = column(d.G, tl, lane & 15, head);
     u32x4 x = {0u, 0u, 0u, 0u};
     if (qi < nq)
       x = *reinterpret_cast<const u32x4*>(q_obs + ((((size_t)(j0 + qi) * d.Bz + b) * d.Hq) + (size_t)h * d.G + head) * kDim + 32 * wave + 8 * (lane >> 4));
@@ -2445,20 +2465,15 @@ __global__ __launch_bounds__(kThreads) void seed_scan_kernel(Dev d, int unit_beg
   const int slot = __builtin_amdgcn_readfirstlane(blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6));
   const int urel = blockIdx.y, u = unit_begin + urel, UL = gridDim.y;
   const int j = lane & 15, kg = lane >> 4;
-  const int G = d.G, nt = (nq + kSeedGroup - 1) / kSeedGroup * G;
+  const int G = d.G, nt = seed_scan_tiles(G, nq);
   const int n_first = P - W + j0 + 1;                     // entries the batch's first query sees
-  seed_stage_queries(d, q_obs, urel, j0, nq, nt, s_q);
+  seed_stage_queries(d, q_obs, urel, j0, nq, nt, seed_scan_column, s_q);
   __syncthreads();
   if (slot >= S) return;
   SeedSpan sp(d, u, slot, S, n_first + nq - 1);
-  int q_lo[kSeedTiles];                                   // the tile's first query; its last is 3 (four heads each) or 15 later
+  int q_lo[kSeedTiles + 1];                               // the tiles' first queries
 #pragma unroll
-  for (int tl = 0; tl < kSeedTiles; ++tl) {
-    int head;
-    q_lo[tl] = seed_column(G, tl, 0, head);
-  }
-  const int rem = G & 3;                                  // a group's last G % 4 tiles hold one head of 16 queries
-  const int q4 = j >> 2, q1 = 4 * (j & 3) + (j >> 2);
+  for (int tl = 0; tl <= kSeedTiles; ++tl) q_lo[tl] = kSeedCols * tl / G;
   float m_run[kSeedTiles], l_run[kSeedTiles];             // of this lane's entries; the four lanes of a column meet at the end
 #pragma unroll
   for (int tl = 0; tl < kSeedTiles; ++tl) {
@@ -2473,12 +2488,9 @@ __global__ __launch_bounds__(kThreads) void seed_scan_kernel(Dev d, int unit_beg
     for (int blk = sp.b; blk < sp.b1; ++blk) {
       load_k(kn, kp + sp.off(min(blk + 1, sp.b1 - 1)));
       const int e0 = blk * kBlk + 4 * kg;
-      int k = 0;                                            // tile within its group
 #pragma unroll
       for (int tl = 0; tl < kSeedTiles; ++tl) {
-        const bool four = k < G - rem;
-        k = k + 1 == G ? 0 : k + 1;
-        if (tl < nt && blk * kBlk < n_first + min(q_lo[tl] + (four ? 3 : 15), nq - 1)) {     // uniform: else no query of the tile sees the block
+        if (tl < nt && blk * kBlk < n_first + min(q_lo[tl + 1], nq - 1)) {     // uniform: else no query of the tile sees the block
           bf16x8 qv[4];
 #pragma unroll
           for (int s4 = 0; s4 < 4; ++s4) qv[s4] = as_bf16x8(s_q[(tl * 4 + s4) * 64 + lane]);
@@ -2494,7 +2506,7 @@ __global__ __launch_bounds__(kThreads) void seed_scan_kernel(Dev d, int unit_beg
             sv[4 + v] = s1[v];
           }
           if ((blk + 1) * kBlk > n_first + q_lo[tl]) {      // a block that the tile's first query sees whole needs no mask
-            const int lim = n_first + q_lo[tl] + (four ? q4 : q1);       // entries this column's query sees
+            const int lim = n_first + (kSeedCols * tl + j) / G;            // entries this column's query sees
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
               sv[v] = (e0 + v < lim) ? sv[v] : -INFINITY;
@@ -2547,7 +2559,7 @@ __global__ __launch_bounds__(kSeedTiles * kSeedCols) void seed_stats_kernel(Dev 
                                                                             float* __restrict__ smi) {
   const int urel = blockIdx.x, UL = gridDim.x;
   const int tl = threadIdx.x / kSeedCols, col = threadIdx.x % kSeedCols;
-  if (tl >= (nq + kSeedGroup - 1) / kSeedGroup * d.G) return;
+  if (tl >= seed_scan_tiles(d.G, nq)) return;
   const float* ml = sml + ((((size_t)tl * UL + urel) * S) * kSeedCols + col) * 2;
   // eight spans' partials are asked for at a time; maxima, then sums
   float M = kNoMax;
@@ -2592,11 +2604,14 @@ __global__ __launch_bounds__(kThreads) void seed_weights_kernel(Dev d, int unit_
   const int n_first = P - W + j0 + 1;
   const float invG = 1.0f / (float)G;
   if ((int)threadIdx.x < nt * kSeedCols) {
-    const float2 mi = *reinterpret_cast<const float2*>(smi + (((size_t)(threadIdx.x / kSeedCols) * UL + urel) * kSeedCols + threadIdx.x % kSeedCols) * 2);
+    int head;
+    const int i = seed_column(G, threadIdx.x / kSeedCols, threadIdx.x % kSeedCols, head) * G + head;         // the column's place in the first pass
+    float2 mi = make_float2(0.f, 0.f);
+    if (i < nq * G) mi = *reinterpret_cast<const float2*>(smi + (((size_t)(i / kSeedCols) * UL + urel) * kSeedCols + i % kSeedCols) * 2);
     s_M[threadIdx.x] = mi.x;
     s_I[threadIdx.x] = mi.y * invG;
   }
-  seed_stage_queries(d, q_obs, urel, j0, nq, nt, s_q);
+  seed_stage_queries(d, q_obs, urel, j0, nq, nt, seed_column, s_q);
   __syncthreads();
   if (slot >= S) return;
   SeedSpan sp(d, u, slot, S, n_first + nq - 1);
@@ -2632,6 +2647,7 @@ __global__ __launch_bounds__(kThreads) void seed_weights_kernel(Dev d, int unit_
         for (int h = 0; h + 4 <= G; h += 4) {
 #pragma unroll
           for (int t = 0; t < 4; ++t) {
+            if (q0 + 4 * t >= nq) continue;               // uniform: a tile without queries
             tile(gr * G + h + t);
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
@@ -2674,7 +2690,7 @@ __global__ __launch_bounds__(kThreads) void seed_weights_kernel(Dev d, int unit_
 // from // `srw`, the hit rule, and in their place the hits, a bit per entry at the start of the row (the query's own entry,
 // the last it sees, is always hit): every thread has its weights in registers (or LDS) before the first bit is written.
 // (As rewards of 4 bytes they were 153 MB per layer of 128 units of 9350 entries and 32 queries, written and read.)
-// grid: (queries of the batch, units of the layer), kSeedThreads threads, kSeedList ints of dynamic LDS (R = 0: cap floats).
+// grid: (queries of the batch, units of the layer), kSeedThreads threads, kSeedList + 8 ints of dynamic LDS (R = 0: cap floats).
 constexpr int kSeedThreads = 512;      // prompts are long
 constexpr int kSeedList = 256;         // candidates among which a threshold is found by one wavefront
 

@@ -36,7 +36,17 @@ def _context(L, batch, hkv, G, P, W, weighted, shape_qk=None):
 @pytest.mark.parametrize("L", [1, 24])                        # one group of queries at a time, and several
 @pytest.mark.parametrize("G", [1, 2, 3, 4, 5, 6, 7, 8])
 def test_weights_of_every_group_size(G, L):
-    P, W = 395, 37
+    _check_weights(L, G, 395, 37)
+
+
+@pytest.mark.parametrize("W", [1, 2, 5, 18])
+@pytest.mark.parametrize("G", [1, 2, 3, 4, 5, 6, 7, 8])
+def test_weights_of_few_queries(G, W):
+    """Batches that leave tiles of the second pass without queries, and columns of the first."""
+    _check_weights(24, G, 130, W)
+
+
+def _check_weights(L, G, P, W):
     torch, crf, tau, weights = _context(L, 2, 3, G, P, W, True)
     pos = torch.arange(P, device=crf.device)
     want, last = (pos < P - W).double().expand_as(crf).clone(), pos.clone()
