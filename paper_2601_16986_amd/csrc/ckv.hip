@@ -876,12 +876,20 @@ int ckv_seed_prompt(ckv_ctx* c, int32_t layer, const void* q_obs, int32_t W, voi
       auto hits = [&](auto kernel, size_t lds) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)nq, (unsigned)count), dim3(kSeedThreads), lds, s, c->dev, begin, j0, P, (int)W, rw);
       };
-      if (per <= 8) hits(seed_hits_kernel<8>, (kSeedList + 8) * 4);
-      else if (per <= 16) hits(seed_hits_kernel<16>, (kSeedList + 8) * 4);
-      else if (per <= 20) hits(seed_hits_kernel<20>, (kSeedList + 8) * 4);
-      else if (per <= 24) hits(seed_hits_kernel<24>, (kSeedList + 8) * 4);
-      else if (per <= 32) hits(seed_hits_kernel<32>, (kSeedList + 8) * 4);
-      else hits(seed_hits_kernel<0>, c->finish_lds);
+      // The fewest registers that hold the row, in steps of four (one step more than needed costs the whole call 2-3 % at 32
+      // queries: 6100 entries 181 us with 12, 185 with 16; 9350 entries 247 with 20, 252 with 24; 12000 entries 290 with 24,
+      // 298 with 28; in LDS instead of 32 registers, 16384 entries, 562 against 355).
+      constexpr size_t list = (kSeedList + 8) * 4;
+      switch ((per + 3) / 4) {
+        case 0: case 1: case 2: hits(seed_hits_kernel<8>, list); break;
+        case 3: hits(seed_hits_kernel<12>, list); break;
+        case 4: hits(seed_hits_kernel<16>, list); break;
+        case 5: hits(seed_hits_kernel<20>, list); break;
+        case 6: hits(seed_hits_kernel<24>, list); break;
+        case 7: hits(seed_hits_kernel<28>, list); break;
+        case 8: hits(seed_hits_kernel<32>, list); break;
+        default: hits(seed_hits_kernel<0>, c->finish_lds);
+      }
       CKV_HIP(c, hipGetLastError());
     }
     const dim3 cgrid((unsigned)((P + 4 * kThreads - 1) / (4 * kThreads)), (unsigned)count);

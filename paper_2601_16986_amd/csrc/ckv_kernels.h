@@ -2732,8 +2732,9 @@ __device__ __forceinline__ void seed_rewards_regs(const Dev& d, Slots base, int 
   }
 }
 
-// R: entries per thread, in registers, chosen by the longest row of the launch, so that short rows do not pay for the
-// registers of long ones (20 of them: three workgroups per compute unit instead of two); 0: weights in LDS, any length.
+// R: entries per thread, in registers, chosen by the longest row of the launch (a multiple of four), so that short rows do not
+// pay for the registers of long ones: up to 16 four workgroups per compute unit, up to 24 three, up to 32 two; 0: weights in
+// LDS, any length.
 template <int R>
 __global__ __launch_bounds__(kSeedThreads, R == 0 || R > 24 ? 4 : R > 16 ? 6 : 8) void seed_hits_kernel(Dev d, int unit_begin, int j0, int P, int W,
                                                                                                       float* __restrict__ srw) {

@@ -59,7 +59,7 @@ def _check_weights(L, G, P, W):
     assert torch.equal(tau, last.expand_as(tau))
 
 
-@pytest.mark.parametrize("P", [33, 4096, 4097, 8192, 8193, 10240, 10241, 12288, 12289, 16384, 16385])
+@pytest.mark.parametrize("P", [33, 4096, 4097, 6144, 6145, 8192, 8193, 10240, 10241, 12288, 12289, 14336, 14337, 16384, 16385])
 def test_hits_of_every_row_length(P):
     torch, crf, tau, weights = _context(1, 2, 2, 5, P, 1, False)
     a = weights[0]
