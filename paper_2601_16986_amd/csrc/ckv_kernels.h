@@ -41,6 +41,8 @@ typedef unsigned long long u64;
 enum { SC_T = 0, SC_WINDOW_STEPS = 1, SC_DONE = 2, SC_STATUS = 3, SC_DONE_RB = 4, SC_QUEUE = 5, SC_SPARE = 6, SC_COUNT = 64 };
 enum { FLAG_HIT = 1, FLAG_SLIP = 2 };
 constexpr uint32_t kLeaveMany = 8u;       // a step's call flag: evictions of several entries from a unit are left to the evict_kernel that follows
+// whether a step leaves a unit of so many entries above its budget to that kernel, which is faster at it
+__device__ __forceinline__ bool leaves_unit(uint32_t call_flags, int excess) { return (call_flags & kLeaveMany) && excess > 1; }
 constexpr int kThreads = 256;
 constexpr int kWideThreads = 1024;        // kernels with one workgroup per unit and few units
 constexpr int kMaxChunks = 128;           // cap <= 32768
@@ -2151,12 +2153,11 @@ __device__ __forceinline__ HitRule top_p_flat(const Dev& d, Slots base, int n, c
   return tie_rule<R, NT>(d, base, n, a, theta, above, ties, -1, rb, phase, tid);
 }
 
-// leave_many: a unit that has to give up several entries keeps them; evict_kernel follows and is faster at it.
 // `after_step1` runs once between Step 1 and the score update (the fused kernel
 // picks up its queue claim there).
 template <int R, int CH, int CP, class Val, int NT = kThreads, class Hook = NoHook>
 __device__ __forceinline__ void lrfu_regs(const Dev& d, int u, Slots base, int n, int B, int t, float (&a)[R], f32x4 (&crf)[CH],
-                                          i32x4 (&tau)[CH], i32x4 (&ps)[CH], Val val, bool evict, bool leave_many, uint32_t* evm, int* lst,
+                                          i32x4 (&tau)[CH], i32x4 (&ps)[CH], Val val, bool evict, uint32_t* evm, int* lst,
                                           int lst_cap, const float* s_tab, int s_tab_n, RedBuf<NT>& rb, int& phase, int* sh,
                                           int tid, Hook after_step1 = Hook{}, NewEntry ne = NewEntry{nullptr, nullptr}) {
   constexpr int C = R / 4;
@@ -2253,7 +2254,7 @@ __device__ __forceinline__ void lrfu_regs(const Dev& d, int u, Slots base, int n
     d.t_unit[u] = t;
   }
   // ---- Step 4
-  if (!(evict && n > B) || (leave_many && n - B > 1)) {
+  if (!(evict && n > B)) {
     if (tid == 0) d.nev[u] = 0;
     return;
   }
@@ -2295,7 +2296,7 @@ __device__ __forceinline__ void unit_bookkeeping(const Dev& d, int u, Slots base
     mean_weights_regs<R, NT>(d, lv, n, sM, sInv, a, tid);
     f32x4 crf[CH];
     i32x4 tau[CH], ps[CH];
-    lrfu_regs<R, CH, 0, ValLinear, NT>(d, u, base, n, B, t, a, crf, tau, ps, ValLinear{val}, (call_flags & 1u) != 0, (call_flags & kLeaveMany) != 0, evm,
+    lrfu_regs<R, CH, 0, ValLinear, NT>(d, u, base, n, B, t, a, crf, tau, ps, ValLinear{val}, (call_flags & 1u) != 0 && !leaves_unit(call_flags, n - B), evm,
                                        reinterpret_cast<int*>(val), d.cap, s_tab, s_tab_n, rb, phase, sh, tid);
   };
   if (n <= 4 * NT) {

@@ -185,7 +185,7 @@ __global__ __launch_bounds__(64 * W, 2) void unit_kernel(Dev d, const uint16_t* 
     load_v(va, d.V + o);
     load_q(u);
   }
-  const bool evict = (call_flags & 1u) != 0, leave_many = (call_flags & kLeaveMany) != 0;
+  const bool evict = (call_flags & 1u) != 0;
 
   __syncthreads();                                 // the first unit's table row is in place
   while (u >= 0) {
@@ -451,8 +451,8 @@ __global__ __launch_bounds__(64 * W, 2) void unit_kernel(Dev d, const uint16_t* 
       auto publish = [&]() {
         if (ftid == 0) s_claim = 3 * grid + claimed;
       };
-      lrfu_regs<R, CH, CH, ValFused, NT>(d, u, base, n, B, t, a, crf, tau, ps, val, evict, leave_many, evm, reinterpret_cast<int*>(smem),
-                                         lds_main / 4, s_tab, s_tab_n, rb, phase, sh, ftid, publish, ne);
+      lrfu_regs<R, CH, CH, ValFused, NT>(d, u, base, n, B, t, a, crf, tau, ps, val, evict && !leaves_unit(call_flags, n - B), evm,
+                                         reinterpret_cast<int*>(smem), lds_main / 4, s_tab, s_tab_n, rb, phase, sh, ftid, publish, ne);
     };
     if (call_flags & 2u) {               // attention only: no bookkeeping, just keep the stream and the queue going
       request_next();
@@ -479,7 +479,7 @@ __global__ __launch_bounds__(64 * W, 2) void unit_kernel(Dev d, const uint16_t* 
         d.window[u] += sfix;
         d.t_unit[u] = t;
       }
-      if (evict && n > B && !(leave_many && n - B > 1))
+      if (evict && n > B && !leaves_unit(call_flags, n - B))
         evict_phase<ValFused, NT>(d, u, base, n, B, val, evm, reinterpret_cast<int*>(smem), lds_main / 4, rb, phase, sh, ftid);
       else if (ftid == 0)
         d.nev[u] = 0;
