@@ -42,7 +42,6 @@ struct ckv_ctx {
   int next_layer = 0;
   int n_cu = 256;
   float* seedmi = nullptr;      // workspace of the prompt replay
-  float* seedml = nullptr;
   float* seedrw = nullptr;
   int device = 0;               // the HIP device the context was created on
   size_t finish_lds = 0;
@@ -158,7 +157,7 @@ std::vector<float> make_decay_table(float lambda) {
 }
 
 struct Carve {
-  size_t n, budget, t_unit, nev, window, sc, tab, partial, ml, logits, btotal, order, layer_ts, arrive, msum, tbl, owned, spare, seedml, seedmi, seedrw, total;
+  size_t n, budget, t_unit, nev, window, sc, tab, partial, ml, logits, btotal, order, layer_ts, arrive, msum, tbl, owned, spare, seedmi, seedrw, total;
 };
 
 Carve carve(const ckv_layout* l, size_t tab_len) {
@@ -187,11 +186,10 @@ Carve carve(const ckv_layout* l, size_t tab_len) {
   c.owned = take(U * 4);
   c.spare = take((size_t)(l->pool_slots / kSeg) * 4);
   // prompt replay (ckv_seed_prompt), one layer at a time: softmax maximum and 1 / sum per query column of a
-  // batch; and, for contexts whose decode workspace is too small to lend the replay room for several groups of
-  // queries, one group's softmax partials (per block at most) and the weights (then hits) of its 16 queries
+  // batch; and, for contexts whose logits are too small to lend the replay room for several groups of queries, the
+  // weights (then hits) of one group's 16 queries
   const size_t UL = (size_t)l->batch * l->n_kv_heads;
   c.seedmi = take((size_t)kSeedTiles * UL * kSeedCols * 2 * 4);
-  c.seedml = take(UL * mc * kSegBlocks * G * kSeedCols * 2 * 4);
   c.seedrw = take(UL * (size_t)l->cap * kSeedCols * 4);
   c.total = off;
   return c;
@@ -410,9 +408,11 @@ int launch_probe(ckv_ctx* c, const Dev& d, int begin, int count, const uint16_t*
 // most one per block.  Three workgroups fit on a compute unit; of the splits that the partials have room for, the one
 // that leaves the least of the chip idle (places in the last round, and the unit's blocks not dividing evenly),
 // the coarsest of equals.
+// Room: a group of 16 queries takes 32 G floats per wavefront and unit, the decode partials hold 128 G per chunk of 256
+// entries, unit and layer: four wavefronts per chunk and layer for one group (a batch has at most one per two layers).
 int seed_spans(const ckv_ctx* c, int entries, int count) {
   const long long blocks = (entries + kBlk - 1) / kBlk, places = 3ll * c->n_cu;
-  const long long most = std::min<long long>((blocks + 3) / 4 * 4, (long long)kSegBlocks * c->dev.max_chunks);
+  const long long most = std::min<long long>((blocks + 3) / 4 * 4, (long long)std::min(kSegBlocks, 4 * c->lay.n_layers) * c->dev.max_chunks);
   int best = 4;
   double best_eff = 0.0;
   for (long long S = 4; S <= most; S += 4) {
@@ -612,7 +612,6 @@ int ckv_init(ckv_ctx** out, const ckv_layout* layout, const int32_t* budgets, co
   d.spare = (int32_t*)(ws + cv.spare);
   d.max_seg = (int32_t)((layout->cap + kSeg - 1) / kSeg);
   c->seedmi = (float*)(ws + cv.seedmi);
-  c->seedml = (float*)(ws + cv.seedml);
   c->seedrw = (float*)(ws + cv.seedrw);
 
   auto bail = [&](int rc) {
@@ -846,17 +845,16 @@ int ckv_seed_prompt(ckv_ctx* c, int32_t layer, const void* q_obs, int32_t W, voi
   const int begin = layer * c->units_per_layer, count = c->units_per_layer;
   // Groups of 16 queries fill G tiles of 16 columns each.  Per batch of groups: a pass over the keys for the softmax
   // partials of all its queries, their maxima and sums, a second pass for the mean weights, the hits (top-p rule),
-  // the score recurrence.  The batch's weights and softmax partials live in the decode paths' logits (a row of cap
-  // floats per unit and query: G rows of every unit) and partials (idle here, rewritten by the next scan before anything
-  // reads them) when those hold at least two groups, else in the replay's own buffers for one.
+  // the score recurrence.  The batch's softmax partials live in the decode paths' partials, its weights in their logits (a row
+  // of cap floats per unit and query: G rows of every unit) when those hold at least two groups, else in the replay's own
+  // buffer for one (partials and logits are idle here and rewritten by the next scan before anything reads them).
   const int G = c->dev.G;
   const int fit = std::min(c->lay.n_layers * G / kSeedGroup, kSeedTiles / G);
-  float *ml = c->seedml, *rw = c->seedrw, *mi = c->seedmi;
+  float *ml = c->dev.partial, *rw = c->seedrw, *mi = c->seedmi;
   int groups = 1;
   if (fit >= 2) {
     groups = fit;
     rw = c->dev.logits;
-    ml = c->dev.partial;
   }
   const int batch = groups * kSeedGroup;
   const bool topp = c->par.reward_mode == CKV_REWARD_TOPP_HIT;

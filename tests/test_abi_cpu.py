@@ -97,3 +97,15 @@ def test_workloads_are_seeded_and_budgets_conserved():
     # bf16 rounding: ties to even
     x = np.array([1.0 + 2.0 ** -8, 1.0 + 3 * 2.0 ** -8, 1.0 + 2.0 ** -9], dtype=np.float32)
     assert wl.bf16_round(x).tolist() == [1.0, 1.015625, 1.0]
+
+
+@pytest.mark.parametrize("geometry,enough", [
+    ((48, 16, 40, 8, 8224), 1644152320), ((32, 64, 32, 8, 1056), 537724416), ((4, 1, 28, 4, 800), 17648128), ((16, 8, 40, 8, 9376), 349824256),
+    ((1, 1, 64, 8, 32768), 46412288), ((1, 32, 64, 8, 32768), 964996352), ((2, 16, 40, 8, 8224), 149918976), ((1, 1, 8, 2, 160), 16819968),
+])
+def test_workspace_does_not_outgrow_what_callers_hold(geometry, enough):
+    """(layers, batch, query heads, KV heads, capacity): a workspace of so many bytes has been enough and stays enough."""
+    layers, batch, hq, hkv, cap = geometry
+    lay = ckv.Layout(layers, batch, hq, hkv, 128, cap, ckv.F32, 1, 1 << 30)
+    par = ckv.LrfuParams(0.5, 0.9, 0.088, 0, 1000, 1, cap - 1)
+    assert 0 < ckv.load().ckv_workspace_bytes(C.byref(lay), C.byref(par)) <= enough
