@@ -864,7 +864,7 @@ int ckv_seed_prompt(ckv_ctx* c, int32_t layer, const void* q_obs, int32_t W, voi
     const dim3 sgrid((unsigned)((S + 3) / 4), (unsigned)count);
     hipLaunchKernelGGL(seed_scan_kernel, sgrid, dim3(kThreads), (size_t)seed_scan_tiles(G, nq) * 4096, s, c->dev, begin, (const uint16_t*)q_obs, j0, nq, P, (int)W, S, ml);
     CKV_HIP(c, hipGetLastError());
-    hipLaunchKernelGGL(seed_stats_kernel, dim3((unsigned)count), dim3(kSeedTiles * kSeedCols), 0, s, c->dev, nq, S, (const float*)ml, mi);
+    hipLaunchKernelGGL(seed_stats_kernel, dim3((unsigned)count, (unsigned)seed_scan_tiles(G, nq)), dim3(8 * kSeedCols), 0, s, S, (const float*)ml, mi);
     CKV_HIP(c, hipGetLastError());
     hipLaunchKernelGGL(seed_weights_kernel, sgrid, dim3(kThreads), (size_t)nt * 4096, s, c->dev, begin, (const uint16_t*)q_obs, j0, nq, P, (int)W, S,
                        (const float*)mi, rw);
