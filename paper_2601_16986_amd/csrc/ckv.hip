@@ -264,27 +264,42 @@ void give_stream(int devid, hipStream_t s) {
 // Eviction of `count` units from `begin` on: select, then move.  A unit's keys sit in the registers of one workgroup:
 // 1024 threads, or 256 where four entries per thread are enough for every unit, or 32 are and there are enough units to
 // fill the chip with small workgroups anyway.
-// The moves' kernel is left out (4 us, 8 with thousands of workgroups) where no unit should hold more than one entry above
-// its budget: `excess` counts what the host has seen.  (Inside a graph it stays: the replays' state is not the host's.)
+// The moves have a kernel of their own where it would have at least four workgroups per unit (up to four units per compute
+// unit; a unit's own workgroup is as fast then: 4096 units of 1000 entries, window policy, 40 evicted each, 198 us with a
+// second kernel, 157 without) and where a unit may have more to move than its workgroup moves in two rounds: `excess` counts
+// what the host has seen (64 units of 9000 entries, 2 / 40 / 150 evicted, one kernel 41 / 51 / 65 us, two 45 / 53 / 57).  Inside a
+// graph the replays' state is not the host's, so there it runs.
 int launch_evict(ckv_ctx* c, hipStream_t s, int begin, int count, int n_sink, int after_step = 0) {
   hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
   CKV_HIP(c, hipStreamIsCapturing(s, &capturing));
+  const int cap = c->lay.cap;
+  const bool small = cap <= 4 * kThreads || (cap <= 32 * kThreads && count >= 4 * c->n_cu);
+  const int threads = small ? kThreads : kWideThreads, per_round = 4 * threads / 64;
   bool moves = after_step || capturing != hipStreamCaptureStatusNone;
   for (int l = begin / c->units_per_layer; l < (begin + count) / c->units_per_layer; ++l) {
-    moves = moves || c->excess[l] > 1;
+    moves = moves || c->excess[l] > 2 * per_round;
     c->excess[l] = 0;
   }
-  if (c->lay.cap <= 4 * kThreads)
-    hipLaunchKernelGGL((evict_kernel<kThreads, true>), dim3((unsigned)count), dim3(kThreads), 0, s, c->dev, begin, n_sink, after_step, moves ? 1 : 0);
-  else if (c->lay.cap <= 32 * kThreads && count >= 4 * c->n_cu)
-    hipLaunchKernelGGL(evict_kernel<kThreads>, dim3((unsigned)count), dim3(kThreads), 0, s, c->dev, begin, n_sink, after_step, moves ? 1 : 0);
-  else
-    hipLaunchKernelGGL(evict_kernel<kWideThreads>, dim3((unsigned)count), dim3(kWideThreads), 0, s, c->dev, begin, n_sink, after_step, moves ? 1 : 0);
+  moves = moves && count <= 4 * c->n_cu;
+  auto select = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)count), dim3((unsigned)threads), 0, s, c->dev, begin, n_sink, after_step, moves ? 1 : 0);
+  };
+  const int per = (cap + threads - 1) / threads;
+  if (small) {
+    if (per <= 4) select(evict_kernel<kThreads, 4>);
+    else if (per <= 8) select(evict_kernel<kThreads, 8>);
+    else if (per <= 16) select(evict_kernel<kThreads, 16>);
+    else select(evict_kernel<kThreads, 32>);
+  } else {
+    if (per <= 4) select(evict_kernel<kWideThreads, 4>);
+    else if (per <= 8) select(evict_kernel<kWideThreads, 8>);
+    else if (per <= 16) select(evict_kernel<kWideThreads, 16>);
+    else select(evict_kernel<kWideThreads, 32>);
+  }
   CKV_HIP(c, hipGetLastError());
   if (!moves) return CKV_OK;
-  const int x = std::min(count, 4 * c->n_cu);
-  const int y = std::max(1, std::min({16 * c->n_cu / count, (c->lay.cap / 2 + 15) / 16, 64}));
-  hipLaunchKernelGGL(evict_move_kernel, dim3((unsigned)x, (unsigned)y), dim3(kThreads), 0, s, c->dev, begin, count);
+  const int y = std::max(1, std::min({16 * c->n_cu / count, (cap / 2 + 15) / 16, 64}));
+  hipLaunchKernelGGL(evict_move_kernel, dim3((unsigned)count, (unsigned)y), dim3(kThreads), 0, s, c->dev, begin);
   CKV_HIP(c, hipGetLastError());
   return CKV_OK;
 }

@@ -1537,14 +1537,13 @@ __device__ __forceinline__ int evict_lists(const Dev& d, int u, Slots base, int 
 // lines with them, about 370 MB for 64 units of 9350 entries cut to 2048 in 79 us.  (Destination blocks put together in LDS
 // and stored whole, instead of a row's 48 partial lines: 85 us.)
 // Units along x, so that a unit's workgroups share an XCD's cache when their number is a multiple of eight.
-__global__ __launch_bounds__(kThreads) void evict_move_kernel(Dev d, int unit_begin, int count) {
+// grid: (units, workgroups per unit), kThreads threads.
+__global__ __launch_bounds__(kThreads) void evict_move_kernel(Dev d, int unit_begin) {
   const int first = 4 * (blockIdx.y * (kThreads / 64) + (threadIdx.x >> 6)), stride = 4 * gridDim.y * (kThreads / 64);
-  for (int w = blockIdx.x; w < count; w += gridDim.x) {
-    const int u = unit_begin + w;
-    const int h = *move_count(d, u);
-    const Slots base = slots_of(d, u);
-    for (int r0 = first; r0 < h; r0 += stride) move_entries4(d, base, move_list(d, u), d.cap, r0, min(4, h - r0), threadIdx.x & 63);
-  }
+  const int u = unit_begin + blockIdx.x;
+  const int h = *move_count(d, u);
+  const Slots base = slots_of(d, u);
+  for (int r0 = first; r0 < h; r0 += stride) move_entries4(d, base, move_list(d, u), d.cap, r0, min(4, h - r0), threadIdx.x & 63);
 }
 
 // ------------------------------------------------------------------ finish
@@ -2938,11 +2937,11 @@ __device__ __forceinline__ void evict_unit(const Dev& d, int u, Slots base, int 
 }
 
 // after_step: behind a decode step that has evicted single entries itself and left the rest (units that it dealt with keep
-// their record).  moves_follow = 0: nobody is expected to have more than one entry to give up, evict_move_kernel does
-// not run, and a unit that has after all moves its survivors here.
-// kShort: no unit holds more than four entries per thread; the kernel then needs a third of the registers and LDS, and
-// thousands of short units fit side by side (4096 units of 300 entries, one evicted each: 7 us less).
-template <int NT, bool kShort = false>
+// their record).  moves_follow = 0: evict_move_kernel does not run, and a unit moves its survivors here.
+// RMAX: entries per thread of the longest unit that the capacity allows.  The widest branch decides the registers of the
+// whole kernel, and with them how many short units are on the chip side by side (256 threads: 64 registers with 4, 153 with
+// 32; 4096 units of 1000 entries, window policy, two evicted each: 87 us with 32, 69 with 8).
+template <int NT, int RMAX>
 __global__ __launch_bounds__(NT) void evict_kernel(Dev d, int unit_begin, int n_sink, int after_step, int moves_follow) {
   __shared__ uint32_t evm[NT];
   __shared__ int32_t s_row[kMaxChunks];
@@ -2965,16 +2964,16 @@ __global__ __launch_bounds__(NT) void evict_kernel(Dev d, int unit_begin, int n_
   if (tid < d.max_seg) s_row[tid] = d.tbl[(size_t)u * d.max_seg + tid];
   __syncthreads();
   const Slots base{s_row};
-  if (kShort || n <= 4 * NT)
-    evict_unit<4, NT>(d, u, base, n, B, n_sink, moves_follow, s_tab, s_tab_n, evm, cb, rb, sh, tid);
-  else if constexpr (!kShort) {
-    if (n <= 8 * NT)
-      evict_unit<8, NT>(d, u, base, n, B, n_sink, moves_follow, s_tab, s_tab_n, evm, cb, rb, sh, tid);
-    else if (n <= 16 * NT)
-      evict_unit<16, NT>(d, u, base, n, B, n_sink, moves_follow, s_tab, s_tab_n, evm, cb, rb, sh, tid);
-    else
-      evict_unit<32, NT>(d, u, base, n, B, n_sink, moves_follow, s_tab, s_tab_n, evm, cb, rb, sh, tid);
-  }
+  auto unit = [&](auto r) {
+    evict_unit<decltype(r)::value, NT>(d, u, base, n, B, n_sink, moves_follow, s_tab, s_tab_n, evm, cb, rb, sh, tid);
+  };
+  if constexpr (RMAX > 16)
+    if (n > 16 * NT) return unit(std::integral_constant<int, 32>{});
+  if constexpr (RMAX > 8)
+    if (n > 8 * NT) return unit(std::integral_constant<int, 16>{});
+  if constexpr (RMAX > 4)
+    if (n > 4 * NT) return unit(std::integral_constant<int, 8>{});
+  unit(std::integral_constant<int, 4>{});
 }
 
 // ------------------------------------------------------------------ probe
