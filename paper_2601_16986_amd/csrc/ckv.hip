@@ -262,8 +262,9 @@ void give_stream(int devid, hipStream_t s) {
 }
 
 // Eviction of `count` units from `begin` on: select, then move.  A unit's keys sit in the registers of one workgroup:
-// 1024 threads, or 256 where four entries per thread are enough for every unit, or 32 are and there are enough units to
-// fill the chip with small workgroups anyway.
+// 1024 threads, or 256 where four entries per thread are enough for every unit, or 32 are and there is more than a unit per
+// compute unit, which has room for one wide workgroup (window policy, two evicted each, 1024 / 256 threads: 256 units of 7500
+// entries 36 / 39 us, 384 units of 2000 32 / 25, 512 units of 2000 32 / 25, 768 units of 7500 91 / 80).
 // The moves have a kernel of their own where it would have at least four workgroups per unit (up to four units per compute
 // unit; a unit's own workgroup is as fast then: 4096 units of 1000 entries, window policy, 40 evicted each, 198 us with a
 // second kernel, 157 without) and where a unit may have more to move than its workgroup moves in two rounds: `excess` counts
@@ -273,7 +274,7 @@ int launch_evict(ckv_ctx* c, hipStream_t s, int begin, int count, int n_sink, in
   hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
   CKV_HIP(c, hipStreamIsCapturing(s, &capturing));
   const int cap = c->lay.cap;
-  const bool small = cap <= 4 * kThreads || (cap <= 32 * kThreads && count >= 4 * c->n_cu);
+  const bool small = cap <= 4 * kThreads || (cap <= 32 * kThreads && count > c->n_cu);
   const int threads = small ? kThreads : kWideThreads, per_round = 4 * threads / 64;
   bool moves = after_step || capturing != hipStreamCaptureStatusNone;
   for (int l = begin / c->units_per_layer; l < (begin + count) / c->units_per_layer; ++l) {
@@ -406,7 +407,8 @@ int launch_schedule(ckv_ctx* c, hipStream_t s) {
   return CKV_OK;
 }
 
-// Answer-probe classes of `count` units from `begin` on.  The classes' workgroups as in launch_evict.
+// Answer-probe classes of `count` units from `begin` on.  Workgroups of 256 threads for the classes where 32 entries per
+// thread are enough and there are units to fill the chip with them.
 int launch_probe(ckv_ctx* c, const Dev& d, int begin, int count, const uint16_t* q, uint8_t* classes, hipStream_t s) {
   const int spans = (d.cap + kProbeSpan - 1) / kProbeSpan;
   hipLaunchKernelGGL(probe_scan_kernel, dim3((unsigned)count, (unsigned)((spans + 3) / 4)), dim3(kThreads), 0, s, d, begin, q);

@@ -87,6 +87,15 @@ def test_many_small_units(ties):
     _check(units, 4608, lengths, budgets, None, range(0, units, 37), ties)
 
 
+@pytest.mark.parametrize("units,cap", [(4, 4096), (300, 2048), (300, 4096)])
+def test_widths_by_capacity(units, cap):
+    """Kernels for four entries per thread of 1024, and for eight and sixteen per thread of 256, up to the last entry they hold."""
+    edge = [cap - 1, cap // 2, cap // 2 + 1, 1024, 1025, 3]
+    lengths = [edge[i % len(edge)] for i in range(units)]
+    budgets = [max(1, n - 1 - (i * 37) % n // 2) for i, n in enumerate(lengths)]
+    _check(units, cap, lengths, budgets, None if cap == 4096 else 40, range(0, units, 1 + units // 24), False)
+
+
 def test_more_units_than_the_moves_have_workgroups_for():
     """Thousands of units with moves: one workgroup per unit, and workgroups that take several units."""
     units, edge = 4500, [1, 40, 300, 511, 700]
