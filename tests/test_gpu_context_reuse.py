@@ -32,22 +32,25 @@ def _run(seed, steps=6):
 
 def test_contexts_hand_their_streams_on():
     want = {seed: _run(seed) for seed in range(3)}
-    got, errors = {}, []
+    got, errors = {seed: [] for seed in range(3)}, []
 
     def work(seed):
         try:
             for _ in range(4):
-                got[seed] = _run(seed)
+                got[seed].append(_run(seed))
         except Exception as e:                 # reported by the main thread
             errors.append(e)
 
-    threads = [threading.Thread(target=work, args=(s,)) for s in range(3)]
+    threads = [threading.Thread(target=work, args=(s,), daemon=True) for s in range(3)]
     for t in threads:
         t.start()
     for t in threads:
         t.join(timeout=100)
+        assert not t.is_alive()
     assert not errors, errors
     for seed, (outs, state) in want.items():
-        assert np.array_equal(outs, got[seed][0])
-        for a, b in zip(state, got[seed][1]):
-            assert a["n"] == b["n"] and all(np.array_equal(a[k], b[k]) for k in ("pos", "crf", "tau", "flags"))
+        assert len(got[seed]) == 4
+        for run_outs, run_state in got[seed]:
+            assert np.array_equal(outs, run_outs)
+            for a, b in zip(state, run_state):
+                assert a["n"] == b["n"] and all(np.array_equal(a[k], b[k]) for k in ("pos", "crf", "tau", "flags"))
