@@ -200,7 +200,7 @@ int ckv_load_cache(ckv_ctx* ctx, int32_t layer, const void* k, const void* v, in
  * cache and the new entry and writes the output (and the new entry's rows into
  * the cache).  The append's records, the hit set, the scores and the eviction of
  * that layer follow on one of two streams the context owns, eight consecutive
- * layers per launch (up to 32 if the layers are small), beside whatever `stream` does next (the next
+ * layers per launch (up to 32 if the layers are small, so that a launch has a workgroup per compute unit), beside whatever `stream` does next (the next
  * layers' steps, the model's other work).  Results are the same up to
  * floating-point summation order.  (A layer with at least two units per compute
  * unit is finished sooner by the fused kernel, bookkeeping included: there the
@@ -288,7 +288,7 @@ int ckv_get_segments(ckv_ctx* ctx, int32_t* owned, int32_t* rows, int32_t* spare
 int ckv_get_time(ckv_ctx* ctx, int32_t* t);
 int ckv_set_time(ckv_ctx* ctx, int32_t t);                   /* also restarts the Alg. 2 window */
 /* CKV_OK; CKV_ECAPACITY if, since the last call, some append found its unit full or the spare list ran short when
- * pool segments were dealt out; CKV_EHIP if a bounded wait inside a kernel gave up (results invalid).  Reported once. */
+ * pool segments were dealt out.  Reported once. */
 int ckv_status(ckv_ctx* ctx);
 
 /* Synchronous state transfer of one unit, row-major on the host side (tests,

@@ -46,8 +46,7 @@ struct ckv_ctx {
   int device = 0;               // the HIP device the context was created on
   size_t finish_lds = 0;
   // fused path (unit_kernel)
-  int path_mode = 0;            // 0 auto, 1 separate kernels, 2 fused kernel, 3 / 4 fused with 4 / 2 wavefronts per unit,
-                                // 5 fused with four book-keeping wavefronts beside four streaming ones
+  int path_mode = 0;            // 0 auto, 1 separate kernels, 2 fused kernel, 3 / 4 fused with 4 / 2 wavefronts per unit
   struct Fused {                // one variant of the fused kernel
     bool ok = false;
     int waves = 0;              // wavefronts per workgroup (= per unit)
@@ -1083,7 +1082,6 @@ int ckv_status(ckv_ctx* c) {
   CKV_HIP(c, hipMemcpy(&st, c->dev.sc + SC_STATUS, 4, hipMemcpyDeviceToHost));
   if (st) {
     CKV_HIP(c, hipMemcpy(c->dev.sc + SC_STATUS, &zero, 4, hipMemcpyHostToDevice));
-    if (st & 2) return fail(c, CKV_EHIP, "a wait between wavefronts of the fused kernel did not end: the last steps' results are invalid");
     if (st & 4) return fail(c, CKV_ECAPACITY, "the spare list ran short when the pool segments were dealt out: some units own less than budget + headroom needs");
     return fail(c, CKV_ECAPACITY, "an append found its unit full");
   }

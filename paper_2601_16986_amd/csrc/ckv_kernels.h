@@ -87,7 +87,7 @@ struct Dev {
 
 // Where a unit's entries live.  Pool memory (K, V and the per-slot arrays) is handed out in segments of 256
 // slots; row u of the segment table names unit u's segments in order, so entry i sits in pool slot
-// row[i / 256] * 256 + i % 256 and whole 256-entry chunks (what one scan work item, one wavefront of the
+// row[i / 256] * 256 + i % 256 and whole 256-entry chunks (what one wavefront or one workgroup of the
 // single-layer scan, eight blocks of the fused kernel's stream cover) are contiguous.  `row` may point to a
 // copy of the row in LDS.
 struct Slots {
@@ -107,32 +107,10 @@ __device__ __forceinline__ int unit_cap(const Dev& d, int u) { return min(d.cap,
 // ------------------------------------------------------------------ helpers
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-template <class T>
-__device__ __forceinline__ T wave_sum(T v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
-}
-
 // Cross-lane moves inside a row of 16 lanes without going through LDS.
 template <int kCtrl>
 __device__ __forceinline__ int dpp_i32(int v) {
   return __builtin_amdgcn_update_dpp(0, v, kCtrl, 0xF, 0xF, true);
-}
-// value of the lane `by` places further up in this lane's row of 16 (0 beyond the row's end); by = 1 .. 7
-__device__ __forceinline__ float row_shl_f32(float v, int by) {
-  const int x = __float_as_int(v);
-  int r = 0;
-  switch (by) {
-    case 1: r = __builtin_amdgcn_update_dpp(0, x, 0x101, 0xF, 0xF, true); break;
-    case 2: r = __builtin_amdgcn_update_dpp(0, x, 0x102, 0xF, 0xF, true); break;
-    case 3: r = __builtin_amdgcn_update_dpp(0, x, 0x103, 0xF, 0xF, true); break;
-    case 4: r = __builtin_amdgcn_update_dpp(0, x, 0x104, 0xF, 0xF, true); break;
-    case 5: r = __builtin_amdgcn_update_dpp(0, x, 0x105, 0xF, 0xF, true); break;
-    case 6: r = __builtin_amdgcn_update_dpp(0, x, 0x106, 0xF, 0xF, true); break;
-    default: r = __builtin_amdgcn_update_dpp(0, x, 0x107, 0xF, 0xF, true); break;
-  }
-  return __int_as_float(r);
 }
 constexpr int kDppQuadSwap1 = 0xB1;      // quad_perm [1,0,3,2]
 constexpr int kDppQuadSwap2 = 0x4E;      // quad_perm [2,3,0,1]
@@ -703,6 +681,7 @@ __device__ __forceinline__ T get_coherent(const T* p) {
 // without unused LDS that keeps a third workgroup off a compute unit); <8, 1> 23 / 34 / 28; <16, 2> 36 / 51 / 40;
 // <16, 1> 49 / 68 / 41.
 // grid: (units of the layer, ceil(max_chunks * kSplit / kW)), 64 kW threads.
+
 // Entry rr of the block in (ka, va) is replaced by the rows in `rows` (LDS: 128 bf16 of the key, then 128 of the
 // value), piece by piece, so that few registers are live at a time.
 __device__ __forceinline__ void inject_entry(KFrag& ka, VFrag& va, int rr, const uint16_t* rows, int lane) {
@@ -2690,7 +2669,7 @@ __global__ __launch_bounds__(kThreads) void seed_weights_kernel(Dev d, int unit_
 }
 
 // seed_hits_kernel (top-p rule only): one workgroup per (query of the batch, unit).  The query's mean weights
-// from // `srw`, the hit rule, and in their place the hits, a bit per entry at the start of the row (the query's own entry,
+// from `srw`, the hit rule, and in their place the hits, a bit per entry at the start of the row (the query's own entry,
 // the last it sees, is always hit): every thread has its weights in registers (or LDS) before the first bit is written.
 // (As rewards of 4 bytes they were 153 MB per layer of 128 units of 9350 entries and 32 queries, written and read.)
 // grid: (queries of the batch, units of the layer), kSeedThreads threads, kSeedList + 8 ints of dynamic LDS (R = 0: cap floats).

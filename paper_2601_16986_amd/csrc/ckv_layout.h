@@ -32,7 +32,7 @@ namespace ckv {
 constexpr int kDim = 128;          // head_dim
 constexpr int kBlk = 32;           // entries per block
 constexpr int kBlkElems = kBlk * kDim;   // bf16 elements per block (4096)
-constexpr int kChunkBlocks = 8;    // blocks per scan work item
+constexpr int kChunkBlocks = 8;    // blocks per chunk (and segment)
 constexpr int kChunk = kBlk * kChunkBlocks;   // 256 entries
 constexpr int kMaxGroup = 8;       // query heads per KV head
 constexpr int kSeg = kChunk;                // entries per segment, the unit in which pool memory is handed to units (64 KB of K, 64 KB of V)

@@ -95,7 +95,7 @@ def test_fused_kernel_with_logits_spilling_out_of_lds(path):
 def test_new_entry_alone_in_its_block(path, hq):
     """Budgets that are multiples of 32: in the steady state every unit holds B + 1 entries while it attends, the
     new one alone in the last block.  The fused kernel then does not stream that block: the entry joins the
-    merge as a state of its own (logits from prep_kernel, value row from the step's input).  From an empty
+    merge as a state of its own (logits and value row from the step's inputs).  From an empty
     cache (the first entry is alone too) through growth over block boundaries into the steady state."""
     cfg = _small("qwen14b", n_layers=2, batch=2, n_q_heads=hq, n_kv_heads=2, prompt=0, decode_steps=150,
                  budget=64, budget_min=1, budget_max=128, seed=37)
@@ -771,7 +771,7 @@ def test_hip_graph_replay_matches_eager(path):
 def test_probe_classes_on_multi_chunk_units_of_a_fused_path_context(path):
     """Sec. 3 classes on units of 300..700 entries (several 256-entry chunks, ragged last blocks, 7 query
     heads per KV head) in a context whose decode steps run the fused kernel: the probe shares the context's
-    workspace (work list, partials, logits buffer) with those steps, leaves the caches untouched, and the
+    workspace (partials, logits buffer) with those steps, leaves the caches untouched, and the
     decode steps that follow still match the oracle."""
     cfg = _small("qwen7b", n_layers=1, batch=3, n_q_heads=14, n_kv_heads=2, prompt=333, decode_steps=16,
                  budget=500, budget_min=300, budget_max=735, seed=5)
