@@ -2367,7 +2367,7 @@ __global__ __launch_bounds__(NT) void finish_kernel(Dev d, int unit_begin, uint3
 // shifts per logit, of which one lane in G was used, and a G that does not divide 16 left columns empty.)
 // Both passes share a unit's blocks out over S wavefronts, as many as fill the chip evenly: with a wavefront per chunk of
 // 256 entries, 128 units of 9350 entries were 1280 workgroups on 768 places.  Measured on that shape, 32 queries,
-// G = 5: first pass 116 -> 85 us, second pass 172 -> 98 us.
+// G = 5: first pass 111 -> 88 us, second pass 163 -> 97 us.
 // Buffers of a batch of nq queries for the UL units of a layer (tiles and columns as in the first pass):
 //   sml [tile][unit][span][column][2]     maximum (rounded up) and sum of the softmax over a wavefront's blocks
 //   smi [tile][unit][column][2]           maximum (rounded up) and 1 / sum over all the entries the column's query sees
