@@ -116,6 +116,7 @@ constexpr int kDppQuadSwap1 = 0xB1;      // quad_perm [1,0,3,2]
 constexpr int kDppQuadSwap2 = 0x4E;      // quad_perm [2,3,0,1]
 constexpr int kDppRowHalfMirror = 0x141;
 constexpr int kDppRowMirror = 0x140;
+constexpr int kDppRowShl = 0x100, kDppRowShr = 0x110;      // + 1 .. 15: from so many lanes up / down, 0 from beyond the row
 
 // Sum over the 64 lanes, same fixed order in every lane: butterfly inside each
 // row of 16 lanes, then the four row sums are read out and added.
@@ -152,6 +153,12 @@ __device__ __forceinline__ u64 readlane_u64(u64 v, int lane) {
   const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane);
   return ((u64)hi << 32) | lo;
 }
+
+template <int kCtrl>
+__device__ __forceinline__ double dpp_f64(double v) {
+  return __longlong_as_double((long long)dpp_u64<kCtrl>((u64)__double_as_longlong(v)));
+}
+__device__ __forceinline__ double readlane_f64(double v, int lane) { return __longlong_as_double((long long)readlane_u64((u64)__double_as_longlong(v), lane)); }
 
 __device__ __forceinline__ u64 wave_sum_u64(u64 v) {
   v += dpp_u64<kDppQuadSwap1>(v);
@@ -247,6 +254,7 @@ __device__ __forceinline__ int block_sum_int(int v, RedBuf<NT>& rb, int& phase, 
 }
 
 // a value that is the same in all lanes, into scalar registers
+__device__ __forceinline__ int uniform_i32(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ float uniform_f32(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
 
 template <int kCtrl>
@@ -1626,13 +1634,13 @@ __device__ __forceinline__ HitRule top_p_lds(const Dev& d, Slots base, int n, Va
       above = block_sum_f32<NT>(above, rb, phase, tid);
       ties = block_sum_int<NT>(ties, rb, phase, tid);
       if (ties > 1) {
-        const float th = __uint_as_float(theta);
-        float c = above;
+        const double th = (double)__uint_as_float(theta), p = (double)d.top_p;
+        double c = (double)above;
         int r = 0;
         do {
           c += th;
           ++r;
-        } while (c <= d.top_p && r < ties);
+        } while (c <= p && r < ties);
         if (r < ties) {
           ties_all = false;
           int X = 0;   // r-th smallest position among the ties
@@ -1803,17 +1811,17 @@ __device__ __forceinline__ EntryRow load_row_input(const NewEntry& ne, int tid) 
 // Entries equal to the threshold: only as many as needed, lower positions first.  above = total weight of the entries
 // above theta, ties = entries equal to it.
 template <int R, int NT>
-__device__ __forceinline__ HitRule tie_rule(const Dev& d, Slots base, int n, const float (&a)[R], uint32_t theta, float above, int ties,
+__device__ __forceinline__ HitRule tie_rule(const Dev& d, Slots base, int n, const float (&a)[R], uint32_t theta, double above, int ties,
                                             int new_last_t, RedBuf<NT>& rb, int& phase, int tid) {
   HitRule rule{theta, true, 0x7FFFFFFF};
   if (ties <= 1) return rule;
-  const float th = __uint_as_float(theta);
-  float c = above;
+  const double th = (double)__uint_as_float(theta), p = (double)d.top_p;      // (in fp32 hundreds of equal additions round the same way)
+  double c = above;
   int r = 0;
   do {
     c += th;
     ++r;
-  } while (c <= d.top_p && r < ties);
+  } while (c <= p && r < ties);
   if (r >= ties) return rule;
   rule.ties_all = false;
   int X = 0;   // r-th smallest position among the ties (rare: positions are re-read from memory)
@@ -1824,169 +1832,166 @@ __device__ __forceinline__ HitRule tie_rule(const Dev& d, Slots base, int n, con
       const int i = 4 * (tid + (k >> 2) * NT) + (k & 3);
       if (__float_as_uint(a[k]) == theta && i < n && ((new_last_t >= 0 && i == n - 1) ? new_last_t : d.pos[base + i]) < trial) ++cnt;
     }
-    cnt = block_sum_int<NT>(cnt, rb, phase, tid);
+    cnt = uniform_i32(block_sum_int<NT>(cnt, rb, phase, tid));
     if (cnt < r) X = trial;
   }
   rule.pos_cut = X;
   return rule;
 }
 
-// Step 1 over weights in registers (a[4 c + e] = mean weight of entry 4 (tid + c NT) + e, 0 beyond n).  lst: 64 ints of
-// LDS (lst_cap >= 64, or the short list is not used); sh: the callers' exchange words (5 .. 7 are used here).
-// new_last_t >= 0: the unit's last entry is not in the cache and has this position.
-// (Fewer rounds by bracketing, top_p_flat below, gain nothing here, where other wavefronts stream meanwhile or the
-// other phases' round trips decide: fused step 0.99-1.00 of the speed, bookkeeping of 128 units 21 us either way.)
-template <int R, int NT = kThreads>
-__device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, const float (&a)[R], int* lst, int lst_cap, int new_last_t,
-                                              RedBuf<NT>& rb, int& phase, int* sh, int tid) {
-  uint32_t theta = 0;
-  if (d.reward_mode == 0) {
-    // largest pattern theta with sum{a >= theta} > p, two bits per round (one barrier each): the three
-    // candidates' sums are nested, so the largest candidate that passes is what bit-by-bit bisection
-    // would reach.  Bit 30 is never set: the weights are <= 1.
-    auto round = [&](int bit) {
-      const uint32_t c1 = theta | (1u << (bit - 1)), c2 = theta | (1u << bit), c3 = c1 | c2;
-      float p1 = 0.f, p2 = 0.f, p3 = 0.f;
-#pragma unroll
-      for (int k = 0; k < R; ++k) {
-        const uint32_t b = __float_as_uint(a[k]);
-        p1 += (b >= c1) ? a[k] : 0.f;
-        p2 += (b >= c2) ? a[k] : 0.f;
-        p3 += (b >= c3) ? a[k] : 0.f;
-      }
-      block_sum3_f32<NT>(p1, p2, p3, rb, phase, tid);
-      theta = p3 > d.top_p ? c3 : p2 > d.top_p ? c2 : p1 > d.top_p ? c1 : theta;
-    };
-    constexpr int kListBit = 17;        // the rounds for the bits above this one run over all entries
-    int bit = 29;
-    bool from_list = false;             // the tail ran on the short list, which also gave:
-    int list_ties = 0;                  //   entries equal to theta
-    float list_above = 0.f;             //   total weight of the entries above theta
-    for (; bit > kListBit; bit -= 2) round(bit);
-    // With the top 12 bits fixed, the weights that can still decide a candidate, those in
-    // [theta, theta + 2^18), are usually a handful.  If at most 64, they are collected in LDS (in a fixed
-    // order: by wavefront, register index, lane) and one wavefront finishes the bisection on them alone:
-    // nine rounds without barriers over one register instead of R.
-    {
-      const uint32_t lo = theta > 1u ? theta : 1u, hi = theta + (2u << kListBit);
-      const int lane = tid & 63, wave = tid >> 6;
-      float ab = 0.f;
-      int mine = 0;
-#pragma unroll
-      for (int k = 0; k < R; ++k) {
-        const uint32_t b = __float_as_uint(a[k]);
-        ab += (b >= hi) ? a[k] : 0.f;
-        mine += (b >= lo && b < hi) ? 1 : 0;
-      }
-      ab = wave_sum_f32(ab);
-      mine = wave_sum_i32(mine);
-      if (lane == 0) *reinterpret_cast<f32x4*>(rb.t[phase][wave]) = f32x4{ab, __int_as_float(mine), 0.f, 0.f};
-      block_sync<NT>(rb);
-      float above_bucket = 0.f;
-      int m = 0, off = 0;
-#pragma unroll
-      for (int w = 0; w < NT / 64; ++w) {
-        const f32x4 q = *reinterpret_cast<const f32x4*>(rb.t[phase][w]);
-        above_bucket += q[0];
-        const int cw = __float_as_int(q[1]);
-        off += w < wave ? cw : 0;
-        m += cw;
-      }
-      phase ^= 1;
-      if (m <= 64 && lst_cap >= 64) {
-#pragma unroll
-        for (int k = 0; k < R; ++k) {
-          const uint32_t b = __float_as_uint(a[k]);
-          const bool in = b >= lo && b < hi;
-          const unsigned long long mask = __ballot(in);
-          const int r = off + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-          if (in) lst[r] = (int)b;
-          off += __popcll(mask);
-        }
-        block_sync<NT>(rb);
-        if (wave == 0) {
-          // One candidate per lane.  The largest pattern theta with sum{a >= theta} > p is a candidate's own
-          // pattern: the largest one whose sum of candidates at least as large, on top of what lies above the
-          // bucket, exceeds p (what the remaining rounds of the bisection would arrive at).  Every entry
-          // equal to theta is in the list too, so the number of such ties and the weight above theta are
-          // known here as well, without two more reductions over all entries.
-          const uint32_t bj = lane < m ? (uint32_t)lst[lane] : 0u;
-          const float aj = __uint_as_float(bj);
-          float sj = 0.f;
-          for (int k = 0; k < m; ++k) {                       // m is uniform; candidates in list order
-            const uint32_t bk = (uint32_t)__builtin_amdgcn_readlane((int)bj, k);
-            sj += (bk >= bj) ? __uint_as_float(bk) : 0.f;
-          }
-          const uint32_t mine_ok = (lane < m && above_bucket + sj > d.top_p) ? bj : 0u;
-          uint32_t th = mine_ok;
-#pragma unroll
-          for (int o = 32; o > 0; o >>= 1) th = max(th, (uint32_t)__shfl_xor((int)th, o));
-          if (th != 0u) theta = th;
-          const int n_ties = __popcll(__ballot(lane < m && bj == theta));
-          const float above_l = above_bucket + wave_sum_f32((lane < m && bj > theta) ? aj : 0.f);
-          if (lane == 0) {
-            sh[7] = (int)theta;
-            sh[5] = n_ties;
-            sh[6] = __float_as_int(above_l);
-          }
-        }
-        block_sync<NT>(rb);
-        theta = (uint32_t)sh[7];
-        list_ties = sh[5];
-        list_above = __int_as_float(sh[6]);
-        from_list = true;
-      } else {
-        for (; bit >= 1; bit -= 2) round(bit);
-      }
-    }
-    if (theta != 0) {
-      float above = list_above;
-      int ties = list_ties;
-      if (!from_list) {
-        above = 0.f;
-        ties = 0;
-#pragma unroll
-        for (int k = 0; k < R; ++k) {
-          const uint32_t b = __float_as_uint(a[k]);
-          above += (b > theta) ? a[k] : 0.f;
-          ties += (b == theta) ? 1 : 0;
-        }
-        above = block_sum_f32<NT>(above, rb, phase, tid);
-        ties = block_sum_int<NT>(ties, rb, phase, tid);
-      }
-      return tie_rule<R, NT>(d, base, n, a, theta, above, ties, new_last_t, rb, phase, tid);
-    }
-  }
-  return HitRule{theta, true, 0x7FFFFFFF};
+// Step 1 over weights in registers (a[4 c + e] = mean weight of entry 4 (tid + c NT) + e, 0 beyond n): the largest pattern
+// theta with sum{a >= theta} > p.
+//
+// One pass over the weights instead of a reduction over all of them per round of a search.  A histogram in LDS over the
+// patterns' top bits (24 octaves below 2 in bins of 1/32 octave) takes per bin the number of its weights and the
+// sum of their low bits in one 64-bit integer addition, so that a bin's sum is known exactly and does not depend on the order; the bin in which
+// the sum from above passes p follows from a scan over the bins in 64 bits.  The bin's weights, usually a few dozen, go to a list, where each
+// finds the sum of those at least as large, again from counts and low bits.  A bin of more than kList weights, and weights outside
+// the bins that might matter (below 2^-23 in all; negative, NaN or 2 and above), take two bits per round over all entries.
+//
+// What bounded the search was issue: nine instructions per weight and round, six rounds (three or four by bracketing), a barrier and a
+// reduction each; now about eight per weight in all and an LDS addition (a wavefront's 64-bit additions to a hundred random
+// bins take 13 cycles of the compute unit).  finish_kernel for 128 units of 2048 entries 20.8 -> 15.6 us, 4096 rows of 9350 weights of a
+// replay 80 -> 68 us, fused step of 896 units of 2048 entries 194.3 -> 190.6 us, of 6144 units 1243 -> 1238 us.
+// The scan over the bins moves through DPP and by one wavefront: its registers come on top of the weights and of what the callers
+// have in flight.
+struct alignas(16) TopBuf {
+  u64 bin[24 << 5];
+  uint32_t list[256 + 8];
+  double above;           // sum of the bins above the one in question
+  int at, count;          // that bin (-1: none), and the number of its weights
+  double above_theta;
+  uint32_t listed, odd, theta, ties;
+  uint32_t pad[2];
+};
+constexpr int kBinShift = 18, kBins = 24 << 5, kBinFirst = (127 - 23) << 5;
+constexpr uint32_t kBinLow = (1u << kBinShift) - 1u;
+constexpr int kBinCount = 34;                 // the count's place: 32768 low parts of 18 bits lie below it
+__device__ __forceinline__ double bin_edge(int i) { return (double)__uint_as_float((uint32_t)(kBinFirst + i) << kBinShift); }
+__device__ __forceinline__ double bin_unit(int i) { return (double)__uint_as_float((uint32_t)((kBinFirst + i) >> 5) << 23) * 0x1p-23; }
+
+__device__ __forceinline__ double bin_sum(u64 v, int i) {
+  return (double)(uint32_t)(v >> kBinCount) * bin_edge(i) + (double)(v & ((1ull << kBinCount) - 1ull)) * bin_unit(i);
 }
 
-// Step 1 over long units of flat weights (the prompt replay): the same threshold in fewer passes over the registers,
-// with a longer list at the end.  lst: kList + 8 ints of LDS, 16-byte aligned; sh[5] and sh[6] are used.  theta = 0: every entry is hit.
-template <int R, int NT, int kList>
-__device__ __forceinline__ HitRule top_p_flat(const Dev& d, Slots base, int n, const float (&a)[R], int* lst, RedBuf<NT>& rb, int& phase, int* sh,
+// lst: a TopBuf of LDS.  new_last_t >= 0: the unit's last entry is not in the cache and has this position.
+template <int R, int NT = kThreads>
+__device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, const float (&a)[R], int* lst, int new_last_t, RedBuf<NT>& rb, int& phase,
                                               int tid) {
-  uint32_t theta = 0;
-  // The largest pattern theta with sum{a >= theta} > p lies in [lo, hi): sum{a >= lo} > p (lo = 0: not known to), and
-  // sum{a >= hi} <= p.  A round (one barrier) tries three patterns.  Patterns of positive floats order like their
-  // logarithms, in which the sum falls smoothly, so after a first round around the mean weight the three are
-  // the linear interpolation and a sixteenth of the bracket to either side of it; every third round, in case
-  // that creeps, the quarters.  It ends when the bracket cannot hold more than kList weights
-  // (each is at least lo, together they are the difference of the two sums): 3 or 4 rounds, where two bits of
-  // the pattern per round took six to reach as short a list (128 units of 9350 entries, 32 queries: 25 us less).
-  // Weights are below 2.
-  uint32_t lo = 0u, hi = 0x40000000u;
-  float s_lo = 1.0f, s_hi = 0.0f;
-  bool from_list = false;             // the tail ran on the short list, which also gave:
-  int list_ties = 0;                  //   entries equal to theta
-  float list_above = 0.f;             //   total weight of the entries above theta
-  bool try_list = true;
-  int turn = 0;
-  // entries below (1 - p) / n cannot make up the rest: theta is rarely lower, nor often far above the mean
-  const float p = d.top_p;
-  uint32_t c1 = min(max(__float_as_uint(fmaxf(1.0f - p, 1e-3f) / (float)n), 1u << 23), 0x3F000000u);
-  uint32_t c2 = c1 + (3u << 22), c3 = min(c1 + (1u << 25), hi - 1u);
+  if (d.reward_mode != 0) return HitRule{0u, true, 0x7FFFFFFF};
+  constexpr int kList = NT < 256 ? NT : 256;
+  TopBuf& tb = *reinterpret_cast<TopBuf*>(lst);
+  const int lane = tid & 63, wave = tid >> 6;
+  // (not known to the compiler as the same in every unit: kept in registers across the units of a persistent kernel it would be
+  // spilled, and a reload is a wait for every load in flight)
+  float top_p = d.top_p;
+  asm volatile("" : "+s"(top_p));
+  const double p = (double)top_p;
+  block_sync<NT>(rb);                               // whatever lay in the buffer has been read
+  for (int i = tid; i < (int)(sizeof(TopBuf) / 16); i += NT) reinterpret_cast<u32x4*>(&tb)[i] = u32x4{0u, 0u, 0u, 0u};
+  block_sync<NT>(rb);
+  uint32_t largest = 0;
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    const uint32_t b = __float_as_uint(a[k]), i = (b >> kBinShift) - (uint32_t)kBinFirst;
+    largest = max(largest, b);
+    if (i < (uint32_t)kBins) atomicAdd(&tb.bin[i], (1ull << kBinCount) | (b & kBinLow));
+    if (k % 4 == 3) __builtin_amdgcn_sched_barrier(0);        // few addresses at a time
+  }
+  if (largest >= 0x40000000u) tb.odd = 1u;
+  block_sync<NT>(rb);
+  if (wave == 0) {
+    // lane l: bins kPer l and up; few registers at a time, since the weights and the callers' prefetches live through this
+    constexpr int kPer = kBins / 64;
+    double mine = 0.0;
 #pragma unroll 1
-  while (true) {
+    for (int i = 0; i < kPer; i += 4) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) mine += bin_sum(tb.bin[kPer * lane + i + e], kPer * lane + i + e);
+    }
+    // sums from each lane up: inside a row of 16 lanes, then the rows above (the sum grows towards the lower lanes)
+    double incl = mine;
+    incl += dpp_f64<kDppRowShl + 1>(incl);
+    incl += dpp_f64<kDppRowShl + 2>(incl);
+    incl += dpp_f64<kDppRowShl + 4>(incl);
+    incl += dpp_f64<kDppRowShl + 8>(incl);
+    const double row3 = readlane_f64(incl, 48), row2 = readlane_f64(incl, 32) + row3, row1 = readlane_f64(incl, 16) + row2;
+    incl += lane < 16 ? row1 : lane < 32 ? row2 : lane < 48 ? row3 : 0.0;
+    const u64 passed = __ballot(incl > p);
+    if (passed) {
+      // the highest lane at which it passes; of that lane's bins, from the top, lane i takes the i-th
+      const int at = 63 - __builtin_clzll(passed), bin = kPer * at + kPer - 1 - min(lane, kPer - 1);
+      const double before = at == 63 ? 0.0 : readlane_f64(incl, min(at + 1, 63));
+      const u64 v = tb.bin[bin];
+      double sum = lane < kPer ? bin_sum(v, bin) : 0.0;
+      sum += dpp_f64<kDppRowShr + 1>(sum);
+      sum += dpp_f64<kDppRowShr + 2>(sum);
+      sum += dpp_f64<kDppRowShr + 4>(sum);
+      sum += dpp_f64<kDppRowShr + 8>(sum);
+      const double above = before + dpp_f64<kDppRowShr + 1>(sum);
+      const u64 here = __ballot(before + sum > p) & ((1ull << kPer) - 1ull);
+      if (lane == (here ? __builtin_ctzll(here) : kPer - 1)) {        // (none only by rounding)
+        tb.at = bin;
+        tb.count = (int)(v >> kBinCount);
+        tb.above = above;
+      }
+    } else if (lane == 0) {
+      tb.at = -1;
+    }
+  }
+  block_sync<NT>(rb);
+  // what every thread reads from LDS is made uniform: the branches on it are then scalar
+  const int bin = uniform_i32(tb.at), m = uniform_i32(tb.count);
+  uint32_t theta = 0;
+  int bit = 29;
+  if (bin >= 0 && uniform_i32((int)tb.odd) == 0) {
+    theta = (uint32_t)(kBinFirst + bin) << kBinShift;
+    bit = kBinShift - 1;
+    if (m <= kList) {
+#pragma unroll
+      for (int k = 0; k < R; ++k) {
+        const uint32_t b = __float_as_uint(a[k]);
+        if ((b ^ theta) <= kBinLow) tb.list[atomicAdd(&tb.listed, 1u)] = b;
+        if (k % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+      }
+      block_sync<NT>(rb);
+      // A candidate per thread: theta is the largest of them whose sum of those at least as large, on top of the bins above, exceeds p.
+      const double edge = bin_edge(bin), unit = bin_unit(bin), above = tb.above;
+      uint32_t mine = 0u, th = 0u, equal = 0u, larger = 0u, low = 0u;
+      if (64 * wave < m) {
+        mine = tb.list[tid];
+        for (int k = 0; k < m; k += 4) {                   // the list ends in zeros
+          const u32x4 four = *reinterpret_cast<const u32x4*>(tb.list + k);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            larger += four[e] > mine ? 1u : 0u;
+            low += four[e] > mine ? four[e] & kBinLow : 0u;
+            equal += four[e] == mine ? 1u : 0u;
+          }
+        }
+        const double sum = above + ((double)(larger + equal) * edge + (double)(low + equal * (mine & kBinLow)) * unit);
+        th = ~wave_min_u32(~((tid < m && sum > p) ? mine : 0u));
+        if (m > 64 && lane == 0) atomicMax(&tb.theta, th);
+      }
+      if (m > 64) {
+        block_sync<NT>(rb);
+        th = tb.theta;
+      }
+      if (tid < m && mine == th) {                         // every such thread has the same to say
+        tb.theta = th;
+        tb.ties = equal;
+        tb.above_theta = above + ((double)larger * edge + (double)low * unit);
+      }
+      block_sync<NT>(rb);
+      const uint32_t found = (uint32_t)uniform_i32((int)tb.theta);
+      if (found == 0u) return HitRule{theta, true, 0x7FFFFFFF};
+      return tie_rule<R, NT>(d, base, n, a, found, readlane_f64(tb.above_theta, 0), uniform_i32((int)tb.ties), new_last_t, rb, phase, tid);
+    }
+  }
+  // two bits per round (one barrier each): the three candidates' sums are nested, so the largest candidate that passes is
+  // what bit-by-bit bisection would reach.  Bit 30 is never set: the weights are <= 1.
+  for (; bit >= 1; bit -= 2) {
+    const uint32_t c1 = theta | (1u << (bit - 1)), c2 = theta | (1u << bit), c3 = c1 | c2;
     float p1 = 0.f, p2 = 0.f, p3 = 0.f;
 #pragma unroll
     for (int k = 0; k < R; ++k) {
@@ -1996,139 +2001,20 @@ __device__ __forceinline__ HitRule top_p_flat(const Dev& d, Slots base, int n, c
       p3 += (b >= c3) ? a[k] : 0.f;
     }
     block_sum3_f32<NT>(p1, p2, p3, rb, phase, tid);
-    p1 = uniform_f32(p1);
-    p2 = uniform_f32(p2);
-    p3 = uniform_f32(p3);
-    // c1 <= c2 <= c3, the sums fall
-    const bool g1 = p1 > p, g2 = p2 > p, g3 = p3 > p;
-    hi = g3 ? hi : g2 ? c3 : g1 ? c2 : c1;
-    s_hi = g3 ? s_hi : g2 ? p3 : g1 ? p2 : p1;
-    lo = g3 ? c3 : g2 ? c2 : g1 ? c1 : lo;
-    s_lo = g3 ? p3 : g2 ? p2 : g1 ? p1 : s_lo;
-    theta = lo;
-    const uint32_t w = hi - lo;
-    if (w <= 1u) break;
-    if (try_list && s_lo - s_hi <= (float)kList * __uint_as_float(lo)) {
-      // The weights that can still decide, collected in LDS (in a fixed order: by wavefront, register index,
-      // lane): one wavefront finishes on them alone.
-      const uint32_t from = max(lo, 1u);
-      const int lane = tid & 63, wave = tid >> 6;
-      int mine = 0;
-#pragma unroll
-      for (int k = 0; k < R; ++k) {
-        mine += __popcll(__ballot(__float_as_uint(a[k]) - from < hi - from));
-      }
-      if (lane == 0) rb.v[phase][wave] = (u64)(uint32_t)mine;
-      block_sync<NT>(rb);
-      const float above_bucket = s_hi;
-      int m = 0, off = 0;
-#pragma unroll
-      for (int ww = 0; ww < NT / 64; ++ww) {
-        const int cw = (int)(uint32_t)rb.v[phase][ww];
-        off += ww < wave ? cw : 0;
-        m += cw;
-      }
-      phase ^= 1;
-      if (m <= kList) {
-        from_list = true;
-#pragma unroll
-        for (int k = 0; k < R; ++k) {
-          const uint32_t b = __float_as_uint(a[k]);
-          const bool in = b - from < hi - from;
-          const unsigned long long mask = __ballot(in);
-          if (mask == 0ull) continue;                      // most registers of a wavefront hold none
-          const int r = off + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-          if (in) lst[r] = (int)b;
-          off += __popcll(mask);
-        }
-        // The list is padded with zeros, which add nothing, to be read four at a time.
-        if (tid < 8) lst[m + tid] = 0;
-        block_sync<NT>(rb);
-        // The largest pattern theta with sum{a >= theta} > p is a candidate's own pattern: the largest one whose sum of
-        // candidates at least as large, on top of what lies above the bracket, exceeds p.  A candidate per
-        // thread (by one wavefront, four per lane, the walk over a full list took 4 us of a row that is on its own),
-        // the others read from LDS, the next four asked for ahead.
-        static_assert(kList <= NT, "a candidate per thread");
-        uint32_t th = 0u;
-        if (64 * wave < m) {
-          const uint32_t bj = tid < m ? (uint32_t)lst[tid] : 0u;
-          float sj = 0.f;
-          u32x4 four = *reinterpret_cast<const u32x4*>(lst);
-          for (int k = 0; k < m; k += 4) {                  // candidates in list order
-            const u32x4 ahead = *reinterpret_cast<const u32x4*>(lst + k + 4);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) sj += (four[e] >= bj) ? __uint_as_float(four[e]) : 0.f;
-            four = ahead;
-          }
-          th = (tid < m && above_bucket + sj > d.top_p) ? bj : 0u;
-        }
-        th = ~wave_min_u32(~th);
-        if (lane == 0) rb.v[phase][wave] = (u64)th;
-        block_sync<NT>(rb);
-#pragma unroll
-        for (int ww = 0; ww < NT / 64; ++ww) th = max(th, (uint32_t)rb.v[phase][ww]);
-        phase ^= 1;
-        if (th != 0u) theta = th;
-        if (wave == 0) {
-          // Every entry equal to theta is in the list too, so the number of such ties and the weight above theta are
-          // known here as well, without two more reductions over all entries.
-          constexpr int kC = kList / 64;                    // kList / 64 candidates per lane (candidate lane + 64 c)
-          uint32_t bj[kC];
-#pragma unroll
-          for (int c = 0; c < kC; ++c) bj[c] = lane + 64 * c < m ? (uint32_t)lst[lane + 64 * c] : 0u;
-          int n_ties = 0;
-          float mine_above = 0.f;
-#pragma unroll
-          for (int c = 0; c < kC; ++c) {
-            const bool in = lane + 64 * c < m;
-            n_ties += __popcll(__ballot(in && bj[c] == theta));
-            mine_above += (in && bj[c] > theta) ? __uint_as_float(bj[c]) : 0.f;
-          }
-          const float above_l = above_bucket + wave_sum_f32(mine_above);
-          if (lane == 0) {
-            sh[5] = n_ties;
-            sh[6] = __float_as_int(above_l);
-          }
-        }
-        block_sync<NT>(rb);
-        list_ties = sh[5];
-        list_above = __int_as_float(sh[6]);
-        break;
-      }
-      try_list = false;
-    }
-    uint32_t g, step;
-    if (turn == 2 || w <= 16u) {
-      step = max(w >> 2, 1u);
-      g = lo + (w >> 1);
-      turn = 0;
-    } else {
-      step = w >> 4;
-      const float f = (s_lo - p) * __builtin_amdgcn_rcpf(s_lo - s_hi);
-      g = lo + (uint32_t)(fminf(fmaxf(f, 0.0f), 1.0f) * (float)w);
-      g = min(max(g, lo + step + 1u), hi - step - 1u);
-      ++turn;
-    }
-    c1 = max(g - step, lo + 1u);
-    c2 = g;
-    c3 = min(g + step, hi - 1u);
+    theta = uniform_f32(p3) > d.top_p ? c3 : uniform_f32(p2) > d.top_p ? c2 : uniform_f32(p1) > d.top_p ? c1 : theta;
   }
   if (theta == 0) return HitRule{0u, true, 0x7FFFFFFF};
-  float above = list_above;
-  int ties = list_ties;
-  if (!from_list) {
-    above = 0.f;
-    ties = 0;
+  float above = 0.f;
+  int ties = 0;
 #pragma unroll
-    for (int k = 0; k < R; ++k) {
-      const uint32_t b = __float_as_uint(a[k]);
-      above += (b > theta) ? a[k] : 0.f;
-      ties += (b == theta) ? 1 : 0;
-    }
-    above = block_sum_f32<NT>(above, rb, phase, tid);
-    ties = block_sum_int<NT>(ties, rb, phase, tid);
+  for (int k = 0; k < R; ++k) {
+    const uint32_t b = __float_as_uint(a[k]);
+    above += (b > theta) ? a[k] : 0.f;
+    ties += (b == theta) ? 1 : 0;
   }
-  return tie_rule<R, NT>(d, base, n, a, theta, above, ties, -1, rb, phase, tid);
+  above = uniform_f32(block_sum_f32<NT>(above, rb, phase, tid));
+  ties = uniform_i32(block_sum_int<NT>(ties, rb, phase, tid));
+  return tie_rule<R, NT>(d, base, n, a, theta, above, ties, new_last_t, rb, phase, tid);
 }
 
 // `after_step1` runs once between Step 1 and the score update (the fused kernel
@@ -2150,7 +2036,7 @@ __device__ __forceinline__ void lrfu_regs(const Dev& d, int u, Slots base, int n
   EntryRow last_row{{0u, 0u, 0u, 0u}, 0, 0};
   if (evict_single) last_row = new_in_regs ? load_row_input<NT>(ne, tid) : load_row<NT>(d, base, n - 1, tid);
   // ---- Step 1: top-p hit set as a threshold on the weight's bit pattern
-  const HitRule rule = top_p_regs<R, NT>(d, base, n, a, lst, lst_cap, new_in_regs ? t : -1, rb, phase, sh, tid);
+  const HitRule rule = top_p_regs<R, NT>(d, base, n, a, lst, new_in_regs ? t : -1, rb, phase, tid);
   after_step1();
   // ---- Steps 2-3: scores; a[k] becomes CRF_temp.  The candidate for Step 4 (lowest score, then
   // highest position) is tracked on the way.
@@ -2674,11 +2560,10 @@ __global__ __launch_bounds__(kThreads) void seed_weights_kernel(Dev d, int unit_
 // (As rewards of 4 bytes they were 153 MB per layer of 128 units of 9350 entries and 32 queries, written and read.)
 // grid: (queries of the batch, units of the layer), kSeedThreads threads, kSeedList + 8 ints of dynamic LDS (R = 0: cap floats).
 constexpr int kSeedThreads = 512;      // prompts are long
-constexpr int kSeedList = 256;         // candidates among which a threshold is found by one wavefront
 
 template <int R>
 __device__ __forceinline__ void seed_rewards_regs(const Dev& d, Slots base, int n, bool last_new, float* rw, int* lst, RedBuf<kSeedThreads>& rb, int& phase,
-                                                  int* sh, int tid) {
+                                                  int tid) {
   float a[R];
 #pragma unroll
   for (int c = 0; c < R / 4; ++c) {
@@ -2687,7 +2572,7 @@ __device__ __forceinline__ void seed_rewards_regs(const Dev& d, Slots base, int 
 #pragma unroll
     for (int e = 0; e < 4; ++e) a[4 * c + e] = (e0 + e < n) ? x[e] : 0.f;
   }
-  const HitRule rule = top_p_flat<R, kSeedThreads, kSeedList>(d, base, n, a, lst, rb, phase, sh, tid);
+  const HitRule rule = top_p_regs<R, kSeedThreads>(d, base, n, a, lst, -1, rb, phase, tid);
   uint32_t* bits = reinterpret_cast<uint32_t*>(rw);
 #pragma unroll
   for (int c = 0; c < R / 4; ++c) {
@@ -2722,7 +2607,6 @@ __global__ __launch_bounds__(kSeedThreads, R == 0 || R > 24 ? 4 : R > 16 ? 6 : 8
                                                                                                       float* __restrict__ srw) {
   extern __shared__ unsigned char smem[];
   __shared__ RedBuf<kSeedThreads> rb;
-  __shared__ int sh[4 + kSeedThreads / 64];
   const int tid = threadIdx.x;
   const int ql = blockIdx.x, urel = blockIdx.y, u = unit_begin + urel;
   const int UL = gridDim.y;
@@ -2733,7 +2617,7 @@ __global__ __launch_bounds__(kSeedThreads, R == 0 || R > 24 ? 4 : R > 16 ? 6 : 8
   int phase = 0;
   float* rw = srw + ((size_t)ql * UL + urel) * d.cap;
   if constexpr (R > 0) {
-    seed_rewards_regs<R>(d, base, n, last_new, rw, reinterpret_cast<int*>(smem), rb, phase, sh, tid);
+    seed_rewards_regs<R>(d, base, n, last_new, rw, reinterpret_cast<int*>(smem), rb, phase, tid);
   } else {
     float* val = reinterpret_cast<float*>(smem);
     for (int i = tid; i < n; i += kSeedThreads) val[i] = rw[i];
