@@ -16,6 +16,7 @@
 
 #include "ckv_books.h"
 #include "ckv_kernels.h"
+#include "ckv_layer_kernel.h"
 #include "ckv_unit_kernel.h"
 
 using namespace ckv;
@@ -44,7 +45,7 @@ struct ckv_ctx {
   float* seedmi = nullptr;      // workspace of the prompt replay
   float* seedrw = nullptr;
   int device = 0;               // the HIP device the context was created on
-  size_t finish_lds = 0;
+  size_t finish_lds = 0, layer_lds = 0;
   // fused path (unit_kernel)
   int path_mode = 0;            // 0 auto, 1 separate kernels, 2 fused kernel, 3 / 4 fused with 4 / 2 wavefronts per unit
   struct Fused {                // one variant of the fused kernel
@@ -315,32 +316,36 @@ bool leave_many_pays(const ckv_ctx* c, int count, bool deferred) {
   return count <= 5 * c->n_cu;
 }
 
-// The bookkeeping of `count` units from `begin` on, behind their scan.  Workgroups of 256 threads where no unit can
+// The deferred bookkeeping of `count` units from `begin` on, behind their scan.  Workgroups of 256 threads where no unit can
 // hold more than eight entries per thread, else 1024.
-int launch_finish(ckv_ctx* c, hipStream_t s, int begin, int count, uint32_t flags, int advance, int layer_time) {
+int launch_finish(ckv_ctx* c, hipStream_t s, int begin, int count, uint32_t flags) {
   if (c->lay.cap <= 8 * kThreads)
-    hipLaunchKernelGGL(finish_kernel<kThreads>, dim3((unsigned)count), dim3(kThreads), c->finish_lds, s, c->dev, begin, flags, advance, layer_time);
+    hipLaunchKernelGGL(finish_kernel<kThreads>, dim3((unsigned)count), dim3(kThreads), c->finish_lds, s, c->dev, begin, flags);
   else
-    hipLaunchKernelGGL(finish_kernel<kWideThreads>, dim3((unsigned)count), dim3(kWideThreads), c->finish_lds, s, c->dev, begin, flags, advance, layer_time);
+    hipLaunchKernelGGL(finish_kernel<kWideThreads>, dim3((unsigned)count), dim3(kWideThreads), c->finish_lds, s, c->dev, begin, flags);
   CKV_HIP(c, hipGetLastError());
   return CKV_OK;
 }
 
-// Attention of `count` units from `begin` on, the new entries included.  Workgroups of eight wavefronts, each over one
-// block of 32 entries or over a chunk of 256.  One block each is a single round trip to memory and decides what the
-// smallest layers wait for; it needs eight times the workgroups, whose starts and partials cost more than they save
-// once they no longer fit the chip side by side.  The line lies at two workgroups per compute unit by the entries that
-// the budgets allow (us per layer, scan alone, one block / one chunk: 8 units of 2048 entries 10 / 23, 32 units 17 / 25,
-// 64 units of 1024 12 / 15, 64 units of 2048 25 / 28, 128 units of 2048 41 / 34, 256 units of 1024 32 / 28).
-int launch_layer_scan(ckv_ctx* c, hipStream_t s, int begin, int count, const uint16_t* q, const uint16_t* k_new, const uint16_t* v_new, void* out,
-                      int logits, int defer_layer, int advance) {
-  const int mc = c->dev.max_chunks;
-  if (c->budget_total / c->units * count <= 2ll * c->n_cu * kChunk)
-    hipLaunchKernelGGL((layer_scan_kernel<8, 8>), dim3((unsigned)count, (unsigned)mc), dim3(512), 0, s, c->dev, begin, q, k_new, v_new, out, logits,
-                       defer_layer, advance);
-  else
-    hipLaunchKernelGGL((layer_scan_kernel<8, 1>), dim3((unsigned)count, (unsigned)((mc + 7) / 8)), dim3(512), 0, s, c->dev, begin, q, k_new, v_new, out,
-                       logits, defer_layer, advance);
+// A step of `count` units from `begin` on (or its scan, or attention alone: `mode`).  A block of 32 entries per wavefront while two
+// workgroups per compute unit cover the entries that the budgets allow, else eight (figures at the kernel).
+int launch_layer_step(ckv_ctx* c, hipStream_t s, int begin, int count, const uint16_t* q, const uint16_t* k_new, const uint16_t* v_new, void* out,
+                      uint32_t flags, int mode, int advance) {
+  const int upl = c->units_per_layer, cap = c->lay.cap;
+  const LayerCall call{q, k_new, v_new, out, begin, flags, mode, begin / upl, count / upl, advance};
+  auto go = [&](auto one_block, auto entries) {
+    constexpr bool kOne = decltype(one_block)::value;
+    constexpr int kRmax = decltype(entries)::value, kPer = kLayerThreads / 64 * kBlk * (kOne ? 1 : kChunkBlocks);
+    hipLaunchKernelGGL((layer_step_kernel<kOne, kRmax>), dim3((unsigned)count, (unsigned)((cap + kPer - 1) / kPer)), dim3(kLayerThreads),
+                       kRmax ? c->layer_lds : (size_t)kLayerScanLds, s, c->dev, call);
+  };
+  auto by_length = [&](auto one_block) {
+    if (mode != kWholeStep) go(one_block, std::integral_constant<int, 0>{});
+    else if (cap <= 4 * kLayerThreads) go(one_block, std::integral_constant<int, 4>{});
+    else go(one_block, std::integral_constant<int, 12>{});
+  };
+  if (c->budget_total / c->units * count <= 2ll * c->n_cu * kChunk) by_length(std::true_type{});
+  else by_length(std::false_type{});
   CKV_HIP(c, hipGetLastError());
   return CKV_OK;
 }
@@ -354,7 +359,7 @@ int flush_group(ckv_ctx* c) {
   CKV_HIP(c, hipEventRecord(c->ev_out, c->group_stream));
   hipStream_t side = c->side[c->group_launches++ % kSide];
   CKV_HIP(c, hipStreamWaitEvent(side, c->ev_out, 0));
-  if (int rc = launch_finish(c, side, first * upl, count * upl, c->group_flags, 0, 1)) return rc;
+  if (int rc = launch_finish(c, side, first * upl, count * upl, c->group_flags)) return rc;
   if (c->group_flags & kLeaveMany)
     if (int rc = launch_evict(c, side, first * upl, count * upl, -1, 1)) return rc;
   CKV_HIP(c, hipEventRecord(c->ev_book[first], side));
@@ -548,6 +553,15 @@ int ckv_init(ckv_ctx** out, const ckv_layout* layout, const int32_t* budgets, co
   if (c->finish_lds + 12288 > (size_t)max_lds) {   // static LDS of the kernels stays below 12 KB
     delete c;
     return CKV_EINVAL;
+  }
+  c->layer_lds = std::max((size_t)kLayerScanLds, c->finish_lds);
+  const void* layer_kernels[4] = {reinterpret_cast<const void*>(layer_step_kernel<false, 4>), reinterpret_cast<const void*>(layer_step_kernel<true, 4>),
+                                  reinterpret_cast<const void*>(layer_step_kernel<false, 12>), reinterpret_cast<const void*>(layer_step_kernel<true, 12>)};
+  for (const void* fn : layer_kernels) {
+    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)c->layer_lds) != hipSuccess) {
+      delete c;
+      return CKV_EHIP;
+    }
   }
   const void* lds_kernels[3] = {reinterpret_cast<const void*>(finish_kernel<kThreads>), reinterpret_cast<const void*>(finish_kernel<kWideThreads>),
                                 reinterpret_cast<const void*>(seed_hits_kernel<0>)};
@@ -786,7 +800,8 @@ int ckv_decode_step(ckv_ctx* c, int32_t layer, const void* q, const void* k_new,
       if (int rc = profile_events(c, &e0, &e1)) return rc;
       CKV_HIP(c, hipEventRecord(e0, s));
     }
-    if (int rc = launch_layer_scan(c, s, begin, count, (const uint16_t*)q, (const uint16_t*)k_new, (const uint16_t*)v_new, out, 1, (int)layer, advance)) return rc;
+    if (int rc = launch_layer_step(c, s, begin, count, (const uint16_t*)q, (const uint16_t*)k_new, (const uint16_t*)v_new, out, flags, kScanOnly, advance))
+      return rc;
     if (c->profile) CKV_HIP(c, hipEventRecord(e1, s));
     const uint32_t kflags = flags & (CKV_FUSE_EVICT | kLeaveMany);
     if (c->group_count && (c->group_flags != kflags || c->group_stream != s || c->group_first + c->group_count != layer))
@@ -829,18 +844,16 @@ int ckv_decode_step(ckv_ctx* c, int32_t layer, const void* q, const void* k_new,
     if (advance && (flags & CKV_FUSE_EVICT)) return rebalance_after_eviction(c);
     return CKV_OK;
   }
-  // Few units: several workgroups per unit attend and write the output, then the bookkeeping (or, without it, what
-  // the append leaves behind).
-  const bool attention_only = (flags & CKV_ATTENTION_ONLY) != 0;
-  if (int rc = launch_layer_scan(c, s, begin, count, (const uint16_t*)q, (const uint16_t*)k_new, (const uint16_t*)v_new, out, attention_only ? 0 : 1, -1, 0))
-    return rc;
+  // Few units: several workgroups per unit, the bookkeeping in the same kernel by a unit's last one of 512 threads, where units
+  // cannot be long; else in a kernel of its own by 1024 (us per layer, captured, one kernel / two: 64 units of 1024 entries on
+  // average, up to 4096, 32 / 31, 256 such units 51 / 54; 128 of 4096, fixed, 74 / 78; 2 of 6000 23 / 26; 64 of 2048, up to 8192, 51 / 44, 128
+  // such units 56 / 53, 16 of 8000, up to 32000, 104 / 76).
+  const int mode = (flags & CKV_ATTENTION_ONLY) ? kAttend : c->lay.cap <= 12 * kLayerThreads ? kWholeStep : kScanOnly;
+  const uint32_t kflags = flags & (CKV_FUSE_EVICT | kLeaveMany);
+  if (int rc = launch_layer_step(c, s, begin, count, (const uint16_t*)q, (const uint16_t*)k_new, (const uint16_t*)v_new, out, kflags, mode, advance)) return rc;
   if (c->profile) CKV_HIP(c, hipEventRecord(e1, s));
-  if (attention_only) {
-    hipLaunchKernelGGL(append_kernel, dim3(1), dim3(kWideThreads), 0, s, c->dev, begin, count, advance);
-    CKV_HIP(c, hipGetLastError());
-    return CKV_OK;
-  }
-  if (int rc = launch_finish(c, s, begin, count, flags & (CKV_FUSE_EVICT | kLeaveMany), advance, 0)) return rc;
+  if (mode == kScanOnly)
+    if (int rc = launch_finish(c, s, begin, count, kflags)) return rc;
   if (flags & kLeaveMany)
     if (int rc = launch_evict(c, s, begin, count, -1, 1)) return rc;
   if (advance && (flags & CKV_FUSE_EVICT)) return rebalance_after_eviction(c);

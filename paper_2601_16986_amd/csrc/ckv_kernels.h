@@ -185,6 +185,7 @@ template <int NT>
 struct alignas(16) RedBuf {
   u64 v[2][NT / 64];    // one slot per wavefront
   float t[2][NT / 64][4];
+  int i[2][NT >= 512 ? NT / 64 : 1];
 };
 
 template <int NT>
@@ -330,6 +331,43 @@ __device__ __forceinline__ u64 block_min_u64(u64 v, RedBuf<NT>& rb, int& phase, 
   }
   phase ^= 1;
   return r;
+}
+
+// The sum of `sum`, the smallest `key`, which comes back in every thread, and the `index` that came with it, in one barrier.
+template <int NT>
+__device__ __forceinline__ u64 block_sum_min(u64 sum, u64& key, int index, int& at, RedBuf<NT>& rb, int& phase, int tid) {
+  constexpr int W = NT / 64;
+  sum = wave_sum_u64(sum);
+  const u64 least = wave_min_u64(key);
+  const int mine = __builtin_amdgcn_readlane(index, __builtin_ctzll(__ballot(key == least)));
+  if ((tid & 63) == 0) {
+    *reinterpret_cast<u64*>(&rb.t[phase][tid >> 6][0]) = sum;
+    *reinterpret_cast<u64*>(&rb.t[phase][tid >> 6][2]) = least;
+    rb.i[phase][tid >> 6] = mine;
+  }
+  block_sync<NT>(rb);
+  const int w = tid & (W - 1);                     // lane l looks at wavefront l % W
+  sum = *reinterpret_cast<const u64*>(&rb.t[phase][w][0]);
+  key = *reinterpret_cast<const u64*>(&rb.t[phase][w][2]);
+  const int there = rb.i[phase][w];
+  const u64 own = key;
+  sum += dpp_u64<kDppQuadSwap1>(sum);
+  key = min_u64(key, dpp_u64<kDppQuadSwap1>(key));
+  if constexpr (W >= 4) {
+    sum += dpp_u64<kDppQuadSwap2>(sum);
+    key = min_u64(key, dpp_u64<kDppQuadSwap2>(key));
+  }
+  if constexpr (W >= 8) {
+    sum += dpp_u64<kDppRowHalfMirror>(sum);
+    key = min_u64(key, dpp_u64<kDppRowHalfMirror>(key));
+  }
+  if constexpr (W >= 16) {
+    sum += dpp_u64<kDppRowMirror>(sum);
+    key = min_u64(key, dpp_u64<kDppRowMirror>(key));
+  }
+  at = __builtin_amdgcn_readlane(there, __builtin_ctzll(__ballot(own == key)));
+  phase ^= 1;
+  return sum;
 }
 
 // ------------------------------------------------------------------ fill
@@ -529,6 +567,34 @@ __global__ __launch_bounds__(kThreads) void load_cache_kernel(Dev d, int unit_be
   }
 }
 
+// Stores and loads that are coherent across the chip's L2 caches one by one (no cache-wide write-back or
+// invalidation, which a fence at that scope would cost every workgroup): how a scan hands its partials from the
+// workgroups that wrote them to the one that combines them.
+template <class T>
+__device__ __forceinline__ void put_coherent(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class T>
+__device__ __forceinline__ T get_coherent(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Sixteen bytes at once: buffer accesses with the cache policy bit (sc1) of those loads and stores, which the language has no atomic
+// of that size for.  (The four words may arrive apart, which nobody sees who waits for the count.)  The array's base and
+// size are the same in all lanes, `at` counts floats and is a multiple of 4.
+constexpr int kSc1 = 16;
+typedef __amdgpu_buffer_rsrc_t Buffer;
+__device__ __forceinline__ Buffer buffer_of(float* base, int floats) { return __builtin_amdgcn_make_buffer_rsrc(base, 0, floats * 4, 0x00027000); }
+__device__ __forceinline__ void put_coherent16(Buffer b, int at, f32x4 v) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), b, at * 4, 0, kSc1);
+}
+template <int kPolicy>
+__device__ __forceinline__ f32x4 get_f32x4(Buffer b, int at) {
+  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(b, at * 4, 0, kPolicy));
+}
+__device__ __forceinline__ u64 pack_f32(float a, float b) { return ((u64)__float_as_uint(b) << 32) | __float_as_uint(a); }
+__device__ __forceinline__ float low_f32(u64 x) { return __uint_as_float((uint32_t)x); }
+__device__ __forceinline__ float high_f32(u64 x) { return __uint_as_float((uint32_t)(x >> 32)); }
+
 // ------------------------------------------------------------------ scan
 struct KFrag {
   u32x4 k[8];
@@ -565,8 +631,15 @@ constexpr int kLgRow = 36;     // floats per head row in the LDS tile (32 + pad 
 // First half of a block of 32 entries: logits on the matrix cores, masked and
 // scaled into sv[8] (this lane's 4 + 4 entries), and sent on their way to the
 // finish phase.  The K fragment is dead afterwards.
+// `forward`, if it is true, takes a block's logits to memory: lane l < 8 G the four at 4 l of the block's [head][32].
+struct LogitsOut {
+  float* dst;          // the span's logits, this lane's four of the first block
+  __device__ __forceinline__ explicit operator bool() const { return dst != nullptr; }
+  __device__ __forceinline__ void operator()(int first, f32x4 row) const { *reinterpret_cast<f32x4*>(dst + first) = row; }
+};
+template <class Forward>
 __device__ __forceinline__ void scan_qk(const KFrag& f, const bf16x8 (&qv)[4], float (&sv)[8], float c_scale, int e_base,
-                                        int n_valid, float* lds_lg, int lds_row, float* lg_dst, int G, int lane) {
+                                        int n_valid, float* lds_lg, int lds_row, Forward forward, int G, int lane) {
   const int j = lane & 15, kg = lane >> 4;
   f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -579,19 +652,16 @@ __device__ __forceinline__ void scan_qk(const KFrag& f, const bf16x8 (&qv)[4], f
     sv[4 + v] = (e_base + 4 * kg + 16 + v < n_valid) ? s1[v] * c_scale : -INFINITY;
   }
   // logits: row j of the LDS buffer (a wave-private staging tile, or the block's
-  // place in a resident logits tile); with lg_dst the tile is forwarded to memory
+  // place in a resident logits tile); with `forward` the tile goes on to memory
   // as one contiguous 128 G-byte store
   if (lds_lg == nullptr) return;            // attention only: nobody looks at the logits afterwards
   if (j < G) {
     *reinterpret_cast<f32x4*>(lds_lg + j * lds_row + 4 * kg) = f32x4{sv[0], sv[1], sv[2], sv[3]};
     *reinterpret_cast<f32x4*>(lds_lg + j * lds_row + 16 + 4 * kg) = f32x4{sv[4], sv[5], sv[6], sv[7]};
   }
-  if (lg_dst) {
+  if (forward) {
     __builtin_amdgcn_wave_barrier();
-    if (lane < 8 * G) {
-      const f32x4 row = *reinterpret_cast<const f32x4*>(lds_lg + (lane >> 3) * lds_row + 4 * (lane & 7));
-      *reinterpret_cast<f32x4*>(lg_dst + e_base * G) = row;
-    }
+    if (lane < 8 * G) forward(e_base * G, *reinterpret_cast<const f32x4*>(lds_lg + (lane >> 3) * lds_row + 4 * (lane & 7)));
     __builtin_amdgcn_wave_barrier();
   }
 }
@@ -649,363 +719,6 @@ __device__ __forceinline__ void scan_pv(const float (&sv)[8], const VFrag& fv, f
       acc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ph, as_bf16x8(fv.v[dt]), acc[dt], 0, 0, 0);
       acc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pl, as_bf16x8(fv.v[dt]), acc[dt], 0, 0, 0);
     }
-  }
-}
-
-// Stores and loads that are coherent across the chip's L2 caches one by one (no cache-wide write-back or
-// invalidation, which a fence at that scope would cost every workgroup): how a scan hands its partials from the
-// workgroups that wrote them to the one that combines them.
-template <class T>
-__device__ __forceinline__ void put_coherent(T* p, T v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <class T>
-__device__ __forceinline__ T get_coherent(const T* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// ------------------------------------------------------------------ scan of few units, which appends by itself
-// The shape a model imposes is one call per layer, a few hundred units at most: too few for the fused kernel
-// (one workgroup per unit).  Here several workgroups share a unit and the grid itself is the work list: workgroup (x, y) takes the y-th few chunks (256 entries each) of the layer's unit x and leaves at once if the unit is shorter.  (Units along x: consecutive
-// workgroups go to different XCDs, so the workgroups that have work - every unit's first, most units' second -
-// spread over all of them; with the chunk groups along x, and eight or a multiple of them, each XCD would get
-// one group index, the first few all the work, and a step takes 1.6 times as long.)  Nothing has to run before it:
-// every workgroup derives the unit's length after the append from the stored one (which stays as it is until
-// finish_kernel or append_kernel, which follows, has recorded the append), and the wavefront whose
-// chunk receives the new entry puts its key and value rows into the block it has just loaded (and into the
-// cache), so that the entry takes part like any cached one.  The wavefronts combine their softmax states
-// in LDS; a unit of one workgroup is finished there and then, a longer one goes through
-// one partial per workgroup, merged by the workgroup that publishes the last (coherent stores and loads).  The unit's softmax maximum and 1 / sum per head stay in `msum` for the bookkeeping.
-// In place of a kernel that appended and built a work list, a persistent scan over it and a merge of its partials by the
-// bookkeeping kernel: 7.6 + 35 us per layer of the 14B geometry then, 36 us now.
-// defer_layer >= 0: the bookkeeping follows on another stream, perhaps after the time has moved on; the step's time
-// is left for it, and moves on here if `advance` says that this was the step's last layer (nothing else in
-// this launch reads it).  logits = 0: attention only, nobody looks at the logits afterwards.
-// kW wavefronts per workgroup, each over 1 / kSplit of a chunk; in use are <8, 1> (eight chunks per workgroup, the
-// blocks of a chunk streamed one ahead) and, for few units, <8, 8> (one chunk per workgroup, a block per wavefront; at
-// most kW = 8 wavefronts may share a chunk, a unit has one partial slot per chunk).  Also measured, us per layer, scan
-// alone, on 8 units / 128 units of 2048 entries on average (257 .. 8193) / 256 units of 1024: <8, 8> 10 / 41 / 32;
-// <16, 8> 11 / 45 / 36; <8, 4> 11 / 45 / 36; <4, 4> 11 / 39 / 31; <4, 2> 12 / 40 / 34; <4, 1> 15 / 36 / 32 (15 % more
-// without unused LDS that keeps a third workgroup off a compute unit); <8, 1> 23 / 34 / 28; <16, 2> 36 / 51 / 40;
-// <16, 1> 49 / 68 / 41.
-// grid: (units of the layer, ceil(max_chunks * kSplit / kW)), 64 kW threads.
-
-// Entry rr of the block in (ka, va) is replaced by the rows in `rows` (LDS: 128 bf16 of the key, then 128 of the
-// value), piece by piece, so that few registers are live at a time.
-__device__ __forceinline__ void inject_entry(KFrag& ka, VFrag& va, int rr, const uint16_t* rows, int lane) {
-  const int j = lane & 15, kg = lane >> 4;
-  const int tt = rr >> 4;
-  const bool krow = j == (rr & 15);
-#pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    const u32x4 kn = *reinterpret_cast<const u32x4*>(rows + 32 * s + 8 * kg);
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-      if (krow && h == tt) ka.k[h * 4 + s] = kn;
-  }
-  const bool vrow = kg == ((rr & 15) >> 2);
-  const int e = tt * 4 + (rr & 3);
-#pragma unroll
-  for (int dt = 0; dt < 8; ++dt) {
-    const uint32_t vn = rows[kDim + 16 * dt + j];
-#pragma unroll
-    for (int wi = 0; wi < 4; ++wi) {
-      const uint32_t old = va.v[dt][wi];
-      const uint32_t nw = (e & 1) ? ((old & 0x0000FFFFu) | (vn << 16)) : ((old & 0xFFFF0000u) | vn);
-      va.v[dt][wi] = (vrow && wi == (e >> 1)) ? nw : old;
-    }
-  }
-}
-
-template <int kW, int kSplit>
-__global__ __launch_bounds__(64 * kW, kSplit >= 4 ? 2 : 3) void layer_scan_kernel(Dev d, int unit_begin, const uint16_t* __restrict__ q,
-                                                                const uint16_t* __restrict__ k_new,
-                                                                const uint16_t* __restrict__ v_new, void* out, int logits,
-                                                                int defer_layer, int advance) {
-  constexpr int kT = 64 * kW;
-  constexpr int kSpanBlk = kChunkBlocks / kSplit, kSpan = kSpanBlk * kBlk;      // blocks and entries one wavefront takes
-  __shared__ float s_lg[kW][kMaxGroup * kLgRow];
-  __shared__ float s_m[kW][kMaxGroup], s_l[kW][kMaxGroup];
-  __shared__ float s_acc[kW][kMaxGroup * kDim];
-  __shared__ float s_w[2 * kMaxChunks * kMaxGroup], s_M[kMaxGroup], s_L[kMaxGroup];
-  __shared__ __align__(16) uint16_t s_new[kW][2 * kDim];
-  __shared__ int s_last;
-  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int urel = blockIdx.x, u = unit_begin + urel, cg = blockIdx.y;
-  const int G = d.G;
-  const int n_old = d.n[u];
-  // this wavefront's span lies in one pool segment (asked for beside the length: neither waits for the other)
-  const int c = cg * kW + w;
-  const int my_seg = d.tbl[(size_t)u * d.max_seg + min(c / kSplit, d.max_seg - 1)];
-  const bool full = n_old >= unit_cap(d, u);
-  const int n = n_old + (full ? 0 : 1);
-  const int nch = (n + kSpan - 1) / kSpan;          // spans of the unit
-  if (cg == 0 && tid == 0) {
-    if (urel == 0 && defer_layer >= 0) {
-      const int t = d.sc[SC_T];
-      d.layer_ts[defer_layer] = t;
-      if (advance) {
-        d.sc[SC_T] = t + 1;
-        d.sc[SC_WINDOW_STEPS] = d.sc[SC_WINDOW_STEPS] + 1;
-      }
-    }
-    if (full) atomicOr(&d.sc[SC_STATUS], 1);
-  }
-  if (cg * kW >= nch) return;
-  const int nwg = (nch + kW - 1) / kW;
-  const int j = lane & 15, kg = lane >> 4;
-  const bool head_lane = j < G;
-  f32x4 acc[8];
-#pragma unroll
-  for (int dt = 0; dt < 8; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m_run = -INFINITY, l_run = 0.f;
-  if (c < nch) {
-    const int e0 = c * kSpan;
-    const int s0 = (c % kSplit) * kSpan;                                  // the span's first slot within its segment
-    const int nv = min(n - e0, kSpan);
-    const int nb = (nv + kBlk - 1) / kBlk;
-    const bool inject = !full && n_old >= e0 && n_old < e0 + kSpan;      // the new entry is then the span's last: entry nv - 1
-    const size_t off = (size_t)my_seg * kSegElems + (size_t)(c % kSplit) * kSpanBlk * kBlkElems + lane * 8;
-    const uint16_t* kcur = d.K + off;
-    const uint16_t* vcur = d.V + off;
-    // a span of one or two blocks is requested whole, a longer one block by block
-    constexpr int kAhead = kSpanBlk <= 2 ? kSpanBlk : 1;
-    KFrag ka[kAhead];
-    VFrag va[kAhead];
-#pragma unroll
-    for (int i = 0; i < kAhead; ++i) load_k(ka[i], kcur + (size_t)min(i, nb - 1) * kBlkElems);
-#pragma unroll
-    for (int i = 0; i < kAhead; ++i) load_v(va[i], vcur + (size_t)min(i, nb - 1) * kBlkElems);
-    bf16x8 qv[4];
-    {
-      const uint16_t* qrow = q + ((size_t)urel * G + (head_lane ? j : 0)) * kDim + 8 * kg;
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        u32x4 x = *reinterpret_cast<const u32x4*>(qrow + 32 * s);
-        if (!head_lane) x = u32x4{0u, 0u, 0u, 0u};
-        qv[s] = as_bf16x8(x);
-      }
-    }
-    // The new entry's rows wait in LDS for their block's turn (the span's last): held in registers through the
-    // loop they would cost the kernel a third wavefront per SIMD.  They also go into the cache, where the next
-    // step finds them.
-    if (inject) {
-      const int row = s0 + n_old - e0;                          // n_old lies in this span
-      if (lane < 32) {
-        const int piece = lane & 15;
-        const uint16_t* src = (lane < 16 ? k_new : v_new) + (size_t)urel * kDim + piece * 8;
-        const u32x4 x = *reinterpret_cast<const u32x4*>(src);
-        *reinterpret_cast<u32x4*>(&s_new[w][(lane < 16 ? 0 : kDim) + piece * 8]) = x;
-        if (lane < 16) *reinterpret_cast<u32x4*>(d.K + (size_t)my_seg * kSegElems + k_offset(row, piece * 8)) = x;
-      }
-      uint16_t* vdst = d.V + (size_t)my_seg * kSegElems;
-      vdst[v_offset(row, lane)] = v_new[(size_t)urel * kDim + lane];
-      vdst[v_offset(row, lane + 64)] = v_new[(size_t)urel * kDim + lane + 64];
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    }
-    float* lds_lg = logits ? s_lg[w] : nullptr;
-    float* lg_dst = d.logits + ((size_t)u * d.cap + (size_t)e0) * G + 4 * min(lane, 8 * G - 1);
-    if constexpr (kAhead == kSpanBlk) {
-#pragma unroll
-      for (int blk = 0; blk < kSpanBlk; ++blk) {
-        if (blk < nb) {
-          if (blk + 1 == nb && inject) {
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            inject_entry(ka[blk], va[blk], (n_old - e0) & 31, s_new[w], lane);
-          }
-          float sv[8];
-          scan_qk(ka[blk], qv, sv, d.scale_log2e, blk * kBlk, nv, lds_lg, kLgRow, lg_dst, G, lane);
-          scan_pv(sv, va[blk], acc, m_run, l_run, lane);
-        }
-      }
-    } else {
-      // one block ahead (two ahead is slower here as well); the loads stay unconditional (the
-      // last block is read twice), so that the waits the compiler inserts are exact
-      for (int blk = 0; blk < nb; ++blk) {
-        const bool last = blk + 1 == nb;
-        const size_t nxt = (size_t)(last ? blk : blk + 1) * kBlkElems;
-        if (last && inject) {
-          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-          inject_entry(ka[0], va[0], (n_old - e0) & 31, s_new[w], lane);
-        }
-        float sv[8];
-        scan_qk(ka[0], qv, sv, d.scale_log2e, blk * kBlk, nv, lds_lg, kLgRow, lg_dst, G, lane);
-        load_k(ka[0], kcur + nxt);
-        scan_pv(sv, va[0], acc, m_run, l_run, lane);
-        load_v(va[0], vcur + nxt);
-      }
-    }
-    l_run += __shfl_xor(l_run, 16);
-    l_run += __shfl_xor(l_run, 32);
-  }
-  // ---- the workgroup's states into one
-  if (head_lane && kg == 0) {
-    s_m[w][j] = m_run;
-    s_l[w][j] = l_run;
-  }
-  if (c < nch) {
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int head = 4 * kg + v;
-      if (head < G) {
-#pragma unroll
-        for (int dt = 0; dt < 8; ++dt) s_acc[w][head * kDim + 16 * dt + j] = acc[dt][v];
-      }
-    }
-  }
-  __syncthreads();
-  const size_t slot0 = (size_t)u * d.slots;
-  constexpr int kPer = (kMaxGroup * kDim) / kT;      // (head, dim) pairs per thread
-  float o[kPer], Mg[kPer], Lg[kPer];
-#pragma unroll
-  for (int k = 0; k < kPer; ++k) {
-    const int e = tid + k * kT, g = e >> 7;
-    o[k] = 0.f;
-    Mg[k] = -INFINITY;
-    Lg[k] = 0.f;
-    if (g < G) {
-      float M = -INFINITY;
-#pragma unroll
-      for (int ww = 0; ww < kW; ++ww) M = fmaxf(M, s_m[ww][g]);
-#pragma unroll
-      for (int ww = 0; ww < kW; ++ww) {
-        const float m = s_m[ww][g];
-        if (m > -INFINITY) {
-          const float wt = fast_exp2(m - M);
-          o[k] += s_acc[ww][e] * wt;
-          Lg[k] += s_l[ww][g] * wt;
-        }
-      }
-      Mg[k] = M;
-    }
-  }
-  auto write_out = [&](int k, float val, float M, float L) {
-    const int e = tid + k * kT, g = e >> 7, dim = e & 127;
-    const float inv = 1.0f / L;
-    const float ov = val * inv;
-    const size_t oi = ((size_t)urel * G + g) * kDim + dim;
-    if (d.out_bf16)
-      reinterpret_cast<__bf16*>(out)[oi] = (__bf16)ov;
-    else
-      reinterpret_cast<float*>(out)[oi] = ov;
-    if (dim == 0) {
-      d.msum[((size_t)u * kMaxGroup + g) * 2] = M;
-      d.msum[((size_t)u * kMaxGroup + g) * 2 + 1] = inv;
-    }
-  };
-  if (nwg == 1) {
-#pragma unroll
-    for (int k = 0; k < kPer; ++k)
-      if (((tid + k * kT) >> 7) < G) write_out(k, o[k], Mg[k], Lg[k]);
-    return;
-  }
-  // ---- one partial per workgroup; the workgroup that publishes the unit's last one merges them
-#pragma unroll
-  for (int k = 0; k < kPer; ++k) {
-    const int e = tid + k * kT, g = e >> 7, dim = e & 127;
-    if (g < G) {
-      put_coherent(&d.partial[((slot0 + cg) * G + g) * kDim + dim], o[k]);
-      if (dim == 0) {
-        put_coherent(&d.ml[((slot0 + cg) * G + g) * 2], Mg[k]);
-        put_coherent(&d.ml[((slot0 + cg) * G + g) * 2 + 1], Lg[k]);
-      }
-    }
-  }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // the partial before the count (coherent stores: completed is enough)
-  __syncthreads();
-  if (tid == 0) {
-    const int lastone = atomicAdd(&d.arrive[u], 1) == nwg - 1;
-    if (lastone) __hip_atomic_store(&d.arrive[u], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    s_last = lastone;
-  }
-  __syncthreads();
-  if (!s_last) return;
-  // the partials' values are asked for first, kRound partials at a time; their maxima and sums go through LDS,
-  // where every head's overall maximum, the partials' weights and the sum's reciprocal are formed once
-  constexpr int kRound = 32 / kPer < 8 ? 32 / kPer : 8;
-  static_assert(kW >= kSplit, "a unit has one partial slot per chunk");
-  float x[kRound][kPer];
-  auto request = [&](int r0) {
-#pragma unroll
-    for (int i = 0; i < kRound; ++i) {
-      const size_t sl = slot0 + min(r0 + i, nwg - 1);
-#pragma unroll
-      for (int k = 0; k < kPer; ++k) {
-        const int e = tid + k * kT, g = e >> 7, dim = e & 127;
-        x[i][k] = get_coherent(&d.partial[(sl * G + min(g, G - 1)) * kDim + dim]);
-      }
-    }
-  };
-  request(0);
-  float* sW = s_w;
-  float* sL = s_w + kMaxChunks * kMaxGroup;
-  for (int i = tid; i < nwg * kMaxGroup; i += kT) {
-    const int sidx = i >> 3, g = i & 7;
-    const float* mlp = d.ml + ((slot0 + sidx) * G + min(g, G - 1)) * 2;
-    const float m = get_coherent(mlp), l = get_coherent(mlp + 1);
-    sW[i] = g < G ? m : -INFINITY;
-    sL[i] = g < G ? l : 0.f;
-  }
-  __syncthreads();
-  if (tid < kMaxGroup) {
-    float M = -INFINITY;
-    for (int r = 0; r < nwg; ++r) M = fmaxf(M, sW[r * kMaxGroup + tid]);
-    s_M[tid] = M;
-  }
-  __syncthreads();
-  for (int i = tid; i < nwg * kMaxGroup; i += kT) {
-    const float m = sW[i];
-    sW[i] = m > -INFINITY ? fast_exp2(m - s_M[i & 7]) : 0.f;
-  }
-  __syncthreads();
-  if (tid < kMaxGroup) {
-    float L = 0.f;
-    for (int r = 0; r < nwg; ++r) L += sL[r * kMaxGroup + tid] * sW[r * kMaxGroup + tid];
-    s_L[tid] = L;
-  }
-  __syncthreads();
-  float val[kPer];
-#pragma unroll
-  for (int k = 0; k < kPer; ++k) val[k] = 0.f;
-  for (int r0 = 0; r0 < nwg; r0 += kRound) {
-#pragma unroll
-    for (int i = 0; i < kRound; ++i) {
-      if (r0 + i < nwg) {
-#pragma unroll
-        for (int k = 0; k < kPer; ++k) {
-          const float wt = sW[(r0 + i) * kMaxGroup + ((tid + k * kT) >> 7)];
-          if (wt != 0.f) val[k] += x[i][k] * wt;
-        }
-      }
-    }
-    if (r0 + kRound < nwg) request(r0 + kRound);
-  }
-#pragma unroll
-  for (int k = 0; k < kPer; ++k) {
-    const int g = (tid + k * kT) >> 7;
-    if (g < G) write_out(k, val[k], s_M[g], s_L[g]);
-  }
-}
-
-// What an attention-only step records of its append, behind layer_scan_kernel (whose late workgroups may still read a
-// unit's length, so it cannot do this itself): one workgroup over all units of the call.
-__global__ __launch_bounds__(kWideThreads) void append_kernel(Dev d, int unit_begin, int count, int advance) {
-  const int t = d.sc[SC_T];
-  for (int u = unit_begin + (int)threadIdx.x; u < unit_begin + count; u += kWideThreads) {
-    const int n = d.n[u];
-    if (n < unit_cap(d, u)) {
-      const size_t s = slots_of(d, u) + n;
-      d.crf[s] = 0.0f;
-      d.tau[s] = t;
-      d.pos[s] = t;
-      d.flags[s] = 0;
-      d.n[u] = n + 1;
-    }
-  }
-  __syncthreads();                                       // every wavefront has read the time
-  if (advance && threadIdx.x == 0) {
-    d.sc[SC_T] = t + 1;
-    d.sc[SC_WINDOW_STEPS] = d.sc[SC_WINDOW_STEPS] + 1;
   }
 }
 
@@ -1092,7 +805,7 @@ __device__ __forceinline__ void move_entries4(const Dev& d, Slots base, const in
 // Eviction of exactly one entry: the last slot's entry moves into the victim's
 // slot `dst`, whose position goes to the last slot, flagged as evicted.  The K
 // row, the V row and the per-slot state are handled by different wavefronts;
-// the state comes from sh[1..4] = {CRF bits, tau, position} of the last slot's
+// the state comes from sh[1..3] = {CRF bits, tau, position} of the last slot's
 // entry and the victim's position, so no per-slot array is read.
 // The K and V rows of the slot that will move are read ahead of time (load_row, by the wavefronts that
 // will store them), so that the eviction itself only stores.
@@ -1117,7 +830,7 @@ __device__ __forceinline__ EntryRow load_row(const Dev& d, Slots base, int src, 
 }
 
 template <int NT = kThreads>
-__device__ __forceinline__ void evict_one(const Dev& d, Slots base, int src, int dst, const int* sh, int tid, const EntryRow& row) {
+__device__ __forceinline__ void evict_one(const Dev& d, Slots base, int src, int dst, int dst_pos, const int* sh, int tid, const EntryRow& row) {
   const int wave = tid >> 6, lane = tid & 63;
   constexpr int W = NT / 64;
   uint16_t* K = d.K;
@@ -1135,7 +848,7 @@ __device__ __forceinline__ void evict_one(const Dev& d, Slots base, int src, int
       d.tau[base + dst] = sh[2];
       d.pos[base + dst] = sh[3];
     }
-    d.pos[base + src] = sh[4];                 // the victim's position (the last slot's own if that is the victim)
+    d.pos[base + src] = dst_pos;               // the victim's position (the last slot's own if that is the victim)
     d.flags[base + src] = FLAG_SLIP;
   }
 }
@@ -1793,6 +1506,12 @@ struct NoHook {
 struct NewEntry {
   const uint16_t* k_row;    // 128 bf16, or nullptr
   const uint16_t* v_row;
+  __device__ __forceinline__ bool there() const { return k_row != nullptr; }
+};
+// The same with the rows in the cache already (a scan that ran before put them there).
+struct NewInCache {
+  bool arrived;
+  __device__ __forceinline__ bool there() const { return arrived; }
 };
 
 template <int NT = kThreads>
@@ -1874,22 +1593,28 @@ __device__ __forceinline__ double bin_sum(u64 v, int i) {
   return (double)(uint32_t)(v >> kBinCount) * bin_edge(i) + (double)(v & ((1ull << kBinCount) - 1ull)) * bin_unit(i);
 }
 
-// lst: a TopBuf of LDS.  new_last_t >= 0: the unit's last entry is not in the cache and has this position.
-template <int R, int NT = kThreads>
-__device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, const float (&a)[R], int* lst, int new_last_t, RedBuf<NT>& rb, int& phase,
+__device__ __forceinline__ void clear_top(TopBuf& tb, int tid, int threads) {
+  for (int i = tid; i < (int)(sizeof(TopBuf) / 16); i += threads) reinterpret_cast<u32x4*>(&tb)[i] = u32x4{0u, 0u, 0u, 0u};
+}
+
+// tb: in LDS, CLEARED (and a barrier since), or where something else may lie.  new_last_t >= 0: the unit's last entry is not in
+// the cache, or not to be looked up there, and has this position.
+template <int R, int NT = kThreads, bool CLEARED = false>
+__device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, const float (&a)[R], TopBuf& tb, int new_last_t, RedBuf<NT>& rb, int& phase,
                                               int tid) {
   if (d.reward_mode != 0) return HitRule{0u, true, 0x7FFFFFFF};
   constexpr int kList = NT < 256 ? NT : 256;
-  TopBuf& tb = *reinterpret_cast<TopBuf*>(lst);
   const int lane = tid & 63, wave = tid >> 6;
   // (not known to the compiler as the same in every unit: kept in registers across the units of a persistent kernel it would be
   // spilled, and a reload is a wait for every load in flight)
   float top_p = d.top_p;
   asm volatile("" : "+s"(top_p));
   const double p = (double)top_p;
-  block_sync<NT>(rb);                               // whatever lay in the buffer has been read
-  for (int i = tid; i < (int)(sizeof(TopBuf) / 16); i += NT) reinterpret_cast<u32x4*>(&tb)[i] = u32x4{0u, 0u, 0u, 0u};
-  block_sync<NT>(rb);
+  if constexpr (!CLEARED) {
+    block_sync<NT>(rb);                             // whatever lay in the buffer has been read
+    clear_top(tb, tid, NT);
+    block_sync<NT>(rb);
+  }
   uint32_t largest = 0;
 #pragma unroll
   for (int k = 0; k < R; ++k) {
@@ -2019,14 +1744,14 @@ __device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, c
 
 // `after_step1` runs once between Step 1 and the score update (the fused kernel
 // picks up its queue claim there).
-template <int R, int CH, int CP, class Val, int NT = kThreads, class Hook = NoHook>
+template <int R, int CH, int CP, class Val, int NT = kThreads, bool TOP_CLEARED = false, class Hook = NoHook, class New = NewEntry>
 __device__ __forceinline__ void lrfu_regs(const Dev& d, int u, Slots base, int n, int B, int t, float (&a)[R], f32x4 (&crf)[CH],
                                           i32x4 (&tau)[CH], i32x4 (&ps)[CH], Val val, bool evict, uint32_t* evm, int* lst,
                                           int lst_cap, const float* s_tab, int s_tab_n, RedBuf<NT>& rb, int& phase, int* sh,
-                                          int tid, Hook after_step1 = Hook{}, NewEntry ne = NewEntry{nullptr, nullptr}) {
+                                          int tid, Hook after_step1 = Hook{}, New ne = New{}, TopBuf* top = nullptr) {
   constexpr int C = R / 4;
   static_assert(C % CH == 0 && CP <= CH, "groups come in chunks of CH");
-  const bool new_in_regs = ne.k_row != nullptr;          // uniform; implies that exactly one entry is evicted below
+  const bool new_last = ne.there();                      // uniform
 #pragma unroll
   for (int c = CP; c < CH; ++c) load_meta<NT>(d, base, n, t, c, tid, crf[c], tau[c], ps[c]);
   // what the end of the step would otherwise wait for: the unit's running sum, and the last slot's rows
@@ -2034,9 +1759,14 @@ __device__ __forceinline__ void lrfu_regs(const Dev& d, int u, Slots base, int n
   const u64 window0 = d.window[u];
   const bool evict_single = evict && n - B == 1;
   EntryRow last_row{{0u, 0u, 0u, 0u}, 0, 0};
-  if (evict_single) last_row = new_in_regs ? load_row_input<NT>(ne, tid) : load_row<NT>(d, base, n - 1, tid);
+  if (evict_single) {
+    if constexpr (std::is_same_v<New, NewEntry>)
+      last_row = new_last ? load_row_input<NT>(ne, tid) : load_row<NT>(d, base, n - 1, tid);
+    else
+      last_row = load_row<NT>(d, base, n - 1, tid);
+  }
   // ---- Step 1: top-p hit set as a threshold on the weight's bit pattern
-  const HitRule rule = top_p_regs<R, NT>(d, base, n, a, lst, new_in_regs ? t : -1, rb, phase, tid);
+  const HitRule rule = top_p_regs<R, NT, TOP_CLEARED>(d, base, n, a, TOP_CLEARED ? *top : *reinterpret_cast<TopBuf*>(lst), new_last ? t : -1, rb, phase, tid);
   after_step1();
   // ---- Steps 2-3: scores; a[k] becomes CRF_temp.  The candidate for Step 4 (lowest score, then
   // highest position) is tracked on the way.
@@ -2068,7 +1798,7 @@ __device__ __forceinline__ void lrfu_regs(const Dev& d, int u, Slots base, int n
     for (int e = 0; e < 4; ++e) {
       const int i = e0 + e;
       const bool ok = i < n;
-      const bool fresh = new_in_regs & (i == n - 1);                 // the new entry, not in the cache: CRF 0, tau = position = t
+      const bool fresh = new_last & (i == n - 1);                    // the new entry: CRF 0, tau = position = t
       const int pe = fresh ? t : ps[c][e];
       const float w = a[4 * cc + e];
       const float dec = fresh ? 1.0f : dec4[e];
@@ -2112,7 +1842,13 @@ __device__ __forceinline__ void lrfu_regs(const Dev& d, int u, Slots base, int n
       }
     }
   }
-  sfix = block_sum_u64<NT>(sfix, rb, phase, tid);
+  // one reduction for both (in the fused kernel, which holds the next unit's first blocks beside this, it costs registers)
+  constexpr bool kOneReduction = NT >= 512;
+  int victim = -1;
+  if (kOneReduction && evict_single)
+    sfix = block_sum_min<NT>(sfix, best, best_i, victim, rb, phase, tid);
+  else
+    sfix = block_sum_u64<NT>(sfix, rb, phase, tid);
   if (tid == 0) {
     d.window[u] = window0 + sfix;
     d.t_unit[u] = t;
@@ -2123,13 +1859,22 @@ __device__ __forceinline__ void lrfu_regs(const Dev& d, int u, Slots base, int n
     return;
   }
   if (evict_single) {
-    const u64 gbest = block_min_u64<NT>(best, rb, phase, tid);
-    if (best == gbest && best_i >= 0) {     // keys are unique: one writer
-      sh[0] = best_i;
-      sh[4] = ~(int)(uint32_t)best;         // the victim's position
+    int dst_pos;
+    if constexpr (kOneReduction) {
+      // (an entry has no key below the largest only if its score is a NaN of all ones: then the last one goes)
+      dst_pos = victim < 0 ? sh[3] : ~(int)(uint32_t)best;
+      victim = victim < 0 ? n - 1 : victim;
+    } else {
+      const u64 gbest = block_min_u64<NT>(best, rb, phase, tid);
+      if (best == gbest && best_i >= 0) {   // keys are unique: one writer
+        sh[0] = best_i;
+        sh[4] = ~(int)(uint32_t)best;       // the victim's position
+      }
+      block_sync<NT>(rb);
+      victim = sh[0];
+      dst_pos = sh[4];
     }
-    block_sync<NT>(rb);
-    evict_one<NT>(d, base, n - 1, sh[0], sh, tid, last_row);
+    evict_one<NT>(d, base, n - 1, victim, dst_pos, sh, tid, last_row);
     if (tid == 0) {
       d.n[u] = B;
       d.nev[u] = 1;
@@ -2145,47 +1890,84 @@ __device__ __forceinline__ void lrfu_regs(const Dev& d, int u, Slots base, int n
   }
 }
 
-// Mean weights of the unit's n entries from its logits (softmax maxima sM and reciprocal denominators
-// sInv per head in LDS), then Alg. 1 Steps 1-3 at time t and, if asked, Step 4.  One workgroup of NT threads with up
-// to 32 entries each (256 threads: up to 8).
-// val: n floats of LDS, evm: the eviction bit mask behind them.
-// sh: 4 + NT / 64 ints.
-template <int NT>
-__device__ __forceinline__ void unit_bookkeeping(const Dev& d, int u, Slots base, int n, int B, int t, LgView lv, const float* sM,
-                                                 const float* sInv, uint32_t call_flags, float* val, uint32_t* evm, const float* s_tab,
-                                                 int s_tab_n, RedBuf<NT>& rb, int& phase, int* sh, int tid) {
+// Bookkeeping (Alg. 1 Steps 1-4) of a unit of n <= RMAX NT entries by one workgroup, from its logits in memory: a chain of memory
+// round trips and block reductions, and what a whole step waits for.  So the entries' scores, times and positions and the first logits are asked for before
+// `merge` (the unit's output and softmax statistics, whose own loads are on their way), later logits two groups ahead.  ne: the unit's last
+// entry arrived in this step (its rows; what the cache says of it is not looked at), or nothing did.  COHERENT: the logits were written within
+// the same launch, perhaps on another XCD.  top: cleared.
+template <int NT, int RMAX, bool COHERENT, bool LEAN, class New, class Merge>
+__device__ __forceinline__ void finish_unit(const Dev& d, int u, Slots base, int n, int B, int t, const float* sM, const float* sInv, uint32_t call_flags,
+                                            float* val, uint32_t* evm, TopBuf* top, const float* s_tab, int s_tab_n, RedBuf<NT>& rb, int* sh, int tid,
+                                            New ne, Merge merge) {
+  int phase = 0;
+  const int G = d.G;
+  const Buffer logits = buffer_of(d.logits + (size_t)u * d.cap * G, d.cap * G);
   auto regs = [&](auto rc) {
-    constexpr int R = decltype(rc)::value, C = R / 4, CH = C < 2 ? C : 2;
-    float a[R];
-    mean_weights_regs<R, NT>(d, lv, n, sM, sInv, a, tid);
+    // 1024 threads have 128 registers each, and so have the 512 of a workgroup that shares its compute unit with another (LEAN)
+    constexpr int R = decltype(rc)::value, C = R / 4;
+    constexpr int CH = C <= 2 ? C : LEAN ? (C % 2 == 0 ? 2 : 1) : C <= 4 ? C : 4, CG = C < 2 || (LEAN && (C > 2 || NT < kWideThreads)) ? 1 : 2;
     f32x4 crf[CH];
     i32x4 tau[CH], ps[CH];
-    lrfu_regs<R, CH, 0, ValLinear, NT>(d, u, base, n, B, t, a, crf, tau, ps, ValLinear{val}, (call_flags & 1u) != 0 && !leaves_unit(call_flags, n - B), evm,
-                                       reinterpret_cast<int*>(val), d.cap, s_tab, s_tab_n, rb, phase, sh, tid);
+#pragma unroll
+    for (int c = 0; c < CH; ++c) load_meta<NT>(d, base, n, t, c, tid, crf[c], tau[c], ps[c]);
+    f32x4 x[2][CG][kMaxGroup];
+    auto request = [&](int c0, f32x4 (&to)[CG][kMaxGroup]) {
+#pragma unroll
+      for (int c = 0; c < CG; ++c) {
+        const int e0 = 4 * (tid + (c0 + c) * NT), at = (e0 >> 5) * (G * kBlk) + (e0 & 31);      // beyond the unit: some value, or 0 from beyond its logits
+#pragma unroll
+        for (int g = 0; g < kMaxGroup; ++g)
+          if (g < G) to[c][g] = get_f32x4<COHERENT ? kSc1 : 0>(logits, at + g * kBlk);
+      }
+    };
+    request(0, x[0]);
+    merge();
+    const float invG = 1.0f / (float)G;
+    float a[R];
+#pragma unroll
+    for (int c0 = 0; c0 < C; c0 += CG) {
+      if (c0 + CG < C) request(c0 + CG, x[(c0 / CG + 1) & 1]);
+      const auto& from = x[(c0 / CG) & 1];
+#pragma unroll
+      for (int c = 0; c < CG; ++c) {
+        const int e0 = 4 * (tid + (c0 + c) * NT);
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int g = 0; g < kMaxGroup; ++g) {
+          if (g < G) {                      // uniform; heads in ascending order, as everywhere
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] += fast_exp2(from[c][g][e] - sM[g]) * sInv[g];
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a[4 * (c0 + c) + e] = (e0 + e < n) ? acc[e] * invG : 0.f;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    lrfu_regs<R, CH, CH, ValLinear, NT, true>(d, u, base, n, leaves_unit(call_flags, n - B) ? n : B, t, a, crf, tau, ps, ValLinear{val},
+                                              (call_flags & 1u) != 0, evm, reinterpret_cast<int*>(val), d.cap, s_tab, s_tab_n, rb, phase, sh, tid, NoHook{}, ne, top);
   };
-  if (n <= 4 * NT) {
-    regs(std::integral_constant<int, 4>{});
-  } else if (NT < kWideThreads || n <= 8 * NT) {
-    regs(std::integral_constant<int, 8>{});
-  } else if constexpr (NT == kWideThreads) {
-    if (n <= 16 * NT)
-      regs(std::integral_constant<int, 16>{});
-    else
-      regs(std::integral_constant<int, 32>{});
-  }
+  if constexpr (RMAX > 16)
+    if (n > 16 * NT) return regs(std::integral_constant<int, 32>{});
+  if constexpr (RMAX > 12)
+    if (n > 8 * NT) return regs(std::integral_constant<int, 16>{});
+  if constexpr (RMAX == 12)
+    if (n > 8 * NT) return regs(std::integral_constant<int, 12>{});
+  if constexpr (RMAX > 4)
+    if (n > 4 * NT) return regs(std::integral_constant<int, 8>{});
+  regs(std::integral_constant<int, 4>{});
 }
 
-// The bookkeeping of a step behind layer_scan_kernel, one workgroup per unit: the new entry's rows are in the cache
-// and its logits with the others, the unit's records still describe the step before.  Records the append, then
-// Alg. 1 Steps 1-4.  layer_time = 0: at the context's time, which moves on at the end if `advance` says so.
-// layer_time = 1 (deferred): at the time that the scan left for the unit's layer.
-// A unit is a chain of about 15 block reductions and as many memory round trips, so few units take 1024 threads each
-// (at most 8 entries per thread up to 8192): 128 units of 2048 entries on average in 21 us, with 256 threads 46.
+// The deferred bookkeeping of a step behind layer_step_kernel, one workgroup per unit, at the time that the scan left for the unit's
+// layer: the new entry's rows are in the cache and its logits with the others, the unit's records still describe the step
+// before.  A unit is a chain of about ten block reductions and memory round trips, so few units take 1024 threads each
+// (at most 8 entries per thread up to 8192).
 template <int NT>
-__global__ __launch_bounds__(NT) void finish_kernel(Dev d, int unit_begin, uint32_t call_flags, int advance, int layer_time) {
-  extern __shared__ unsigned char smem[];
+__global__ __launch_bounds__(NT) void finish_kernel(Dev d, int unit_begin, uint32_t call_flags) {
+  extern __shared__ __align__(16) unsigned char smem[];
   float* val = reinterpret_cast<float*>(smem);
   uint32_t* evm = reinterpret_cast<uint32_t*>(smem + (size_t)d.cap * 4);
+  __shared__ TopBuf top;
   __shared__ float sM[kMaxGroup], sInv[kMaxGroup];
   __shared__ int32_t s_row[kMaxChunks];
   __shared__ RedBuf<NT> rb;
@@ -2193,37 +1975,33 @@ __global__ __launch_bounds__(NT) void finish_kernel(Dev d, int unit_begin, uint3
   __shared__ float s_tab[kTabLds];
   const int tid = threadIdx.x;
   const int u = unit_begin + blockIdx.x;
-  int n = d.n[u];
-  const int t = layer_time ? d.layer_ts[u / (d.Bz * d.Hkv)] : d.sc[SC_T];
+  const int n_old = d.n[u];
+  const int t = d.layer_ts[u / (d.Bz * d.Hkv)];
   const int B = d.budget[u];
   const int s_tab_n = min(kTabLds, d.tab_last + 1);
-  const bool room = n < unit_cap(d, u);
-  if (tid < s_tab_n) s_tab[tid] = d.tab[tid];
+  const bool room = n_old < unit_cap(d, u);
   if (tid < d.max_seg) s_row[tid] = d.tbl[(size_t)u * d.max_seg + tid];
+  if (tid < s_tab_n) s_tab[tid] = d.tab[tid];
   if (tid < d.G) {
     sM[tid] = d.msum[((size_t)u * kMaxGroup + tid) * 2];
     sInv[tid] = d.msum[((size_t)u * kMaxGroup + tid) * 2 + 1];
   }
-  int phase = 0;
+  clear_top(top, tid, NT);
   // Every wavefront has read the stored length before the first thread replaces it: a wavefront that started late
   // would otherwise count the new entry twice and part ways with the others.
   __syncthreads();
   const Slots base{s_row};
-  if (room) {
-    if (tid == 0) {
-      const size_t s = base + n;
-      d.crf[s] = 0.0f;
-      d.tau[s] = t;
-      d.pos[s] = t;
-      d.flags[s] = 0;
-      d.n[u] = n + 1;
-    }
-    n += 1;
+  const int n = n_old + (room ? 1 : 0);
+  if (room && tid == NT - 1) {                             // (its score and time are written with the others')
+    const size_t s = base + n_old;
+    d.pos[s] = t;
+    d.flags[s] = 0;
+    d.n[u] = n;
   }
-  __threadfence_block();
-  __syncthreads();
-  if (n > 0) unit_bookkeeping<NT>(d, u, base, n, B, t, unit_logits(d, u), sM, sInv, call_flags, val, evm, s_tab, s_tab_n, rb, phase, sh, tid);
-  if (advance) step_epilogue(d, t, advance, tid);          // the time moves on behind the last layer (deferred steps: in its scan)
+  // the new entry's rows are in the last slot like any other's, but nothing else there is yet
+  if (n > 0)
+    finish_unit<NT, NT == kWideThreads ? 32 : 8, false, NT == kWideThreads>(d, u, base, n, B, t, sM, sInv, call_flags, val, evm, &top, s_tab, s_tab_n, rb, sh, tid,
+                                                        NewInCache{room}, []() {});
 }
 
 // ------------------------------------------------------------------ prompt replay (scores of a loaded prompt)
@@ -2572,7 +2350,7 @@ __device__ __forceinline__ void seed_rewards_regs(const Dev& d, Slots base, int 
 #pragma unroll
     for (int e = 0; e < 4; ++e) a[4 * c + e] = (e0 + e < n) ? x[e] : 0.f;
   }
-  const HitRule rule = top_p_regs<R, kSeedThreads>(d, base, n, a, lst, -1, rb, phase, tid);
+  const HitRule rule = top_p_regs<R, kSeedThreads>(d, base, n, a, *reinterpret_cast<TopBuf*>(lst), -1, rb, phase, tid);
   uint32_t* bits = reinterpret_cast<uint32_t*>(rw);
 #pragma unroll
   for (int c = 0; c < R / 4; ++c) {
@@ -2876,7 +2654,7 @@ __global__ __launch_bounds__(kThreads, 2) void probe_scan_kernel(Dev d, int unit
   for (int b = 0; b < kProbeBlks; ++b) {
     if (b < nb) {
       float sv[8];
-      scan_qk(k[b], qv, sv, d.scale_log2e, b * kBlk, nv, s_lg[w], kLgRow, lg_dst, G, lane);
+      scan_qk(k[b], qv, sv, d.scale_log2e, b * kBlk, nv, s_lg[w], kLgRow, LogitsOut{lg_dst}, G, lane);
       const float bm = fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
       if (bm > m) {
         l *= fast_exp2(m - bm);

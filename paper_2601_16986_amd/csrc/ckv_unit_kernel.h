@@ -245,7 +245,7 @@ __global__ __launch_bounds__(64 * W, 2) void unit_kernel(Dev d, const uint16_t* 
       const bool resident = blk < res_blk;
       float* lds_dst = (call_flags & 2u) ? nullptr : resident ? lg + (size_t)blk * (G * kBlk) : s_buf + wave * (kMaxGroup * kLgRow);
       scan_qk(ka, qv, sv, d.scale_log2e, 0, ns - blk * kBlk, lds_dst, resident ? kBlk : kLgRow,
-              resident ? nullptr : lg_glob + (size_t)blk * (G * kBlk), G, slane);
+              LogitsOut{resident ? nullptr : lg_glob + (size_t)blk * (G * kBlk)}, G, slane);
     };
     for (int i = 0; i + 1 < my_cnt; ++i) {
       const int blk = wave + W * i;
