@@ -16,6 +16,9 @@ HIPCC_FLAGS = [
     # keep the fused kernel's queue atomic a plain atomic: the wave-level rewrite of atomics reads the
     # result back at once, and that wait is a wait for every load in flight
     "-mllvm", "-amdgpu-atomic-optimizer-strategy=None",
+    # results of the matrix products stay in ordinary registers: in accumulation registers every use is a copy first, a third of
+    # the prompt replay's vector instructions
+    "-mllvm", "-amdgpu-mfma-vgpr-form=1",
     "-Wall", "-Wno-unused-function",
 ]
 

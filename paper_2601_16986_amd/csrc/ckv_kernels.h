@@ -620,6 +620,9 @@ __device__ __forceinline__ void load_v(VFrag& f, const uint16_t* vb) {
   for (int i = 0; i < 8; ++i) f.v[i] = stream_load(vb + i * 512);
 }
 
+// s_waitcnt vmcnt(0) alone
+constexpr int kWaitLoads = 0x0F70;
+
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 x) { return __builtin_bit_cast(bf16x8, x); }
 
 // One block of 32 entries is processed in two halves so that each fragment's
@@ -2032,6 +2035,11 @@ __global__ __launch_bounds__(NT) void finish_kernel(Dev d, int unit_begin, uint3
 // Both passes share a unit's blocks out over S wavefronts, as many as fill the chip evenly: with a wavefront per chunk of
 // 256 entries, 128 units of 9350 entries were 1280 workgroups on 768 places.  Measured on that shape, 32 queries,
 // G = 5: first pass 111 -> 88 us, second pass 163 -> 97 us.
+// Then, the same shape: results of the products in ordinary registers (a compiler option), the maximum looked for once per span, two tiles
+// at a time with registers for three wavefronts per SIMD (the scheduler, left to itself, saves registers and waits for every LDS read),
+// the segment table in a register: 89 -> 76 and 98 -> 94 us. The first pass issues 18 M vector instructions where it issued 26 M, and is bound by
+// their and the products' issue; the second by the products and by its stores (without them 77, without the products 66, without
+// the exponentials 92 us).
 // Buffers of a batch of nq queries for the UL units of a layer (tiles and columns as in the first pass):
 //   sml [tile][unit][span][column][2]     maximum (rounded up) and sum of the softmax over a wavefront's blocks
 //   smi [tile][unit][column][2]           maximum (rounded up) and 1 / sum over all the entries the column's query sees
@@ -2073,34 +2081,45 @@ __device__ __forceinline__ int seed_column(int G, int tl, int c, int& head) {
 template <class Column>
 __device__ __forceinline__ void seed_stage_queries(const Dev& d, const uint16_t* q_obs, int urel, int j0, int nq, int nt, Column column, u32x4* s_q) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, b = urel / d.Hkv, h = urel % d.Hkv;
-  for (int tl = 0; tl < nt; ++tl) {
-    int head;
-    const int qi = column(d.G, tl, lane & 15, head);
-    u32x4 x = {0u, 0u, 0u, 0u};
-    if (qi < nq)
-      x = *reinterpret_cast<const u32x4*>(q_obs + ((((size_t)(j0 + qi) * d.Bz + b) * d.Hq) + (size_t)h * d.G + head) * kDim + 32 * wave + 8 * (lane >> 4));
-    s_q[(tl * 4 + wave) * 64 + lane] = x;
+  u32x4 x[kSeedTiles];                                    // all asked for before the first is stored
+#pragma unroll
+  for (int tl = 0; tl < kSeedTiles; ++tl) {
+    x[tl] = u32x4{0u, 0u, 0u, 0u};
+    if (tl < nt) {
+      int head;
+      const int qi = column(d.G, tl, lane & 15, head);
+      if (qi < nq)
+        x[tl] = *reinterpret_cast<const u32x4*>(q_obs + ((((size_t)(j0 + qi) * d.Bz + b) * d.Hq) + (size_t)h * d.G + head) * kDim + 32 * wave + 8 * (lane >> 4));
+    }
   }
+#pragma unroll
+  for (int tl = 0; tl < kSeedTiles; ++tl)
+    if (tl < nt) s_q[(tl * 4 + wave) * 64 + lane] = x[tl];
 }
 
-// This wavefront's blocks [b, b1) of the unit, and where block b lies.
+// This wavefront's blocks [b, b1) of the unit, and where they lie: the segments of up to 512 blocks sit in a register, one per lane (a look at
+// the table per block was a vector load, since the kernel stores elsewhere, and the wait for it one for every store before it).
 struct SeedSpan {
-  const int32_t* row;
+  int segs, first;
   int b, b1;
   __device__ __forceinline__ SeedSpan(const Dev& d, int u, int slot, int S, int n_last) {
     const int blocks = (n_last + kBlk - 1) / kBlk, per = (blocks + S - 1) / S;
-    row = d.tbl + (size_t)u * d.max_seg;
     b = min(slot * per, blocks);
     b1 = min(b + per, blocks);
+    first = b / kSegBlocks;
+    segs = d.tbl[(size_t)u * d.max_seg + min(first + (int)(threadIdx.x & 63), d.max_seg - 1)];
   }
-  __device__ __forceinline__ size_t off(int blk) const { return (size_t)row[blk >> 3] * kSegElems + (size_t)(blk & (kSegBlocks - 1)) * kBlkElems; }
+  __device__ __forceinline__ size_t off(int blk) const {
+    const int seg = __builtin_amdgcn_readlane(segs, blk / kSegBlocks - first);
+    return (size_t)seg * kSegElems + (size_t)(blk & (kSegBlocks - 1)) * kBlkElems;
+  }
 };
 
 // seed_scan_kernel: per span and column the maximum and sum of the softmax over the entries the column's query sees:
 // query j of the window sees the entries of positions <= its own, i.e. indices < P - W + j + 1 (the prompt's entries
 // sit in position order).
 // grid: (ceil(S / 4), units of the layer), kThreads threads, nt * 4096 bytes of dynamic LDS.
-__global__ __launch_bounds__(kThreads) void seed_scan_kernel(Dev d, int unit_begin, const uint16_t* __restrict__ q_obs, int j0, int nq, int P, int W,
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 3))) void seed_scan_kernel(Dev d, int unit_begin, const uint16_t* __restrict__ q_obs, int j0, int nq, int P, int W,
                                                              int S, float* __restrict__ sml) {
   extern __shared__ unsigned char smem[];
   u32x4* s_q = reinterpret_cast<u32x4*>(smem);
@@ -2125,62 +2144,99 @@ __global__ __launch_bounds__(kThreads) void seed_scan_kernel(Dev d, int unit_beg
   }
   const float c = d.scale_log2e;
   const uint16_t* kp = d.K + lane * 8;
-  auto sweep = [&](auto rounded) {
-    KFrag ka, kn;
+  KFrag ka, kn;
+  auto products = [&](int tl, float (&sv)[8]) {
+    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s4 = 0; s4 < 4; ++s4) {
+      const bf16x8 qv = as_bf16x8(s_q[(tl * 4 + s4) * 64 + lane]);
+      s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ka.k[s4]), qv, s0, 0, 0, 0);
+      s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ka.k[4 + s4]), qv, s1, 0, 0, 0);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      sv[v] = s0[v];
+      sv[4 + v] = s1[v];
+    }
+  };
+  auto sum = [&](int tl, const float (&sv)[8], auto rounded) {
+    float p[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) p[i] = seed_exp<decltype(rounded)::value>(sv[i], c, m_run[tl]);
+    l_run[tl] += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+  };
+  // TRACK: the maximum follows every block.  Otherwise only the span's first block and those that need a mask look for it: the
+  // others' sums are relative to what those left, which is as good as any maximum unless a sum grows beyond 2^60; then everything
+  // is done again with TRACK.  (Looking for it is a quarter of a tile's vector instructions, which is what bounds the pass.)
+  auto sweep = [&](auto track, auto rounded) {
     if (sp.b < sp.b1) load_k(ka, kp + sp.off(sp.b));
     for (int blk = sp.b; blk < sp.b1; ++blk) {
       load_k(kn, kp + sp.off(min(blk + 1, sp.b1 - 1)));
-      const int e0 = blk * kBlk + 4 * kg;
+      if (!decltype(track)::value && blk > sp.b && (blk + 1) * kBlk <= n_first) {      // every query sees the block whole
+        // two tiles at a time, to have one's products under the other's exponentials
 #pragma unroll
-      for (int tl = 0; tl < kSeedTiles; ++tl) {
-        if (tl < nt && blk * kBlk < n_first + min(q_lo[tl + 1], nq - 1)) {     // uniform: else no query of the tile sees the block
-          bf16x8 qv[4];
-#pragma unroll
-          for (int s4 = 0; s4 < 4; ++s4) qv[s4] = as_bf16x8(s_q[(tl * 4 + s4) * 64 + lane]);
-          f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int s4 = 0; s4 < 4; ++s4) s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ka.k[s4]), qv[s4], s0, 0, 0, 0);
-#pragma unroll
-          for (int s4 = 0; s4 < 4; ++s4) s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ka.k[4 + s4]), qv[s4], s1, 0, 0, 0);
-          float sv[8];
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            sv[v] = s0[v];
-            sv[4 + v] = s1[v];
+        for (int tl = 0; tl < kSeedTiles; tl += 2) {
+          if (tl + 1 < nt) {
+            float sa[8], sb[8];
+            products(tl, sa);
+            products(tl + 1, sb);
+            sum(tl, sa, rounded);
+            sum(tl + 1, sb, rounded);
+          } else if (tl < nt) {
+            float sv[8];
+            products(tl, sv);
+            sum(tl, sv, rounded);
           }
-          if ((blk + 1) * kBlk > n_first + q_lo[tl]) {      // a block that the tile's first query sees whole needs no mask
-            const int lim = n_first + (kSeedCols * tl + j) / G;            // entries this column's query sees
+        }
+      } else {
+        const int e0 = blk * kBlk + 4 * kg;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-              sv[v] = (e0 + v < lim) ? sv[v] : -INFINITY;
-              sv[4 + v] = (e0 + 16 + v < lim) ? sv[4 + v] : -INFINITY;
+        for (int tl = 0; tl < kSeedTiles; ++tl) {
+          if (tl < nt && blk * kBlk < n_first + min(q_lo[tl + 1], nq - 1)) {     // uniform: else no query of the tile sees the block
+            float sv[8];
+            products(tl, sv);
+            if ((blk + 1) * kBlk > n_first + q_lo[tl]) {      // a block that the tile's first query sees whole needs no mask
+              const int lim = n_first + (kSeedCols * tl + j) / G;            // entries this column's query sees
+#pragma unroll
+              for (int v = 0; v < 4; ++v) {
+                sv[v] = (e0 + v < lim) ? sv[v] : -INFINITY;
+                sv[4 + v] = (e0 + 16 + v < lim) ? sv[4 + v] : -INFINITY;
+              }
             }
+            // The maximum is kept rounded up to a whole number: sums are then rescaled by exact powers of two, here and
+            // where partials meet.
+            const float bm = c * fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
+            if (bm > m_run[tl]) {
+              const float m_new = ceilf(bm);
+              l_run[tl] *= fast_exp2(m_run[tl] - m_new);      // 0 the first time
+              m_run[tl] = m_new;
+            }
+            sum(tl, sv, rounded);
           }
-          // The maximum is kept rounded up to a whole number: sums are then rescaled by exact powers of two, here and
-          // where partials meet.
-          const float bm = c * fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
-          if (bm > m_run[tl]) {
-            const float m_new = ceilf(bm);
-            l_run[tl] *= fast_exp2(m_run[tl] - m_new);      // 0 the first time
-            m_run[tl] = m_new;
-          }
-          float p[8];
-#pragma unroll
-          for (int i = 0; i < 8; ++i) p[i] = seed_exp<decltype(rounded)::value>(sv[i], c, m_run[tl]);
-          l_run[tl] += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
         }
       }
       ka = kn;
     }
   };
-  sweep(std::false_type{});
-  bool far = false;
+  sweep(std::false_type{}, std::false_type{});
+  bool again = false;
 #pragma unroll
-  for (int tl = 0; tl < kSeedTiles; ++tl) far |= is_far(m_run[tl]);
-  if (__any(far)) {                                       // the maxima stand; the sums once more
+  for (int tl = 0; tl < kSeedTiles; ++tl) again |= !(l_run[tl] <= 0x1p60f) || is_far(m_run[tl]);
+  if (__any(again)) {
 #pragma unroll
-    for (int tl = 0; tl < kSeedTiles; ++tl) l_run[tl] = 0.f;
-    sweep(std::true_type{});
+    for (int tl = 0; tl < kSeedTiles; ++tl) {
+      m_run[tl] = kNoMax;
+      l_run[tl] = 0.f;
+    }
+    sweep(std::true_type{}, std::false_type{});
+    bool far = false;
+#pragma unroll
+    for (int tl = 0; tl < kSeedTiles; ++tl) far |= is_far(m_run[tl]);
+    if (__any(far)) {                                     // the maxima stand; the sums once more
+#pragma unroll
+      for (int tl = 0; tl < kSeedTiles; ++tl) l_run[tl] = 0.f;
+      sweep(std::true_type{}, std::true_type{});
+    }
   }
   // per tile, the column's four lanes (kg = 0..3): maximum, then the sums rescaled to it, in a fixed order
 #pragma unroll
@@ -2237,7 +2293,7 @@ __global__ __launch_bounds__(8 * kSeedCols) void seed_stats_kernel(int S, const 
 // seed_weights_kernel: every logit normalised with its column's maximum and 1 / sum, the mean over a query's heads
 // (summed in head order, as the decode path's mean weights are) to `srw`; entries that a query does not see, but others of the
 // batch in the same block do, get 0.  Grid and LDS as seed_scan_kernel.
-__global__ __launch_bounds__(kThreads) void seed_weights_kernel(Dev d, int unit_begin, const uint16_t* __restrict__ q_obs, int j0, int nq, int P,
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 3))) void seed_weights_kernel(Dev d, int unit_begin, const uint16_t* __restrict__ q_obs, int j0, int nq, int P,
                                                                 int W, int S, const float* __restrict__ smi, float* __restrict__ srw) {
   extern __shared__ unsigned char smem[];
   u32x4* s_q = reinterpret_cast<u32x4*>(smem);
@@ -2265,11 +2321,9 @@ __global__ __launch_bounds__(kThreads) void seed_weights_kernel(Dev d, int unit_
   for (int i = lane; i < nt * kSeedCols; i += 64) far |= is_far(s_M[i]);
   const float c = d.scale_log2e;
   const uint16_t* kp = d.K + lane * 8;
+  const size_t lane_row = (size_t)kg * UL * d.cap + j;
   auto sweep = [&](auto rounded) {
-    KFrag ka, kn;
-    if (sp.b < sp.b1) load_k(ka, kp + sp.off(sp.b));
-    for (int blk = sp.b; blk < sp.b1; ++blk) {
-      load_k(kn, kp + sp.off(min(blk + 1, sp.b1 - 1)));
+    auto block = [&](const KFrag& ka, int blk) {
 #pragma unroll 1
       for (int gr = 0; gr < groups; ++gr) {
         const int q0 = kSeedGroup * gr;
@@ -2277,53 +2331,93 @@ __global__ __launch_bounds__(kThreads) void seed_weights_kernel(Dev d, int unit_
         float mean[4][2];                                   // queries q0 + 4 t + kg, entries j and 16 + j of the block
 #pragma unroll
         for (int t = 0; t < 4; ++t) mean[t][0] = mean[t][1] = 0.f;
-        f32x4 s0, s1, M, I;
-        auto tile = [&](int tl) {
-          s0 = s1 = f32x4{0.f, 0.f, 0.f, 0.f};
+        struct Tile {
+          f32x4 s0, s1;
+        };
+        auto products = [&](int tl) -> Tile {
+          Tile x{{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
           for (int s4 = 0; s4 < 4; ++s4) {
             const bf16x8 qv = as_bf16x8(s_q[(tl * 4 + s4) * 64 + lane]);
-            s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qv, as_bf16x8(ka.k[s4]), s0, 0, 0, 0);
-            s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qv, as_bf16x8(ka.k[4 + s4]), s1, 0, 0, 0);
+            x.s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qv, as_bf16x8(ka.k[s4]), x.s0, 0, 0, 0);
+            x.s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qv, as_bf16x8(ka.k[4 + s4]), x.s1, 0, 0, 0);
           }
-          M = *reinterpret_cast<const f32x4*>(s_M + tl * kSeedCols + 4 * kg);
-          I = *reinterpret_cast<const f32x4*>(s_I + tl * kSeedCols + 4 * kg);
+          return x;
+        };
+        // four heads of one query
+        auto heads = [&](int tl, const Tile& x, float (&m)[2]) {
+          const f32x4 M = *reinterpret_cast<const f32x4*>(s_M + tl * kSeedCols + 4 * kg), I = *reinterpret_cast<const f32x4*>(s_I + tl * kSeedCols + 4 * kg);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            m[0] = __builtin_fmaf(seed_exp<decltype(rounded)::value>(x.s0[v], c, M[v]), I[v], m[0]);
+            m[1] = __builtin_fmaf(seed_exp<decltype(rounded)::value>(x.s1[v], c, M[v]), I[v], m[1]);
+          }
         };
 #pragma unroll 1
         for (int h = 0; h + 4 <= G; h += 4) {
+          const int tl = gr * G + h;
+          if (q0 + 12 < nq) {                             // no tile without queries: two at a time, one's products under the other's exponentials
+            const Tile x0 = products(tl), x1 = products(tl + 1);
+            heads(tl, x0, mean[0]);
+            heads(tl + 1, x1, mean[1]);
+            const Tile x2 = products(tl + 2), x3 = products(tl + 3);
+            heads(tl + 2, x2, mean[2]);
+            heads(tl + 3, x3, mean[3]);
+          } else {
 #pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            if (q0 + 4 * t >= nq) continue;               // uniform: a tile without queries
-            tile(gr * G + h + t);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-              mean[t][0] = __builtin_fmaf(seed_exp<decltype(rounded)::value>(s0[v], c, M[v]), I[v], mean[t][0]);
-              mean[t][1] = __builtin_fmaf(seed_exp<decltype(rounded)::value>(s1[v], c, M[v]), I[v], mean[t][1]);
+            for (int t = 0; t < 4; ++t) {
+              if (q0 + 4 * t >= nq) continue;             // uniform
+              heads(tl + t, products(tl + t), mean[t]);
             }
           }
         }
 #pragma unroll 1
         for (int h = G & ~3; h < G; ++h) {
-          tile(gr * G + h);
+          const int tl = gr * G + h;
+          const Tile x = products(tl);
+          const f32x4 M = *reinterpret_cast<const f32x4*>(s_M + tl * kSeedCols + 4 * kg), I = *reinterpret_cast<const f32x4*>(s_I + tl * kSeedCols + 4 * kg);
 #pragma unroll
           for (int v = 0; v < 4; ++v) {
-            mean[v][0] = __builtin_fmaf(seed_exp<decltype(rounded)::value>(s0[v], c, M[v]), I[v], mean[v][0]);
-            mean[v][1] = __builtin_fmaf(seed_exp<decltype(rounded)::value>(s1[v], c, M[v]), I[v], mean[v][1]);
+            mean[v][0] = __builtin_fmaf(seed_exp<decltype(rounded)::value>(x.s0[v], c, M[v]), I[v], mean[v][0]);
+            mean[v][1] = __builtin_fmaf(seed_exp<decltype(rounded)::value>(x.s1[v], c, M[v]), I[v], mean[v][1]);
           }
         }
-        const int e0 = blk * kBlk + j;
+        // The next block's keys, on their way since this one began, and the last group's stores are waited for here: a wait for the keys
+        // behind stores whose number the compiler does not know would be a wait for those stores, just issued.
+        __builtin_amdgcn_s_waitcnt(kWaitLoads);
+        // (a lane's rows are 4 queries apart: one 64-bit addition each to addresses that are the same in all lanes)
+        if ((blk + 1) * kBlk <= n_first + q0 && q0 + kSeedGroup <= nq) {       // every query of the group is there and sees the block whole
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const int qi = q0 + 4 * t + kg;
-          if (qi < nq) {
-            const int lim = n_first + qi;                   // entries the query sees
-            float* dst = srw + ((size_t)qi * UL + urel) * d.cap + e0;
-            dst[0] = e0 < lim ? mean[t][0] : 0.f;
-            dst[16] = e0 + 16 < lim ? mean[t][1] : 0.f;
+          for (int t = 0; t < 4; ++t) {
+            float* dst = srw + ((size_t)(q0 + 4 * t) * UL + urel) * d.cap + blk * kBlk + lane_row;
+            dst[0] = mean[t][0];
+            dst[16] = mean[t][1];
+          }
+        } else {
+          const int e0 = blk * kBlk + j;
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            const int qi = q0 + 4 * t + kg;
+            if (qi < nq) {
+              const int lim = n_first + qi;                   // entries the query sees
+              float* dst = srw + ((size_t)(q0 + 4 * t) * UL + urel) * d.cap + blk * kBlk + lane_row;
+              dst[0] = e0 < lim ? mean[t][0] : 0.f;
+              dst[16] = e0 + 16 < lim ? mean[t][1] : 0.f;
+            }
           }
         }
       }
-      ka = kn;
+    };
+    // two blocks in turn, the next always on its way
+    KFrag k0, k1;
+    if (sp.b < sp.b1) load_k(k0, kp + sp.off(sp.b));
+    for (int blk = sp.b; blk < sp.b1; blk += 2) {
+      load_k(k1, kp + sp.off(min(blk + 1, sp.b1 - 1)));
+      block(k0, blk);
+      if (blk + 1 < sp.b1) {
+        load_k(k0, kp + sp.off(min(blk + 2, sp.b1 - 1)));
+        block(k1, blk + 1);
+      }
     }
   };
   if (__any(far))
