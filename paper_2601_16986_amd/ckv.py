@@ -219,6 +219,11 @@ class CrystalKV:
                                self.tau.data_ptr(), self.pos.data_ptr(), self.flags.data_ptr(), wptr, ws)
         b = np.ascontiguousarray(np.asarray(budgets, dtype=np.int32).reshape(n_layers, batch, n_kv_heads))
         self.ctx = C.c_void_p()
+        # what every step looks at, formed once: shapes with and without the layer dimension, the output's type, the
+        # device whose current stream is asked for
+        self._shapes = {lead: (lead + (batch, n_q_heads, head_dim), lead + (batch, n_kv_heads, head_dim)) for lead in ((n_layers,), ())}
+        self._out_dtype = torch.float32 if out_dtype == F32 else torch.bfloat16
+        self._raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) if self.device.index is not None else None
         with torch.cuda.device(self.device):
             rc = self.lib.ckv_init(C.byref(self.ctx), C.byref(self.layout), _np_ptr(b), C.byref(self.params),
                                    C.byref(self.buffers), self._stream())
@@ -228,7 +233,9 @@ class CrystalKV:
 
     # ------------------------------------------------------------------ plumbing
     def _stream(self):
-        return C.c_void_p(self.torch.cuda.current_stream(self.device).cuda_stream)
+        if self._raw_stream is not None:
+            return self._raw_stream(self.device.index)
+        return self.torch.cuda.current_stream(self.device).cuda_stream
 
     def _check(self, rc):
         if rc != OK:
@@ -248,6 +255,8 @@ class CrystalKV:
 
     def _dev_bf16(self, x, shape):
         t = self.torch
+        if type(x) is t.Tensor and x.dtype is t.bfloat16 and x.shape == shape and x.is_contiguous():
+            return x
         if isinstance(x, np.ndarray):
             x = t.from_numpy(np.ascontiguousarray(x, dtype=np.float32)).to(self.device).to(t.bfloat16)
         assert x.dtype == t.bfloat16 and x.is_contiguous() and tuple(x.shape) == tuple(shape), (x.dtype, x.shape, shape)
@@ -290,17 +299,17 @@ class CrystalKV:
         """q [L][Bz][Hq][d], k_new / v_new [L][Bz][Hkv][d] (no leading [L] for a single layer).
         Returns the device tensor `out` of the same shape as q.  defer (single layers only): the layer's
         bookkeeping runs on one of the context's own streams, see `join`."""
-        t = self.torch
-        lead = (self.L,) if layer == -1 else ()
-        q = self._dev_bf16(q, lead + (self.Bz, self.Hq, self.d))
-        k_new = self._dev_bf16(k_new, lead + (self.Bz, self.Hkv, self.d))
-        v_new = self._dev_bf16(v_new, lead + (self.Bz, self.Hkv, self.d))
+        q_shape, kv_shape = self._shapes[(self.L,) if layer == -1 else ()]
+        q = self._dev_bf16(q, q_shape)
+        k_new = self._dev_bf16(k_new, kv_shape)
+        v_new = self._dev_bf16(v_new, kv_shape)
         if out is None:
-            out = t.empty(q.shape, dtype=t.float32 if self.out_dtype == F32 else t.bfloat16, device=self.device)
-        self._check(self.lib.ckv_decode_step(self.ctx, layer, q.data_ptr(), k_new.data_ptr(), v_new.data_ptr(),
-                                             out.data_ptr(),
-                                             (ATTENTION_ONLY if attention_only else (FUSE_EVICT if evict else 0))
-                                             | (DEFER_BOOKKEEPING if defer else 0), self._stream()))
+            out = self.torch.empty(q_shape, dtype=self._out_dtype, device=self.device)
+        rc = self.lib.ckv_decode_step(self.ctx, layer, q.data_ptr(), k_new.data_ptr(), v_new.data_ptr(), out.data_ptr(),
+                                      (ATTENTION_ONLY if attention_only else (FUSE_EVICT if evict else 0)) | (DEFER_BOOKKEEPING if defer else 0),
+                                      self._stream())
+        if rc != OK:
+            self._check(rc)
         return out
 
     def join(self):
@@ -496,7 +505,7 @@ def place_pools(pool_bytes, device="cuda:0", max_fraction=0.92, verbose=False, r
     spacer_bytes = max(0, span // 48 - one) // (2 << 20) * (2 << 20)
     while True:
         free_b, total_b = torch.cuda.mem_get_info(dev)
-        if free_b < one + (4 << 30) or (total_b - free_b + one) > max_fraction * total_b:
+        if len(cands) == 48 or free_b < one + (4 << 30) or (total_b - free_b + one) > max_fraction * total_b:
             break
         buf = torch.empty(one, dtype=torch.uint8, device=dev)
         cands.append(buf)

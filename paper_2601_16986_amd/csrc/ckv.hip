@@ -9,6 +9,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <map>
 #include <mutex>
 #include <new>
 #include <string>
@@ -471,6 +472,23 @@ int fill32(ckv_ctx* c, void* p, uint32_t v, size_t count, hipStream_t s) {
   return CKV_OK;
 }
 
+// Dynamic LDS that a kernel may be launched with on a device: raised when a context needs more than any before it.
+std::mutex g_lds_mutex;
+std::map<std::pair<int, const void*>, size_t> g_lds;
+
+bool allow_lds(int devid, const void* fn, size_t bytes) {
+  try {
+    std::lock_guard<std::mutex> lock(g_lds_mutex);
+    size_t& have = g_lds[{devid, fn}];
+    if (bytes <= have) return true;
+    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess) return false;
+    have = bytes;
+    return true;
+  } catch (const std::bad_alloc&) {
+    return false;
+  }
+}
+
 // Address of the library's static scratch on each device.
 std::mutex g_scratch_mutex;
 unsigned char* g_scratch_ptr[kMaxDevices] = {};
@@ -555,26 +573,18 @@ int ckv_init(ckv_ctx** out, const ckv_layout* layout, const int32_t* budgets, co
     return CKV_EINVAL;
   }
   c->layer_lds = std::max((size_t)kLayerScanLds, c->finish_lds);
-  const void* layer_kernels[4] = {reinterpret_cast<const void*>(layer_step_kernel<false, 4>), reinterpret_cast<const void*>(layer_step_kernel<true, 4>),
-                                  reinterpret_cast<const void*>(layer_step_kernel<false, 12>), reinterpret_cast<const void*>(layer_step_kernel<true, 12>)};
-  for (const void* fn : layer_kernels) {
-    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)c->layer_lds) != hipSuccess) {
-      delete c;
-      return CKV_EHIP;
-    }
-  }
-  const void* lds_kernels[3] = {reinterpret_cast<const void*>(finish_kernel<kThreads>), reinterpret_cast<const void*>(finish_kernel<kWideThreads>),
-                                reinterpret_cast<const void*>(seed_hits_kernel<0>)};
-  if (hipFuncSetAttribute(reinterpret_cast<const void*>(seed_scan_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kSeedTiles * 4096) != hipSuccess ||
-      hipFuncSetAttribute(reinterpret_cast<const void*>(seed_weights_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kSeedTiles * 4096) != hipSuccess) {
+  bool lds_ok = true;
+  for (const void* fn : {reinterpret_cast<const void*>(layer_step_kernel<false, 4>), reinterpret_cast<const void*>(layer_step_kernel<true, 4>),
+                         reinterpret_cast<const void*>(layer_step_kernel<false, 12>), reinterpret_cast<const void*>(layer_step_kernel<true, 12>)})
+    lds_ok = lds_ok && allow_lds(devid, fn, c->layer_lds);
+  for (const void* fn : {reinterpret_cast<const void*>(seed_scan_kernel), reinterpret_cast<const void*>(seed_weights_kernel)})
+    lds_ok = lds_ok && allow_lds(devid, fn, kSeedTiles * 4096);
+  for (const void* fn : {reinterpret_cast<const void*>(finish_kernel<kThreads>), reinterpret_cast<const void*>(finish_kernel<kWideThreads>),
+                         reinterpret_cast<const void*>(seed_hits_kernel<0>)})
+    lds_ok = lds_ok && allow_lds(devid, fn, c->finish_lds);
+  if (!lds_ok) {
     delete c;
     return CKV_EHIP;
-  }
-  for (const void* fn : lds_kernels) {
-    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)c->finish_lds) != hipSuccess) {
-      delete c;
-      return CKV_EHIP;
-    }
   }
 
   // fused kernel: 8 / W workgroups of W wavefronts per CU, each with its share of the CU's 160 KB of LDS
@@ -593,7 +603,7 @@ int ckv_init(ckv_ctx** out, const ckv_layout* layout, const int32_t* budgets, co
     f.lds_main = main_bytes;
     f.lds = (size_t)main_bytes + evm_bytes + tbl_bytes;
     const void* fn = v == 0 ? reinterpret_cast<const void*>(unit_kernel<4>) : reinterpret_cast<const void*>(unit_kernel<2>);
-    if (f.ok && hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)f.lds) != hipSuccess) f.ok = false;
+    if (f.ok && !allow_lds(devid, fn, f.lds)) f.ok = false;
   }
   Dev& d = c->dev;
   d.L = layout->n_layers;
@@ -658,45 +668,54 @@ int ckv_init(ckv_ctx** out, const ckv_layout* layout, const int32_t* budgets, co
     if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) return bail(CKV_EHIP);
     c->ev_book.push_back(e);
   }
-  const size_t S = (size_t)layout->pool_slots;
-  int rc;
-  if ((rc = fill32(c, d.K, 0u, S * kDim / 2, s))) return bail(rc);
-  if ((rc = fill32(c, d.V, 0u, S * kDim / 2, s))) return bail(rc);
-  if ((rc = fill32(c, d.crf, 0u, S, s))) return bail(rc);
-  if ((rc = fill32(c, d.tau, 0u, S, s))) return bail(rc);
-  if ((rc = fill32(c, d.pos, 0u, S, s))) return bail(rc);
-  if ((rc = fill32(c, d.flags, 0u, S / 4, s))) return bail(rc);
-  // per-unit state and scalars (everything up to the decay table)
-  if ((rc = fill32(c, ws, 0u, cv.tab / 4, s))) return bail(rc);
-  if ((rc = fill32(c, d.t_unit, (uint32_t)(params->t0 - 1), (size_t)c->units, s))) return bail(rc);
-  if ((rc = fill32(c, d.sc + SC_T, (uint32_t)params->t0, 1, s))) return bail(rc);
-  if ((rc = fill32(c, d.sc + SC_QUEUE, 0u, 1, s))) return bail(rc);
-  if (hipMemcpyAsync((void*)d.tab, tab.data(), tab.size() * 4, hipMemcpyHostToDevice, s) != hipSuccess) return bail(CKV_EHIP);
-  if ((rc = upload_budgets(c, budgets, s))) return bail(rc);
-  {
-    // Segment table.  headroom 0: every unit owns room for cap entries for good.  Otherwise a unit starts with
-    // the segments that budget + headroom entries need, handed out in unit order (so a unit's segments are
-    // contiguous to begin with); the rest of the pool is spare.
-    const int mseg = d.max_seg;
-    const long long pool_segs = layout->pool_slots / kSeg;
-    std::vector<int32_t> tbl((size_t)c->units * mseg, 0), owned((size_t)c->units, 0), spare;
-    long long next = 0;
-    for (long long u = 0; u < c->units; ++u) {
-      const int need = layout->headroom == 0 ? mseg : std::min<long long>(mseg, ((long long)budgets[u] + layout->headroom + kSeg - 1) / kSeg);
-      if (next + need > pool_segs) return bail(fail(c, CKV_EINVAL, "pool_slots too small for these budgets: see ckv_pool_slots"));
-      for (int j = 0; j < need; ++j) tbl[(size_t)u * mseg + j] = (int32_t)(next + j);
-      owned[u] = need;
-      next += need;
+  // Segment table.  headroom 0: every unit owns room for cap entries for good.  Otherwise a unit starts with
+  // the segments that budget + headroom entries need, handed out in unit order (so a unit's segments are
+  // contiguous to begin with); the rest of the pool is spare.
+  const size_t S = (size_t)layout->pool_slots, U = (size_t)c->units;
+  std::vector<int32_t> stage;
+  InitJob job{};
+  try {
+    const size_t totals_at = 3 * U + (U & 1), tab_at = totals_at + 2 * (size_t)layout->batch;
+    const bool tab_staged = (tab_at + tab.size()) * 4 <= cv.ml - cv.partial;      // the staging place: the decode partials
+    stage.assign(tab_at + (tab_staged ? tab.size() : 0), 0);
+    std::vector<long long> tot(layout->batch, 0);
+    job.pool_segs = layout->pool_slots / kSeg;
+    for (size_t u = 0; u < U; ++u) {
+      const int need = layout->headroom == 0 ? d.max_seg : std::min<long long>(d.max_seg, ((long long)budgets[u] + layout->headroom + kSeg - 1) / kSeg);
+      if (job.given + need > job.pool_segs) return bail(CKV_EINVAL);       // pool_slots too small for these budgets: see ckv_pool_slots
+      stage[u] = budgets[u];
+      stage[U + u] = (int32_t)job.given;
+      stage[2 * U + u] = need;
+      job.given += need;
+      tot[u / layout->n_kv_heads % layout->batch] += budgets[u];
     }
-    for (long long sg = pool_segs - 1; sg >= next; --sg) spare.push_back((int32_t)sg);     // popped from the end: lowest first
-    const int32_t nspare = (int32_t)spare.size();
-    if (hipMemcpyAsync(d.tbl, tbl.data(), tbl.size() * 4, hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipMemcpyAsync(d.owned, owned.data(), owned.size() * 4, hipMemcpyHostToDevice, s) != hipSuccess ||
-        (nspare && hipMemcpyAsync(d.spare, spare.data(), spare.size() * 4, hipMemcpyHostToDevice, s) != hipSuccess) ||
-        hipMemcpyAsync(d.sc + SC_SPARE, &nspare, 4, hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-      return bail(CKV_EHIP);
+    for (long long t : tot) c->budget_total += t;
+    std::memcpy(stage.data() + totals_at, tot.data(), tot.size() * 8);
+    if (tab_staged) std::memcpy(stage.data() + tab_at, tab.data(), tab.size() * 4);
+    job.tab_n = tab_staged ? (int)tab.size() : 0;
+  } catch (const std::bad_alloc&) {
+    return bail(CKV_EHIP);
   }
+  auto region = [](void* p, size_t bytes, uint32_t v = 0u) { return InitFill{(u32x4*)p, v, bytes / 16}; };
+  job.fill[0] = region(d.K, S * kDim * 2);
+  job.fill[1] = region(d.V, S * kDim * 2);
+  job.fill[2] = region(d.crf, S * 4);
+  job.fill[3] = region(d.tau, S * 4);
+  job.fill[4] = region(d.pos, S * 4);
+  job.fill[5] = region(d.flags, S);
+  // per-unit state (everything up to the scalars, budgets excepted, which follow from the staged copy)
+  job.fill[6] = region(ws + cv.n, cv.budget - cv.n);
+  job.fill[7] = region(ws + cv.t_unit, cv.nev - cv.t_unit, (uint32_t)(params->t0 - 1));
+  job.fill[8] = region(ws + cv.nev, cv.sc - cv.nev);
+  job.stage = (const int32_t*)d.partial;
+  job.tab = (int32_t*)d.tab;
+  job.t0 = params->t0;
+  if (hipMemcpyAsync(d.partial, stage.data(), stage.size() * 4, hipMemcpyHostToDevice, s) != hipSuccess) return bail(CKV_EHIP);
+  if (!job.tab_n && hipMemcpyAsync((void*)d.tab, tab.data(), tab.size() * 4, hipMemcpyHostToDevice, s) != hipSuccess) return bail(CKV_EHIP);
+  const unsigned blocks = (unsigned)std::min<size_t>(8ull * c->n_cu, std::max<size_t>(1, (S * kDim / 8 + kThreads - 1) / kThreads));
+  hipLaunchKernelGGL(init_kernel, dim3(blocks), dim3(kThreads), 0, s, d, job);
+  if (hipGetLastError() != hipSuccess) return bail(CKV_EHIP);
+  if (int rc = launch_schedule(c, s)) return bail(rc);
   if (hipStreamSynchronize(s) != hipSuccess) return bail(CKV_EHIP);
   *out = c;
   return CKV_OK;
