@@ -702,7 +702,11 @@ int ckv_init(ckv_ctx** out, const ckv_layout* layout, const int32_t* budgets, co
   job.fill[2] = region(d.crf, S * 4);
   job.fill[3] = region(d.tau, S * 4);
   job.fill[4] = region(d.pos, S * 4);
-  job.fill[5] = region(d.flags, S);
+  // (the flags are the one array that need not lie at a multiple of 16 bytes)
+  if ((uintptr_t)d.flags % 16 == 0)
+    job.fill[5] = region(d.flags, S);
+  else if (int rc = fill32(c, d.flags, 0u, S / 4, s))
+    return bail(rc);
   // per-unit state (everything up to the scalars, budgets excepted, which follow from the staged copy)
   job.fill[6] = region(ws + cv.n, cv.budget - cv.n);
   job.fill[7] = region(ws + cv.t_unit, cv.nev - cv.t_unit, (uint32_t)(params->t0 - 1));

@@ -2,11 +2,11 @@
 // v_mfma_f32_16x16x32_bf16).  One decode step runs as one of
 //
 //   unit_kernel<W> (ckv_unit_kernel.h)  everything in one persistent kernel, a workgroup per unit at a time
-//   layer_scan_kernel, finish_kernel   the units of one layer, or of a small context: append, attention and output in
-//                  one kernel with several workgroups per unit, then the bookkeeping, one workgroup per unit: mean
-//                  attention weight per entry, top-p hit mask, CRF update, aggregated CRF, and (optionally) eviction +
-//                  compaction; on the caller's stream, or later on a stream of the context's (deferred)
-//   layer_scan_kernel, append_kernel   the same without bookkeeping (attention-only steps)
+//   layer_step_kernel (ckv_layer_kernel.h)  the units of one layer, or of a small context: append, attention and output with
+//                  several workgroups per unit, then the bookkeeping (mean attention weight per entry, top-p hit mask, CRF
+//                  update, aggregated CRF, and, optionally, eviction + compaction) by the workgroup that finishes the unit
+//   layer_step_kernel, finish_kernel   the same with the bookkeeping in a kernel of its own, one workgroup per unit: where units
+//                  may be long, or later, on a stream of the context's (deferred)
 //
 // and beside the step:
 //
@@ -78,9 +78,9 @@ struct Dev {
   float* logits;         // [units][cap/32][G][32] scaled logits (base-2 domain)
   long long* btotal;     // [Bz] budget total per sequence
   int32_t* order;        // [units] unit indices by descending budget (schedule of the fused kernel)
-  int32_t* layer_ts;     // [layers] time of a layer's last step with deferred bookkeeping (layer_scan_kernel -> finish_kernel)
+  int32_t* layer_ts;     // [layers] time of a layer's last step with its bookkeeping in a kernel of its own (layer_step_kernel -> finish_kernel)
   int32_t* arrive;       // [units] workgroups of the unit that have published their partial (zero between launches)
-  float* msum;           // [units][8][2] softmax maximum (base-2 domain) and 1 / sum per query head, left by layer_scan_kernel for finish_kernel
+  float* msum;           // [units][8][2] softmax maximum (base-2 domain) and 1 / sum per query head, left by layer_step_kernel for finish_kernel
 };
 
 
@@ -2472,7 +2472,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 3))
 // from `srw`, the hit rule, and in their place the hits, a bit per entry at the start of the row (the query's own entry,
 // the last it sees, is always hit): every thread has its weights in registers (or LDS) before the first bit is written.
 // (As rewards of 4 bytes they were 153 MB per layer of 128 units of 9350 entries and 32 queries, written and read.)
-// grid: (queries of the batch, units of the layer), kSeedThreads threads, kSeedList + 8 ints of dynamic LDS (R = 0: cap floats).
+// grid: (queries of the batch, units of the layer), kSeedThreads threads, a TopBuf of dynamic LDS (R = 0: cap floats).
 constexpr int kSeedThreads = 512;      // prompts are long
 
 template <int R>
