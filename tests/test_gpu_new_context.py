@@ -35,6 +35,25 @@ def test_state(L, batch, hkv, cap, headroom):
     g.close()
 
 
+@pytest.mark.parametrize("offset", [0, 4, 8, 12, 16])
+def test_flags_anywhere(offset):
+    """The flags need not lie at a multiple of 16 bytes; nothing around them is written."""
+    import ctypes as C
+    import torch
+    from paper_2601_16986_amd import ckv
+    g = ckv.CrystalKV(2, 2, 3, 3, 128, 288, np.full((2, 2, 3), 200, np.int32))
+    S = g.pool_slots
+    mem = torch.full((S + 64,), 0xA7, dtype=torch.uint8, device=g.device)
+    buffers, budgets, ctx = ckv.Buffers.from_buffer_copy(g.buffers), g.budgets(), C.c_void_p()
+    buffers.flags = mem.data_ptr() + offset
+    g.close()
+    rc = g.lib.ckv_init(C.byref(ctx), C.byref(g.layout), budgets.ctypes.data_as(C.c_void_p), C.byref(g.params), C.byref(buffers), g._stream())
+    assert rc == ckv.OK
+    torch.cuda.synchronize()
+    g.lib.ckv_destroy(ctx)
+    assert not bool(mem[offset:offset + S].any()) and bool((mem[:offset] == 0xA7).all()) and bool((mem[offset + S:] == 0xA7).all())
+
+
 @pytest.mark.parametrize("lam,delta", [(0.5, 3), (0.9, 700), (0.9999, 60000), (1.0, 60000)])
 @pytest.mark.parametrize("batch,hkv", [(1, 1), (4, 8)])
 def test_decay_table(batch, hkv, lam, delta):
