@@ -328,8 +328,11 @@ int launch_finish(ckv_ctx* c, hipStream_t s, int begin, int count, uint32_t flag
   return CKV_OK;
 }
 
-// A step of `count` units from `begin` on (or its scan, or attention alone: `mode`).  A block of 32 entries per wavefront while two
-// workgroups per compute unit cover the entries that the budgets allow, else eight (figures at the kernel).
+// A block of 32 entries per wavefront while two workgroups per compute unit cover the entries that the budgets allow, else
+// eight (figures at the kernel).
+bool one_block_each(const ckv_ctx* c, int count) { return c->budget_total / c->units * count <= 2ll * c->n_cu * kChunk; }
+
+// A step of `count` units from `begin` on (or its scan, or attention alone: `mode`).
 int launch_layer_step(ckv_ctx* c, hipStream_t s, int begin, int count, const uint16_t* q, const uint16_t* k_new, const uint16_t* v_new, void* out,
                       uint32_t flags, int mode, int advance) {
   const int upl = c->units_per_layer, cap = c->lay.cap;
@@ -345,7 +348,7 @@ int launch_layer_step(ckv_ctx* c, hipStream_t s, int begin, int count, const uin
     else if (cap <= 4 * kLayerThreads) go(one_block, std::integral_constant<int, 4>{});
     else go(one_block, std::integral_constant<int, 12>{});
   };
-  if (c->budget_total / c->units * count <= 2ll * c->n_cu * kChunk) by_length(std::true_type{});
+  if (one_block_each(c, count)) by_length(std::true_type{});
   else by_length(std::false_type{});
   CKV_HIP(c, hipGetLastError());
   return CKV_OK;
@@ -871,7 +874,14 @@ int ckv_decode_step(ckv_ctx* c, int32_t layer, const void* q, const void* k_new,
   // cannot be long; else in a kernel of its own by 1024 (us per layer, captured, one kernel / two: 64 units of 1024 entries on
   // average, up to 4096, 32 / 31, 256 such units 51 / 54; 128 of 4096, fixed, 74 / 78; 2 of 6000 23 / 26; 64 of 2048, up to 8192, 51 / 44, 128
   // such units 56 / 53, 16 of 8000, up to 32000, 104 / 76).
-  const int mode = (flags & CKV_ATTENTION_ONLY) ? kAttend : c->lay.cap <= 12 * kLayerThreads ? kWholeStep : kScanOnly;
+  // The same where the reward is the weight itself, so that the bookkeeping has no threshold to find, the work list with its places for
+  // the longest units goes beyond the two workgroups per compute unit that run at once, and 512 threads have more than six entries each
+  // (four layers, captured, one kernel / two: 32 units of 1200 entries on average, up to 4800, 107 / 96, 56 of 924, up to 3696, 113 / 105; but 104
+  // of 600, up to 2400, 101 / 108, 48 of 2500, fixed, 124 / 138, 8 of 4654 88 / 97; with the threshold 56 of 924 143 / 159).
+  const int cap = c->lay.cap;
+  const bool beyond = (long long)count * ((cap + kChunk - 1) / kChunk) > 2ll * c->n_cu;
+  const bool apart = cap > 12 * kLayerThreads || (c->dev.reward_mode != 0 && cap > 6 * kLayerThreads && beyond && one_block_each(c, count));
+  const int mode = (flags & CKV_ATTENTION_ONLY) ? kAttend : apart ? kScanOnly : kWholeStep;
   const uint32_t kflags = flags & (CKV_FUSE_EVICT | kLeaveMany);
   if (int rc = launch_layer_step(c, s, begin, count, (const uint16_t*)q, (const uint16_t*)k_new, (const uint16_t*)v_new, out, kflags, mode, advance)) return rc;
   if (c->profile) CKV_HIP(c, hipEventRecord(e1, s));

@@ -84,6 +84,15 @@ def test_weighted_reward(copies):
     _same_state(one, ref, exact_scores=False)
 
 
+# few places in the work list, or many; either side of the capacity from which many of them take two kernels
+@pytest.mark.parametrize("lengths,cap,copies", [(LONG, 6112, 1), (LENGTHS + [3000], 3072, 2), (LENGTHS + [3070], 3104, 1), (LENGTHS + [3070], 3104, 2)])
+@pytest.mark.parametrize("extra", [3, -6])
+def test_weighted_reward_in_one_kernel_or_two(lengths, cap, copies, extra):
+    one, ref = (_steps(path, lengths, copies, extra, cap, 5, False, weighted=True) for path in (1, 2))
+    assert np.all(np.abs(one[0] - ref[0]) <= 4e-5 * np.abs(ref[0]).max(-1, keepdims=True))
+    _same_state(one, ref, exact_scores=False)
+
+
 @pytest.mark.parametrize("extra", [0, -6])
 def test_repeats_and_replays(extra):
     a, b, c = (_steps(1, LENGTHS + LONG, 1, extra, 6112, 5, False, graph=graph) for graph in (False, False, True))
