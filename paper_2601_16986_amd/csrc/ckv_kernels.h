@@ -29,6 +29,7 @@
 #include <type_traits>
 
 #include "ckv_layout.h"
+#include "ckv_plan.h"
 
 namespace ckv {
 
@@ -1948,9 +1949,10 @@ __device__ __forceinline__ void finish_unit(const Dev& d, int u, Slots base, int
   const int G = d.G;
   const Buffer logits = buffer_of(d.logits + (size_t)u * d.cap * G, d.cap * G);
   auto regs = [&](auto rc) {
-    // 1024 threads have 128 registers each, and so have the 512 of a workgroup that shares its compute unit with another (LEAN)
+    // (LEAN: few registers, as at logit_groups)
     constexpr int R = decltype(rc)::value, C = R / 4;
-    constexpr int CH = C <= 2 ? C : LEAN ? (C % 2 == 0 ? 2 : 1) : C <= 4 ? C : 4, CG = C < 2 || (LEAN && (C > 2 || NT < kWideThreads)) ? 1 : 2;
+    constexpr int CH = C <= 2 ? C : LEAN ? (C % 2 == 0 ? 2 : 1) : C <= 4 ? C : 4, CG = logit_groups(C, NT, LEAN);
+    static_assert(C % CG == 0, "groups come in chunks of CG");
     f32x4 crf[CH];
     i32x4 tau[CH], ps[CH];
 #pragma unroll
