@@ -2079,11 +2079,10 @@ __global__ __launch_bounds__(NT) void finish_kernel(Dev d, int unit_begin, uint3
 // Both passes share a unit's blocks out over S wavefronts, as many as fill the chip evenly: with a wavefront per chunk of
 // 256 entries, 128 units of 9350 entries were 1280 workgroups on 768 places.  Measured on that shape, 32 queries,
 // G = 5: first pass 111 -> 88 us, second pass 163 -> 97 us.
-// Then, the same shape: results of the products in ordinary registers (a compiler option), the maximum looked for once per span, two tiles
-// at a time with registers for three wavefronts per SIMD (the scheduler, left to itself, saves registers and waits for every LDS read),
-// the segment table in a register: 89 -> 76 and 98 -> 94 us. The first pass issues 18 M vector instructions where it issued 26 M, and is bound by
-// their and the products' issue; the second by the products and by its stores (without them 77, without the products 66, without
-// the exponentials 92 us).
+// Then, the same shape: results of the products in ordinary registers (a compiler option), queries staged with all loads in flight, the
+// segment table in a register, and in the second pass two tiles at a time with registers for three wavefronts per SIMD: 92 -> 88 and 98 -> 95 us.
+// The first pass is bound by the issue of vector instructions and products; the second by the products and by its stores (without them 77,
+// without the products 66, without the exponentials 92 us).
 // Buffers of a batch of nq queries for the UL units of a layer (tiles and columns as in the first pass):
 //   sml [tile][unit][span][column][2]     maximum (rounded up) and sum of the softmax over a wavefront's blocks
 //   smi [tile][unit][column][2]           maximum (rounded up) and 1 / sum over all the entries the column's query sees
@@ -2163,7 +2162,7 @@ struct SeedSpan {
 // query j of the window sees the entries of positions <= its own, i.e. indices < P - W + j + 1 (the prompt's entries
 // sit in position order).
 // grid: (ceil(S / 4), units of the layer), kThreads threads, nt * 4096 bytes of dynamic LDS.
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 3))) void seed_scan_kernel(Dev d, int unit_begin, const uint16_t* __restrict__ q_obs, int j0, int nq, int P, int W,
+__global__ __launch_bounds__(kThreads) void seed_scan_kernel(Dev d, int unit_begin, const uint16_t* __restrict__ q_obs, int j0, int nq, int P, int W,
                                                              int S, float* __restrict__ sml) {
   extern __shared__ unsigned char smem[];
   u32x4* s_q = reinterpret_cast<u32x4*>(smem);
@@ -2188,99 +2187,65 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 3))
   }
   const float c = d.scale_log2e;
   const uint16_t* kp = d.K + lane * 8;
-  KFrag ka, kn;
-  auto products = [&](int tl, float (&sv)[8]) {
-    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int s4 = 0; s4 < 4; ++s4) {
-      const bf16x8 qv = as_bf16x8(s_q[(tl * 4 + s4) * 64 + lane]);
-      s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ka.k[s4]), qv, s0, 0, 0, 0);
-      s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ka.k[4 + s4]), qv, s1, 0, 0, 0);
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      sv[v] = s0[v];
-      sv[4 + v] = s1[v];
-    }
-  };
-  auto sum = [&](int tl, const float (&sv)[8], auto rounded) {
-    float p[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) p[i] = seed_exp<decltype(rounded)::value>(sv[i], c, m_run[tl]);
-    l_run[tl] += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
-  };
-  // TRACK: the maximum follows every block.  Otherwise only the span's first block and those that need a mask look for it: the
-  // others' sums are relative to what those left, which is as good as any maximum unless a sum grows beyond 2^60; then everything
-  // is done again with TRACK.  (Looking for it is a quarter of a tile's vector instructions, which is what bounds the pass.)
-  auto sweep = [&](auto track, auto rounded) {
+  auto sweep = [&](auto rounded) {
+    KFrag ka, kn;
     if (sp.b < sp.b1) load_k(ka, kp + sp.off(sp.b));
     for (int blk = sp.b; blk < sp.b1; ++blk) {
       load_k(kn, kp + sp.off(min(blk + 1, sp.b1 - 1)));
-      if (!decltype(track)::value && blk > sp.b && (blk + 1) * kBlk <= n_first) {      // every query sees the block whole
-        // two tiles at a time, to have one's products under the other's exponentials
+      const int e0 = blk * kBlk + 4 * kg;
 #pragma unroll
-        for (int tl = 0; tl < kSeedTiles; tl += 2) {
-          if (tl + 1 < nt) {
-            float sa[8], sb[8];
-            products(tl, sa);
-            products(tl + 1, sb);
-            sum(tl, sa, rounded);
-            sum(tl + 1, sb, rounded);
-          } else if (tl < nt) {
-            float sv[8];
-            products(tl, sv);
-            sum(tl, sv, rounded);
+      for (int tl = 0; tl < kSeedTiles; ++tl) {
+        if (tl < nt && blk * kBlk < n_first + min(q_lo[tl + 1], nq - 1)) {     // uniform: else no query of the tile sees the block
+          bf16x8 qv[4];
+#pragma unroll
+          for (int s4 = 0; s4 < 4; ++s4) qv[s4] = as_bf16x8(s_q[(tl * 4 + s4) * 64 + lane]);
+          f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int s4 = 0; s4 < 4; ++s4) s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ka.k[s4]), qv[s4], s0, 0, 0, 0);
+#pragma unroll
+          for (int s4 = 0; s4 < 4; ++s4) s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ka.k[4 + s4]), qv[s4], s1, 0, 0, 0);
+          float sv[8];
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            sv[v] = s0[v];
+            sv[4 + v] = s1[v];
           }
-        }
-      } else {
-        const int e0 = blk * kBlk + 4 * kg;
+          if ((blk + 1) * kBlk > n_first + q_lo[tl]) {      // a block that the tile's first query sees whole needs no mask
+            const int lim = n_first + (kSeedCols * tl + j) / G;            // entries this column's query sees
 #pragma unroll
-        for (int tl = 0; tl < kSeedTiles; ++tl) {
-          if (tl < nt && blk * kBlk < n_first + min(q_lo[tl + 1], nq - 1)) {     // uniform: else no query of the tile sees the block
-            float sv[8];
-            products(tl, sv);
-            if ((blk + 1) * kBlk > n_first + q_lo[tl]) {      // a block that the tile's first query sees whole needs no mask
-              const int lim = n_first + (kSeedCols * tl + j) / G;            // entries this column's query sees
-#pragma unroll
-              for (int v = 0; v < 4; ++v) {
-                sv[v] = (e0 + v < lim) ? sv[v] : -INFINITY;
-                sv[4 + v] = (e0 + 16 + v < lim) ? sv[4 + v] : -INFINITY;
-              }
+            for (int v = 0; v < 4; ++v) {
+              sv[v] = (e0 + v < lim) ? sv[v] : -INFINITY;
+              sv[4 + v] = (e0 + 16 + v < lim) ? sv[4 + v] : -INFINITY;
             }
-            // The maximum is kept rounded up to a whole number: sums are then rescaled by exact powers of two, here and
-            // where partials meet.
-            const float bm = c * fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
-            if (bm > m_run[tl]) {
-              const float m_new = ceilf(bm);
-              l_run[tl] *= fast_exp2(m_run[tl] - m_new);      // 0 the first time
-              m_run[tl] = m_new;
-            }
-            sum(tl, sv, rounded);
           }
+          // The maximum is kept rounded up to a whole number: sums are then rescaled by exact powers of two, here and
+          // where partials meet.  Every tile looks for it, so that the exponents of what weighs are small and carry the rounding of
+          // small numbers.  (Looked for in a span's first block alone, sums redone from 2^60 on: 12 us less, but weights off by
+          // 1.6e-6 where logits rise by 40 behind that block, else by 3e-7.  Tiles done again where eight exponentials pass 16:
+          // no slower on even prompts, 22 us slower on ones with heavy entries here and there.)
+          const float bm = c * fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
+          if (bm > m_run[tl]) {
+            const float m_new = ceilf(bm);
+            l_run[tl] *= fast_exp2(m_run[tl] - m_new);      // 0 the first time
+            m_run[tl] = m_new;
+          }
+          float p[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) p[i] = seed_exp<decltype(rounded)::value>(sv[i], c, m_run[tl]);
+          l_run[tl] += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
         }
       }
       ka = kn;
     }
   };
-  sweep(std::false_type{}, std::false_type{});
-  bool again = false;
+  sweep(std::false_type{});
+  bool far = false;
 #pragma unroll
-  for (int tl = 0; tl < kSeedTiles; ++tl) again |= !(l_run[tl] <= 0x1p60f) || is_far(m_run[tl]);
-  if (__any(again)) {
+  for (int tl = 0; tl < kSeedTiles; ++tl) far |= is_far(m_run[tl]);
+  if (__any(far)) {                                       // the maxima stand; the sums once more
 #pragma unroll
-    for (int tl = 0; tl < kSeedTiles; ++tl) {
-      m_run[tl] = kNoMax;
-      l_run[tl] = 0.f;
-    }
-    sweep(std::true_type{}, std::false_type{});
-    bool far = false;
-#pragma unroll
-    for (int tl = 0; tl < kSeedTiles; ++tl) far |= is_far(m_run[tl]);
-    if (__any(far)) {                                     // the maxima stand; the sums once more
-#pragma unroll
-      for (int tl = 0; tl < kSeedTiles; ++tl) l_run[tl] = 0.f;
-      sweep(std::true_type{}, std::true_type{});
-    }
+    for (int tl = 0; tl < kSeedTiles; ++tl) l_run[tl] = 0.f;
+    sweep(std::true_type{});
   }
   // per tile, the column's four lanes (kg = 0..3): maximum, then the sums rescaled to it, in a fixed order
 #pragma unroll
