@@ -1363,13 +1363,17 @@ struct HitRule {
   __device__ __forceinline__ bool operator()(uint32_t b, int pe) const { return (b > theta) | ((b == theta) & (ties_all | (pe <= pos_cut))); }
 };
 
+// No threshold to look for: the reward is the weight itself, or p >= 1 marks every entry (the weights' sum, which rounding may leave above 1, is
+// not asked).
+__device__ __forceinline__ bool every_entry_hit(const Dev& d) { return (d.reward_mode != 0) | (d.top_p >= 1.0f); }
+
 // Step 1 over weights in val(0 .. n - 1) (LDS), any n
 template <class Val, int NT = kThreads>
 __device__ __forceinline__ HitRule top_p_lds(const Dev& d, Slots base, int n, Val val, RedBuf<NT>& rb, int& phase, int tid) {
   uint32_t theta = 0;
   bool ties_all = true;
   int pos_cut = 0x7FFFFFFF;
-  if (d.reward_mode == 0) {
+  if (!every_entry_hit(d)) {
     for (int bit = 30; bit >= 0; --bit) {
       const uint32_t cand = theta | (1u << bit);
       float part = 0.f;
@@ -1648,7 +1652,7 @@ __device__ __forceinline__ void clear_top(TopBuf& tb, int tid, int threads) {
 template <int R, int NT = kThreads, bool CLEARED = false>
 __device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, const float (&a)[R], TopBuf& tb, int new_last_t, RedBuf<NT>& rb, int& phase,
                                               int tid) {
-  if (d.reward_mode != 0) return HitRule{0u, true, 0x7FFFFFFF};
+  if (every_entry_hit(d)) return HitRule{0u, true, 0x7FFFFFFF};
   constexpr int kList = NT < 256 ? NT : 256;
   const int lane = tid & 63, wave = tid >> 6;
   // (not known to the compiler as the same in every unit: kept in registers across the units of a persistent kernel it would be
