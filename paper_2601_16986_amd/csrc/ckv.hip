@@ -336,11 +336,12 @@ bool one_block_each(const ckv_ctx* c, int count) { return c->budget_total / c->u
 int launch_layer_step(ckv_ctx* c, hipStream_t s, int begin, int count, const uint16_t* q, const uint16_t* k_new, const uint16_t* v_new, void* out,
                       uint32_t flags, int mode, int advance) {
   const int upl = c->units_per_layer, cap = c->lay.cap;
-  const LayerCall call{q, k_new, v_new, out, begin, flags, mode, begin / upl, count / upl, advance};
   auto go = [&](auto one_block, auto entries) {
     constexpr bool kOne = decltype(one_block)::value;
     constexpr int kRmax = decltype(entries)::value, kPer = kLayerThreads / 64 * kBlk * (kOne ? 1 : kChunkBlocks);
-    hipLaunchKernelGGL((layer_step_kernel<kOne, kRmax>), dim3((unsigned)count, (unsigned)((cap + kPer - 1) / kPer)), dim3(kLayerThreads),
+    const int pieces = (cap + kPer - 1) / kPer;
+    const LayerCall call{q, k_new, v_new, out, begin, flags, mode, begin / upl, count / upl, advance, looks_early((long long)count * pieces, c->n_cu)};
+    hipLaunchKernelGGL((layer_step_kernel<kOne, kRmax>), dim3((unsigned)count, (unsigned)pieces), dim3(kLayerThreads),
                        kRmax ? c->layer_lds : (size_t)kLayerScanLds, s, c->dev, call);
   };
   auto by_length = [&](auto one_block) {

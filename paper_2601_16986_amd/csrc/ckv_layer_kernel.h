@@ -15,7 +15,10 @@
 // whole step, goes on with the bookkeeping from the unit's logits, which therefore went to memory the coherent way.  It
 // changes the unit's length, so every workgroup of the unit arrives, those without work too (unless the bookkeeping follows in
 // another launch): none can start late and take the new length for the old one.  A workgroup that finds all others arrived before it publishes
-// its own partial keeps it in registers.
+// its own partial keeps it in registers, if it looks at all: where the whole work list runs at once, a workgroup per compute unit,
+// that saves a unit's last workgroup a round trip (2 units of 200 entries, attention only, 7.3 against 8.2 us per layer, 8 units of 700, whole
+// step, 16.3 / 18.3); with more of them the looks, past every cache at words that the others are counting on, hold everybody up (16 units
+// of 5000 entries, scan alone, 23.4 / 18.4 us, 32 of 3700, deferred, 29.7 / 22.5, 56 of 2000, whole step, 38.2 / 28.9).
 //
 // Two shapes, <true, .> a block per wavefront, a single round trip to memory, two workgroups per compute unit, while the entries that the
 // budgets allow are no more than those hold (us per layer, scan alone, one block / eight: 8 units of 2048 entries 10 / 23, 32 units
@@ -46,6 +49,7 @@ struct LayerCall {
   int mode;              // kAttend: attention only, kWholeStep, kScanOnly: the bookkeeping follows in finish_kernel
   int layer, layers;     // kScanOnly: the first layer, and how many
   int advance;           // the time moves on with this launch
+  int early;             // a workgroup looks at its unit's counter before it publishes (looks_early)
 };
 
 // Entry rr of the block in (ka, va) is replaced by the rows in `rows` (LDS: 128 bf16 of the key, then 128 of the
@@ -229,7 +233,7 @@ __global__ __launch_bounds__(kLayerThreads, kOne ? 4 : 2) void layer_step_kernel
       l_run += __shfl_xor(l_run, 16);
       l_run += __shfl_xor(l_run, 32);
     }
-    if (tid == 0 && arrivals > 1) seen = get_coherent(&d.arrive[u]);
+    if (tid == 0 && arrivals > 1 && call.early) seen = get_coherent(&d.arrive[u]);
     // ---- the workgroup's states into one: wavefront w takes head w
     if (head_lane && kg == 0) {
       s_m[w][j] = m_run;

@@ -17,4 +17,8 @@ CKV_PLAN int logit_groups(int groups, int threads, bool lean) {
   return 2;
 }
 
+// Whether the workgroups of a step look at their unit's counter of arrivals before they publish their own part: only if all of them run at
+// once, one per compute unit (figures at layer_step_kernel).
+CKV_PLAN bool looks_early(long long workgroups, int n_cu) { return workgroups < n_cu; }
+
 }  // namespace ckv

@@ -28,3 +28,10 @@ def test_logits_are_asked_for_in_portions_that_divide_a_thread_s_groups(tmp_path
         const int n = ckv::logit_groups(groups, threads, lean);
         if (n < 1 || groups % n != 0) return std::printf("%d of %d groups, %d threads\n", n, groups, threads), 1;
       }""")
+
+
+def test_counters_are_looked_at_early_only_if_every_workgroup_runs_at_once(tmp_path):
+    _run(tmp_path, r"""
+  for (int n_cu : {256, 80})
+    for (long long workgroups : {1ll, 10ll, n_cu - 1ll, n_cu + 0ll, n_cu + 1ll, 100000ll})
+      if (ckv::looks_early(workgroups, n_cu) != (workgroups < n_cu)) return std::printf("%lld workgroups, %d compute units\n", workgroups, n_cu), 1;""")
