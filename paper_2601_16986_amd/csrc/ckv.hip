@@ -328,9 +328,8 @@ int launch_finish(ckv_ctx* c, hipStream_t s, int begin, int count, uint32_t flag
   return CKV_OK;
 }
 
-// A block of 32 entries per wavefront while two workgroups per compute unit cover the entries that the budgets allow, else
-// eight (figures at the kernel).
-bool one_block_each(const ckv_ctx* c, int count) { return c->budget_total / c->units * count <= 2ll * c->n_cu * kChunk; }
+// Entries that a unit's budget allows, on average.
+long long mean_budget(const ckv_ctx* c) { return c->budget_total / c->units; }
 
 // A step of `count` units from `begin` on (or its scan, or attention alone: `mode`).
 int launch_layer_step(ckv_ctx* c, hipStream_t s, int begin, int count, const uint16_t* q, const uint16_t* k_new, const uint16_t* v_new, void* out,
@@ -338,9 +337,9 @@ int launch_layer_step(ckv_ctx* c, hipStream_t s, int begin, int count, const uin
   const int upl = c->units_per_layer, cap = c->lay.cap;
   auto go = [&](auto one_block, auto entries) {
     constexpr bool kOne = decltype(one_block)::value;
-    constexpr int kRmax = decltype(entries)::value, kPer = kLayerThreads / 64 * kBlk * (kOne ? 1 : kChunkBlocks);
-    const int pieces = (cap + kPer - 1) / kPer;
-    const LayerCall call{q, k_new, v_new, out, begin, flags, mode, begin / upl, count / upl, advance, looks_early((long long)count * pieces, c->n_cu)};
+    constexpr int kRmax = decltype(entries)::value;
+    const int pieces = step_pieces(cap, kOne);
+    const LayerCall call{q, k_new, v_new, out, begin, flags, mode, begin / upl, count / upl, advance, looks_early((long long)count * pieces, kOne, c->n_cu)};
     hipLaunchKernelGGL((layer_step_kernel<kOne, kRmax>), dim3((unsigned)count, (unsigned)pieces), dim3(kLayerThreads),
                        kRmax ? c->layer_lds : (size_t)kLayerScanLds, s, c->dev, call);
   };
@@ -349,7 +348,7 @@ int launch_layer_step(ckv_ctx* c, hipStream_t s, int begin, int count, const uin
     else if (cap <= 4 * kLayerThreads) go(one_block, std::integral_constant<int, 4>{});
     else go(one_block, std::integral_constant<int, 12>{});
   };
-  if (one_block_each(c, count)) by_length(std::true_type{});
+  if (one_block_each(mean_budget(c), count, c->n_cu)) by_length(std::true_type{});
   else by_length(std::false_type{});
   CKV_HIP(c, hipGetLastError());
   return CKV_OK;
@@ -881,13 +880,17 @@ int ckv_decode_step(ckv_ctx* c, int32_t layer, const void* q, const void* k_new,
   // of 600, up to 2400, 101 / 108, 48 of 2500, fixed, 124 / 138, 8 of 4654 88 / 97; with the threshold 56 of 924 143 / 159).
   const int cap = c->lay.cap;
   const bool beyond = (long long)count * ((cap + kChunk - 1) / kChunk) > 2ll * c->n_cu;
-  const bool apart = cap > 12 * kLayerThreads || (c->dev.reward_mode != 0 && cap > 6 * kLayerThreads && beyond && one_block_each(c, count));
-  const int mode = (flags & CKV_ATTENTION_ONLY) ? kAttend : apart ? kScanOnly : kWholeStep;
+  const bool apart = cap > 12 * kLayerThreads || (c->dev.reward_mode != 0 && cap > 6 * kLayerThreads && beyond && one_block_each(mean_budget(c), count, c->n_cu));
+  const int mode = (flags & CKV_ATTENTION_ONLY) ? (attends_apart(mean_budget(c), count, cap, c->n_cu) ? kAttendOnly : kAttend) : apart ? kScanOnly : kWholeStep;
   const uint32_t kflags = flags & (CKV_FUSE_EVICT | kLeaveMany);
   if (int rc = launch_layer_step(c, s, begin, count, (const uint16_t*)q, (const uint16_t*)k_new, (const uint16_t*)v_new, out, kflags, mode, advance)) return rc;
   if (c->profile) CKV_HIP(c, hipEventRecord(e1, s));
   if (mode == kScanOnly)
     if (int rc = launch_finish(c, s, begin, count, kflags)) return rc;
+  if (mode == kAttendOnly) {
+    hipLaunchKernelGGL(append_kernel, dim3(1), dim3(kWideThreads), 0, s, c->dev, begin, count, advance);
+    CKV_HIP(c, hipGetLastError());
+  }
   if (flags & kLeaveMany)
     if (int rc = launch_evict(c, s, begin, count, -1, 1)) return rc;
   if (advance && (flags & CKV_FUSE_EVICT)) return rebalance_after_eviction(c);

@@ -2055,6 +2055,28 @@ __global__ __launch_bounds__(NT) void finish_kernel(Dev d, int unit_begin, uint3
                                                         NewInCache{room}, []() {});
 }
 
+// What an attention-only step leaves besides the new entry's rows, behind a scan that leaves the records alone.
+// grid: one workgroup.
+__global__ __launch_bounds__(kWideThreads) void append_kernel(Dev d, int unit_begin, int count, int advance) {
+  const int t = d.sc[SC_T];
+  for (int u = unit_begin + (int)threadIdx.x; u < unit_begin + count; u += kWideThreads) {
+    const int n = d.n[u];
+    if (n < unit_cap(d, u)) {
+      const size_t s = slots_of(d, u) + n;
+      d.crf[s] = 0.0f;
+      d.tau[s] = t;
+      d.pos[s] = t;
+      d.flags[s] = 0;
+      d.n[u] = n + 1;
+    }
+  }
+  __syncthreads();                                       // every wavefront has read the time
+  if (advance && threadIdx.x == 0) {
+    d.sc[SC_T] = t + 1;
+    d.sc[SC_WINDOW_STEPS] = d.sc[SC_WINDOW_STEPS] + 1;
+  }
+}
+
 // ------------------------------------------------------------------ prompt replay (scores of a loaded prompt)
 // The prompt's last W queries in a few kernels per batch of queries.  What a query does to the scores splits
 // into a part that does not depend on the scores - its mean attention weights over the entries it sees and,

@@ -36,8 +36,11 @@
 
 namespace ckv {
 
-enum { kAttend = 0, kWholeStep = 1, kScanOnly = 2 };
+// What a launch does: a whole step; attention alone and the append's records; or either without what follows in another launch
+// (kScanOnly: the bookkeeping, in finish_kernel; kAttendOnly: the records, in append_kernel).
+enum { kAttend = 0, kWholeStep = 1, kScanOnly = 2, kAttendOnly = 3 };
 constexpr int kLayerWaves = 8, kLayerThreads = 64 * kLayerWaves;
+static_assert(kLayerWaves * kBlk == kChunk, "a workgroup's pieces as step_pieces counts them");
 
 struct LayerCall {
   const uint16_t* q;
@@ -46,7 +49,7 @@ struct LayerCall {
   void* out;
   int unit_begin;
   uint32_t flags;        // the step's call flags (bookkeeping)
-  int mode;              // kAttend: attention only, kWholeStep, kScanOnly: the bookkeeping follows in finish_kernel
+  int mode;
   int layer, layers;     // kScanOnly: the first layer, and how many
   int advance;           // the time moves on with this launch
   int early;             // a workgroup looks at its unit's counter before it publishes (looks_early)
@@ -84,7 +87,7 @@ struct LayerLogits {
   Buffer unit;
   int at;
   int mode;
-  __device__ __forceinline__ explicit operator bool() const { return mode != kAttend; }
+  __device__ __forceinline__ explicit operator bool() const { return mode == kWholeStep || mode == kScanOnly; }
   __device__ __forceinline__ void operator()(int first, f32x4 row) const {
     if (mode == kWholeStep)
       put_coherent16(unit, at + first, row);
@@ -131,7 +134,8 @@ __global__ __launch_bounds__(kLayerThreads, kOne ? 4 : 2) void layer_step_kernel
   const int n = n_old + (full ? 0 : 1);
   const int nblk = (n + kBlk - 1) / kBlk;
   const int nwg = (nblk + kLayerWaves * span - 1) / (kLayerWaves * span);
-  const int arrivals = mode == kScanOnly ? nwg : (int)gridDim.y;
+  const bool apart = mode == kScanOnly || mode == kAttendOnly;      // nothing in this launch changes a unit's length
+  const int arrivals = apart ? nwg : (int)gridDim.y;
   if (cg == 0) {
     // the bookkeeping in another launch finds the step's time at its layer; nothing else in this launch reads the time
     if (urel == 0 && mode == kScanOnly) {
@@ -146,10 +150,10 @@ __global__ __launch_bounds__(kLayerThreads, kOne ? 4 : 2) void layer_step_kernel
     if (full && tid == 0) atomicOr(&d.sc[SC_STATUS], 1);
   }
   const bool active = cg < nwg;
-  if (!active && mode == kScanOnly) return;
+  if (!active && apart) return;
   // what the finishing workgroup needs of the unit and of the decay table
   const int s_tab_n = min(kTabLds, d.tab_last + 1);
-  if (mode != kScanOnly) {
+  if (!apart) {
     if (tid < d.max_seg) s_row[tid] = row[tid];
     if (tid < s_tab_n) s_tab[tid] = d.tab[tid];
     if (mode == kWholeStep) clear_top(*top, tid, NT);
@@ -203,7 +207,7 @@ __global__ __launch_bounds__(kLayerThreads, kOne ? 4 : 2) void layer_step_kernel
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       }
-      float* lds_lg = mode == kAttend ? nullptr : s_lg[w];
+      float* lds_lg = mode == kAttend || mode == kAttendOnly ? nullptr : s_lg[w];
       const LayerLogits lg{buffer_of(d.logits + (size_t)u * d.cap * G, d.cap * G), e0 * G + 4 * lane, mode};
       if constexpr (kOne) {
         if (inject) {
@@ -354,7 +358,7 @@ __global__ __launch_bounds__(kLayerThreads, kOne ? 4 : 2) void layer_step_kernel
         if (mode == kScanOnly) {
           d.msum[((size_t)u * kMaxGroup + w) * 2] = M;
           d.msum[((size_t)u * kMaxGroup + w) * 2 + 1] = inv;
-        } else {
+        } else if (mode == kWholeStep) {
           sM[w] = M;
           sInv[w] = inv;
         }
@@ -362,7 +366,7 @@ __global__ __launch_bounds__(kLayerThreads, kOne ? 4 : 2) void layer_step_kernel
     }
     if (mode == kWholeStep) __syncthreads();                 // the statistics are there, and the scan's LDS is free
   };
-  if (mode == kScanOnly) {
+  if (apart) {
     merge();
     return;
   }

@@ -1,5 +1,6 @@
 // Choices that kernels and host make by sizes alone.  Plain C++, no HIP, so that a host program can include it.
 #pragma once
+#include "ckv_layout.h"
 
 #if defined(__HIPCC__)
 #define CKV_PLAN __host__ __device__ constexpr
@@ -17,8 +18,31 @@ CKV_PLAN int logit_groups(int groups, int threads, bool lean) {
   return 2;
 }
 
-// Whether the workgroups of a step look at their unit's counter of arrivals before they publish their own part: only if all of them run at
-// once, one per compute unit (figures at layer_step_kernel).
-CKV_PLAN bool looks_early(long long workgroups, int n_cu) { return workgroups < n_cu; }
+// A step of few units: a block of 32 entries per wavefront while two workgroups per compute unit cover the entries that the budgets (`mean`
+// each, on average) allow, else eight (figures at layer_step_kernel).
+CKV_PLAN bool one_block_each(long long mean, int count, int n_cu) { return mean * count <= 2ll * n_cu * kChunk; }
+// Its workgroups per unit, by the capacity: most of them have nothing to do where the budgets stay far below it.
+CKV_PLAN int step_pieces(int cap, bool one_block) {
+  const int piece = kChunk * (one_block ? 1 : kChunkBlocks);
+  return (cap + piece - 1) / piece;
+}
+
+// Workgroups of a step that run about at once: with a block per wavefront two fit on a compute unit, but only one each is as good as alone.
+CKV_PLAN long long at_once(bool one_block, int n_cu) { return (one_block ? 1ll : 2ll) * n_cu; }
+// Whether the workgroups look at their unit's counter of arrivals before they publish their own part: only if none has to wait for its place
+// (figures at layer_step_kernel; eight blocks each, attention only, with the look / without: 64 units of 2000 entries, 256 workgroups, 26.8 / 28.7 us,
+// 200 of 600, 400 workgroups, 17.7 / 18.8).
+CKV_PLAN bool looks_early(long long workgroups, bool one_block, int n_cu) { return workgroups < at_once(one_block, n_cu); }
+
+// An attention-only step leaves its records to a launch of their own (append_kernel) unless all its workgroups run at once, or nearly. In one
+// launch the workgroups without work must arrive at their unit's counter like the others before its length may change, and queue for their
+// places to do so (us per layer, captured, one launch / two: a block per wavefront, 2 units of 1000 entries at capacity 8192, 64 workgroups, 9.5 / 10.5,
+// 32 of 600 at 1184, 160, 10.8 / 11.6, 16 of 200 at 4096, 256, 9.0 / 8.3, 64 of 200 at 4096, 1024, 13.7 / 9.4, 64 of 200 at 32768, 8192,
+// 47 / 12.7; eight blocks each, 128 of 600 at 4096, 256, 14.2 / 14.9, 104 of 1000 at 8192, 416, 17.9 / 18.5, 256 of 200 at 4096, 512, 17.4 / 14.7,
+// 400 of 1000 at 32768, 6400, 67 / 46).
+CKV_PLAN bool attends_apart(long long mean, int count, int cap, int n_cu) {
+  const bool one_block = one_block_each(mean, count, n_cu);
+  return (long long)count * step_pieces(cap, one_block) >= at_once(one_block, n_cu);
+}
 
 }  // namespace ckv

@@ -1,0 +1,74 @@
+"""Attention-only steps in one launch or two (by the workgroups that the capacity makes), in both shapes: outputs, the appended entry and its
+records against the kernel that takes whole units; units that are empty, at the edges of blocks and workgroups, and full; captured."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+LENGTHS = [0, 1, 31, 32, 255, 256, 257, 511, 512, 1000, 1500, 1919, 2015, 2046]
+
+
+def _steps(path, cap, budget, G, bf16, graph=False, layers=1):
+    import torch
+    from paper_2601_16986_amd import ckv
+    B, H, t, steps = len(LENGTHS), 1, 9000, 3
+    g = ckv.CrystalKV(layers, B, H * G, H, 128, cap, np.full((layers, B, H), budget, np.int32), t0=t, budget_min=1, budget_max=cap - 1,
+                      headroom=1 if cap > 2048 else 0,
+                      out_dtype=ckv.BF16 if bf16 else ckv.F32)
+    g.set_path(path)
+    gen = torch.Generator(device=g.device)
+    gen.manual_seed(5)
+    rnd = lambda *s: torch.randn(s, generator=gen, device=g.device).to(torch.bfloat16)
+    P = max(LENGTHS)
+    n = torch.tensor(LENGTHS, dtype=torch.int32, device=g.device).reshape(B, H)
+    pos = torch.arange(P, device=g.device, dtype=torch.int32).expand(B, H, P).contiguous()
+    crf = torch.rand((B, H, P), generator=gen, device=g.device) + 0.25
+    for l in range(layers):
+        g.load_cache(l, rnd(B, H, P, 128), rnd(B, H, P, 128), n, crf, pos, pos)
+    q, kn, vn = rnd(steps, layers, B, H * G, 128), rnd(steps, layers, B, H, 128), rnd(steps, layers, B, H, 128)
+    out = torch.empty((layers, B, H * G, 128), dtype=torch.bfloat16 if bf16 else torch.float32, device=g.device)
+    now = [x[0].clone() for x in (q, kn, vn)]
+    outs = []
+
+    def step():
+        for l in range(layers):
+            g.decode_step(now[0][l], now[1][l], now[2][l], layer=l, out=out[l], attention_only=True, evict=False)
+
+    if graph:
+        torch.cuda.synchronize()
+        cg = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(cg):
+            step()
+    for s in range(steps):
+        for x, y in zip(now, (q, kn, vn)):
+            x.copy_(y[s])
+        cg.replay() if graph else step()
+        outs.append(out.clone())
+    state = [g.export_unit(l, b, 0) for l in range(layers) for b in range(B)]
+    got = torch.stack(outs).double().cpu().numpy(), state, g.lengths(), g.time(), g.status()
+    g.close()
+    return got
+
+
+def _same(a, b, exact):
+    assert np.array_equal(a[2], b[2]) and a[3:] == b[3:]
+    bound = 0.0 if exact else 4e-5                       # fp32 accumulation and probabilities to 16 bits, in another split of the unit
+    assert np.all(np.abs(a[0] - b[0]) <= bound * np.abs(b[0]).max(-1, keepdims=True))
+    for x, y in zip(a[1], b[1]):
+        for f in ("n", "n_evicted"):
+            assert x[f] == y[f]
+        for f in ("pos", "tau", "crf", "K", "V", "flags"):
+            assert np.array_equal(x[f], y[f]), f
+
+
+# 14 units: 112 workgroups (one launch), 462 and 896 (two) of a block per wavefront; with budgets near the capacity 70 of eight blocks (one).
+# At capacity 2048 the longest unit is full from the second step on.
+@pytest.mark.parametrize("cap,budget", [(2048, 2047), (8224, 3000), (16384, 2100), (10016, 9600)])
+@pytest.mark.parametrize("G", [1, 5])
+def test_against_whole_units(G, cap, budget):
+    _same(_steps(1, cap, budget, G, False), _steps(2, cap, budget, G, False), exact=False)
+
+
+@pytest.mark.parametrize("cap,budget", [(2048, 2047), (8224, 3000)])
+def test_captured_layers(cap, budget):
+    _same(_steps(1, cap, budget, 3, True, graph=True, layers=3), _steps(1, cap, budget, 3, True, layers=3), exact=True)
