@@ -870,18 +870,10 @@ int ckv_decode_step(ckv_ctx* c, int32_t layer, const void* q, const void* k_new,
     if (advance && (flags & CKV_FUSE_EVICT)) return rebalance_after_eviction(c);
     return CKV_OK;
   }
-  // Few units: several workgroups per unit, the bookkeeping in the same kernel by a unit's last one of 512 threads, where units
-  // cannot be long; else in a kernel of its own by 1024 (us per layer, captured, one kernel / two: 64 units of 1024 entries on
-  // average, up to 4096, 32 / 31, 256 such units 51 / 54; 128 of 4096, fixed, 74 / 78; 2 of 6000 23 / 26; 64 of 2048, up to 8192, 51 / 44, 128
-  // such units 56 / 53, 16 of 8000, up to 32000, 104 / 76).
-  // The same where the reward is the weight itself, so that the bookkeeping has no threshold to find, the work list with its places for
-  // the longest units goes beyond the two workgroups per compute unit that run at once, and 512 threads have more than six entries each
-  // (four layers, captured, one kernel / two: 32 units of 1200 entries on average, up to 4800, 107 / 96, 56 of 924, up to 3696, 113 / 105; but 104
-  // of 600, up to 2400, 101 / 108, 48 of 2500, fixed, 124 / 138, 8 of 4654 88 / 97; with the threshold 56 of 924 143 / 159).
-  const int cap = c->lay.cap;
-  const bool beyond = (long long)count * ((cap + kChunk - 1) / kChunk) > 2ll * c->n_cu;
-  const bool apart = cap > 12 * kLayerThreads || (c->dev.reward_mode != 0 && cap > 6 * kLayerThreads && beyond && one_block_each(mean_budget(c), count, c->n_cu));
-  const int mode = (flags & CKV_ATTENTION_ONLY) ? (attends_apart(mean_budget(c), count, cap, c->n_cu) ? kAttendOnly : kAttend) : apart ? kScanOnly : kWholeStep;
+  // Few units: several workgroups per unit, what follows the attention by a unit's last one, or in a kernel of its own.
+  const long long mean = mean_budget(c);
+  const int mode = (flags & CKV_ATTENTION_ONLY) ? (attends_apart(mean, count, c->lay.cap, c->n_cu) ? kAttendOnly : kAttend)
+                   : books_apart(mean, count, c->lay.cap, c->n_cu, kLayerThreads, 12 * kLayerThreads) ? kScanOnly : kWholeStep;
   const uint32_t kflags = flags & (CKV_FUSE_EVICT | kLeaveMany);
   if (int rc = launch_layer_step(c, s, begin, count, (const uint16_t*)q, (const uint16_t*)k_new, (const uint16_t*)v_new, out, kflags, mode, advance)) return rc;
   if (c->profile) CKV_HIP(c, hipEventRecord(e1, s));

@@ -54,3 +54,18 @@ def test_attention_only_steps_do_not_wait_for_idle_workgroups(tmp_path):
           const bool one_block = ckv::one_block_each(mean, count, 256);
           if ((long long)count * ckv::step_pieces(cap, one_block) > (one_block ? 256 : 512)) return std::printf("%d units at %d\n", count, cap), 1;
         }""")
+
+
+def test_bookkeeping_in_the_step_or_apart(tmp_path):
+    """Shapes measured both ways, and the bound that the registers of the one kernel set."""
+    _run(tmp_path, r"""
+  struct { int mean, count, cap; bool apart; } measured[] = {
+      {200, 64, 6144, true}, {200, 256, 6144, true}, {200, 256, 2048, true}, {200, 52, 6144, false}, {200, 256, 256, false}, {700, 128, 6144, false},
+      {1200, 104, 6144, false}, {600, 200, 2432, false}, {3700, 64, 3712, true}, {3700, 72, 3712, true}, {5900, 56, 5920, true}, {5900, 32, 5920, false},
+      {5900, 104, 5920, false}, {2000, 72, 6144, false}, {2000, 128, 2016, false}, {128, 2, 160, false}, {2048, 8, 8224, true}};
+  for (auto& m : measured)
+    if (ckv::books_apart(m.mean, m.count, m.cap, 256, 512, 6144) != m.apart) return std::printf("%d units of %d at capacity %d\n", m.count, m.mean, m.cap), 1;
+  for (int mean = 1; mean < 32768; mean = mean * 3 / 2 + 1)
+    for (int count = 1; count < 2000; count = count * 3 / 2 + 1)
+      for (int cap : {6176, 8192, 32768})
+        if (!ckv::books_apart(mean, count, cap, 256, 512, 6144)) return std::printf("%d units at %d\n", count, cap), 1;""")
