@@ -1636,6 +1636,8 @@ struct alignas(16) TopBuf {
 constexpr int kBinShift = 18, kBins = 24 << 5, kBinFirst = (127 - 23) << 5;
 constexpr uint32_t kBinLow = (1u << kBinShift) - 1u;
 constexpr int kBinCount = 34;                 // the count's place: 32768 low parts of 18 bits lie below it
+constexpr int kSubShift = kBinShift - 8;      // a bin's 256 parts
+constexpr uint32_t kSubLow = (1u << kSubShift) - 1u;
 __device__ __forceinline__ double bin_edge(int i) { return (double)__uint_as_float((uint32_t)(kBinFirst + i) << kBinShift); }
 __device__ __forceinline__ double bin_unit(int i) { return (double)__uint_as_float((uint32_t)((kBinFirst + i) >> 5) << 23) * 0x1p-23; }
 
@@ -1649,7 +1651,8 @@ __device__ __forceinline__ void clear_top(TopBuf& tb, int tid, int threads) {
 
 // tb: in LDS, CLEARED (and a barrier since), or where something else may lie.  new_last_t >= 0: the unit's last entry is not in
 // the cache, or not to be looked up there, and has this position.
-template <int R, int NT = kThreads, bool CLEARED = false>
+// REFINE: long rows of flat weights, where a bin holds more than the list: the bin once more, by its next eight bits.
+template <int R, int NT = kThreads, bool CLEARED = false, bool REFINE = false>
 __device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, const float (&a)[R], TopBuf& tb, int new_last_t, RedBuf<NT>& rb, int& phase,
                                               int tid) {
   if (every_entry_hit(d)) return HitRule{0u, true, 0x7FFFFFFF};
@@ -1716,22 +1719,72 @@ __device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, c
   }
   block_sync<NT>(rb);
   // what every thread reads from LDS is made uniform: the branches on it are then scalar
-  const int bin = uniform_i32(tb.at), m = uniform_i32(tb.count);
-  uint32_t theta = 0;
+  const int bin = uniform_i32(tb.at);
+  int m = uniform_i32(tb.count);
+  uint32_t theta = 0, low_bits = kBinLow;         // the pattern's bits below `theta` that are still open
   int bit = 29;
   if (bin >= 0 && uniform_i32((int)tb.odd) == 0) {
     theta = (uint32_t)(kBinFirst + bin) << kBinShift;
     bit = kBinShift - 1;
+    if constexpr (REFINE) {
+      if (__builtin_expect(m > kList, 0)) {
+        for (int i = tid; i < 256; i += NT) tb.bin[i] = 0ull;
+        block_sync<NT>(rb);
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+          const uint32_t b = __float_as_uint(a[k]);
+          if ((b ^ theta) <= kBinLow) atomicAdd(&tb.bin[(b & kBinLow) >> kSubShift], (1ull << kBinCount) | (b & kSubLow));
+          if (k % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+        }
+        block_sync<NT>(rb);
+        if (wave == 0) {
+          // lane l: the four parts from 4 (63 - l) up, the highest first
+          const double unit = bin_unit(bin);
+          double part[4], mine = 0.0;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int i = 4 * (63 - lane) + 3 - e;
+            const u64 v = tb.bin[i];
+            part[e] = (double)(uint32_t)(v >> kBinCount) * (double)__uint_as_float(theta | ((uint32_t)i << kSubShift)) +
+                      (double)(v & ((1ull << kBinCount) - 1ull)) * unit;
+            mine += part[e];
+          }
+          double incl = mine;                              // sums up to each lane: inside a row of 16 lanes, then the rows before
+          incl += dpp_f64<kDppRowShr + 1>(incl);
+          incl += dpp_f64<kDppRowShr + 2>(incl);
+          incl += dpp_f64<kDppRowShr + 4>(incl);
+          incl += dpp_f64<kDppRowShr + 8>(incl);
+          const double row0 = readlane_f64(incl, 15), row1 = row0 + readlane_f64(incl, 31), row2 = row1 + readlane_f64(incl, 47);
+          incl += lane < 16 ? 0.0 : lane < 32 ? row0 : lane < 48 ? row1 : row2;
+          const double from = readlane_f64(tb.above, 0);
+          const u64 passed = __ballot(from + incl > p);
+          if (lane == (passed ? __builtin_ctzll(passed) : 63)) {        // (none only by rounding)
+            double above = from + (incl - mine);
+            int e = 0;
+            while (e < 3 && above + part[e] <= p) above += part[e++];
+            const int i = 4 * (63 - lane) + 3 - e;
+            tb.at = i;
+            tb.count = (int)(tb.bin[i] >> kBinCount);
+            tb.above = above;
+          }
+        }
+        block_sync<NT>(rb);
+        theta |= (uint32_t)uniform_i32(tb.at) << kSubShift;
+        m = uniform_i32(tb.count);
+        low_bits = kSubLow;
+        bit = kSubShift - 1;
+      }
+    }
     if (m <= kList) {
 #pragma unroll
       for (int k = 0; k < R; ++k) {
         const uint32_t b = __float_as_uint(a[k]);
-        if ((b ^ theta) <= kBinLow) tb.list[atomicAdd(&tb.listed, 1u)] = b;
+        if ((b ^ theta) <= low_bits) tb.list[atomicAdd(&tb.listed, 1u)] = b;
         if (k % 4 == 3) __builtin_amdgcn_sched_barrier(0);
       }
       block_sync<NT>(rb);
       // A candidate per thread: theta is the largest of them whose sum of those at least as large, on top of the bins above, exceeds p.
-      const double edge = bin_edge(bin), unit = bin_unit(bin), above = tb.above;
+      const double edge = REFINE ? (double)__uint_as_float(theta) : bin_edge(bin), unit = bin_unit(bin), above = tb.above;
       uint32_t mine = 0u, th = 0u, equal = 0u, larger = 0u, low = 0u;
       if (64 * wave < m) {
         mine = tb.list[tid];
@@ -1740,11 +1793,11 @@ __device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, c
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             larger += four[e] > mine ? 1u : 0u;
-            low += four[e] > mine ? four[e] & kBinLow : 0u;
+            low += four[e] > mine ? four[e] & low_bits : 0u;
             equal += four[e] == mine ? 1u : 0u;
           }
         }
-        const double sum = above + ((double)(larger + equal) * edge + (double)(low + equal * (mine & kBinLow)) * unit);
+        const double sum = above + ((double)(larger + equal) * edge + (double)(low + equal * (mine & low_bits)) * unit);
         th = ~wave_min_u32(~((tid < m && sum > p) ? mine : 0u));
         if (m > 64 && lane == 0) atomicMax(&tb.theta, th);
       }
@@ -2479,7 +2532,7 @@ __device__ __forceinline__ void seed_rewards_regs(const Dev& d, Slots base, int 
 #pragma unroll
     for (int e = 0; e < 4; ++e) a[4 * c + e] = (e0 + e < n) ? x[e] : 0.f;
   }
-  const HitRule rule = top_p_regs<R, kSeedThreads>(d, base, n, a, *reinterpret_cast<TopBuf*>(lst), -1, rb, phase, tid);
+  const HitRule rule = top_p_regs<R, kSeedThreads, false, true>(d, base, n, a, *reinterpret_cast<TopBuf*>(lst), -1, rb, phase, tid);
   uint32_t* bits = reinterpret_cast<uint32_t*>(rw);
 #pragma unroll
   for (int c = 0; c < R / 4; ++c) {
