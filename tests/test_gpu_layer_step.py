@@ -66,8 +66,9 @@ def _same_state(a, b, exact_scores=True):
         assert np.array_equal(np.sort(x["evicted_pos"]), np.sort(y["evicted_pos"]))
 
 
-# 13 lengths below 2048, and nine more up to 6111; few copies: a block per wavefront, many: eight
-@pytest.mark.parametrize("lengths,cap,copies", [(LENGTHS, 2048, 1), (LENGTHS, 2048, 8), (LENGTHS + LONG, 6112, 1), (LENGTHS + LONG, 6112, 2)])
+# 13 lengths below 2048, nine more up to 6111, or those alone; a block per wavefront while the budgets come to no more than 131072 entries (the
+# first and the third), else eight
+@pytest.mark.parametrize("lengths,cap,copies", [(LENGTHS, 2048, 1), (LENGTHS, 2048, 8), (LONG, 6112, 1), (LENGTHS + LONG, 6112, 1), (LENGTHS + LONG, 6112, 2)])
 @pytest.mark.parametrize("extra", [3, 0, -6])
 @pytest.mark.parametrize("G", [1, 5, 8])
 def test_against_whole_units(G, extra, lengths, cap, copies):
@@ -84,18 +85,19 @@ def test_weighted_reward(copies):
     _same_state(one, ref, exact_scores=False)
 
 
-# few places in the work list, or many; either side of the capacity from which many of them take two kernels
+# work lists that run at once, or queue
 @pytest.mark.parametrize("lengths,cap,copies", [(LONG, 6112, 1), (LENGTHS + [3000], 3072, 2), (LENGTHS + [3070], 3104, 1), (LENGTHS + [3070], 3104, 2)])
 @pytest.mark.parametrize("extra", [3, -6])
-def test_weighted_reward_in_one_kernel_or_two(lengths, cap, copies, extra):
+def test_weighted_reward_of_uneven_work_lists(lengths, cap, copies, extra):
     one, ref = (_steps(path, lengths, copies, extra, cap, 5, False, weighted=True) for path in (1, 2))
     assert np.all(np.abs(one[0] - ref[0]) <= 4e-5 * np.abs(ref[0]).max(-1, keepdims=True))
     _same_state(one, ref, exact_scores=False)
 
 
+@pytest.mark.parametrize("lengths", [LONG, LENGTHS + LONG])
 @pytest.mark.parametrize("extra", [0, -6])
-def test_repeats_and_replays(extra):
-    a, b, c = (_steps(1, LENGTHS + LONG, 1, extra, 6112, 5, False, graph=graph) for graph in (False, False, True))
+def test_repeats_and_replays(extra, lengths):
+    a, b, c = (_steps(1, lengths, 1, extra, 6112, 5, False, graph=graph) for graph in (False, False, True))
     assert np.array_equal(a[0], b[0]) and np.array_equal(a[0], c[0])
     _same_state(a, b)
     _same_state(a, c)

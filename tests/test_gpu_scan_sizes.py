@@ -1,5 +1,6 @@
 """The scan of few units in both of its shapes (chosen by the entries the budgets allow) at the edges of its blocks, chunks
-and workgroups, against attention in 64 bits; the step's records behind it, with and without bookkeeping."""
+and workgroups, against attention in 64 bits; the step's records behind it, in a launch of their own at this capacity (deferred, plain, or
+without bookkeeping)."""
 import numpy as np
 import pytest
 

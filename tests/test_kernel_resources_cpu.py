@@ -47,6 +47,6 @@ def test_static_lds_of_the_fused_kernels(kernels, waves, bound):
 
 def test_static_lds_of_kernels_that_hold_a_value_per_entry(kernels):
     """Their dynamic LDS takes 4 bytes per entry and a bit, up to 132 KB; 12 KB are left for what they declare."""
-    names = [n for n in kernels if "finish_kernel" in n or "seed_hits_kernelILi0E" in n]
-    assert len(names) == 3
+    names = [n for n in kernels if "finish_kernel" in n or "seed_hits_kernelILi0E" in n or "layer_step_kernel" in n]
+    assert len(names) == 3 + 6
     assert all(kernels[n]["group_segment_fixed_size"] <= 12 * 1024 for n in names)
