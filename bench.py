@@ -8,8 +8,9 @@ budgets, Alg. 2 at its interval.  Inputs are synthetic and resident in HBM
 before the timed region.  Prints ONE JSON line.
 
   value        decode steps/s from HIP-graph replays of the all-layers call
-  roofline     the dominant kernel (the fused per-unit kernel, or the scan kernel
-               when the separate kernels are used): algorithmic bytes per launch
+  roofline     the dominant kernel (the fused per-unit kernel, or, where units are
+               split, the one that attends, with the bytes of the bookkeeping
+               where that runs in it): algorithmic bytes per launch
                over its average duration, measured with HIP events around each
                launch in a separate eager pass
   cpu_baseline the numpy oracle timed on the host on a bounded sample
@@ -426,9 +427,11 @@ def main():
     if fullkv:                                           # attention only: K, V, q, out
         fused_bytes = step_bytes = scan_bytes + int(cfg.n_units) * cfg.group * 512
     fused_waves, _ = g.path_info()
-    # dominant kernel of an all-layers step: the fused per-unit kernel if the context uses it, else the scan kernel
-    kernel_name = f"unit_kernel<{fused_waves}>" if fused_waves else "layer_step_kernel"
-    kernel_bytes = fused_bytes if fused_waves else scan_bytes
+    # dominant kernel of an all-layers step: the fused per-unit kernel if the context uses it, else the one that attends, which
+    # includes the bookkeeping unless units may be long (as a rule)
+    whole = g.cap <= 6144
+    kernel_name = f"unit_kernel<{fused_waves}>" if fused_waves else f"layer_step_kernel ({'whole step' if whole else 'scan'})"
+    kernel_bytes = fused_bytes if fused_waves else step_bytes if whole else scan_bytes
     scan_avg_ms = scan_ms / max(launches, 1)
     achieved = kernel_bytes / (scan_avg_ms * 1e-3) / 1e9
     traffic = None if fullkv else measured_traffic(kernel_name, cfg.name)

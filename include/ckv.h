@@ -306,26 +306,29 @@ int ckv_import_unit(ckv_ctx* ctx, int32_t layer, int32_t seq, int32_t head, int3
                     const int32_t* pos, int32_t t_unit);
 
 /* Timing hook for benchmarks: while enabled, every ckv_decode_step brackets
- * its dominant kernel (the fused per-unit kernel, or the scan kernel when the
- * separate kernels are used) with HIP events on the launch stream (do not
- * enable while the stream is being captured into a graph).  ckv_profile_read
+ * its dominant kernel with HIP events on the launch stream (do not
+ * enable while the stream is being captured into a graph): the fused per-unit
+ * kernel, which does the whole step; or, where units are split among workgroups, the
+ * kernel that attends, which includes the bookkeeping unless that has a kernel of
+ * its own (deferred steps; as a rule capacities above 6144; see ckv_set_path).  ckv_profile_read
  * waits for the device and returns that kernel's summed time and launch count
  * since enabling. */
 int ckv_profile_enable(ckv_ctx* ctx, int32_t on);
 int ckv_profile_read(ckv_ctx* ctx, double* scan_ms, int32_t* launches);
 
 /* Which kernels ckv_decode_step uses: 0 = choose by unit count (default),
- * 1 = separate scan and finish kernels, 2 = the fused per-unit kernel, which
- * keeps the logits in LDS, in the widest variant that fits; 3 / 4 = the fused
+ * 1 = several workgroups per unit (one kernel, or the bookkeeping, or an attention-only
+ * step's records, in a second one where the capacity is large or makes many idle
+ * workgroups), 2 = the fused per-unit kernel, which keeps the logits in LDS, in the widest variant that fits; 3 / 4 = the fused
  * kernel with 4 / 2 wavefronts per unit (2 / 4 workgroups per compute unit).
- * Whatever the mode, a single-layer call takes the separate kernels if the
+ * Whatever the mode, a single-layer call splits the units if the
  * layer has fewer units than the fused kernel has workgroups or if its
  * bookkeeping is deferred.  A variant needs 4 * cap
  * bytes of LDS in its workgroup's share (CKV_EINVAL otherwise).  Results do not depend on the choice beyond
  * floating-point summation order.
  * ckv_path_info reports what all-layer steps use under the current mode:
- * *fused_waves = wavefronts per unit of the fused variant (0: separate
- * kernels), *lds_main_bytes = bytes of its LDS tile for logits and per-entry
+ * *fused_waves = wavefronts per unit of the fused variant (0: units are
+ * split), *lds_main_bytes = bytes of its LDS tile for logits and per-entry
  * values. */
 int ckv_set_path(ckv_ctx* ctx, int32_t mode);
 int ckv_path_info(ckv_ctx* ctx, int32_t* fused_waves, int32_t* lds_main_bytes);

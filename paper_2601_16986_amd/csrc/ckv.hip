@@ -48,7 +48,7 @@ struct ckv_ctx {
   int device = 0;               // the HIP device the context was created on
   size_t finish_lds = 0, layer_lds = 0;
   // fused path (unit_kernel)
-  int path_mode = 0;            // 0 auto, 1 separate kernels, 2 fused kernel, 3 / 4 fused with 4 / 2 wavefronts per unit
+  int path_mode = 0;            // 0 auto, 1 units split among workgroups, 2 fused kernel, 3 / 4 fused with 4 / 2 wavefronts per unit
   struct Fused {                // one variant of the fused kernel
     bool ok = false;
     int waves = 0;              // wavefronts per workgroup (= per unit)
@@ -205,7 +205,7 @@ int check_budgets(ckv_ctx* c, const ckv_layout* l, const ckv_lrfu_params* p, con
   return CKV_OK;
 }
 
-// The variant of the fused kernel the current path mode selects (nullptr: none fits or separate kernels).
+// The variant of the fused kernel the current path mode selects (nullptr: none fits, or units are split).
 const ckv_ctx::Fused* fused_variant(const ckv_ctx* c) {
   if (c->path_mode == 1) return nullptr;
   const ckv_ctx::Fused* f = c->path_mode == 3 ? &c->fused[0] : c->path_mode == 4 ? &c->fused[1]
@@ -317,7 +317,7 @@ bool leave_many_pays(const ckv_ctx* c, int count, bool deferred) {
   return count <= 5 * c->n_cu;
 }
 
-// The deferred bookkeeping of `count` units from `begin` on, behind their scan.  Workgroups of 256 threads where no unit can
+// The bookkeeping of `count` units from `begin` on in a kernel of its own, behind their scan (deferred or not).  Workgroups of 256 threads where no unit can
 // hold more than eight entries per thread, else 1024.
 int launch_finish(ckv_ctx* c, hipStream_t s, int begin, int count, uint32_t flags) {
   if (c->lay.cap <= 8 * kThreads)

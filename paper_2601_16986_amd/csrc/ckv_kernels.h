@@ -5,8 +5,9 @@
 //   layer_step_kernel (ckv_layer_kernel.h)  the units of one layer, or of a small context: append, attention and output with
 //                  several workgroups per unit, then the bookkeeping (mean attention weight per entry, top-p hit mask, CRF
 //                  update, aggregated CRF, and, optionally, eviction + compaction) by the workgroup that finishes the unit
-//   layer_step_kernel, finish_kernel   the same with the bookkeeping in a kernel of its own, one workgroup per unit: where units
-//                  may be long, or later, on a stream of the context's (deferred)
+//   layer_step_kernel, finish_kernel   the same with the bookkeeping in a kernel of its own, one workgroup per unit: straight behind
+//                  where that is faster (books_apart), or later, on a stream of the context's (deferred)
+//   layer_step_kernel, append_kernel   an attention-only step whose records have a launch of their own (attends_apart)
 //
 // and beside the step:
 //
@@ -1615,13 +1616,14 @@ __device__ __forceinline__ HitRule tie_rule(const Dev& d, Slots base, int n, con
 // patterns' top bits (24 octaves below 2 in bins of 1/32 octave) takes per bin the number of its weights and the
 // sum of their low bits in one 64-bit integer addition, so that a bin's sum is known exactly and does not depend on the order; the bin in which
 // the sum from above passes p follows from a scan over the bins in 64 bits.  The bin's weights, usually a few dozen, go to a list, where each
-// finds the sum of those at least as large, again from counts and low bits.  A bin of more than kList weights, and weights outside
+// finds the sum of those at least as large, again from counts and low bits.  A bin of more than kList weights (long rows: what is left of it after
+// another histogram over its next eight bits), and weights outside
 // the bins that might matter (below 2^-23 in all; negative, NaN or 2 and above), take two bits per round over all entries.
 //
 // What bounded the search was issue: nine instructions per weight and round, six rounds (three or four by bracketing), a barrier and a
 // reduction each; now about eight per weight in all and an LDS addition (a wavefront's 64-bit additions to a hundred random
 // bins take 13 cycles of the compute unit).  finish_kernel for 128 units of 2048 entries 20.8 -> 15.6 us, 4096 rows of 9350 weights of a
-// replay 80 -> 68 us, fused step of 896 units of 2048 entries 194.3 -> 190.6 us, of 6144 units 1243 -> 1238 us.
+// replay 80 -> 70 us, fused step of 896 units of 2048 entries 194.3 -> 190.6 us, of 6144 units 1243 -> 1238 us.
 // The scan over the bins moves through DPP and by one wavefront: its registers come on top of the weights and of what the callers
 // have in flight.
 struct alignas(16) TopBuf {
@@ -2062,8 +2064,8 @@ __device__ __forceinline__ void finish_unit(const Dev& d, int u, Slots base, int
   regs(std::integral_constant<int, 4>{});
 }
 
-// The deferred bookkeeping of a step behind layer_step_kernel, one workgroup per unit, at the time that the scan left for the unit's
-// layer: the new entry's rows are in the cache and its logits with the others, the unit's records still describe the step
+// The bookkeeping of a step in a kernel of its own, deferred or straight behind layer_step_kernel, one workgroup per unit, at the time that the scan
+// left for the unit's layer: the new entry's rows are in the cache and its logits with the others, the unit's records still describe the step
 // before.  A unit is a chain of about ten block reductions and memory round trips, so few units take 1024 threads each
 // (at most 8 entries per thread up to 8192).
 template <int NT>

@@ -13,8 +13,8 @@
 // The wavefronts combine their softmax states in LDS, a unit's workgroups through one partial each (coherent stores and
 // loads): the last of them to arrive at the unit's counter merges the partials in index order, writes the output and, in a
 // whole step, goes on with the bookkeeping from the unit's logits, which therefore went to memory the coherent way.  It
-// changes the unit's length, so every workgroup of the unit arrives, those without work too (unless the bookkeeping follows in
-// another launch): none can start late and take the new length for the old one.  A workgroup that finds all others arrived before it publishes
+// changes the unit's length, so every workgroup of the unit arrives, those without work too (unless what follows has another
+// launch, see books_apart and attends_apart): none can start late and take the new length for the old one.  A workgroup that finds all others arrived before it publishes
 // its own partial keeps it in registers, if it looks at all: where the whole work list runs at once, a workgroup per compute unit,
 // that saves a unit's last workgroup a round trip (2 units of 200 entries, attention only, 7.3 against 8.2 us per layer, 8 units of 700, whole
 // step, 16.3 / 18.3); with more of them the looks, past every cache at words that the others are counting on, hold everybody up (16 units
