@@ -31,18 +31,23 @@ CKV_PLAN int step_pieces(int cap, bool one_block) {
 CKV_PLAN long long at_once(bool one_block, int n_cu) { return (one_block ? 1ll : 2ll) * n_cu; }
 // Whether the workgroups look at their unit's counter of arrivals before they publish their own part: only if none has to wait for its place
 // (figures at layer_step_kernel; eight blocks each, attention only, with the look / without: 64 units of 2000 entries, 256 workgroups, 26.8 / 28.7 us,
-// 200 of 600, 400 workgroups, 17.7 / 18.8).
-CKV_PLAN bool looks_early(long long workgroups, bool one_block, int n_cu) { return workgroups < at_once(one_block, n_cu); }
+// 200 of 600, 400 workgroups, 17.7 / 18.8; a block per wavefront, 128 units of 100 at capacity 448, 256 workgroups, 7.7 / 9.1).
+CKV_PLAN bool looks_early(long long workgroups, bool one_block, int n_cu) { return workgroups <= at_once(one_block, n_cu); }
 
-// An attention-only step leaves its records to a launch of their own (append_kernel) unless all its workgroups run at once, or nearly. In one
-// launch the workgroups without work must arrive at their unit's counter like the others before its length may change, and queue for their
-// places to do so (us per layer, captured, one launch / two: a block per wavefront, 2 units of 1000 entries at capacity 8192, 64 workgroups, 9.5 / 10.5,
-// 32 of 600 at 1184, 160, 10.8 / 11.6, 16 of 200 at 4096, 256, 9.0 / 8.3, 64 of 200 at 4096, 1024, 13.7 / 9.4, 64 of 200 at 32768, 8192,
-// 47 / 12.7; eight blocks each, 128 of 600 at 4096, 256, 14.2 / 14.9, 104 of 1000 at 8192, 416, 17.9 / 18.5, 256 of 200 at 4096, 512, 17.4 / 14.7,
-// 400 of 1000 at 32768, 6400, 67 / 46).
+// An attention-only step leaves its records to a launch of their own (append_kernel) where the capacity makes many more workgroups than the
+// budgets have work for. In one launch these must arrive at their unit's counter like the others before its length may change, and queue for their
+// places to do so; a second launch costs 1.2 us, 3 where the host waits for it. Us per layer, captured, one launch / two:
+//  - a block per wavefront, units of one workgroup (its busy one often ends behind the idle ones): 128 of 100 entries at capacity 448, 128 idle, 7.7 / 8.7,
+//    200 of 150 at 512, 200 idle, 11.1 / 10.1, 400 of 100 at 448, 400 idle, 16.3 / 12.6;
+//  - longer units: 128 of 600 at 1408, 384 idle, 13.9 / 15.9, 104 of 1000 at 2240, 416 idle, 16.0 / 17.2, 32 of 1000 at 4096, 384 idle, 12.4 / 12.9; but
+//    16 of 2000 at 8192, 352 idle, 13.6 / 12.8, 32 of 200 at 4096, 416 idle, 10.7 / 8.4, 8 of 1000 at 32768, 976 idle, 18.5 / 11.9, 64 of 200, 8000 idle, 45 / 12.4;
+//  - eight blocks: 64 of 5000 at 10240, 128 idle, 34.8 / 36.0, 200 of 2500 at 5248, 200 idle, 53.3 / 55.1, 256 of 1000 at 2240, 256 idle, 30.2 / 28.8,
+//    256 of 200 at 4096, 256 idle, 17.8 / 15.0, 400 of 1000 at 32768, 6000 idle, 67 / 46.
 CKV_PLAN bool attends_apart(long long mean, int count, int cap, int n_cu) {
   const bool one_block = one_block_each(mean, count, n_cu);
-  return (long long)count * step_pieces(cap, one_block) >= at_once(one_block, n_cu);
+  const int piece = kChunk * (one_block ? 1 : kChunkBlocks);
+  const long long idle = (step_pieces(cap, one_block) - (mean + piece - 1) / piece) * count;
+  return 4 * idle >= (!one_block ? 4 : mean <= kChunk ? 3 : 6) * n_cu;
 }
 
 // A whole step leaves its bookkeeping to a kernel of its own (finish_kernel):

@@ -1,4 +1,4 @@
-"""Attention-only steps in one launch or two (by the workgroups that the capacity makes), in both shapes: outputs, the appended entry and its
+"""Attention-only steps in one launch or two (by the workgroups that the capacity leaves idle), in both shapes: outputs, the appended entry and its
 records against the kernel that takes whole units; units that are empty, at the edges of blocks and workgroups, and full; captured."""
 import numpy as np
 import pytest
@@ -61,7 +61,8 @@ def _same(a, b, exact):
             assert np.array_equal(x[f], y[f]), f
 
 
-# 14 units: 112 workgroups (one launch), 462 and 896 (two) of a block per wavefront; with budgets near the capacity 70 of eight blocks (one).
+# 14 units: 112 workgroups, 462 of which 294 are idle by the budgets (one launch each), 896 of which 770 are (two) of a block per wavefront; with
+# budgets near the capacity 70 of eight blocks (one).
 # At capacity 2048 the longest unit is full from the second step on.
 @pytest.mark.parametrize("cap,budget", [(2048, 2047), (8224, 3000), (16384, 2100), (10016, 9600)])
 @pytest.mark.parametrize("G", [1, 5])
@@ -69,6 +70,6 @@ def test_against_whole_units(G, cap, budget):
     _same(_steps(1, cap, budget, G, False), _steps(2, cap, budget, G, False), exact=False)
 
 
-@pytest.mark.parametrize("cap,budget", [(2048, 2047), (8224, 3000)])
+@pytest.mark.parametrize("cap,budget", [(2048, 2047), (16384, 2100)])
 def test_captured_layers(cap, budget):
     _same(_steps(1, cap, budget, 3, True, graph=True, layers=3), _steps(1, cap, budget, 3, True, layers=3), exact=True)

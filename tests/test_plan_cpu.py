@@ -33,27 +33,28 @@ def test_logits_are_asked_for_in_portions_that_divide_a_thread_s_groups(tmp_path
 def test_counters_are_looked_at_early_only_if_every_workgroup_runs_at_once(tmp_path):
     _run(tmp_path, r"""
   for (int n_cu : {256, 80})
-    for (long long workgroups : {1ll, 10ll, n_cu - 1ll, n_cu + 0ll, 2ll * n_cu - 1, 2ll * n_cu, 100000ll})
+    for (long long workgroups : {1ll, 10ll, n_cu + 0ll, n_cu + 1ll, 2ll * n_cu, 2ll * n_cu + 1, 100000ll})
       for (bool one_block : {true, false})
-        if (ckv::looks_early(workgroups, one_block, n_cu) != (workgroups < (one_block ? 1 : 2) * n_cu))
+        if (ckv::looks_early(workgroups, one_block, n_cu) != (workgroups <= (one_block ? 1 : 2) * n_cu))
           return std::printf("%lld workgroups, %d compute units\n", workgroups, n_cu), 1;""")
 
 
 def test_attention_only_steps_do_not_wait_for_idle_workgroups(tmp_path):
-    """In one launch only if all of its workgroups, idle ones included, find a place (about) at once; shapes measured both ways."""
+    """Shapes measured both ways; one launch where the capacity leaves no workgroup idle, two where it leaves two or more per compute unit."""
     _run(tmp_path, r"""
   struct { int mean, count, cap; bool apart; } measured[] = {
-      {1512, 2, 8192, false}, {1112, 32, 1184, false}, {712, 56, 768, false}, {712, 16, 4096, true}, {712, 64, 4096, true}, {712, 64, 32768, true},
-      {1512, 8, 32768, true}, {1112, 128, 4096, false}, {1512, 104, 8192, false}, {712, 256, 4096, true}, {1512, 400, 32768, true}};
+      {1512, 2, 8192, false}, {1112, 32, 1184, false}, {712, 56, 768, false}, {712, 64, 4096, true}, {712, 64, 32768, true}, {1512, 8, 32768, true},
+      {1112, 128, 4096, false}, {712, 256, 4096, true}, {1512, 400, 32768, true}, {369, 256, 416, false}, {190, 128, 448, false}, {190, 400, 448, true},
+      {690, 64, 1408, false}, {390, 104, 832, false}, {1090, 256, 2240, true}, {2590, 200, 5248, false}, {1590, 32, 3200, false}};
   for (auto& m : measured)
     if (ckv::attends_apart(m.mean, m.count, m.cap, 256) != m.apart) return std::printf("%d units of %d at capacity %d\n", m.count, m.mean, m.cap), 1;
   for (int mean = 1; mean < 32768; mean = mean * 3 / 2 + 1)
     for (int count = 1; count < 2000; count = count * 3 / 2 + 1)
-      for (int cap = (mean + 32) / 32 * 32; cap <= 32768; cap = cap * 2 / 32 * 32)
-        if (!ckv::attends_apart(mean, count, cap, 256)) {
-          const bool one_block = ckv::one_block_each(mean, count, 256);
-          if ((long long)count * ckv::step_pieces(cap, one_block) > (one_block ? 256 : 512)) return std::printf("%d units at %d\n", count, cap), 1;
-        }""")
+      for (int cap = (mean + 32) / 32 * 32; cap <= 32768; cap = cap * 2 / 32 * 32) {
+        const bool one_block = ckv::one_block_each(mean, count, 256);
+        const long long idle = (long long)count * (ckv::step_pieces(cap, one_block) - ckv::step_pieces(mean, one_block));
+        if ((idle == 0 || idle >= 512) && ckv::attends_apart(mean, count, cap, 256) != (idle != 0)) return std::printf("%d units at %d\n", count, cap), 1;
+      }""")
 
 
 def test_bookkeeping_in_the_step_or_apart(tmp_path):
