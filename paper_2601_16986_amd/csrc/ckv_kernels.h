@@ -1578,11 +1578,29 @@ __device__ __forceinline__ EntryRow load_row_input(const NewEntry& ne, int tid) 
   return r;
 }
 
+// What top_p_regs keeps in LDS.
+struct alignas(16) TopBuf {
+  u64 bin[24 << 5];
+  uint32_t list[256 + 8];
+  double above;           // sum of the bins above the one in question
+  int at, count;          // that bin (-1: none), and the number of its weights
+  double above_theta;
+  uint32_t listed, odd, theta, ties;
+  uint32_t tied;          // entries equal to the threshold in the list
+  int cut;
+};
+
+template <int NT>
+__device__ constexpr int top_list() { return NT < 256 ? NT : 256; }      // entries of the list, a thread each
+
 // Entries equal to the threshold: only as many as needed, lower positions first.  above = total weight of the entries
-// above theta, ties = entries equal to it.
-template <int R, int NT>
+// above theta, ties = entries equal to it.  Of a list's worth, each counts the lower positions (LIST: not in the fused kernel, whose streaming
+// loop is short of registers for it); more take 31 rounds over all entries, each with a block's reduction and another trip to the positions. Those rounds
+// were half of a step on caches where keys repeat (336 units of 550 entries after 16000 steps, four to eight ties each, 69 us per step, 38 with the
+// list; 240 of 222 on average 40 / 23).
+template <int R, int NT, bool LIST>
 __device__ __forceinline__ HitRule tie_rule(const Dev& d, Slots base, int n, const float (&a)[R], uint32_t theta, double above, int ties,
-                                            int new_last_t, RedBuf<NT>& rb, int& phase, int tid) {
+                                            TopBuf& tb, int new_last_t, RedBuf<NT>& rb, int& phase, int tid) {
   HitRule rule{theta, true, 0x7FFFFFFF};
   if (ties <= 1) return rule;
   const double th = (double)__uint_as_float(theta), p = (double)d.top_p;      // (in fp32 hundreds of equal additions round the same way)
@@ -1594,7 +1612,27 @@ __device__ __forceinline__ HitRule tie_rule(const Dev& d, Slots base, int n, con
   } while (c <= p && r < ties);
   if (r >= ties) return rule;
   rule.ties_all = false;
-  int X = 0;   // r-th smallest position among the ties (rare: positions are re-read from memory)
+  if (LIST && ties <= top_list<NT>()) {
+    for (int k = 0; k < R; ++k) {
+      const int i = 4 * (tid + (k >> 2) * NT) + (k & 3);
+      if (__float_as_uint(a[k]) == theta && i < n)
+        tb.list[atomicAdd(&tb.tied, 1u)] = (uint32_t)((new_last_t >= 0 && i == n - 1) ? new_last_t : d.pos[base + i]);
+    }
+    block_sync<NT>(rb);
+    if (tid < ties) {
+      const int mine = (int)tb.list[tid];
+      int lower = 0, equal = 0;
+      for (int k = 0; k < ties; ++k) {
+        lower += (int)tb.list[k] < mine ? 1 : 0;
+        equal += (int)tb.list[k] == mine ? 1 : 0;
+      }
+      if (lower < r && lower + equal >= r) tb.cut = max(mine, 0);        // every such thread has the same to say
+    }
+    block_sync<NT>(rb);
+    rule.pos_cut = uniform_i32(tb.cut);
+    return rule;
+  }
+  int X = 0;   // r-th smallest position among the ties (positions are re-read from memory)
   for (int bit = 30; bit >= 0; --bit) {
     const int trial = X | (1 << bit);
     int cnt = 0;
@@ -1626,15 +1664,6 @@ __device__ __forceinline__ HitRule tie_rule(const Dev& d, Slots base, int n, con
 // replay 80 -> 70 us, fused step of 896 units of 2048 entries 194.3 -> 190.6 us, of 6144 units 1243 -> 1238 us.
 // The scan over the bins moves through DPP and by one wavefront: its registers come on top of the weights and of what the callers
 // have in flight.
-struct alignas(16) TopBuf {
-  u64 bin[24 << 5];
-  uint32_t list[256 + 8];
-  double above;           // sum of the bins above the one in question
-  int at, count;          // that bin (-1: none), and the number of its weights
-  double above_theta;
-  uint32_t listed, odd, theta, ties;
-  uint32_t pad[2];
-};
 constexpr int kBinShift = 18, kBins = 24 << 5, kBinFirst = (127 - 23) << 5;
 constexpr uint32_t kBinLow = (1u << kBinShift) - 1u;
 constexpr int kBinCount = 34;                 // the count's place: 32768 low parts of 18 bits lie below it
@@ -1658,7 +1687,7 @@ template <int R, int NT = kThreads, bool CLEARED = false, bool REFINE = false>
 __device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, const float (&a)[R], TopBuf& tb, int new_last_t, RedBuf<NT>& rb, int& phase,
                                               int tid) {
   if (every_entry_hit(d)) return HitRule{0u, true, 0x7FFFFFFF};
-  constexpr int kList = NT < 256 ? NT : 256;
+  constexpr int kList = top_list<NT>();
   const int lane = tid & 63, wave = tid >> 6;
   // (not known to the compiler as the same in every unit: kept in registers across the units of a persistent kernel it would be
   // spilled, and a reload is a wait for every load in flight)
@@ -1815,7 +1844,7 @@ __device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, c
       block_sync<NT>(rb);
       const uint32_t found = (uint32_t)uniform_i32((int)tb.theta);
       if (found == 0u) return HitRule{theta, true, 0x7FFFFFFF};
-      return tie_rule<R, NT>(d, base, n, a, found, readlane_f64(tb.above_theta, 0), uniform_i32((int)tb.ties), new_last_t, rb, phase, tid);
+      return tie_rule<R, NT, CLEARED>(d, base, n, a, found, readlane_f64(tb.above_theta, 0), uniform_i32((int)tb.ties), tb, new_last_t, rb, phase, tid);
     }
   }
   // two bits per round (one barrier each): the three candidates' sums are nested, so the largest candidate that passes is
@@ -1844,7 +1873,7 @@ __device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, c
   }
   above = uniform_f32(block_sum_f32<NT>(above, rb, phase, tid));
   ties = uniform_i32(block_sum_int<NT>(ties, rb, phase, tid));
-  return tie_rule<R, NT>(d, base, n, a, theta, above, ties, new_last_t, rb, phase, tid);
+  return tie_rule<R, NT, CLEARED>(d, base, n, a, theta, above, ties, tb, new_last_t, rb, phase, tid);
 }
 
 // `after_step1` runs once between Step 1 and the score update (the fused kernel
