@@ -42,10 +42,13 @@ CKV_PLAN bool looks_early(long long workgroups, bool one_block, int n_cu) { retu
 //  - longer units: 128 of 600 at 1408, 384 idle, 13.9 / 15.9, 104 of 1000 at 2240, 416 idle, 16.0 / 17.2, 32 of 1000 at 4096, 384 idle, 12.4 / 12.9; but
 //    16 of 2000 at 8192, 352 idle, 13.6 / 12.8, 32 of 200 at 4096, 416 idle, 10.7 / 8.4, 8 of 1000 at 32768, 976 idle, 18.5 / 11.9, 64 of 200, 8000 idle, 45 / 12.4;
 //  - eight blocks: 64 of 5000 at 10240, 128 idle, 34.8 / 36.0, 200 of 2500 at 5248, 200 idle, 53.3 / 55.1, 256 of 1000 at 2240, 256 idle, 30.2 / 28.8,
-//    256 of 200 at 4096, 256 idle, 17.8 / 15.0, 400 of 1000 at 32768, 6000 idle, 67 / 46.
+//    256 of 200 at 4096, 256 idle, 17.8 / 15.0, 400 of 1000 at 32768, 6000 idle, 67 / 46;
+//  - short units of one workgroup of eight blocks, more of them than compute units, none idle: the busy ones share a compute unit, and the records keep
+//    registers from the next: 400 of 300 at 416 25.8 / 23.4, 400 of 600 at 704 31.8 / 31.3, 256 of 600 20.1 / 19.9.
 CKV_PLAN bool attends_apart(long long mean, int count, int cap, int n_cu) {
   const bool one_block = one_block_each(mean, count, n_cu);
   const int piece = kChunk * (one_block ? 1 : kChunkBlocks);
+  if (!one_block && count > n_cu && cap <= piece && mean <= 3 * kChunk) return true;
   const long long idle = (step_pieces(cap, one_block) - (mean + piece - 1) / piece) * count;
   return 4 * idle >= (!one_block ? 4 : mean <= kChunk ? 3 : 6) * n_cu;
 }

@@ -8,10 +8,10 @@ pytestmark = pytest.mark.gpu
 LENGTHS = [0, 1, 31, 32, 255, 256, 257, 511, 512, 1000, 1500, 1919, 2015, 2046]
 
 
-def _steps(path, cap, budget, G, bf16, graph=False, layers=1):
+def _steps(path, cap, budget, G, bf16, graph=False, layers=1, lengths=LENGTHS):
     import torch
     from paper_2601_16986_amd import ckv
-    B, H, t, steps = len(LENGTHS), 1, 9000, 3
+    B, H, t, steps = len(lengths), 1, 9000, 3
     g = ckv.CrystalKV(layers, B, H * G, H, 128, cap, np.full((layers, B, H), budget, np.int32), t0=t, budget_min=1, budget_max=cap - 1,
                       headroom=1 if cap > 2048 else 0,
                       out_dtype=ckv.BF16 if bf16 else ckv.F32)
@@ -19,8 +19,8 @@ def _steps(path, cap, budget, G, bf16, graph=False, layers=1):
     gen = torch.Generator(device=g.device)
     gen.manual_seed(5)
     rnd = lambda *s: torch.randn(s, generator=gen, device=g.device).to(torch.bfloat16)
-    P = max(LENGTHS)
-    n = torch.tensor(LENGTHS, dtype=torch.int32, device=g.device).reshape(B, H)
+    P = max(lengths)
+    n = torch.tensor(lengths, dtype=torch.int32, device=g.device).reshape(B, H)
     pos = torch.arange(P, device=g.device, dtype=torch.int32).expand(B, H, P).contiguous()
     crf = torch.rand((B, H, P), generator=gen, device=g.device) + 0.25
     for l in range(layers):
@@ -68,6 +68,14 @@ def _same(a, b, exact):
 @pytest.mark.parametrize("G", [1, 5])
 def test_against_whole_units(G, cap, budget):
     _same(_steps(1, cap, budget, G, False), _steps(2, cap, budget, G, False), exact=False)
+
+
+# 266 units of one workgroup of eight blocks, the longest full from the second step on (two launches)
+@pytest.mark.parametrize("G", [1, 5])
+def test_short_and_many(G):
+    lengths = [37 * i % 703 for i in range(266)]
+    lengths[7] = 702
+    _same(*(_steps(path, 704, 703, G, False, lengths=lengths) for path in (1, 2)), exact=False)
 
 
 @pytest.mark.parametrize("cap,budget", [(2048, 2047), (16384, 2100)])

@@ -40,12 +40,14 @@ def test_counters_are_looked_at_early_only_if_every_workgroup_runs_at_once(tmp_p
 
 
 def test_attention_only_steps_do_not_wait_for_idle_workgroups(tmp_path):
-    """Shapes measured both ways; one launch where the capacity leaves no workgroup idle, two where it leaves two or more per compute unit."""
+    """Shapes measured both ways; one launch where the capacity leaves no workgroup idle (unless units are short and many), two where it leaves two or
+    more per compute unit."""
     _run(tmp_path, r"""
   struct { int mean, count, cap; bool apart; } measured[] = {
       {1512, 2, 8192, false}, {1112, 32, 1184, false}, {712, 56, 768, false}, {712, 64, 4096, true}, {712, 64, 32768, true}, {1512, 8, 32768, true},
       {1112, 128, 4096, false}, {712, 256, 4096, true}, {1512, 400, 32768, true}, {369, 256, 416, false}, {190, 128, 448, false}, {190, 400, 448, true},
-      {690, 64, 1408, false}, {390, 104, 832, false}, {1090, 256, 2240, true}, {2590, 200, 5248, false}, {1590, 32, 3200, false}};
+      {690, 64, 1408, false}, {390, 104, 832, false}, {1090, 256, 2240, true}, {2590, 200, 5248, false}, {1590, 32, 3200, false},
+      {680, 480, 704, true}, {390, 400, 416, true}, {690, 256, 704, false}, {1590, 400, 1600, false}};
   for (auto& m : measured)
     if (ckv::attends_apart(m.mean, m.count, m.cap, 256) != m.apart) return std::printf("%d units of %d at capacity %d\n", m.count, m.mean, m.cap), 1;
   for (int mean = 1; mean < 32768; mean = mean * 3 / 2 + 1)
@@ -53,7 +55,8 @@ def test_attention_only_steps_do_not_wait_for_idle_workgroups(tmp_path):
       for (int cap = (mean + 32) / 32 * 32; cap <= 32768; cap = cap * 2 / 32 * 32) {
         const bool one_block = ckv::one_block_each(mean, count, 256);
         const long long idle = (long long)count * (ckv::step_pieces(cap, one_block) - ckv::step_pieces(mean, one_block));
-        if ((idle == 0 || idle >= 512) && ckv::attends_apart(mean, count, cap, 256) != (idle != 0)) return std::printf("%d units at %d\n", count, cap), 1;
+        const bool short_and_many = !one_block && count > 256 && cap <= 2048 && mean <= 768;
+        if ((idle == 0 || idle >= 512) && ckv::attends_apart(mean, count, cap, 256) != (idle != 0 || short_and_many)) return std::printf("%d units at %d\n", count, cap), 1;
       }""")
 
 
