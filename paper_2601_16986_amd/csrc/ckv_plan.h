@@ -57,12 +57,12 @@ CKV_PLAN bool attends_apart(long long mean, int count, int cap, int n_cu) {
 //  - where units may be longer than `most` entries, what the workgroup that finishes a unit has registers for. 1024 threads per unit are
 //    also the faster way then (us per layer, captured, one kernel / two: 64 units of 2048 entries, up to 8192, 51 / 44, 16 of 8000, up to 32000, 104 / 76);
 //  - where workgroups without work, which must arrive in one kernel and pass through in rounds of two per compute unit at 1.3 us each, cost more
-//    than the second kernel does. That is 3 us where units have one workgroup each, 7 where more of them meet (capacity 6144: 64 units of 200 35.7 / 35.0,
-//    256 of 200 49.8 / 44.9, under the attention-weighted reward 23.6 / 23.7 and at capacity 2048 20.8 / 17.1; but 56 of 200 32.4 / 34.1, 128 of 700
-//    39.6 / 41.4, 104 of 1200 38.9 / 42.3);
+//    than the second kernel does. That is 3 us where units have one workgroup each, 7 where more of them meet (capacity 6144: 64 units of 200 19.5 / 18.5,
+//    256 of 200 34.4 / 27.0, under the attention-weighted reward 31.3 / 23.6 and at capacity 2048 21.0 / 17.3; but 56 of 200 17.7 / 18.6, 128 of 700
+//    27.4 / 28.6, 104 of 1200 30.6 / 32.4);
 //  - where few long units leave compute units idle, which 1024 threads per unit then use better than 512 (48 .. 85 units of at least six entries per
-//    thread on average: 64 of 3700 52.3 / 49.4, 72 of 3700 50.4 / 48.9, weighted 45.6 / 42.8, 56 of 5900 58.2 / 56.5; but 32 of 5900 45.5 / 48.5, 104 of
-//    5900 92.5 / 99.0, 72 of 2000 40.4 / 45.0).
+//    thread on average: 64 of 3700 47.5 / 45.4, 72 of 3700 49.8 / 46.8, weighted 45.9 / 43.4, 56 of 5900 56.9 / 53.9; but 32 of 5900 45.6 / 47.9, 104 of
+//    5900 91.0 / 96.4, 72 of 2000 34.8 / 39.7).
 CKV_PLAN bool books_apart(long long mean, int count, int cap, int n_cu, int threads, int most) {
   if (cap > most) return true;
   if (!one_block_each(mean, count, n_cu)) return mean >= 6 * threads && 16 * count >= 3 * n_cu && 3 * count <= n_cu;
