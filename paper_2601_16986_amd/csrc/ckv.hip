@@ -948,7 +948,9 @@ int ckv_seed_prompt(ckv_ctx* c, int32_t layer, const void* q_obs, int32_t W, voi
       CKV_HIP(c, hipGetLastError());
     }
     const dim3 cgrid((unsigned)((P + 4 * kThreads - 1) / (4 * kThreads)), (unsigned)count);
-    if (topp)
+    if (topp && c->dev.tab_last < kTabLds)                 // LDS holds the whole table (lambda up to 0.7)
+      hipLaunchKernelGGL(seed_crf_hits_kernel, cgrid, dim3(kThreads), 0, s, c->dev, begin, j0, nq, P, (int)W, c->par.t0 - 1, (const uint32_t*)rw);
+    else if (topp)
       hipLaunchKernelGGL(seed_crf_kernel<true>, cgrid, dim3(kThreads), 0, s, c->dev, begin, j0, nq, P, (int)W, c->par.t0 - 1, (const float*)rw);
     else
       hipLaunchKernelGGL(seed_crf_kernel<false>, cgrid, dim3(kThreads), 0, s, c->dev, begin, j0, nq, P, (int)W, c->par.t0 - 1, (const float*)rw);

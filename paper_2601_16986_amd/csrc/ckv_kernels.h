@@ -2627,6 +2627,7 @@ __global__ __launch_bounds__(kSeedThreads, R == 0 || R > 24 ? 4 : R > 16 ? 6 : 8
 // seed_crf_kernel: Alg. 1 Step 3 for the batch's queries in order, four consecutive entries per thread: an entry
 // takes part from the query of its own position on; under the top-p rule only a hit replaces (CRF, tau).
 // BITS: the queries' hits, a bit per entry at the start of each query's row (the top-p rule); else the weights themselves.
+// (Hits under a table that LDS holds whole: seed_crf_hits_kernel.)
 // The replay's first batch starts from the state before it (every entry referenced once, on arrival: CRF 1, tau =
 // position; the W entries of the window not yet arrived: CRF 0), the last one leaves the units' records as a fresh
 // context has them: no trace in the aggregated-CRF window, last-step time t_unit.
@@ -2682,24 +2683,6 @@ __global__ __launch_bounds__(kThreads) void seed_crf_kernel(Dev d, int unit_begi
     }
     changed |= m != 0u;
   };
-  // The same for hits with the whole table in LDS: a score that 1 is added to needs no look at the smallest number, and an
-  // entry's time is within the table's reach or clamped to its end (18 instructions per entry and
-  // query without this, 10 with it; 128 units of 9350 entries, 32 queries, 26 -> 23 us, 64 such units 18 -> 15: the table's
-  // reads cost as much as the issue now; the hits' words asked for a batch ahead change nothing).
-  const bool short_table = BITS && s_tab_n > d.tab_last;
-  auto update_hits = [&](uint32_t m, int t) {
-    float dec[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) dec[e] = s_tab[min(max(t - tau[e], 0), d.tab_last)];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const bool in = (m & (1u << e)) != 0u;
-      const float tmp = __fadd_rn(__fmul_rn(dec[e], crf[e]), 1.0f);
-      crf[e] = in ? tmp : crf[e];
-      tau[e] = in ? t : tau[e];
-    }
-    changed |= m != 0u;
-  };
   // bits of the entries that the query at time t sees: positions 0 .. t
   auto seen = [&](int t) -> uint32_t { return t >= e0 + 3 ? 0xFu : t < e0 ? 0u : (2u << (t - e0)) - 1u; };
   for (int q0 = 0; q0 < nq; q0 += 8) {
@@ -2710,11 +2693,7 @@ __global__ __launch_bounds__(kThreads) void seed_crf_kernel(Dev d, int unit_begi
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
         const int t = t_first + q0 + k;
-        const uint32_t m = q0 + k < nq ? (r[k] >> (e0 & 31)) & seen(t) : 0u;
-        if (short_table)
-          update_hits(m, t);
-        else
-          update(m, t, f32x4{1.0f, 1.0f, 1.0f, 1.0f});
+        update(q0 + k < nq ? (r[k] >> (e0 & 31)) & seen(t) : 0u, t, f32x4{1.0f, 1.0f, 1.0f, 1.0f});
       }
     } else {
       f32x4 r[8];
@@ -2735,6 +2714,103 @@ __global__ __launch_bounds__(kThreads) void seed_crf_kernel(Dev d, int unit_begi
     for (int e = 0; e < 4 && e0 + e < P; ++e) {
       d.crf[s0 + e] = crf[e];
       d.tau[s0 + e] = tau[e];
+    }
+  }
+}
+
+// The same for hits where LDS holds the whole decay table (a score that 1 is added to needs no look at the smallest number, and an entry's
+// time is within the table's reach or clamped to its end).  A lane has four entries 64 apart, so that a wavefront's hits of a query are
+// eight words in scalar registers, whose pairs are the selects' conditions as they are: no bit is tested per lane.  An entry's time is kept as its
+// place in the table at the chunk's first query; later queries read on from there, at an offset known when it is compiled.  Four vector
+// instructions and an LDS read per entry and query; with four consecutive entries per lane, bits and times looked at in vector registers, it
+// took 14, and their issue was what bounded it.  128 units of 9350 entries, 32 queries: 20.3 -> 12.7 us,
+// 64 such units 14.3 -> 9.2, 4 units of 777, 16 queries 6.1 -> 4.8.  (Words through scalar loads, eight queries at a time: no faster than before, and 8.6 for
+// the last; the trips to memory follow one another.)
+// An entry that has not arrived has score 0, so that its time, which starts at its position, does not matter before its first hit.
+// grid: (ceil(P / (4 kThreads)), units of the layer), kThreads threads.
+constexpr int kCrfChunk = 8;                              // queries per vector register of hits
+constexpr int kMaxSeedBatch = kSeedTiles * kSeedGroup;    // queries of a batch, at most (G = 1)
+__global__ __launch_bounds__(kThreads) void seed_crf_hits_kernel(Dev d, int unit_begin, int j0, int nq, int P, int W, int t_unit, const uint32_t* __restrict__ hits) {
+  __shared__ float s_tab[kTabLds + kMaxSeedBatch + kCrfChunk];      // no time of the batch lies beyond it
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int urel = blockIdx.y, u = unit_begin + urel;
+  const int first = __builtin_amdgcn_readfirstlane((blockIdx.x * (kThreads / 64) + (tid >> 6)) * 256);      // the wavefront's first entry
+  const int t_first = P - W + j0;
+  const size_t q_stride = (size_t)gridDim.y * d.cap;
+  const uint32_t* row = hits + (size_t)urel * d.cap + min(first, P - 1) / 32 + (lane & 7);
+  for (int i = tid; i < d.tab_last + nq + kCrfChunk; i += kThreads) s_tab[i] = d.tab[min(i, d.tab_last)];
+  // four registers of hits: lane l has word l % 8 of query l / 8 of its eight
+  constexpr int kRegs = 4;
+  uint32_t w[kRegs];
+  auto request = [&](int q0) {
+#pragma unroll
+    for (int i = 0; i < kRegs; ++i) w[i] = row[(size_t)min(q0 + kCrfChunk * i + (lane >> 3), nq - 1) * q_stride];
+  };
+  request(0);
+  if (j0 + nq == W && blockIdx.x == 0 && tid == 0) {
+    d.window[u] = 0;
+    d.t_unit[u] = t_unit;
+  }
+  const size_t s0 = (size_t)d.tbl[(size_t)u * d.max_seg + min(first / kSeg, d.max_seg - 1)] * kSeg + lane;      // its entries are a segment
+  __syncthreads();
+  if (first >= P) return;
+  float crf[4];
+  int at[4];                                              // place in the table at the chunk's first query, in bytes
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int i = first + 64 * e + lane;
+    int tau = i;
+    if (j0 == 0) {
+      crf[e] = i < P - W ? 1.0f : 0.0f;
+    } else {
+      crf[e] = d.crf[s0 + 64 * e];                        // (the whole segment is the unit's)
+      tau = d.tau[s0 + 64 * e];
+    }
+    at[e] = 4 * min(max(t_first - tau, 0), d.tab_last);
+  }
+  u64 any[4] = {0, 0, 0, 0};
+  int q_end = 0;                                          // the query at which `at` is the entry's age
+  for (int q0 = 0; q0 < nq; q0 += kRegs * kCrfChunk) {
+    uint32_t seen[kRegs];
+#pragma unroll
+    for (int i = 0; i < kRegs; ++i) {                     // positions 0 .. t; what lies beyond a row's hits is not theirs
+      const int q = q0 + kCrfChunk * i + (lane >> 3), left = t_first + q + 1 - (first + 32 * (lane & 7));
+      seen[i] = q >= nq || left <= 0 ? 0u : left >= 32 ? w[i] : w[i] & ((1u << left) - 1u);
+    }
+    if (q0 + kRegs * kCrfChunk < nq) request(q0 + kRegs * kCrfChunk);
+#pragma unroll
+    for (int i = 0; i < kRegs; ++i) {
+      if (q0 + kCrfChunk * i >= nq) break;                // uniform
+#pragma unroll
+      for (int k = 0; k < kCrfChunk; ++k) {
+        float dec[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dec[e] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(s_tab) + at[e] + 4 * k);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) asm volatile("" : "+v"(dec[e]));      // by every lane: else each becomes a branch, with a wait of its own
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const u64 m = ((u64)(uint32_t)__builtin_amdgcn_readlane((int)seen[i], 8 * k + 2 * e + 1) << 32) |
+                        (uint32_t)__builtin_amdgcn_readlane((int)seen[i], 8 * k + 2 * e);
+          any[e] |= m;
+          const bool in = __builtin_amdgcn_inverse_ballot_w64(m);
+          const float tmp = __fadd_rn(__fmul_rn(dec[e], crf[e]), 1.0f);
+          crf[e] = in ? tmp : crf[e];
+          at[e] = in ? -4 * k : at[e];                    // read again from the next query on
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) at[e] += 4 * kCrfChunk;
+      q_end += kCrfChunk;
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int i = first + 64 * e + lane;
+    const bool hit = __builtin_amdgcn_inverse_ballot_w64(any[e]);
+    if (i < P && (hit || j0 == 0)) {
+      d.crf[s0 + 64 * e] = crf[e];
+      d.tau[s0 + 64 * e] = hit ? t_first + q_end - at[e] / 4 : i;
     }
   }
 }
