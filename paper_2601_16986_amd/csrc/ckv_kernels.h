@@ -120,6 +120,19 @@ constexpr int kDppRowHalfMirror = 0x141;
 constexpr int kDppRowMirror = 0x140;
 constexpr int kDppRowShl = 0x100, kDppRowShr = 0x110;      // + 1 .. 15: from so many lanes up / down, 0 from beyond the row
 
+// Lanes j, j + 16, j + 32 and j + 48 into one value, the same in all four: op(op(v0, v1), op(v2, v3)).  By swaps of rows, without a trip through LDS.
+template <class Op>
+__device__ __forceinline__ float rows_combine(float v, Op op) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return op(__uint_as_float(h[0]), __uint_as_float(h[1]));
+}
+
+// Maxima that are NaN if an operand is.
+__device__ __forceinline__ float max2(float a, float b) { return __builtin_elementwise_maximum(a, b); }
+__device__ __forceinline__ float max3(float a, float b, float c) { return max2(max2(a, b), c); }
+
 // Sum over the 64 lanes, same fixed order in every lane: butterfly inside each
 // row of 16 lanes, then the four row sums are read out and added.
 __device__ __forceinline__ float wave_sum_f32(float v) {
@@ -2191,8 +2204,10 @@ __global__ __launch_bounds__(kWideThreads) void append_kernel(Dev d, int unit_be
 // G = 5: first pass 111 -> 88 us, second pass 163 -> 97 us.
 // Then, the same shape: results of the products in ordinary registers (a compiler option), queries staged with all loads in flight, the
 // segment table in a register, and in the second pass two tiles at a time with registers for three wavefronts per SIMD: 92 -> 88 and 98 -> 95 us.
-// The first pass is bound by the issue of vector instructions and products; the second by the products and by its stores (without them 77,
-// without the products 66, without the exponentials 92 us).
+// The first pass waits for its keys and for the issue of vector instructions in turn (with one tile in place of ten 56 us, without the
+// exponentials 64); the second is bound by the products and by its stores (without them 77, without the products 66, without the exponentials 92 us).
+// With three-operand maxima, the first keys asked for beside the queries and no divisions in front: first pass 79 -> 75 us, 64 such units 48.8 -> 47.2, 4
+// units of 777 entries, 16 queries 9.1 -> 7.6.  (Two tiles at a time there: 78; keys two blocks ahead: 79; blocks dealt evenly to a block: no change.)
 // Buffers of a batch of nq queries for the UL units of a layer (tiles and columns as in the first pass):
 //   sml [tile][unit][span][column][2]     maximum (rounded up) and sum of the softmax over a wavefront's blocks
 //   smi [tile][unit][column][2]           maximum (rounded up) and 1 / sum over all the entries the column's query sees
@@ -2216,35 +2231,47 @@ __device__ __forceinline__ float seed_exp(float logit, float scale, float max) {
 // Tiles of the first pass.
 __host__ __device__ __forceinline__ int seed_scan_tiles(int G, int nq) { return (nq * G + kSeedCols - 1) / kSeedCols; }
 
+// Columns by the group size, as a product: exact for 0 <= i < 2^13 and G <= 8.  (A division is twenty instructions, and each wavefront
+// had one per tile for its lanes' queries and another for their limits.)
+struct PerGroup {
+  int m;
+  __device__ __forceinline__ explicit PerGroup(int G) : m(65536 / G + 1) {}
+  __device__ __forceinline__ int operator()(int i) const { return (i * m) >> 16; }
+};
+static_assert(kSeedCols * (kSeedTiles + 1) <= 8192 && kMaxGroup <= 8, "what PerGroup divides");
+
 // Query (of the batch) and head of column c of tile tl: first pass (of any tile's columns those beyond the batch have queries
 // from nq on), second pass.
-__device__ __forceinline__ int seed_scan_column(int G, int tl, int c, int& head) {
-  const int i = kSeedCols * tl + c, q = i / G;
+__device__ __forceinline__ int seed_scan_column(int G, PerGroup per_group, int tl, int c, int& head) {
+  const int i = kSeedCols * tl + c, q = per_group(i);
   head = i - q * G;
   return q;
 }
-__device__ __forceinline__ int seed_column(int G, int tl, int c, int& head) {
-  const int group = tl / G, k = tl - group * G;
+__device__ __forceinline__ int seed_column(int G, PerGroup per_group, int tl, int c, int& head) {
+  const int group = per_group(tl), k = tl - group * G;
   const bool four = k < (G & ~3);
   head = four ? (k & ~3) + (c & 3) : k;
   return kSeedGroup * group + (four ? 4 * (k & 3) + (c >> 2) : 4 * (c & 3) + (c >> 2));
 }
 
 // The batch's queries as operands in LDS ([tile][32-dim slice][lane], 16 bytes each); 0 in columns without a query.
-template <class Column>
-__device__ __forceinline__ void seed_stage_queries(const Dev& d, const uint16_t* q_obs, int urel, int j0, int nq, int nt, Column column, u32x4* s_q) {
+// `meanwhile` runs when they have been asked for.
+template <class Column, class Meanwhile>
+__device__ __forceinline__ void seed_stage_queries(const Dev& d, const uint16_t* q_obs, int urel, int j0, int nq, int nt, Column column, u32x4* s_q, Meanwhile meanwhile) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, b = urel / d.Hkv, h = urel % d.Hkv;
+  const PerGroup per_group(d.G);
   u32x4 x[kSeedTiles];                                    // all asked for before the first is stored
 #pragma unroll
   for (int tl = 0; tl < kSeedTiles; ++tl) {
     x[tl] = u32x4{0u, 0u, 0u, 0u};
     if (tl < nt) {
       int head;
-      const int qi = column(d.G, tl, lane & 15, head);
+      const int qi = column(d.G, per_group, tl, lane & 15, head);
       if (qi < nq)
         x[tl] = *reinterpret_cast<const u32x4*>(q_obs + ((((size_t)(j0 + qi) * d.Bz + b) * d.Hq) + (size_t)h * d.G + head) * kDim + 32 * wave + 8 * (lane >> 4));
     }
   }
+  meanwhile();
 #pragma unroll
   for (int tl = 0; tl < kSeedTiles; ++tl)
     if (tl < nt) s_q[(tl * 4 + wave) * 64 + lane] = x[tl];
@@ -2282,13 +2309,17 @@ __global__ __launch_bounds__(kThreads) void seed_scan_kernel(Dev d, int unit_beg
   const int j = lane & 15, kg = lane >> 4;
   const int G = d.G, nt = seed_scan_tiles(G, nq);
   const int n_first = P - W + j0 + 1;                     // entries the batch's first query sees
-  seed_stage_queries(d, q_obs, urel, j0, nq, nt, seed_scan_column, s_q);
+  SeedSpan sp(d, u, slot, S, n_first + nq - 1);
+  const uint16_t* kp = d.K + lane * 8;
+  KFrag ka;
+  // the first keys (of a wavefront without blocks, some that nobody looks at) are on their way before the queries are there
+  seed_stage_queries(d, q_obs, urel, j0, nq, nt, seed_scan_column, s_q, [&]() { load_k(ka, kp + sp.off(sp.b)); });
   __syncthreads();
   if (slot >= S) return;
-  SeedSpan sp(d, u, slot, S, n_first + nq - 1);
+  const PerGroup per_group(G);
   int q_lo[kSeedTiles + 1];                               // the tiles' first queries
 #pragma unroll
-  for (int tl = 0; tl <= kSeedTiles; ++tl) q_lo[tl] = kSeedCols * tl / G;
+  for (int tl = 0; tl <= kSeedTiles; ++tl) q_lo[tl] = per_group(kSeedCols * tl);
   float m_run[kSeedTiles], l_run[kSeedTiles];             // of this lane's entries; the four lanes of a column meet at the end
 #pragma unroll
   for (int tl = 0; tl < kSeedTiles; ++tl) {
@@ -2296,10 +2327,8 @@ __global__ __launch_bounds__(kThreads) void seed_scan_kernel(Dev d, int unit_beg
     l_run[tl] = 0.f;
   }
   const float c = d.scale_log2e;
-  const uint16_t* kp = d.K + lane * 8;
   auto sweep = [&](auto rounded) {
-    KFrag ka, kn;
-    if (sp.b < sp.b1) load_k(ka, kp + sp.off(sp.b));
+    KFrag kn;
     for (int blk = sp.b; blk < sp.b1; ++blk) {
       load_k(kn, kp + sp.off(min(blk + 1, sp.b1 - 1)));
       const int e0 = blk * kBlk + 4 * kg;
@@ -2321,7 +2350,7 @@ __global__ __launch_bounds__(kThreads) void seed_scan_kernel(Dev d, int unit_beg
             sv[4 + v] = s1[v];
           }
           if ((blk + 1) * kBlk > n_first + q_lo[tl]) {      // a block that the tile's first query sees whole needs no mask
-            const int lim = n_first + (kSeedCols * tl + j) / G;            // entries this column's query sees
+            const int lim = n_first + per_group(kSeedCols * tl + j);       // entries this column's query sees
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
               sv[v] = (e0 + v < lim) ? sv[v] : -INFINITY;
@@ -2333,12 +2362,11 @@ __global__ __launch_bounds__(kThreads) void seed_scan_kernel(Dev d, int unit_beg
           // small numbers.  (Looked for in a span's first block alone, sums redone from 2^60 on: 12 us less, but weights off by
           // 1.6e-6 where logits rise by 40 behind that block, else by 3e-7.  Tiles done again where eight exponentials pass 16:
           // no slower on even prompts, 22 us slower on ones with heavy entries here and there.)
-          const float bm = c * fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
-          if (bm > m_run[tl]) {
-            const float m_new = ceilf(bm);
-            l_run[tl] *= fast_exp2(m_run[tl] - m_new);      // 0 the first time
-            m_run[tl] = m_new;
-          }
+          // (Of a maximum that propagates NaN there is an instruction for three, and its operands need no look at signalling ones.)
+          const float bm = c * max3(max3(sv[0], sv[1], sv[2]), max3(sv[3], sv[4], sv[5]), max2(sv[6], sv[7]));
+          const float m_new = max2(m_run[tl], ceilf(bm));
+          l_run[tl] *= fast_exp2(m_run[tl] - m_new);        // 0 the first time
+          m_run[tl] = m_new;
           float p[8];
 #pragma unroll
           for (int i = 0; i < 8; ++i) p[i] = seed_exp<decltype(rounded)::value>(sv[i], c, m_run[tl]);
@@ -2355,18 +2383,18 @@ __global__ __launch_bounds__(kThreads) void seed_scan_kernel(Dev d, int unit_beg
   if (__any(far)) {                                       // the maxima stand; the sums once more
 #pragma unroll
     for (int tl = 0; tl < kSeedTiles; ++tl) l_run[tl] = 0.f;
+    if (sp.b < sp.b1) load_k(ka, kp + sp.off(sp.b));
     sweep(std::true_type{});
   }
-  // per tile, the column's four lanes (kg = 0..3): maximum, then the sums rescaled to it, in a fixed order
+  // per tile, the column's four lanes (kg = 0..3): maximum, then the sums rescaled to it
 #pragma unroll
   for (int tl = 0; tl < kSeedTiles; ++tl) {
     if (tl < nt) {
-      float M = fmaxf(m_run[tl], __shfl_xor(m_run[tl], 16));
-      M = fmaxf(M, __shfl_xor(M, 32));
-      const float mine = l_run[tl] * fast_exp2(m_run[tl] - M);
-      const float l0 = __shfl(mine, j), l1 = __shfl(mine, j + 16), l2 = __shfl(mine, j + 32), l3 = __shfl(mine, j + 48);
+      auto max_of = [](float x, float y) { return fmaxf(x, y); };
+      const float M = rows_combine(m_run[tl], max_of);
+      const float l = rows_combine(l_run[tl] * fast_exp2(m_run[tl] - M), [](float x, float y) { return x + y; });
       if (kg == 0)
-        *reinterpret_cast<float2*>(sml + ((((size_t)tl * UL + urel) * S + slot) * kSeedCols + j) * 2) = make_float2(M, (l0 + l1) + (l2 + l3));
+        *reinterpret_cast<float2*>(sml + ((((size_t)tl * UL + urel) * S + slot) * kSeedCols + j) * 2) = make_float2(M, l);
     }
   }
 }
@@ -2424,22 +2452,25 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 3))
   const int G = d.G, groups = (nq + kSeedGroup - 1) / kSeedGroup, nt = groups * G;
   const int n_first = P - W + j0 + 1;
   const float invG = 1.0f / (float)G;
+  SeedSpan sp(d, u, slot, S, n_first + nq - 1);
+  float2 mi = make_float2(0.f, 0.f);
   if ((int)threadIdx.x < nt * kSeedCols) {
     int head;
-    const int i = seed_column(G, threadIdx.x / kSeedCols, threadIdx.x % kSeedCols, head) * G + head;         // the column's place in the first pass
-    float2 mi = make_float2(0.f, 0.f);
+    const int i = seed_column(G, PerGroup(G), threadIdx.x / kSeedCols, threadIdx.x % kSeedCols, head) * G + head;         // the column's place in the first pass
     if (i < nq * G) mi = *reinterpret_cast<const float2*>(smi + (((size_t)(i / kSeedCols) * UL + urel) * kSeedCols + i % kSeedCols) * 2);
+  }
+  const uint16_t* kp = d.K + lane * 8;
+  KFrag k0, k1;
+  seed_stage_queries(d, q_obs, urel, j0, nq, nt, seed_column, s_q, [&]() { load_k(k0, kp + sp.off(sp.b)); });
+  if ((int)threadIdx.x < nt * kSeedCols) {
     s_M[threadIdx.x] = mi.x;
     s_I[threadIdx.x] = mi.y * invG;
   }
-  seed_stage_queries(d, q_obs, urel, j0, nq, nt, seed_column, s_q);
   __syncthreads();
   if (slot >= S) return;
-  SeedSpan sp(d, u, slot, S, n_first + nq - 1);
   bool far = false;
   for (int i = lane; i < nt * kSeedCols; i += 64) far |= is_far(s_M[i]);
   const float c = d.scale_log2e;
-  const uint16_t* kp = d.K + lane * 8;
   const size_t lane_row = (size_t)kg * UL * d.cap + j;
   auto sweep = [&](auto rounded) {
     auto block = [&](const KFrag& ka, int blk) {
@@ -2528,8 +2559,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 3))
       }
     };
     // two blocks in turn, the next always on its way
-    KFrag k0, k1;
-    if (sp.b < sp.b1) load_k(k0, kp + sp.off(sp.b));
     for (int blk = sp.b; blk < sp.b1; blk += 2) {
       load_k(k1, kp + sp.off(min(blk + 1, sp.b1 - 1)));
       block(k0, blk);
