@@ -266,8 +266,8 @@ void give_stream(int devid, hipStream_t s) {
 // 1024 threads, or 256 where four entries per thread are enough for every unit, or 32 are and there is more than a unit per
 // compute unit, which has room for one wide workgroup (window policy, two evicted each, 1024 / 256 threads: 256 units of 7500
 // entries 36 / 39 us, 384 units of 2000 32 / 25, 512 units of 2000 32 / 25, 768 units of 7500 91 / 80).
-// The moves have a kernel of their own where it would have at least four workgroups per unit (up to four units per compute
-// unit; a unit's own workgroup is as fast then: 4096 units of 1000 entries, window policy, 40 evicted each, 198 us with a
+// The moves have a kernel of their own for up to four units per compute
+// unit (a unit's own workgroup is as fast then: 4096 units of 1000 entries, window policy, 40 evicted each, 198 us with a
 // second kernel, 157 without) and where a unit may have more to move than its workgroup moves in two rounds: `excess` counts
 // what the host has seen (64 units of 9000 entries, 2 / 40 / 150 evicted, one kernel 41 / 51 / 65 us, two 45 / 53 / 57).  A
 // replayed graph may find more than was seen when it was captured; it then takes longer and does the same.  (With the second kernel in
@@ -281,7 +281,7 @@ int launch_evict(ckv_ctx* c, hipStream_t s, int begin, int count, int n_sink, in
     moves = moves || c->excess[l] > 2 * per_round;
     c->excess[l] = 0;
   }
-  moves = moves && count <= 4 * c->n_cu;
+  moves = moves && count <= std::min(4 * c->n_cu, kMoveUnits);
   auto select = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)count), dim3((unsigned)threads), 0, s, c->dev, begin, n_sink, after_step, moves ? 1 : 0);
   };
@@ -299,8 +299,10 @@ int launch_evict(ckv_ctx* c, hipStream_t s, int begin, int count, int n_sink, in
   }
   CKV_HIP(c, hipGetLastError());
   if (!moves) return CKV_OK;
-  const int y = std::max(1, std::min({16 * c->n_cu / count, (cap / 2 + 15) / 16, 64}));
-  hipLaunchKernelGGL(evict_move_kernel, dim3((unsigned)count, (unsigned)y), dim3(kThreads), 0, s, c->dev, begin);
+  // two workgroups per compute unit, or as many as have four moves per wavefront if every unit moves half of what it may hold
+  const long long most = ((long long)count * (cap / 2) + 15) / 16;
+  const int groups = std::max(8, (int)std::min<long long>(2ll * c->n_cu, (most + 7) / 8 * 8) & ~7);
+  hipLaunchKernelGGL(evict_move_kernel, dim3((unsigned)groups), dim3(kThreads), 0, s, c->dev, begin, count);
   CKV_HIP(c, hipGetLastError());
   return CKV_OK;
 }

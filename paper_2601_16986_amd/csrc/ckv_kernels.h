@@ -1291,19 +1291,96 @@ __device__ __forceinline__ int evict_lists(const Dev& d, int u, Slots base, int 
 }
 
 // Second kernel of an eviction: the survivors' rows, four per wavefront at a time (every load of a batch before
-// its first store), the unit's batches dealt over the workgroups along y (a unit's own y-th, as many as fill the
-// chip: one workgroup per unit leaves a layer of 64 units to 64 compute units and needs 100 round trips each).
-// What bounds it is what it has to read: survivors lie seven to a block of 32 on average and bring most of their blocks'
-// lines with them, about 370 MB for 64 units of 9350 entries cut to 2048 in 79 us.  (Destination blocks put together in LDS
-// and stored whole, instead of a row's 48 partial lines: 85 us.)
-// Units along x, so that a unit's workgroups share an XCD's cache when their number is a multiple of eight.
-// grid: (units, workgroups per unit), kThreads threads.
-__global__ __launch_bounds__(kThreads) void evict_move_kernel(Dev d, int unit_begin) {
-  const int first = 4 * (blockIdx.y * (kThreads / 64) + (threadIdx.x >> 6)), stride = 4 * gridDim.y * (kThreads / 64);
-  const int u = unit_begin + blockIdx.x;
-  const int h = *move_count(d, u);
-  const Slots base = slots_of(d, u);
-  for (int r0 = first; r0 < h; r0 += stride) move_entries4(d, base, move_list(d, u), d.cap, r0, min(4, h - r0), threadIdx.x & 63);
+// its first store).  All units' moves are one sequence, an eighth of it for each XCD, whose wavefronts go through it side by side.
+// What bounds it is what it has to read and write: survivors lie seven to a block of 32 on average and bring most of their blocks'
+// lines with them, and a row is 16 pieces of a key and 128 single values, each in another piece of its block.  The cache of
+// an XCD makes that up only for moves that follow one another at about the same time.  64 units of 9350 entries cut to 2048 on average, and 1024
+// of 2048 after a re-allocation: units with a few workgroups each 79 and 310 us; runs of the sequence, a wavefront each 75 and
+// 350, a workgroup each, four moves in turn for its wavefronts, 70 and 229; side by side as it is, eight workgroups per compute unit 63 and 208, four 63 and 207, two
+// 56 and 198, one 62 and 188; two, with eight rows per wavefront 62 and 200.  (Destination blocks put together in LDS and stored whole, instead of a
+// row's 48 partial lines, units with workgroups of their own: 85 us for the first.)
+// Places in the lists and in the segment table are looked up by a lane per move, sixteen batches at once; the units' numbers of moves are
+// summed up by every workgroup for itself.
+// grid: a multiple of 8 workgroups of kThreads threads; count <= kMoveUnits.
+constexpr int kMoveUnits = 4 * kThreads;
+__global__ __launch_bounds__(kThreads) void evict_move_kernel(Dev d, int unit_begin, int count) {
+  __shared__ int s_first[kMoveUnits];                      // each unit's first move in the sequence
+  __shared__ int s_part[kThreads / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int h[4], sum = 0;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) h[e] = 4 * tid + e < count ? *move_count(d, unit_begin + 4 * tid + e) : 0;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) sum += h[e];
+  const int incl = wave_scan_i32(sum, lane);
+  if (lane == 63) s_part[wave] = incl;
+  __syncthreads();
+  int first = incl - sum, moves = 0;
+#pragma unroll
+  for (int w = 0; w < kThreads / 64; ++w) {
+    first += w < wave ? s_part[w] : 0;
+    moves += s_part[w];
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    s_first[4 * tid + e] = first;
+    first += h[e];
+  }
+  __syncthreads();
+  constexpr int kStep = 4 * (kThreads / 64);               // moves that a workgroup's wavefronts have in flight, four each
+  const int eighth = (moves + 7) / 8, hop = (gridDim.x >> 3) * kStep;
+  const int begin = (blockIdx.x & 7) * eighth, end = min(moves, begin + eighth);
+  uint16_t* K = d.K;
+  uint16_t* V = d.V;
+  for (int r0 = begin + (blockIdx.x >> 3) * kStep + 4 * wave; r0 < end; r0 += 16 * hop) {
+    const int mine = r0 + hop * (lane >> 2) + (lane & 3), n = __popcll(__ballot(mine < end));      // lane 4 b + m: the m-th of batch b
+    const int r = min(mine, end - 1);
+    int k = 0;                                             // the last unit whose moves begin at r or before (units without any begin where the next does)
+#pragma unroll
+    for (int step = kMoveUnits / 2; step > 0; step >>= 1)
+      if (k + step < count && s_first[k + step] <= r) k += step;
+    const int u = unit_begin + k, rank = r - s_first[k];
+    const int* lst = move_list(d, u);
+    const int src = lst[d.cap - 1 - rank], dst = lst[rank];
+    const int32_t* row = d.tbl + (size_t)u * d.max_seg;
+    const int src_seg = row[src >> 8], dst_seg = row[dst >> 8], src_in = src & (kSeg - 1), dst_in = dst & (kSeg - 1);
+    const size_t from = (size_t)src_seg * kSeg + src_in, to = (size_t)dst_seg * kSeg + dst_in;
+    const float crf = d.crf[from];
+    const int tau = d.tau[from], ps = d.pos[from], pd = d.pos[to];
+    const uint8_t fl = d.flags[from];
+    for (int m0 = 0; m0 < n; m0 += 4) {
+      // lane l: the key piece l % 16 of move l / 16, two value elements of every move
+      const int mk = min(m0 + (lane >> 4), n - 1), piece = (lane & 15) * 8;
+      const u32x4 kx = *reinterpret_cast<const u32x4*>(K + (size_t)__shfl(src_seg, mk) * kSegElems + k_offset(__shfl(src_in, mk), piece));
+      uint16_t* to_k = K + (size_t)__shfl(dst_seg, mk) * kSegElems + k_offset(__shfl(dst_in, mk), piece);
+      uint16_t v0[4], v1[4];
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const int mm = min(m0 + m, n - 1), in = __builtin_amdgcn_readlane(src_in, mm);
+        const uint16_t* p = V + (size_t)__builtin_amdgcn_readlane(src_seg, mm) * kSegElems;
+        v0[m] = p[v_offset(in, lane)];
+        v1[m] = p[v_offset(in, lane + 64)];
+      }
+      if (m0 + (lane >> 4) < n) *reinterpret_cast<u32x4*>(to_k) = kx;
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        if (m0 + m < n) {
+          const int in = __builtin_amdgcn_readlane(dst_in, m0 + m);
+          uint16_t* p = V + (size_t)__builtin_amdgcn_readlane(dst_seg, m0 + m) * kSegElems;
+          p[v_offset(in, lane)] = v0[m];
+          p[v_offset(in, lane + 64)] = v1[m];
+        }
+      }
+    }
+    if (lane < n) {
+      d.crf[to] = crf;
+      d.tau[to] = tau;
+      d.pos[to] = ps;
+      d.pos[from] = pd;
+      d.flags[to] = fl;
+      d.flags[from] = FLAG_SLIP;
+    }
+  }
 }
 
 // ------------------------------------------------------------------ finish

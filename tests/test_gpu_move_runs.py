@@ -1,0 +1,54 @@
+"""What is dealt out over the whole chip from per-unit counts: an eviction's moves and the segments that change hands."""
+import numpy as np
+import pytest
+
+from tests.test_gpu_evict_sizes import _check
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("units", [1, 9, 1024])
+def test_moves_of_units_with_very_different_lists(units):
+    """One unit with thousands of moves, most with a few or none, the first and the last among either."""
+    lengths = [(4000 if i % 97 == units % 97 else 1500) if units <= 9 else (3100 if i % 97 == 5 or i == units - 1 else 300 + i % 5) for i in range(units)]
+    budgets = [n // 2 if n >= 1000 else (n if i % 3 else n - 7) for i, n in enumerate(lengths)]
+    _check(units, 4032, lengths, budgets, None, sorted({0, 5, units - 1} & set(range(units))) + list(range(0, units, 89)), False)
+
+
+def _deal(own, rows, spare, need):
+    """Segments as the definition deals them out: surplus of units in order to the stack, then what units lack from its top."""
+    for u in range(len(own)):
+        spare += [rows[u][j] for j in range(need[u], own[u])]
+        rows[u] = rows[u][:min(own[u], need[u])]
+    if sum(max(0, need[u] - own[u]) for u in range(len(own))) > len(spare):
+        return False
+    for u in range(len(own)):
+        while len(rows[u]) < need[u]:
+            rows[u].append(spare.pop())
+    return True
+
+
+@pytest.mark.parametrize("short", [False, True])
+@pytest.mark.parametrize("units", [3, 1023, 1024, 1025, 2500])
+def test_segments_are_dealt_as_defined(units, short):
+    from paper_2601_16986_amd import ckv
+    rng = np.random.default_rng(units)
+    cap = 3072
+    old = rng.integers(1, cap - 64, (1, units, 1)).astype(np.int32)
+    g = ckv.CrystalKV(1, units, 1, 1, 128, cap, old, t0=1, headroom=1, budget_min=1, budget_max=cap - 2)
+    seg = lambda b: (b.reshape(-1) + 1 + 255) // 256
+    before = g.segment_table()
+    rows = [list(before["rows"][u, :before["owned"][u]]) for u in range(units)]
+    spare = list(before["spare"])
+    # the same budgets dealt to other units, or (short) more than the pools hold
+    new = np.full_like(old, cap - 2) if short else rng.permutation(old.reshape(-1)).reshape(old.shape)
+    g.set_budgets(new)
+    g.rebalance()
+    enough = _deal(list(before["owned"]), rows, spare, seg(new))
+    assert enough != short and bool(g.status() & 4) == short
+    after = g.segment_table()
+    assert np.array_equal(after["owned"], [len(r) for r in rows])
+    for u in range(units):
+        assert list(after["rows"][u, :len(rows[u])]) == rows[u] and not after["rows"][u, len(rows[u]):].any()
+    assert list(after["spare"]) == spare
+    g.close()
