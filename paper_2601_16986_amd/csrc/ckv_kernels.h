@@ -476,16 +476,16 @@ __global__ __launch_bounds__(kThreads) void probe_copy_kernel(const u32x4* __res
 // does not depend on timing.  If the spare list is short nobody is given anything and bit 2 of the status
 // word is set; a unit that still holds more entries than its budget (its eviction has not run yet) keeps
 // its segments until a later call.  Unowned columns of a table row hold 0.
-// A unit's segments move eight at a time (every load before the first store): one by one, the 28 segments that a
-// prompt of 9350 entries needs above a budget of 2048 were as many round trips, twice (64 such units: 42 us, now 22).
+// The segments that change hands are dealt out to the threads one by one, each looks up the unit it comes from or goes to: what a prompt
+// passes from layer to layer, 28 segments of each of 64 neighbouring units, was fetched and stored by 64 threads, in as many
+// round trips as a unit has eights (22 us, now 8.4; the first version, one segment at a time, 42).
 constexpr int kBalanceThreads = 1024;
 __global__ __launch_bounds__(kBalanceThreads) void rebalance_kernel(Dev d, int headroom, int x_begin, int x_count, int x_entries,
                                                                     const int32_t* x_len) {
-  __shared__ int s_part[kBalanceThreads / 64];
-  __shared__ int s_total;
+  __shared__ u64 s_part[kBalanceThreads / 64];
+  __shared__ int s_first[kBalanceThreads];       // of a thousand units: where each one's segments begin among those that change hands,
+  __shared__ int s_from[kBalanceThreads];        // and the first column of its row that is concerned
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int per = (d.units + kBalanceThreads - 1) / kBalanceThreads;
-  const int u0 = min(d.units, tid * per), u1 = min(d.units, u0 + per);
   // what this kernel writes and reads back (ownership, table cells, the spare stack) goes through accesses that
   // are coherent one by one, whichever thread wrote them
   auto ld = [](const int32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
@@ -495,52 +495,58 @@ __global__ __launch_bounds__(kBalanceThreads) void rebalance_kernel(Dev d, int h
     if (u >= x_begin && u < x_begin + x_count) e = max(e, x_len ? min(max(x_len[u - x_begin], 0) + headroom, x_entries) : x_entries);
     return min(d.max_seg, (e + kSeg - 1) / kSeg);
   };
-  // exclusive prefix over the threads' ranges of a per-thread count; the total lands in s_total
-  auto scan = [&](int local) -> int {
-    int incl = local;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int v = __shfl_up(incl, o);
-      if (lane >= o) incl += v;
-    }
+  // of two counts per thread, sums over the threads before; the sums over all
+  auto scan = [&](int a, int b, int& a_before, int& b_before, int& a_all, int& b_all) {
+    const int ia = wave_scan_i32(a, lane), ib = wave_scan_i32(b, lane);
     __syncthreads();                       // the previous scan's readers are done
-    if (lane == 63) s_part[wave] = incl;
+    if (lane == 63) s_part[wave] = ((u64)(uint32_t)ib << 32) | (uint32_t)ia;
     __syncthreads();
-    int before = incl - local;
-    for (int w = 0; w < wave; ++w) before += s_part[w];
-    if (tid == kBalanceThreads - 1) s_total = before + local;
+    a_before = ia - a;
+    b_before = ib - b;
+    a_all = b_all = 0;
+    for (int w = 0; w < kBalanceThreads / 64; ++w) {
+      const int x = (int)(uint32_t)s_part[w], y = (int)(s_part[w] >> 32);
+      a_before += w < wave ? x : 0;
+      b_before += w < wave ? y : 0;
+      a_all += x;
+      b_all += y;
+    }
+  };
+  // f(unit, column of its row, number among all) for every one of `total` segments
+  auto each = [&](int c0, int first, int from, int total, auto f) {
+    s_first[tid] = first;
+    s_from[tid] = from;
     __syncthreads();
-    return before;
+    for (int i = tid; i < total; i += kBalanceThreads) {
+      int k = 0;                           // the last thread whose segments begin at i or before
+#pragma unroll
+      for (int step = kBalanceThreads / 2; step > 0; step >>= 1)
+        if (s_first[k + step] <= i) k += step;
+      f(c0 + k, s_from[k] + (i - s_first[k]), i);
+    }
   };
   int spare_n = d.sc[SC_SPARE];
   // ---- release
-  int local = 0;
-  for (int u = u0; u < u1; ++u) local += max(0, ld(d.owned + u) - need_of(u));
-  int at = spare_n + scan(local);
-  for (int u = u0; u < u1; ++u) {
-    const int need = need_of(u), own = ld(d.owned + u);
-    int32_t* row = d.tbl + (size_t)u * d.max_seg;
-    for (int j = need; j < own; j += 8) {
-      int32_t seg[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) seg[k] = ld(row + min(j + k, own - 1));
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        if (j + k < own) {
-          st(d.spare + at++, seg[k]);
-          st(row + j + k, 0);
-        }
-      }
+  int wanted = 0, want_before = 0;         // (of the only thousand units, if there are no more)
+  for (int c0 = 0; c0 < d.units; c0 += kBalanceThreads) {
+    const int u = c0 + tid;
+    const int need = u < d.units ? need_of(u) : 0, own = u < d.units ? ld(d.owned + u) : 0;
+    int first, total, want;
+    scan(max(0, own - need), max(0, need - own), first, want_before, total, want);
+    wanted += want;
+    if (total > 0) {
+      each(c0, first, need, total, [&](int v, int j, int i) {
+        int32_t* cell = d.tbl + (size_t)v * d.max_seg + j;
+        st(d.spare + spare_n + i, ld(cell));
+        st(cell, 0);
+      });
+      if (own > need) st(d.owned + u, need);
+      spare_n += total;
     }
-    if (own > need) st(d.owned + u, need);
   }
-  spare_n += s_total;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the stack's new entries before anyone pops them
+  __syncthreads();
   // ---- grant
-  local = 0;
-  for (int u = u0; u < u1; ++u) local += max(0, need_of(u) - ld(d.owned + u));
-  int from = scan(local);
-  const int wanted = s_total;
   if (wanted > spare_n) {
     if (tid == 0) {
       atomicOr(&d.sc[SC_STATUS], 4);
@@ -548,18 +554,17 @@ __global__ __launch_bounds__(kBalanceThreads) void rebalance_kernel(Dev d, int h
     }
     return;
   }
-  for (int u = u0; u < u1; ++u) {
-    const int need = need_of(u), own = ld(d.owned + u);
-    for (int j = own; j < need; j += 8) {
-      int32_t seg[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) seg[k] = ld(d.spare + (spare_n - 1 - (from + min(k, need - 1 - j))));
-#pragma unroll
-      for (int k = 0; k < 8; ++k)
-        if (j + k < need) st(d.tbl + (size_t)u * d.max_seg + j + k, seg[k]);
-      from += min(8, need - j);
+  int top = spare_n;
+  for (int c0 = 0; wanted > 0 && c0 < d.units; c0 += kBalanceThreads) {
+    const int u = c0 + tid;
+    const int need = u < d.units ? need_of(u) : 0, own = u < d.units ? ld(d.owned + u) : 0;
+    int first = want_before, total = wanted, none, none_all;
+    if (d.units > kBalanceThreads) scan(max(0, need - own), 0, first, none, total, none_all);
+    if (total > 0) {
+      each(c0, first, own, total, [&](int v, int j, int i) { st(d.tbl + (size_t)v * d.max_seg + j, ld(d.spare + (top - 1 - i))); });
+      if (need > own) st(d.owned + u, need);
+      top -= total;
     }
-    if (need > own) st(d.owned + u, need);
   }
   if (tid == 0) d.sc[SC_SPARE] = spare_n - wanted;
 }
