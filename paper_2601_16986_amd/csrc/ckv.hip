@@ -936,7 +936,7 @@ int ckv_seed_prompt(ckv_ctx* c, int32_t layer, const void* q_obs, int32_t W, voi
       // The fewest registers that hold the row, in steps of four (one step more than needed costs the whole call 2-3 % at 32
       // queries: 6100 entries 181 us with 12, 185 with 16; 9350 entries 247 with 20, 252 with 24; 12000 entries 290 with 24,
       // 298 with 28; in LDS instead of 32 registers, 16384 entries, 562 against 355).
-      constexpr size_t list = sizeof(TopBuf);
+      constexpr size_t list = kSeedHitsLds;
       switch ((per + 3) / 4) {
         case 0: case 1: case 2: hits(seed_hits_kernel<8>, list); break;
         case 3: hits(seed_hits_kernel<12>, list); break;

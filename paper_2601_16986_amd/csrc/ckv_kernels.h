@@ -1770,6 +1770,12 @@ constexpr uint32_t kSubLow = (1u << kSubShift) - 1u;
 __device__ __forceinline__ double bin_edge(int i) { return (double)__uint_as_float((uint32_t)(kBinFirst + i) << kBinShift); }
 __device__ __forceinline__ double bin_unit(int i) { return (double)__uint_as_float((uint32_t)((kBinFirst + i) >> 5) << 23) * 0x1p-23; }
 
+// The same sum in units of 2^-46, the lowest bin's (24 octaves of 32768 weights stay below 2^62), for the scan over the bins.
+constexpr double kFixedBin = 0x1p46;
+__device__ __forceinline__ u64 bin_fixed(u64 v, int i) {
+  return (((u64)((uint32_t)(v >> kBinCount) * (uint32_t)(32 + (i & 31))) << kBinShift) + (v & ((1ull << kBinCount) - 1ull))) << (i >> 5);
+}
+
 __device__ __forceinline__ double bin_sum(u64 v, int i) {
   return (double)(uint32_t)(v >> kBinCount) * bin_edge(i) + (double)(v & ((1ull << kBinCount) - 1ull)) * bin_unit(i);
 }
@@ -1780,12 +1786,17 @@ __device__ __forceinline__ void clear_top(TopBuf& tb, int tid, int threads) {
 
 // tb: in LDS, CLEARED (and a barrier since), or where something else may lie.  new_last_t >= 0: the unit's last entry is not in
 // the cache, or not to be looked up there, and has this position.
-// REFINE: long rows of flat weights, where a bin holds more than the list: the bin once more, by its next eight bits.
-template <int R, int NT = kThreads, bool CLEARED = false, bool REFINE = false>
+// REFINE: long rows of flat weights, where a bin holds more than the list: the bin once more, by its next eight bits.  64 places of 8 bytes lie behind tb.
+template <int R, int NT = kThreads, bool CLEARED = false, bool REFINE = false, bool LIST = CLEARED && !REFINE>
 __device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, const float (&a)[R], TopBuf& tb, int new_last_t, RedBuf<NT>& rb, int& phase,
                                               int tid) {
   if (every_entry_hit(d)) return HitRule{0u, true, 0x7FFFFFFF};
   constexpr int kList = top_list<NT>();
+  // Steps that one wavefront, or a few, would take alone are shared by all, with the registers this needs (not in the fused kernel, whose
+  // workgroups wait for each other less and which has none left): the list's places taken once per wavefront, candidates compared by all, sums over the bins
+  // in whole numbers.  4096 rows of 9350 weights 65.7 -> 62.9 us, 2048 of them 33.2 -> 29.8 (with fewer instructions per weight around it), the
+  // bookkeeping of 128 units 14.9 -> 14.7.
+  constexpr bool kShare = CLEARED || REFINE;
   const int lane = tid & 63, wave = tid >> 6;
   // (not known to the compiler as the same in every unit: kept in registers across the units of a persistent kernel it would be
   // spilled, and a reload is a wait for every load in flight)
@@ -1798,16 +1809,69 @@ __device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, c
     block_sync<NT>(rb);
   }
   uint32_t largest = 0;
+  if constexpr (REFINE) {
+    // Weights outside the bins go to one of 64 behind the buffer, a lane's own, instead of nowhere: a minimum in place of a compare and a branch
+    // over the addition.  (The caller's rows are zero beyond their end, which only the last few registers reach.)
+    const uint32_t beyond = (uint32_t)sizeof(TopBuf) + 8u * lane;
+    unsigned char* bins = reinterpret_cast<unsigned char*>(tb.bin);
 #pragma unroll
-  for (int k = 0; k < R; ++k) {
-    const uint32_t b = __float_as_uint(a[k]), i = (b >> kBinShift) - (uint32_t)kBinFirst;
-    largest = max(largest, b);
-    if (i < (uint32_t)kBins) atomicAdd(&tb.bin[i], (1ull << kBinCount) | (b & kBinLow));
-    if (k % 4 == 3) __builtin_amdgcn_sched_barrier(0);        // few addresses at a time
+    for (int k = 0; k < R; ++k) {
+      const uint32_t b = __float_as_uint(a[k]);
+      largest = max(largest, b);
+      atomicAdd(reinterpret_cast<u64*>(bins + min(((b >> kBinShift) << 3) - (uint32_t)(kBinFirst << 3), beyond)), (1ull << kBinCount) | (b & kBinLow));
+      if (k % 4 == 3) __builtin_amdgcn_sched_barrier(0);        // few addresses at a time
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      const uint32_t b = __float_as_uint(a[k]), i = (b >> kBinShift) - (uint32_t)kBinFirst;
+      largest = max(largest, b);
+      if (i < (uint32_t)kBins) atomicAdd(&tb.bin[i], (1ull << kBinCount) | (b & kBinLow));
+      if (k % 4 == 3) __builtin_amdgcn_sched_barrier(0);        // few addresses at a time
+    }
   }
   if (largest >= 0x40000000u) tb.odd = 1u;
   block_sync<NT>(rb);
-  if (wave == 0) {
+  if (kShare && wave == 0) {
+    // lane l: bins kPer l and up
+    constexpr int kPer = kBins / 64;
+    const u64 pass = (u64)(p * kFixedBin);                // a sum exceeds p if it exceeds this
+    u64 mine = 0;
+#pragma unroll
+    for (int i = 0; i < kPer; i += 4) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) mine += bin_fixed(tb.bin[kPer * lane + i + e], kPer * lane + i + e);
+      __builtin_amdgcn_sched_barrier(0);                    // the weights need the registers
+    }
+    // sums from each lane up: inside a row of 16 lanes, then the rows above (the sum grows towards the lower lanes)
+    u64 incl = mine;
+    incl += dpp_u64<kDppRowShl + 1>(incl);
+    incl += dpp_u64<kDppRowShl + 2>(incl);
+    incl += dpp_u64<kDppRowShl + 4>(incl);
+    incl += dpp_u64<kDppRowShl + 8>(incl);
+    const u64 row3 = readlane_u64(incl, 48), row2 = readlane_u64(incl, 32) + row3, row1 = readlane_u64(incl, 16) + row2;
+    incl += lane < 16 ? row1 : lane < 32 ? row2 : lane < 48 ? row3 : 0;
+    const u64 passed = __ballot(incl > pass);
+    if (passed) {
+      // the highest lane at which it passes; of that lane's bins, from the top, lane i takes the i-th
+      const int at = 63 - __builtin_clzll(passed), bin = kPer * at + kPer - 1 - min(lane, kPer - 1);
+      const u64 before = readlane_u64(incl - mine, at), v = tb.bin[bin], own = lane < kPer ? bin_fixed(v, bin) : 0;
+      u64 sum = own;
+      sum += dpp_u64<kDppRowShr + 1>(sum);
+      sum += dpp_u64<kDppRowShr + 2>(sum);
+      sum += dpp_u64<kDppRowShr + 4>(sum);
+      sum += dpp_u64<kDppRowShr + 8>(sum);
+      const u64 here = __ballot(before + sum > pass) & ((1ull << kPer) - 1ull);
+      if (lane == __builtin_ctzll(here)) {                  // (sums of whole numbers: it passes at one of them)
+        tb.at = bin;
+        tb.count = (int)(v >> kBinCount);
+        tb.above = (double)(before + (sum - own)) / kFixedBin;
+      }
+    } else if (lane == 0) {
+      tb.at = -1;
+    }
+  }
+  if (!kShare && wave == 0) {
     // lane l: bins kPer l and up; few registers at a time, since the weights and the callers' prefetches live through this
     constexpr int kPer = kBins / 64;
     double mine = 0.0;
@@ -1905,11 +1969,51 @@ __device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, c
       }
     }
     if (m <= kList) {
+      if constexpr (kShare) {
+        // a wavefront's places in the list are taken by one addition (one per register, each waited for: 1.4 us of a workgroup's 10 on rows of 9350)
+        for (int i = tid; i < kList; i += NT) tb.bin[i] = 0ull;            // the bins have been read: what follows adds up here
+        int mine = 0;
 #pragma unroll
-      for (int k = 0; k < R; ++k) {
-        const uint32_t b = __float_as_uint(a[k]);
-        if ((b ^ theta) <= low_bits) tb.list[atomicAdd(&tb.listed, 1u)] = b;
-        if (k % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+        for (int k = 0; k < R; ++k) mine += __popcll(__ballot((__float_as_uint(a[k]) ^ theta) <= low_bits));
+        int at = 0;
+        if (lane == 0 && mine > 0) at = (int)atomicAdd(&tb.listed, (uint32_t)mine);
+        at = uniform_i32(at);
+        if (mine > 0) {
+#pragma unroll
+          for (int k = 0; k < R; ++k) {
+            const uint32_t b = __float_as_uint(a[k]);
+            const u64 here = __ballot((b ^ theta) <= low_bits);
+            if (here) {                                      // uniform
+              const int before = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(here >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)here, 0u));
+              if ((b ^ theta) <= low_bits) tb.list[at + before] = b;
+              at += __popcll(here);
+            }
+          }
+        }
+        block_sync<NT>(rb);
+        // every wavefront compares all candidates with its part of the list
+        const int part = ((m + NT / 64 - 1) / (NT / 64) + 3) & ~3, k0 = wave * part, k1 = min(m, k0 + part);
+        for (int c0 = 0; c0 < m && k0 < m; c0 += 64) {
+          const uint32_t mine = tb.list[min(c0 + lane, m - 1)];
+          uint32_t larger = 0u, equal = 0u, low = 0u;
+          for (int k = k0; k < k1; k += 4) {               // the list ends in zeros
+            const u32x4 four = *reinterpret_cast<const u32x4*>(tb.list + k);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              larger += four[e] > mine ? 1u : 0u;
+              low += four[e] > mine ? four[e] & low_bits : 0u;
+              equal += four[e] == mine ? 1u : 0u;
+            }
+          }
+          if (c0 + lane < m) atomicAdd(&tb.bin[c0 + lane], (u64)low | (u64)larger << 32 | (u64)equal << 48);      // low: 256 parts of 18 bits
+        }
+      } else {
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+          const uint32_t b = __float_as_uint(a[k]);
+          if ((b ^ theta) <= low_bits) tb.list[atomicAdd(&tb.listed, 1u)] = b;
+          if (k % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+        }
       }
       block_sync<NT>(rb);
       // A candidate per thread: theta is the largest of them whose sum of those at least as large, on top of the bins above, exceeds p.
@@ -1917,13 +2021,20 @@ __device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, c
       uint32_t mine = 0u, th = 0u, equal = 0u, larger = 0u, low = 0u;
       if (64 * wave < m) {
         mine = tb.list[tid];
-        for (int k = 0; k < m; k += 4) {                   // the list ends in zeros
-          const u32x4 four = *reinterpret_cast<const u32x4*>(tb.list + k);
+        if constexpr (kShare) {
+          const u64 v = tid < m ? tb.bin[tid] : 0ull;
+          low = (uint32_t)v;
+          larger = (uint32_t)(v >> 32) & 0xFFFFu;
+          equal = (uint32_t)(v >> 48);
+        } else {
+          for (int k = 0; k < m; k += 4) {                 // the list ends in zeros
+            const u32x4 four = *reinterpret_cast<const u32x4*>(tb.list + k);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            larger += four[e] > mine ? 1u : 0u;
-            low += four[e] > mine ? four[e] & low_bits : 0u;
-            equal += four[e] == mine ? 1u : 0u;
+            for (int e = 0; e < 4; ++e) {
+              larger += four[e] > mine ? 1u : 0u;
+              low += four[e] > mine ? four[e] & low_bits : 0u;
+              equal += four[e] == mine ? 1u : 0u;
+            }
           }
         }
         const double sum = above + ((double)(larger + equal) * edge + (double)(low + equal * (mine & low_bits)) * unit);
@@ -1942,7 +2053,7 @@ __device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, c
       block_sync<NT>(rb);
       const uint32_t found = (uint32_t)uniform_i32((int)tb.theta);
       if (found == 0u) return HitRule{theta, true, 0x7FFFFFFF};
-      return tie_rule<R, NT, CLEARED>(d, base, n, a, found, readlane_f64(tb.above_theta, 0), uniform_i32((int)tb.ties), tb, new_last_t, rb, phase, tid);
+      return tie_rule<R, NT, LIST>(d, base, n, a, found, readlane_f64(tb.above_theta, 0), uniform_i32((int)tb.ties), tb, new_last_t, rb, phase, tid);
     }
   }
   // two bits per round (one barrier each): the three candidates' sums are nested, so the largest candidate that passes is
@@ -1971,7 +2082,7 @@ __device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, c
   }
   above = uniform_f32(block_sum_f32<NT>(above, rb, phase, tid));
   ties = uniform_i32(block_sum_int<NT>(ties, rb, phase, tid));
-  return tie_rule<R, NT, CLEARED>(d, base, n, a, theta, above, ties, tb, new_last_t, rb, phase, tid);
+  return tie_rule<R, NT, LIST>(d, base, n, a, theta, above, ties, tb, new_last_t, rb, phase, tid);
 }
 
 // `after_step1` runs once between Step 1 and the score update (the fused kernel
@@ -2663,21 +2774,34 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 3))
 // from `srw`, the hit rule, and in their place the hits, a bit per entry at the start of the row (the query's own entry,
 // the last it sees, is always hit): every thread has its weights in registers (or LDS) before the first bit is written.
 // (As rewards of 4 bytes they were 153 MB per layer of 128 units of 9350 entries and 32 queries, written and read.)
-// grid: (queries of the batch, units of the layer), kSeedThreads threads, a TopBuf of dynamic LDS (R = 0: cap floats).
+// grid: (queries of the batch, units of the layer), kSeedThreads threads, kSeedHitsLds of dynamic LDS (R = 0: cap floats).
 constexpr int kSeedThreads = 512;      // prompts are long
+constexpr size_t kSeedHitsLds = sizeof(TopBuf) + 64 * 8;
 
 template <int R>
 __device__ __forceinline__ void seed_rewards_regs(const Dev& d, Slots base, int n, bool last_new, float* rw, int* lst, RedBuf<kSeedThreads>& rb, int& phase,
                                                   int tid) {
   float a[R];
+  f32x4 x[R / 4];
 #pragma unroll
   for (int c = 0; c < R / 4; ++c) {
     const int e0 = 4 * (tid + c * kSeedThreads);
-    const f32x4 x = e0 < n ? *reinterpret_cast<const f32x4*>(rw + e0) : f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) a[4 * c + e] = (e0 + e < n) ? x[e] : 0.f;
+    x[c] = *reinterpret_cast<const f32x4*>(rw + min(e0, (n - 1) & ~3));
   }
-  const HitRule rule = top_p_regs<R, kSeedThreads, false, true>(d, base, n, a, *reinterpret_cast<TopBuf*>(lst), -1, rb, phase, tid);
+  clear_top(*reinterpret_cast<TopBuf*>(lst), tid, kSeedThreads);            // while the weights are on their way
+#pragma unroll
+  for (int c = 0; c < R / 4; ++c) {
+    const int left = n - 4 * (tid + c * kSeedThreads);
+    if (4 * kSeedThreads * (c + 1) <= n) {                   // uniform: the row goes on behind them
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a[4 * c + e] = x[c][e];
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a[4 * c + e] = e < left ? x[c][e] : 0.f;
+    }
+  }
+  block_sync<kSeedThreads>(rb);
+  const HitRule rule = top_p_regs<R, kSeedThreads, true, true>(d, base, n, a, *reinterpret_cast<TopBuf*>(lst), -1, rb, phase, tid);
   uint32_t* bits = reinterpret_cast<uint32_t*>(rw);
 #pragma unroll
   for (int c = 0; c < R / 4; ++c) {
@@ -2685,7 +2809,7 @@ __device__ __forceinline__ void seed_rewards_regs(const Dev& d, Slots base, int 
     uint32_t word = 0;
     if (rule.ties_all) {                                   // uniform, nearly always
 #pragma unroll
-      for (int e = 0; e < 4; ++e) word |= (__float_as_uint(a[4 * c + e]) >= rule.theta ? 1u : 0u) << e;
+      for (int e = 3; e >= 0; --e) word += word + (__float_as_uint(a[4 * c + e]) >= rule.theta ? 1u : 0u);      // an addition with carry each
     } else if (e0 < n) {
       const i32x4 ps = *reinterpret_cast<const i32x4*>(d.pos + (base + e0));
 #pragma unroll
