@@ -701,7 +701,11 @@ int ckv_init(ckv_ctx** out, const ckv_layout* layout, const int32_t* budgets, co
   } catch (const std::bad_alloc&) {
     return bail(CKV_EHIP);
   }
-  auto region = [](void* p, size_t bytes, uint32_t v = 0u) { return InitFill{(u32x4*)p, v, bytes / 16}; };
+  const unsigned blocks = (unsigned)std::min<size_t>(8ull * c->n_cu, std::max<size_t>(1, (S * kDim / 8 + kThreads - 1) / kThreads));
+  auto region = [&](void* p, size_t bytes, uint32_t v = 0u) {
+    const size_t count = bytes / 16, rounds = count / ((size_t)blocks * kThreads);
+    return InitFill{(u32x4*)p, v, count, rounds >= 16 ? rounds * kThreads : 0};
+  };
   job.fill[0] = region(d.K, S * kDim * 2);
   job.fill[1] = region(d.V, S * kDim * 2);
   job.fill[2] = region(d.crf, S * 4);
@@ -721,7 +725,6 @@ int ckv_init(ckv_ctx** out, const ckv_layout* layout, const int32_t* budgets, co
   job.t0 = params->t0;
   if (hipMemcpyAsync(d.partial, stage.data(), stage.size() * 4, hipMemcpyHostToDevice, s) != hipSuccess) return bail(CKV_EHIP);
   if (!job.tab_n && hipMemcpyAsync((void*)d.tab, tab.data(), tab.size() * 4, hipMemcpyHostToDevice, s) != hipSuccess) return bail(CKV_EHIP);
-  const unsigned blocks = (unsigned)std::min<size_t>(8ull * c->n_cu, std::max<size_t>(1, (S * kDim / 8 + kThreads - 1) / kThreads));
   hipLaunchKernelGGL(init_kernel, dim3(blocks), dim3(kThreads), 0, s, d, job);
   if (hipGetLastError() != hipSuccess) return bail(CKV_EHIP);
   if (int rc = launch_schedule(c, s)) return bail(rc);
