@@ -1190,7 +1190,7 @@ __device__ __forceinline__ KeyCut select_low_keys(const uint32_t (&b)[R], const 
 #pragma unroll
       for (int i = 0; i < R; ++i) {
         uint32_t v;
-        if (value(i, v) && ((v ^ X) >> s) < digits) atomicAdd(&h[(v >> s) & (digits - 1)], 1u);
+        if (value(i, v) && (v >> s) - (X >> s) < digits) atomicAdd(&h[(v >> s) - (X >> s)], 1u);      // (X ends in zeros from the digit on)
       }
       turn = turn == 2 ? 0 : turn + 1;
       for (int i = tid; i < 256; i += NT) cb.hist[turn][i] = 0u;       // read last two rounds ago
@@ -3140,6 +3140,8 @@ __device__ __forceinline__ void evict_unit(const Dev& d, int u, Slots base, int 
 // RMAX: entries per thread of the longest unit that the capacity allows.  The widest branch decides the registers of the
 // whole kernel, and with them how many short units are on the chip side by side (256 threads: 64 registers with 4, 153 with
 // 32; 4096 units of 1000 entries, window policy, two evicted each: 87 us with 32, 69 with 8).
+// Units take 4, 8, 12, 16, 24 or 32, the least that hold them: what bounds a round is its sixteen wavefronts' issue on one compute unit
+// (64 units of 9350 entries, ten per thread, 23.3 us with 16, 21.6 with 12; 512 units of 9351, window policy, one evicted each, 14.8 / 13.5).
 template <int NT, int RMAX>
 __global__ __launch_bounds__(NT) void evict_kernel(Dev d, int unit_begin, int n_sink, int after_step, int moves_follow) {
   __shared__ uint32_t evm[NT];
@@ -3166,10 +3168,14 @@ __global__ __launch_bounds__(NT) void evict_kernel(Dev d, int unit_begin, int n_
   auto unit = [&](auto r) {
     evict_unit<decltype(r)::value, NT>(d, u, base, n, B, n_sink, moves_follow, s_tab, s_tab_n, evm, cb, rb, sh, tid);
   };
-  if constexpr (RMAX > 16)
-    if (n > 16 * NT) return unit(std::integral_constant<int, 32>{});
-  if constexpr (RMAX > 8)
-    if (n > 8 * NT) return unit(std::integral_constant<int, 16>{});
+  if constexpr (RMAX > 16) {
+    if (n > 24 * NT) return unit(std::integral_constant<int, 32>{});
+    if (n > 16 * NT) return unit(std::integral_constant<int, 24>{});
+  }
+  if constexpr (RMAX > 8) {
+    if (n > 12 * NT) return unit(std::integral_constant<int, 16>{});
+    if (n > 8 * NT) return unit(std::integral_constant<int, 12>{});
+  }
   if constexpr (RMAX > 4)
     if (n > 4 * NT) return unit(std::integral_constant<int, 8>{});
   unit(std::integral_constant<int, 4>{});

@@ -15,6 +15,15 @@ def test_moves_of_units_with_very_different_lists(units):
     _check(units, 4032, lengths, budgets, None, sorted({0, 5, units - 1} & set(range(units))) + list(range(0, units, 89)), False)
 
 
+@pytest.mark.parametrize("units,cap,edge", [(4, 24608, [12288, 12289, 24576, 24577]), (300, 8160, [3072, 3073, 6144, 6145])])
+@pytest.mark.parametrize("n_sink", [None, 20])
+def test_widths_between_the_powers_of_two(units, cap, edge, n_sink):
+    """Twelve and twenty-four entries per thread, of 1024 and of 256."""
+    lengths = [edge[i % 4] for i in range(units)]
+    budgets = [max(1, n - 1 - (i * 371) % (n - 1)) for i, n in enumerate(lengths)]
+    _check(units, cap, lengths, budgets, n_sink, range(0, units, 1 + units // 12), False)
+
+
 def _deal(own, rows, spare, need):
     """Segments as the definition deals them out: surplus of units in order to the stack, then what units lack from its top."""
     for u in range(len(own)):
