@@ -1819,7 +1819,7 @@ __device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, c
   }
   uint32_t largest = 0;
   if constexpr (REFINE) {
-    // Weights outside the bins go to one of 64 behind the buffer, a lane's own, instead of nowhere: a minimum in place of a compare and a branch
+    // Weights outside the bins go to one of 64 behind the buffer, a lane's own, instead of nowhere: a select in place of a branch
     // over the addition.  (The caller's rows are zero beyond their end, which only the last few registers reach.)
     const uint32_t beyond = (uint32_t)sizeof(TopBuf) + 8u * lane;
     unsigned char* bins = reinterpret_cast<unsigned char*>(tb.bin);
@@ -1827,7 +1827,8 @@ __device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, c
     for (int k = 0; k < R; ++k) {
       const uint32_t b = __float_as_uint(a[k]);
       largest = max(largest, b);
-      atomicAdd(reinterpret_cast<u64*>(bins + min(((b >> kBinShift) << 3) - (uint32_t)(kBinFirst << 3), beyond)), (1ull << kBinCount) | (b & kBinLow));
+      const uint32_t at = ((b >> kBinShift) << 3) - (uint32_t)(kBinFirst << 3);
+      atomicAdd(reinterpret_cast<u64*>(bins + (at < (uint32_t)(kBins << 3) ? at : beyond)), (1ull << kBinCount) | (b & kBinLow));
       if (k % 4 == 3) __builtin_amdgcn_sched_barrier(0);        // few addresses at a time
     }
   } else {
