@@ -1136,7 +1136,7 @@ struct KeyCut {
 // left of 32 for a unit that spans 16384 tokens): a histogram of the digit in LDS over the entries that still
 // match the prefix, then every wavefront finds the digit at which the count passes `want` by itself.  Scores that have decayed to
 // zero (most of a prompt's) are counted first: their common digit would serialise the LDS atomics of every round.
-// 64 units of 9350 entries, 7300 of them evicted, the whole kernel: 26 us; with two-bit rounds that count with ballots
+// 64 units of 9350 entries, 7300 of them evicted, the whole kernel: 21.6 us; with two-bit rounds that count with ballots
 // 70 us (16 entries per thread and three compares each make such a round 2.5 us of issue); with two-bit rounds over
 // scores in LDS and positions in memory by 256 threads, moves included, 632 us.
 template <int R, int NT>
@@ -3186,7 +3186,7 @@ __global__ __launch_bounds__(NT) void evict_kernel(Dev d, int unit_begin, int n_
 // Sec. 3 needs the probe query's weights only: a pass over the keys (values are never read), then one workgroup per
 // unit for the classes.  Before, the probe ran the decode path's scan (keys and values, behind a kernel that built its work list)
 // and found the two class boundaries with 126 one-bit rounds over weights in LDS and positions in memory: 5 + 29 +
-// 390 us for a layer of 128 units of 2048 entries on average (up to 8192); now 16 + 16 us.
+// 390 us for a layer of 128 units of 2048 entries on average (up to 8192); now 16 + 15 us.
 //
 // probe_scan_kernel: one wavefront per 128 entries, whose four blocks of keys are requested at once (the pass is a
 // single round trip to memory per wavefront: a layer is too little work for a pipeline to fill).  Leaves the scaled
