@@ -763,9 +763,12 @@ int ckv_load_cache(ckv_ctx* c, int32_t layer, const void* k, const void* v, int3
     if (int rc = launch_rebalance(c, (hipStream_t)stream, layer * c->units_per_layer, c->units_per_layer, (int)P + c->lay.headroom, lengths)) return rc;
   }
   dim3 grid((unsigned)((P + kBlk - 1) / kBlk), (unsigned)c->units_per_layer);
-  hipLaunchKernelGGL(load_cache_kernel, grid, dim3(kThreads), 0, (hipStream_t)stream, c->dev,
-                     layer * c->units_per_layer, (const uint16_t*)k, (const uint16_t*)v, (int)P, lengths, crf0, tau0,
-                     pos0);
+  auto load = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, (hipStream_t)stream, c->dev, layer * c->units_per_layer, (const uint16_t*)k,
+                       (const uint16_t*)v, (int)P, lengths, crf0, tau0, pos0);
+  };
+  if (loads_past_caches((long long)c->units_per_layer * P)) load(load_cache_kernel<true>);
+  else load(load_cache_kernel<false>);
   CKV_HIP(c, hipGetLastError());
   return CKV_OK;
 }

@@ -579,12 +579,13 @@ __global__ __launch_bounds__(kBalanceThreads) void rebalance_kernel(Dev d, int h
 }
 
 // ------------------------------------------------------------------ cache load
-// What bounds it is the copy: 612 MB for 64 units of 9350 entries.  Values go past the caches, where they would push out keys that a replay of the
-// prompt reads next (113 -> 102 us, that replay's first pass 47 -> 49; keys past them too: 108, 43, but 11 us more for the
-// moves of the eviction that follows; both as they come in: 104 and 50).
+// What bounds it is the copy: 612 MB for 64 units of 9350 entries.  PAST: values go past the caches, where those of a large layer would push out keys
+// that a replay of the prompt reads next (64 such units in an admission 113 -> 102 us, that replay's first pass 47 -> 49; keys past them too: 108, 43, but 11 us
+// more for the moves of the eviction that follows; both as they come in: 104 and 50).
 // grid: (ceil(P/32), units of the layer); converts 32 row-major rows to one
 // tiled block.  k, v: [units][P][128]; unit `urel` holds len[urel] (or P)
 // entries; rows beyond that become zero.
+template <bool PAST>
 __global__ __launch_bounds__(kThreads) void load_cache_kernel(Dev d, int unit_begin, const uint16_t* k,
                                                               const uint16_t* v, int P, const int32_t* len,
                                                               const float* crf0, const int32_t* tau0,
@@ -636,7 +637,10 @@ __global__ __launch_bounds__(kThreads) void load_cache_kernel(Dev d, int unit_be
     x.y = e8[2] | ((uint32_t)e8[3] << 16);
     x.z = e8[4] | ((uint32_t)e8[5] << 16);
     x.w = e8[6] | ((uint32_t)e8[7] << 16);
-    __builtin_nontemporal_store(x, reinterpret_cast<u32x4*>(vdst + (size_t)p * 8));
+    if constexpr (PAST)
+      __builtin_nontemporal_store(x, reinterpret_cast<u32x4*>(vdst + (size_t)p * 8));
+    else
+      *reinterpret_cast<u32x4*>(vdst + (size_t)p * 8) = x;
   }
   // per-slot state
   const Slots base = sl;

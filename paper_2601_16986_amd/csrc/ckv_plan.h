@@ -70,4 +70,12 @@ CKV_PLAN bool books_apart(long long mean, int count, int cap, int n_cu, int thre
   return idle > (mean <= kChunk ? 5 : 11) * n_cu;
 }
 
+// Loading a layer stores its values past the caches where keys and values together fill the last cache (256 MiB): they would push out keys
+// that a replay of the prompt reads next. Of a smaller layer the next step, or the moves of an eviction, still find the values there. Whole admissions (per
+// layer load, replay of 16 queries, eviction to a quarter, then a step; 3 .. 8 layers, us, values kept / past the caches): 8 units of 9350 entries 821 / 838,
+// 32 of 3000 732 / 759, 128 of 2048 (134 MB a layer) 1389 / 1407, 32 of 9350 (153) 1630 / 1650, 40 of 9350 (191) 1852 / 1850, 48 of 9350 (230) 2185 / 2183, 64 of
+// 9350 (306) 2723 / 2663, 512 of 1024 (268) 2621 / 2575, 128 of 9350 (612) 5112 / 5008; a load and a step behind it, 4 units of 777 25.6 / 26.5, 32 of 777 30.8 / 31.9.
+// (`entries`: units times the longest's length, which is all that the host knows of a ragged load.)
+CKV_PLAN bool loads_past_caches(long long entries) { return entries * kDim * 4 >= (256ll << 20); }
+
 }  // namespace ckv

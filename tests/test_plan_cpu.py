@@ -73,3 +73,13 @@ def test_bookkeeping_in_the_step_or_apart(tmp_path):
     for (int count = 1; count < 2000; count = count * 3 / 2 + 1)
       for (int cap : {6176, 8192, 32768})
         if (!ckv::books_apart(mean, count, cap, 256, 512, 6144)) return std::printf("%d units at %d\n", count, cap), 1;""")
+
+
+def test_only_large_layers_are_loaded_past_the_caches(tmp_path):
+    """Admissions measured both ways, and the last cache's 256 MiB of keys and values as the line."""
+    _run(tmp_path, r"""
+  struct { long long units, length; bool past; } measured[] = {
+      {4, 777, false}, {32, 777, false}, {8, 9350, false}, {32, 3000, false}, {128, 2048, false}, {32, 9350, false}, {48, 9350, false},
+      {512, 1024, true}, {64, 9350, true}, {128, 9350, true}, {64, 8191, false}, {64, 8192, true}};
+  for (auto& m : measured)
+    if (ckv::loads_past_caches(m.units * m.length) != m.past) return std::printf("%lld units of %lld\n", m.units, m.length), 1;""")
