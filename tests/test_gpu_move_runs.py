@@ -7,12 +7,15 @@ from tests.test_gpu_evict_sizes import _check
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("units", [1, 9, 1024])
-def test_moves_of_units_with_very_different_lists(units):
-    """One unit with thousands of moves, most with a few or none, the first and the last among either."""
-    lengths = [(4000 if i % 97 == units % 97 else 1500) if units <= 9 else (3100 if i % 97 == 5 or i == units - 1 else 300 + i % 5) for i in range(units)]
-    budgets = [n // 2 if n >= 1000 else (n if i % 3 else n - 7) for i, n in enumerate(lengths)]
-    _check(units, 4032, lengths, budgets, None, sorted({0, 5, units - 1} & set(range(units))) + list(range(0, units, 89)), False)
+# the long units first, last and in between; in a thousand, one in 97 and the last
+@pytest.mark.parametrize("units,long", [(1, [0]), (9, [0]), (9, [4]), (9, [8]), (1024, list(range(5, 1024, 97)) + [1023])])
+def test_moves_of_units_with_very_different_lists(units, long):
+    """Units with some thousand moves beside units with a few or none."""
+    lengths = [4000 if i in long else 300 + i % 5 for i in range(units)]
+    budgets = [n // 2 if i in long else (n if i % 3 else n - 7) for i, n in enumerate(lengths)]
+    evicted = np.subtract(lengths, budgets)
+    assert (evicted == 2000).sum() == len(long) and (units == 1 or ((evicted == 0).any() and (evicted == 7).any()))
+    _check(units, 4032, lengths, budgets, None, sorted(set(long) | set(range(0, units, 1 if units < 10 else 89))), False)
 
 
 @pytest.mark.parametrize("units,cap,edge", [(4, 24608, [12288, 12289, 24576, 24577]), (300, 8160, [3072, 3073, 6144, 6145])])
