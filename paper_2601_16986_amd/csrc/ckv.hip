@@ -265,11 +265,14 @@ void give_stream(int devid, hipStream_t s) {
 // Eviction of `count` units from `begin` on: select, then move.  A unit's keys sit in the registers of one workgroup:
 // 1024 threads, or 256 where four entries per thread are enough for every unit, or 32 are and there is more than a unit per
 // compute unit, which has room for one wide workgroup (window policy, two evicted each, 1024 / 256 threads: 256 units of 7500
-// entries 36 / 39 us, 384 units of 2000 32 / 25, 512 units of 2000 32 / 25, 768 units of 7500 91 / 80).
-// The moves have a kernel of their own for up to four units per compute
-// unit (a unit's own workgroup is as fast then: 4096 units of 1000 entries, window policy, 40 evicted each, 198 us with a
-// second kernel, 157 without) and where a unit may have more to move than its workgroup moves in two rounds: `excess` counts
-// what the host has seen (64 units of 9000 entries, 2 / 40 / 150 evicted, one kernel 41 / 51 / 65 us, two 45 / 53 / 57).  A
+// entries 31.7 / 35.1 us, 384 units of 2000 27.1 / 21.3, 512 units of 2000 28.3 / 22.1, 768 units of 7500 84.0 / 74.7).
+// The moves have a kernel of their own where a unit may have more to move than its workgroup moves in two rounds: `excess` counts
+// what the host has seen (window policy, 64 units of 9000 entries, 1024 threads each, 2 / 40 / 150 evicted, one kernel 35.4 / 39.3 / 48.5 us,
+// two 40.3 / 41.5 / 45.1; half of the entries evicted by score, 64 of 9000 267 / 92 us, 256 of 7500 439 / 365, 1024 of 2048 416 / 395.  With 256
+// threads the two are level up to about 150 evicted: 512 of 2000, window policy, 40 each 31.6 / 36.0, by score 150 each 96 / 97, half 184 / 175);
+// and for up to four units per compute unit, beyond which a unit's own workgroup is as fast (window policy, 40 evicted each, one kernel / two, the moves
+// in a launch per 1024 units: 4096 units of 1000 103 / 150, 8192 of 500 160 / 242; half by score, 2048 of 1000 411 / 372, 8192 of 500 821 / 826).
+// Never for more than kMoveUnits, whatever the chip: that kernel keeps a place in LDS for each unit's first move and would leave out those beyond.  A
 // replayed graph may find more than was seen when it was captured; it then takes longer and does the same.  (With the second kernel in
 // every captured eviction: 512 units of 300 entries, a captured attention-only step with a window eviction, 36 us, without 34.)
 int launch_evict(ckv_ctx* c, hipStream_t s, int begin, int count, int n_sink, int after_step = 0) {
@@ -308,12 +311,13 @@ int launch_evict(ckv_ctx* c, hipStream_t s, int begin, int count, int n_sink, in
 }
 
 // Whether a step after a change of budgets leaves evictions of several entries per unit to the kernels behind it.  Those
-// use more threads per unit, but with many units evict_move_kernel has few workgroups for each and waits for the
-// units with the most moves, while the step's own kernel deals units out as workgroups come free.  Measured, re-allocation and
-// the two steps behind it beyond two ordinary steps, us, in the step's kernel / left: all layers 128 units 126 / 57,
-// 512 units 219 / 174, 1024 units 476 / 377, 2048 units 790 / 938, 6144 units 1705 / 2474, 8192 units 1326 / 1615 (medians of three
-// processes: where the pools lie moves the large ones by a fifth); one call per layer of 1280 units 971 / 897, of 2048 units
-// 782 / 913.  Deferred bookkeeping, several layers per launch: 512 units 273 / 253, 1024 units 551 / 613, 2048 units 476 / 641.
+// use more threads per unit; the step's own kernel deals units out as workgroups come free.  Re-allocation and the two steps behind it beyond two
+// ordinary steps, us, in the step's kernel / left, units of 1024 entries on average and G = 4: all layers 128 units 117 / 27, 512 177 / 85, 1024
+// 284 / 142, 1280 315 / 240, 2048 425 / 325, 6144 745 / 645; one call per layer of 1024 424 / 200, of 1280 590 / 350, of 2048 670 / 475; deferred bookkeeping of
+// several layers of 128 per launch, 4 layers 126 / 53, 8 188 / 85, 16 242 / 137.  Of 2048 on average and G = 5: all layers 512 units 395 / 150, 2048 816 / 590, 6144
+// 1220 .. 1770 / 1075; one call per layer of 2048 1235 / 850; deferred, 8 layers 336 / 170, 16 460 / 290.  The lines date from moves that
+// had a few workgroups per unit, where the unit with the most decided (2048 units 790 / 938, 6144 units 1705 / 2474): since moves are dealt out over the whole chip,
+// leaving them is the faster at all of these sizes, and what lies above the lines could follow.
 bool leave_many_pays(const ckv_ctx* c, int count, bool deferred) {
   if (deferred) return count * std::min(book_group(c->n_cu, c->units_per_layer), c->lay.n_layers) <= 3 * c->n_cu;
   return count <= 5 * c->n_cu;

@@ -12,7 +12,7 @@
 // and beside the step:
 //
 //   load_cache_kernel   fills a layer's caches
-//   seed_scan_kernel, seed_stats_kernel, seed_weights_kernel, seed_hits_kernel, seed_crf_kernel   scores of a loaded prompt from its last queries
+//   seed_scan_kernel, seed_stats_kernel, seed_weights_kernel, seed_hits_kernel, seed_crf_hits_kernel, seed_crf_kernel   scores of a loaded prompt from its last queries
 //   evict_kernel, evict_move_kernel   eviction + compaction on its own (Alg. 1 Step 4, or the sink + recent window policy)
 //   probe_scan_kernel, probe_kernel   answer-probe classes
 //   rebudget_kernel  Alg. 2 with integer apportionment, one workgroup/sequence
@@ -487,7 +487,8 @@ __global__ __launch_bounds__(kThreads) void probe_copy_kernel(const u32x4* __res
 // its segments until a later call.  Unowned columns of a table row hold 0.
 // The segments that change hands are dealt out to the threads one by one, each looks up the unit it comes from or goes to: what a prompt
 // passes from layer to layer, 28 segments of each of 64 neighbouring units, was fetched and stored by 64 threads, in as many
-// round trips as a unit has eights (22 us, now 8.4; the first version, one segment at a time, 42).
+// round trips as a unit has eights (22 us, now 8.3; the first version, one segment at a time, 42).  Budgets of 1024 units permuted 20.7 -> 9.4 us, of
+// 6144 136 -> 41, of 16384 450 -> 101; nothing to deal out, 6144 units 16.2 -> 11.5.
 constexpr int kBalanceThreads = 1024;
 __global__ __launch_bounds__(kBalanceThreads) void rebalance_kernel(Dev d, int headroom, int x_begin, int x_count, int x_entries,
                                                                     const int32_t* x_len) {
@@ -1140,7 +1141,7 @@ struct KeyCut {
 // left of 32 for a unit that spans 16384 tokens): a histogram of the digit in LDS over the entries that still
 // match the prefix, then every wavefront finds the digit at which the count passes `want` by itself.  Scores that have decayed to
 // zero (most of a prompt's) are counted first: their common digit would serialise the LDS atomics of every round.
-// 64 units of 9350 entries, 7300 of them evicted, the whole kernel: 21.6 us; with two-bit rounds that count with ballots
+// 64 units of 9350 entries, 7300 of them evicted, the whole kernel: 21.7 us; with two-bit rounds that count with ballots
 // 70 us (16 entries per thread and three compares each make such a round 2.5 us of issue); with two-bit rounds over
 // scores in LDS and positions in memory by 256 threads, moves included, 632 us.
 template <int R, int NT>
@@ -1319,7 +1320,8 @@ __device__ __forceinline__ int evict_lists(const Dev& d, int u, Slots base, int 
 // of 2048 after a re-allocation: units with a few workgroups each 79 and 310 us; runs of the sequence, a wavefront each 75 and
 // 350, a workgroup each, four moves in turn for its wavefronts, 70 and 229; side by side as it is, eight workgroups per compute unit 63 and 208, four 63 and 207, two
 // 56 and 198, one 62 and 188; two, with eight rows per wavefront 62 and 200.  (Destination blocks put together in LDS and stored whole, instead of a
-// row's 48 partial lines, units with workgroups of their own: 85 us for the first.)
+// row's 48 partial lines, units with workgroups of their own: 85 us for the first.)  By the counters the first reads 164 MB and writes 68, for about 50 MB
+// of rows each way, 4.1 TB/s; the second 259 and 332 MB, 3.0 TB/s.
 // Places in the lists and in the segment table are looked up by a lane per move, sixteen batches at once; the units' numbers of moves are
 // summed up by every workgroup for itself.
 // grid: a multiple of 8 workgroups of kThreads threads; count <= kMoveUnits.
@@ -1805,9 +1807,9 @@ __device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, c
                                               int tid) {
   if (every_entry_hit(d)) return HitRule{0u, true, 0x7FFFFFFF};
   constexpr int kList = top_list<NT>();
-  // Steps that one wavefront, or a few, would take alone are shared by all, with the registers this needs (not in the fused kernel, whose
-  // workgroups wait for each other less and which has none left): the list's places taken once per wavefront, candidates compared by all, sums over the bins
-  // in whole numbers.  4096 rows of 9350 weights 65.7 -> 62.9 us, 2048 of them 33.2 -> 29.8 (with fewer instructions per weight around it), the
+  // Steps that one wavefront, or a few, would take alone are shared by all: the list's places taken once per wavefront, candidates compared by all, sums over
+  // the bins in whole numbers.  (Not in the fused kernel, where it gains nothing: with this / without, 896 units of 2048, G = 7, 193.0 / 192.6 us,
+  // 6144 of 2048 1240 / 1238, 16384 of 1024 1695 / 1696, 87 and 88 registers spilled.)  4096 rows of 9350 weights 65.7 -> 62.9 us, 2048 of them 33.2 -> 29.8 (with fewer instructions per weight around it), the
   // bookkeeping of 128 units 14.9 -> 14.7.
   constexpr bool kShare = CLEARED || REFINE;
   const int lane = tid & 63, wave = tid >> 6;
@@ -1824,7 +1826,8 @@ __device__ __forceinline__ HitRule top_p_regs(const Dev& d, Slots base, int n, c
   uint32_t largest = 0;
   if constexpr (REFINE) {
     // Weights outside the bins go to one of 64 behind the buffer, a lane's own, instead of nowhere: a select in place of a branch
-    // over the addition.  (The caller's rows are zero beyond their end, which only the last few registers reach.)
+    // over the addition.  (The caller's rows are zero beyond their end, which only the last few registers reach.  Rows with half, nine tenths or all but fifty
+    // of their weights below the bins, 128 units of 9350, 32 queries, a whole replay 521 / 452 / 381 -> 516 / 443 / 379 us.)
     const uint32_t beyond = (uint32_t)sizeof(TopBuf) + 8u * lane;
     unsigned char* bins = reinterpret_cast<unsigned char*>(tb.bin);
 #pragma unroll
@@ -2393,7 +2396,7 @@ __global__ __launch_bounds__(kWideThreads) void append_kernel(Dev d, int unit_be
 //   seed_stats_kernel    per query head: softmax maximum and 1 / sum over the entries the query sees
 //   seed_weights_kernel  a second pass: the logits again, normalised, the mean over the heads -> weights
 //   seed_hits_kernel     per (unit, query): hit rule, a bit per entry in place of the weights (top-p rule only)
-//   seed_crf_kernel      per entry: the queries' rewards applied in order, from the state before the replay
+//   seed_crf_kernel      per entry: the queries' rewards applied in order, from the state before the replay (seed_crf_hits_kernel: hits, short decay tables)
 // (Two passes over the keys, 256 B per entry each, instead of the logits of every query head going through
 // memory, 4 G B per entry and query written and read back.)  Only the weights are wanted (no output), so V is
 // never read.
@@ -3143,10 +3146,10 @@ __device__ __forceinline__ void evict_unit(const Dev& d, int u, Slots base, int 
 // after_step: behind a decode step that has evicted single entries itself and left the rest (units that it dealt with keep
 // their record).  moves_follow = 0: evict_move_kernel does not run, and a unit moves its survivors here.
 // RMAX: entries per thread of the longest unit that the capacity allows.  The widest branch decides the registers of the
-// whole kernel, and with them how many short units are on the chip side by side (256 threads: 64 registers with 4, 153 with
-// 32; 4096 units of 1000 entries, window policy, two evicted each: 87 us with 32, 69 with 8).
+// whole kernel, and with them how many short units are on the chip side by side (256 threads, window policy, two evicted each, with 32 / as
+// chosen: 4096 units of 1000 entries 75.5 / 58.7 us, 8192 of 500 101 / 66).
 // Units take 4, 8, 12, 16, 24 or 32, the least that hold them: what bounds a round is its sixteen wavefronts' issue on one compute unit
-// (64 units of 9350 entries, ten per thread, 23.3 us with 16, 21.6 with 12; 512 units of 9351, window policy, one evicted each, 14.8 / 13.5).
+// (64 units of 9350 entries, ten per thread, 23.3 us with 16, 21.7 with 12; 512 units of 9351, window policy, one evicted each, 14.8 / 13.4).
 template <int NT, int RMAX>
 __global__ __launch_bounds__(NT) void evict_kernel(Dev d, int unit_begin, int n_sink, int after_step, int moves_follow) {
   __shared__ uint32_t evm[NT];
@@ -3190,7 +3193,7 @@ __global__ __launch_bounds__(NT) void evict_kernel(Dev d, int unit_begin, int n_
 // Sec. 3 needs the probe query's weights only: a pass over the keys (values are never read), then one workgroup per
 // unit for the classes.  Before, the probe ran the decode path's scan (keys and values, behind a kernel that built its work list)
 // and found the two class boundaries with 126 one-bit rounds over weights in LDS and positions in memory: 5 + 29 +
-// 390 us for a layer of 128 units of 2048 entries on average (up to 8192); now 16 + 15 us.
+// 390 us for a layer of 128 units of 2048 entries on average (up to 8192); now 16.5 + 14.4 us.
 //
 // probe_scan_kernel: one wavefront per 128 entries, whose four blocks of keys are requested at once (the pass is a
 // single round trip to memory per wavefront: a layer is too little work for a pipeline to fill).  Leaves the scaled
